@@ -1,0 +1,207 @@
+// Device helpers shared by the convolution kernels: list entries, tap masks, the
+// per-tile prologue, buffer loads.
+#pragma once
+
+#include "mdcnn_internal.h"
+
+namespace mdcnn {
+
+typedef _Float16 f16;
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ int wrapc(int v, int n) { return v >= n ? v - n : v; }
+
+__device__ __forceinline__ size_t pdst_offset(const EdgeDev& e, int wy, int wx) {
+    int py = wrapc(e.p_oy + wy, e.Hp), px = wrapc(e.p_ox + wx, e.Wp);
+    return ((size_t)py * e.Wp + px) * e.Cout;
+}
+
+// Decode list entry -> conv-output coordinates (cy, cx) in the source-aligned
+// frame and the top-left destination window pixel (wy, wx).
+__device__ __forceinline__ void decode_entry(const EdgeDev& e, int idx, int& cy, int& cx, int& wy, int& wx) {
+    if (e.up) {                       // entry = updated source pixel (1x1 conv)
+        cy = idx / e.sW; cx = idx - cy * e.sW;
+        wy = (cy << e.up) + e.by0; wx = (cx << e.up) + e.bx0;
+    } else {                          // entry = destination padded-window pixel
+        wy = idx / e.Wp; wx = idx - wy * e.Wp;
+        cy = wy - e.by0; cx = wx - e.bx0;
+    }
+}
+
+// Update flags of the K x K footprint of output (cy, cx) as a bit mask.  All loads go out together
+// (a pixel outside the source reads flag 0 of the site and is masked afterwards).
+template <int K>
+__device__ __forceinline__ unsigned tap_mask_k(const EdgeDev& e, int cy, int cx) {
+    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
+    unsigned f[K * K];
+#pragma unroll
+    for (int t = 0; t < K * K; ++t) {
+        const int iy = y0 + t / K, ix = x0 + t % K;
+        const bool ok = iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW;
+        const unsigned v = e.sflags[ok ? iy * e.sW + ix : 0];
+        f[t] = ok ? v : 0u;
+    }
+    unsigned m = 0;
+#pragma unroll
+    for (int t = 0; t < K * K; ++t) m |= ((f[t] >> 2) & 1u) << t;      // kFlagM == 4
+    return m;
+}
+
+__device__ __forceinline__ unsigned tap_mask(const EdgeDev& e, int cy, int cx) {
+    switch (e.k) {
+        case 1: return tap_mask_k<1>(e, cy, cx);
+        case 3: return tap_mask_k<3>(e, cy, cx);
+        case 5: return tap_mask_k<5>(e, cy, cx);
+        default: break;
+    }
+    unsigned m = 0;
+    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
+    for (int jy = 0; jy < e.k; ++jy) {
+        const int iy = y0 + jy;
+        const bool yok = iy >= 0 && iy < e.sH;
+        for (int jx = 0; jx < e.k; ++jx) {
+            const int ix = x0 + jx;
+            const bool ok = yok && ix >= 0 && ix < e.sW;
+            const unsigned f = ok ? e.sflags[iy * e.sW + ix] : 0u;
+            m |= ((f >> 2) & 1u) << (jy * e.k + jx);
+        }
+    }
+    return m;
+}
+
+// Number of list segments an edge walks: upsampling edges walk the source
+// pixels (view order), all others the destination's padded window.
+__device__ __forceinline__ int edge_segments(const EdgeDev& e) {
+    const int n = e.up ? e.sH * e.sW : e.Hp * e.Wp;
+    return (n + kSegPixels - 1) / kSegPixels;
+}
+
+// Statistics: add taps x Cin x Cout to one of the partial multiply-accumulate
+// sums of the destination (which: 0 MFMA kernels, 1 plain kernels).
+__device__ __forceinline__ void add_macs(const EdgeDev& e, long long taps, int which) {
+    if (taps)
+        atomicAdd(reinterpret_cast<unsigned long long*>(e.dcounters) + kAccMacsSpread + 8 * which + (blockIdx.x & 7),
+                  (unsigned long long)taps * (unsigned long long)(e.Cin * e.Cout));
+}
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+__device__ __forceinline__ void mark_touched(const EdgeDev& e, int wy, int wx) {
+    if (!e.dflags) return;
+    const int f = 1 << e.up;
+    for (int a = 0; a < f; ++a)
+        for (int b = 0; b < f; ++b) {
+            const int oy = wy + a - e.by0, ox = wx + b - e.bx0;
+            if (oy >= 0 && oy < e.dH && ox >= 0 && ox < e.dW) {
+                // an atomic OR on the word that holds the flag byte, its result unused: nothing comes back to the wave, so the
+                // loads that follow do not queue behind a read-modify-write round trip (the flag region is 256-byte aligned)
+                const int idx = oy * e.dW + ox;
+                atomicOr(reinterpret_cast<unsigned*>(e.dflags + (idx & ~3)), (unsigned)kFlagU << (8 * (idx & 3)));
+            }
+        }
+}
+
+// Per-tile prologue shared by all convolution kernels.  Thread t looks at index
+// seg * kSegPixels + t of the edge's index space, gathers the update flags of its
+// footprint (they become the tap mask), and the block ranks the non-empty ones
+// with ballot + popcount: the rank is the position in the segment's compute list.
+// Entries with rank in [first, first + bm) are decoded into the LDS rows
+// s_base / s_wy / s_wx / s_vm (s_vm = 0 beyond the live rows).  With `publish`
+// the segment is also written to the destination's compute list.  `touch` marks
+// the destination pixels as touched.  Returns the number of entries of the
+// segment; sh[4] = valid taps of the tile, sh[5] = OR of its tap masks.
+// Block-uniform; two barriers; the caller must have a barrier before the call.
+__device__ __forceinline__ int tile_prologue(const EdgeDev& e, int seg, int first, int bm, bool publish, bool touch,
+                                             int* s_base, int* s_wy, int* s_wx, unsigned* s_vm, int* sh) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = e.up ? e.sH * e.sW : e.Hp * e.Wp;
+    const int p = seg * kSegPixels + tid;
+    if (tid < bm) s_vm[tid] = 0;
+    if (tid == 0) { sh[4] = 0; sh[5] = 0; }
+    int cy = 0, cx = 0, wy = 0, wx = 0;
+    unsigned vm = 0;
+    if (p < n) {
+        decode_entry(e, p, cy, cx, wy, wx);
+        if (e.k == 0) vm = (cy >= 0 && cy < e.sH && cx >= 0 && cx < e.sW && (e.sflags[cy * e.sW + cx] & kFlagM)) ? 1u : 0u;
+        else if (e.op && (cy < 0 || cy >= e.dH || cx < 0 || cx >= e.dW)) vm = 0;     // pooling outputs exist inside the view only
+        else vm = tap_mask(e, cy, cx);
+    }
+    const bool has = vm != 0;
+    const unsigned long long bal = __ballot(has);
+    const int rank = __popcll(bal & ((1ull << lane) - 1ull));
+    if (lane == 0) sh[wave] = __popcll(bal);
+    __syncthreads();
+    int off = rank;
+    for (int i = 0; i < wave; ++i) off += sh[i];
+    const int tot = sh[0] + sh[1] + sh[2] + sh[3];
+    const int r = off - first;
+    const bool mine = has && r >= 0 && r < bm;
+    if (mine) {
+        s_vm[r] = vm;
+        s_base[r] = (cy * e.stride - e.pad) * e.sW + (cx * e.stride - e.pad);
+        s_wy[r] = wy;
+        s_wx[r] = wx;
+        if (touch) mark_touched(e, wy, wx);
+    }
+    if (publish && has) e.clist[seg * kSegPixels + off] = p;
+    if (publish && tid == 0) {                             // single writer per segment: no atomics
+        e.ccnt[seg] = tot;
+        e.cacc[seg] += (unsigned long long)tot;
+    }
+    unsigned orm = mine ? vm : 0u;
+    int taps = mine ? __popc(vm) : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { orm |= __shfl_xor(orm, o); taps += __shfl_xor(taps, o); }
+    if (lane == 0 && orm) { atomicOr(reinterpret_cast<unsigned*>(&sh[5]), orm); atomicAdd(&sh[4], taps); }
+    __syncthreads();
+    return tot;
+}
+
+// The first edge of a forward call also compacts the update mask of the source
+// site into its list L (segment-local, ascending) and adds up the per-frame
+// statistics.  Called by all threads of every block before their own work.
+__device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* sh) {
+    if (!e.pub_list || blockIdx.y != 0) return;
+    const int HW = e.sH * e.sW;
+    const int nseg = (HW + kSegPixels - 1) / kSegPixels;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
+        const int p = seg * kSegPixels + tid;
+        const int f = p < HW && tid < kSegPixels ? e.sflags[p] : 0;       // waves beyond the fourth only keep the barriers
+        const unsigned long long bm = __ballot(f & kFlagM), bc = __ballot(f & kFlagC);
+        __syncthreads();                                   // sh is free again
+        if (lane == 0 && wave < 4) { sh[wave] = __popcll(bm); sh[4 + wave] = __popcll(bc); }
+        __syncthreads();
+        int off = __popcll(bm & ((1ull << lane) - 1ull));
+        for (int i = 0; i < wave; ++i) off += sh[i];
+        if (f & kFlagM) e.pub_list[seg * kSegPixels + off] = p;
+        if (tid == 0) {                                    // single writer per segment: no atomics
+            const int tot = sh[0] + sh[1] + sh[2] + sh[3], c = sh[4] + sh[5] + sh[6] + sh[7];
+            e.pub_lcnt[2 * seg] = tot;
+            e.pub_lcnt[2 * seg + 1] = c;
+            e.pub_lacc[2 * seg] += (unsigned long long)tot;
+            e.pub_lacc[2 * seg + 1] += (unsigned long long)c;
+        }
+    }
+    __syncthreads();
+}
+
+// Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a
+// scalar byte offset, so a wave spends one vector register on all the addresses of a tensor instead of a
+// 64-bit pointer per load (reads past `bytes` return zero instead of faulting).
+using rsrc_t = __amdgpu_buffer_rsrc_t;
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ f16x8 buf_load16(rsrc_t r, unsigned lane_bytes, unsigned wave_bytes) {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)wave_bytes, 0);
+    return __builtin_bit_cast(f16x8, v);
+}
+
+}  // namespace mdcnn

@@ -194,6 +194,9 @@ hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls
 hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, hipStream_t st, int* cls);
+// convolution tile straight from global memory (kernels_direct.hip): shapes it takes, launch
+bool direct_applies(const EdgeDev& e, int dtype);
+hipError_t launch_conv_direct(const EdgeBatch& eb, int nb, int dtype, hipStream_t st);
 extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // convolution tuning knobs
 // host-only: the rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);

@@ -1,0 +1,49 @@
+"""Convolution tiles that read their operands straight from global memory (fp32 layers of many channels),
+against the oracle on ragged windows, partial cout tiles, strides and upsampling edges."""
+import numpy as np
+import pytest
+
+from inputs.nets import NetSpec, _Builder, tiny_net
+
+pytestmark = pytest.mark.gpu
+
+
+def frames_of(net, seed, n=3):
+    rng = np.random.default_rng(seed)
+    x = rng.normal(0, 1, (net.H, net.W, net.sites[0].C)).astype(np.float32)
+    out = [x.astype(net.np_dtype)]
+    for _ in range(n - 1):
+        x = x.copy()
+        y0, x0 = int(rng.integers(0, max(1, net.H - 5))), int(rng.integers(0, max(1, net.W - 7)))
+        x[y0:y0 + 5, x0:x0 + 7] += rng.normal(0, 1, x[y0:y0 + 5, x0:x0 + 7].shape).astype(np.float32)
+        x[rng.random((net.H, net.W)) < 0.03] += 0.5
+        out.append(x.astype(net.np_dtype))
+    return out
+
+
+@pytest.mark.parametrize("cin,cout,H,W,k,stride", [
+    (128, 32, 8, 8, 3, 1),         # one tile and a bit: the 10 x 10 window in 8 x 4 tiles
+    (8, 32, 5, 37, 3, 1),          # one K block per tap: waves share the taps
+    (24, 96, 33, 18, 3, 1),        # three blocks per tap, three cout tiles
+    (72, 16, 30, 22, 1, 1),        # half a cout tile
+    (128, 128, 48, 40, 3, 2),      # stride 2
+    (40, 64, 90, 100, 5, 1),       # 25 taps; enough pixels for the larger tiles
+    (512, 64, 11, 9, 3, 1),        # a long K loop
+])
+def test_fp32_layers_straight_from_memory(cin, cout, H, W, k, stride):
+    import gpu_harness as G
+    H, W = H * stride, W * stride
+    net = tiny_net("f32", H, W, (cin, cout), k=k, stride=stride, theta=0.05, seed=cin + cout, total_stride=stride)
+    G.teacher_forced(net, frames_of(net, cin * 10 + cout), [(0, 0), (0, 0), (1, -1)])
+
+
+def test_fp32_upsampling_edge_straight_from_memory():
+    import gpu_harness as G
+    net = NetSpec("up", "f32", 36, 52, 4)
+    b = _Builder(net, np.random.default_rng(3), 0.1)
+    x = b.site("in", 8, 1, "input", False, 0.05)
+    s = b.site("low", 96, 4, theta=0.02)
+    y = b.site("out", 32, 1, "output", False, 0.0)
+    b.conv(x, s, 5, 4, pad=2)
+    b.conv(s, y, 1, 1, pad=0, up=2)
+    G.teacher_forced(net, frames_of(net, 1), [(0, 0), (0, 1), (0, 0)])
