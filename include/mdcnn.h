@@ -271,7 +271,8 @@ mdcnn_status mdcnn_frame_crop(mdcnn_net* net, const void* frame_dev, const uint8
  * gets none; a site without such edges gets one compaction launch).
  * stream_of[i]: stream of launch i (0 = the caller's); waits_of[2i], waits_of[2i+1]:
  * launches on other streams that launch i waits for, or -1 (launches on one stream
- * run in order anyway).  Both arrays are caller-owned with room for `cap` launches
+ * run in order anyway).  Where the library puts independent launches together instead
+ * (streams = 0, see MDCNN_OPT_STREAMS), it keeps the order of this plan for every site.  Both arrays are caller-owned with room for `cap` launches
  * (2 * cap ints for waits_of) and may be NULL; *n_launches and *n_streams (optional)
  * get the number of launches and of streams used.
  * Errors: MDCNN_ERR_SIZE if cap is too small or streams out of range. */
@@ -522,10 +523,11 @@ typedef enum {
                              /* them after the camera shift and waits for them before the readout, */
                              /* so the call stays in stream order; launches that write one site    */
                              /* keep their order, so the results do not change by a bit.  1: all   */
-                             /* launches on the caller's stream.  0 (default): four streams if the */
-                             /* network has parallel branches that shorten a frame by a fifth or   */
-                             /* more (counted in launches, a wait for another stream as one), else */
-                             /* the caller's stream only                                           */
+                             /* launches on the caller's stream.  0 (default): the caller's stream,  */
+                             /* and launches of an fp16 network that do not depend on each other   */
+                             /* go out as one (in profiling mode and for fp32: four streams where  */
+                             /* they shorten a frame by a fifth or more, counted in launches, a    */
+                             /* wait for another stream as one; else the caller's stream only)     */
 } mdcnn_option;
 mdcnn_status mdcnn_set_option(int option, int value);
 

@@ -91,19 +91,21 @@ __device__ __forceinline__ int wave_sum(int v) {
     return v;
 }
 
-__device__ __forceinline__ void mark_touched(const EdgeDev& e, int wy, int wx) {
+// Marks a window pixel as touched, if it is in the view: an atomic OR on the word that holds the flag byte, its result
+// unused: nothing comes back to the wave, so the loads that follow do not queue behind a read-modify-write round trip
+// (the flag region is 256-byte aligned).
+__device__ __forceinline__ void mark_pixel(const EdgeDev& e, int wy, int wx) {
     if (!e.dflags) return;
+    const int oy = wy - e.by0, ox = wx - e.bx0;
+    if (oy >= 0 && oy < e.dH && ox >= 0 && ox < e.dW) {
+        const int idx = oy * e.dW + ox;
+        atomicOr(reinterpret_cast<unsigned*>(e.dflags + (idx & ~3)), (unsigned)kFlagU << (8 * (idx & 3)));
+    }
+}
+__device__ __forceinline__ void mark_touched(const EdgeDev& e, int wy, int wx) {
     const int f = 1 << e.up;
     for (int a = 0; a < f; ++a)
-        for (int b = 0; b < f; ++b) {
-            const int oy = wy + a - e.by0, ox = wx + b - e.bx0;
-            if (oy >= 0 && oy < e.dH && ox >= 0 && ox < e.dW) {
-                // an atomic OR on the word that holds the flag byte, its result unused: nothing comes back to the wave, so the
-                // loads that follow do not queue behind a read-modify-write round trip (the flag region is 256-byte aligned)
-                const int idx = oy * e.dW + ox;
-                atomicOr(reinterpret_cast<unsigned*>(e.dflags + (idx & ~3)), (unsigned)kFlagU << (8 * (idx & 3)));
-            }
-        }
+        for (int b = 0; b < f; ++b) mark_pixel(e, wy + a, wx + b);
 }
 
 // Per-tile prologue shared by all convolution kernels.  Thread t looks at index
@@ -165,12 +167,13 @@ __device__ __forceinline__ int tile_prologue(const EdgeDev& e, int seg, int firs
 // The first edge of a forward call also compacts the update mask of the source
 // site into its list L (segment-local, ascending) and adds up the per-frame
 // statistics.  Called by all threads of every block before their own work.
-__device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* sh) {
+// (blk, nblk: this block's number among those of the edge)
+__device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* sh, unsigned blk = blockIdx.x, unsigned nblk = gridDim.x) {
     if (!e.pub_list || blockIdx.y != 0) return;
     const int HW = e.sH * e.sW;
     const int nseg = (HW + kSegPixels - 1) / kSegPixels;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
+    for (int seg = (int)blk; seg < nseg; seg += (int)nblk) {
         const int p = seg * kSegPixels + tid;
         const int f = p < HW && tid < kSegPixels ? e.sflags[p] : 0;       // waves beyond the fourth only keep the barriers
         const unsigned long long bm = __ballot(f & kFlagM), bc = __ballot(f & kFlagC);

@@ -1,0 +1,734 @@
+// Convolution tiles on the matrix cores (fp16): the gather-GEMM tile and the halo-staged tile, as device functions that
+// a kernel of one edge (kernels_conv.hip) or of several independent edges (kernels_multi.hip) runs.
+#pragma once
+
+#include <type_traits>
+
+#include "conv_device.h"
+
+namespace mdcnn {
+
+// ---------------------------------------------------------------------------
+// Tiled MFMA gather-GEMM (the fast path for fp16 layers with Cin % 32 == 0).
+// Block tile = BM list entries (pixels) x BN couts, 4 waves arranged WM x WN,
+// each wave owning TM x TN 32x32 accumulators.  K runs over (active tap,
+// KC-channel chunk) steps; per step the weight slab [BN][KC] and the gathered
+// delta slab [BM][KC] (rows of taps that miss the update mask are zero) go
+// global -> registers -> LDS (rows padded by 16 bytes) while the previous step is
+// multiplied out of LDS.  Taps no entry of the tile uses are skipped.  The
+// accumulators are transposed through LDS so that P is updated with 16-byte
+// accesses that are contiguous along the channels.
+// v_mfma_f32_32x32x16_f16: operand A = 32 couts x 16 cin (weights), operand
+// B = 16 cin x 32 pixels; lane l feeds row/col l%32 with the 8 consecutive cin
+// starting at 8*(l/32); the result puts pixel l%32 on lane l with couts
+// 8*(r/4) + 4*(l/32) + r%4 in accumulator register r.
+// ---------------------------------------------------------------------------
+template <int WM, int WN, int TM, int TN, int KC, int PIPE>
+struct TiledCfg {
+    static constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
+    static constexpr int LDK = KC + 8;             // slab row, halves
+    static constexpr int LDC = BN + 4;             // transposed accumulator row, floats
+    static constexpr int CPR = KC / 8;             // 16-byte chunks per slab row
+    static constexpr int STAGE_HALVES = (BM + BN) * LDK;
+    static constexpr int SLAB_BYTES = PIPE * STAGE_HALVES * 2;
+    static constexpr int C_BYTES = BM * LDC * 4;
+    static constexpr int SMEM = SLAB_BYTES > C_BYTES ? SLAB_BYTES : C_BYTES;
+    static constexpr int TPS = kSegPixels / BM;    // tiles per list segment
+};
+
+// Work item u of a 1-D grid -> (pixel tile m, cout tile n).  Work groups are
+// dealt round-robin to the 8 XCDs, each with its own L2: tying u % 8 to the
+// cout tile makes all blocks of one XCD share the same weight slice.
+__device__ __forceinline__ void map_tile(int u, int NT, int xcd_map, int& m, int& n) {
+    if (xcd_map) {
+        const int q = 8 / NT, x = u & 7, r = u >> 3;
+        n = x % NT;
+        m = r * q + x / NT;
+    } else {
+        n = u % NT;
+        m = u / NT;
+    }
+}
+
+// PIPE = 1: one LDS buffer, loads one step ahead (two barriers per step).
+// PIPE = 2: two LDS buffers and two register stages, loads two steps ahead
+//           (one barrier per step).
+// blk, nblk: this block's number among the blocks that work on the edge (the grid may hold blocks of other edges too).
+template <int WM, int WN, int TM, int TN, int KC, int PIPE>
+__device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsigned nblk, int NT, int work_items, int xcd_map) {
+    using Cfg = TiledCfg<WM, WN, TM, TN, KC, PIPE>;
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, LDK = Cfg::LDK, LDC = Cfg::LDC, CPR = Cfg::CPR, TPS = Cfg::TPS;
+    constexpr int NB = (BM * CPR + 255) / 256, NA = (BN * CPR + 255) / 256;
+    static_assert(WM * WN == 4 && kSegPixels % BM == 0, "4 waves; tiles do not straddle segments");
+    extern __shared__ __align__(16) unsigned char smem[];
+    f16* slab = reinterpret_cast<f16*>(smem);            // PIPE x { [BM][LDK] deltas, [BN][LDK] weights }
+    float* sC = reinterpret_cast<float*>(smem);          // [BM][LDC] after the K loop
+    __shared__ int s_base[BM], s_wy[BM], s_wx[BM];
+    __shared__ unsigned s_vm[BM];
+    __shared__ int sh[8];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % WM, wn = wave / WM;
+    const int r32 = lane & 31, kh = lane >> 5;
+    const int MT = edge_segments(e) * TPS;
+    // (the host checks that both tensors are smaller than 2 GiB)
+    const rsrc_t drs = make_rsrc(e.delta, (unsigned)e.sH * (unsigned)e.sW * (unsigned)e.Cin * 2u);
+    const rsrc_t wrs = make_rsrc(e.w, (unsigned)(e.k * e.k) * (unsigned)e.Cin * (unsigned)e.Cout * 2u);
+
+    carry_source_compaction(e, sh, blk, nblk);
+
+    // The f x f pixels an entry of an upsampling edge adds to are dealt to f * f / 4 items, which all make the entry's sums
+    // (a 1x1 convolution: a step or two): in one block they were up to 64 read-add-write round trips in a row (12 x 9 source
+    // pixels, 256 -> 32 channels, 8-fold: 31 us, now 12).
+    const int f = 1 << e.up, splits = f > 2 ? f * f / 4 : 1, split_items = work_items / splits;
+    for (int u = (int)blk; u < work_items; u += (int)nblk) {
+        const int part = u / split_items;                 // (0 without upsampling)
+        int mt, nt;
+        map_tile(u - part * split_items, NT, xcd_map, mt, nt);
+        if (mt >= MT) continue;
+        const int seg = mt / TPS, first = (mt - seg * TPS) * BM;
+        const int n0 = nt * BN;
+        __syncthreads();                                  // previous tile is done with LDS
+        const int tot = tile_prologue(e, seg, first, BM, nt == 0 && first == 0 && !e.up, nt == 0 && !e.up,
+                                      s_base, s_wy, s_wx, s_vm, sh);
+        const int live = tot - first < BM ? tot - first : BM;     // entries of this tile (block-uniform)
+        if (live <= 0) continue;
+        const unsigned tilemask = (unsigned)sh[5];
+        if (tid == 0 && nt == 0 && part == 0) add_macs(e, sh[4], 0);    // statistics: one atomic per tile
+
+        f32x16 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+        // Per-thread chunk descriptors of this tile: which slab rows this thread
+        // moves, their source offsets (elements) and tap masks.  Per step only a
+        // block-uniform offset is added; a row whose tap misses the update mask is
+        // loaded from beyond the end of the tensor, which a buffer load answers with
+        // zeros (no divergent branches and no selects on the data in the K loop).
+        int offB[NB];
+        unsigned offA[NA];
+        unsigned vmB[NB];
+        int ldsB[NB], ldsA[NA];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int ch = tid + 256 * i;
+            const int row = (ch / CPR) % BM, cc = ch % CPR;          // % BM: keep partial last rounds in range
+            offB[i] = (s_base[row] * e.Cin + cc * 8) * 2;      // bytes; may be negative: the top left tap of a border pixel
+            vmB[i] = (BM * CPR) % 256 == 0 || ch < BM * CPR ? s_vm[row] : 0u;
+            ldsB[i] = row * LDK + cc * 8;
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int ch = tid + 256 * i;
+            const int row = (ch / CPR) % BN, cc = ch % CPR;
+            offA[i] = ((unsigned)(n0 + row) * (unsigned)e.Cin + cc * 8) * 2u;      // bytes
+            ldsA[i] = row * LDK + cc * 8;
+        }
+        const unsigned tap_stride_w = (unsigned)e.Cout * (unsigned)e.Cin * 2u;    // bytes
+
+        // the load iterator runs PIPE steps ahead of the multiplication
+        unsigned ld_rem = tilemask;
+        int ld_tap = ld_rem ? __ffs(ld_rem) - 1 : -1, ld_c0 = 0;
+        f16x8 rb[PIPE][NB], ra[PIPE][NA];
+        auto load_next = [&](auto stage) {
+            constexpr int S = decltype(stage)::value;
+            if (ld_tap < 0) return;
+            const int jy = ld_tap / e.k, jx = ld_tap - jy * e.k;
+            const int stepB = ((jy * e.sW + jx) * e.Cin + ld_c0) * 2;                 // block-uniform, bytes
+            const unsigned stepA = (unsigned)ld_tap * tap_stride_w + (unsigned)ld_c0 * 2u;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const bool valid = (vmB[i] >> ld_tap) & 1u;                           // then offB + stepB is a pixel of the source
+                rb[S][i] = buf_load16(drs, valid ? (unsigned)(offB[i] + stepB) : 0x80000000u, 0u);
+            }
+#pragma unroll
+            for (int i = 0; i < NA; ++i) ra[S][i] = buf_load16(wrs, offA[i], stepA);
+            ld_c0 += KC;
+            if (ld_c0 >= e.Cin) { ld_c0 = 0; ld_rem &= ld_rem - 1; ld_tap = ld_rem ? __ffs(ld_rem) - 1 : -1; }
+        };
+        auto store_stage = [&](auto stage) {
+            constexpr int S = decltype(stage)::value;
+            f16* sB = slab + S * Cfg::STAGE_HALVES;
+            f16* sA = sB + BM * LDK;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                if ((BM * CPR) % 256 == 0 || tid + 256 * i < BM * CPR) *reinterpret_cast<f16x8*>(sB + ldsB[i]) = rb[S][i];
+            }
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if ((BN * CPR) % 256 == 0 || tid + 256 * i < BN * CPR) *reinterpret_cast<f16x8*>(sA + ldsA[i]) = ra[S][i];
+        };
+        auto multiply = [&](auto stage) {
+            constexpr int S = decltype(stage)::value;
+            constexpr int KK = KC / 16;
+            const f16* sB = slab + S * Cfg::STAGE_HALVES + (wm * TM * 32 + r32) * LDK + kh * 8;
+            const f16* sA = slab + S * Cfg::STAGE_HALVES + BM * LDK + (wn * TN * 32 + r32) * LDK + kh * 8;
+            f16x8 fb[KK][TM], fa[KK][TN];                    // all fragments of the step, then the MFMAs
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fb[kk][i] = *reinterpret_cast<const f16x8*>(sB + i * 32 * LDK + kk * 16);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fa[kk][j] = *reinterpret_cast<const f16x8*>(sA + j * 32 * LDK + kk * 16);
+            }
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[kk][j], fb[kk][i], acc[i][j], 0, 0, 0);
+        };
+        using S0 = std::integral_constant<int, 0>;
+        using S1 = std::integral_constant<int, PIPE - 1>;
+        int steps = __popc(tilemask) * (e.Cin / KC);
+        if constexpr (PIPE == 1) {
+            load_next(S0{});
+            store_stage(S0{});
+            __syncthreads();
+            while (steps > 0) {
+                load_next(S0{});                             // in flight while this step is multiplied
+                multiply(S0{});
+                __syncthreads();
+                if (--steps > 0) store_stage(S0{});
+                __syncthreads();
+            }
+        } else {
+            load_next(S0{});
+            load_next(S1{});
+            while (steps > 0) {
+                store_stage(S0{});
+                load_next(S0{});                             // refill the registers just drained
+                __syncthreads();
+                multiply(S0{});
+                if (--steps == 0) break;
+                store_stage(S1{});
+                load_next(S1{});
+                __syncthreads();
+                multiply(S1{});
+                --steps;
+            }
+            __syncthreads();                                 // all multiplications done: LDS becomes the C tile
+        }
+
+        // accumulators -> LDS as [pixel][cout]
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                float* dst = sC + ((wm * TM + i) * 32 + r32) * LDC + (wn * TN + j) * 32 + 4 * kh;
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<float4*>(dst + 8 * g) =
+                        make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+            }
+        __syncthreads();
+        constexpr int TPR = BN / 8;                        // threads per pixel row, 8 couts each
+        const int c8 = (tid % TPR) * 8;
+        if (f == 1) {
+            // P <- P + sum: all reads of P go out first (their latency is paid once), then the stores
+            constexpr int RPP = 256 / TPR, NPASS = (BM + RPP - 1) / RPP;
+            f16x8 pold[NPASS];
+            f16* pp[NPASS];
+#pragma unroll
+            for (int t = 0; t < NPASS; ++t) {
+                const int row = tid / TPR + t * RPP;
+                const int rr = row < live ? row : 0;        // dead rows read entry 0 and store nothing
+                pp[t] = (f16*)e.P + pdst_offset(e, s_wy[rr], s_wx[rr]) + n0 + c8;
+                pold[t] = *reinterpret_cast<const f16x8*>(pp[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < NPASS; ++t) {
+                const int row = tid / TPR + t * RPP;
+                if (row < live) {
+                    const float4 v0 = *reinterpret_cast<const float4*>(sC + row * LDC + c8);
+                    const float4 v1 = *reinterpret_cast<const float4*>(sC + row * LDC + c8 + 4);
+                    const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                    f16x8 o = pold[t];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) o[q] = (f16)((float)o[q] + v[q]);
+                    *reinterpret_cast<f16x8*>(pp[t]) = o;
+                }
+            }
+            continue;
+        }
+        for (int row = tid / TPR; row < BM && row < live; row += 256 / TPR) {
+            const float4 v0 = *reinterpret_cast<const float4*>(sC + row * LDC + c8);
+            const float4 v1 = *reinterpret_cast<const float4*>(sC + row * LDC + c8 + 4);
+            const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+            f16x8 o[4];
+            f16* p[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = part * 4 + q;                 // 2-fold: all four
+                p[q] = (f16*)e.P + pdst_offset(e, s_wy[row] + (at >> e.up), s_wx[row] + (at & (f - 1))) + n0 + c8;
+                o[q] = *reinterpret_cast<f16x8*>(p[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) o[q][c] = (f16)((float)o[q][c] + v[c]);
+                *reinterpret_cast<f16x8*>(p[q]) = o[q];
+                if (nt == 0 && c8 == 0) mark_pixel(e, s_wy[row] + ((part * 4 + q) >> e.up), s_wx[row] + ((part * 4 + q) & (f - 1)));
+            }
+        }
+    }
+}
+
+// Variant of tile_prologue for tiles that are index sub-ranges of a segment: the
+// tile takes the entries among indices [sub_lo, sub_lo + sub_n) of segment `seg`
+// (sub_lo a multiple of 64).  Returns their number; rows s_* are filled for them.
+__device__ __forceinline__ int tile_prologue_sub(const EdgeDev& e, int seg, int sub_lo, int sub_n, bool publish, bool touch,
+                                                 int* s_wy, int* s_wx, int* sh) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = e.Hp * e.Wp;
+    const int p = seg * kSegPixels + tid;
+    if (tid == 0) sh[4] = 0;
+    int cy = 0, cx = 0, wy = 0, wx = 0;
+    unsigned vm = 0;
+    if (p < n && tid < kSegPixels) {                       // waves beyond the fourth only keep the barriers
+        decode_entry(e, p, cy, cx, wy, wx);
+        vm = tap_mask(e, cy, cx);
+    }
+    const bool has = vm != 0;
+    const unsigned long long bal = __ballot(has);
+    const int rank = __popcll(bal & ((1ull << lane) - 1ull));
+    if (lane == 0 && wave < 4) sh[wave] = __popcll(bal);
+    __syncthreads();
+    int off = rank, base = 0, cnt = 0;
+    for (int i = 0; i < 4; ++i) {
+        if (i < wave) off += sh[i];
+        if (i * 64 < sub_lo) base += sh[i];
+        else if (i * 64 < sub_lo + sub_n) cnt += sh[i];
+    }
+    const bool mine = has && tid >= sub_lo && tid < sub_lo + sub_n;
+    if (mine) {
+        s_wy[off - base] = wy;
+        s_wx[off - base] = wx;
+        if (touch) mark_touched(e, wy, wx);
+    }
+    if (publish && has) e.clist[seg * kSegPixels + off] = p;
+    if (publish && tid == 0) {                             // single writer per segment: no atomics
+        const int tot = sh[0] + sh[1] + sh[2] + sh[3];
+        e.ccnt[seg] = tot;
+        e.cacc[seg] += (unsigned long long)tot;
+    }
+    int taps = mine ? __popc(vm) : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) taps += __shfl_xor(taps, o);
+    if (lane == 0 && taps) atomicAdd(&sh[4], taps);
+    __syncthreads();
+    return cnt;
+}
+
+// Variant of tile_prologue for tiles that are th x tw rectangles of the padded window (th * tw <= 256, top-left
+// corner (wy0, wx0)): thread t looks at tile pixel (t / tw, t % tw); the live ones are ranked in that order.
+// Returns their number; rows s_wy / s_wx are filled for them, sh[4] = valid taps of the tile.
+// The tap mask of a tile pixel is read off the tile's staged rectangle: s_pix[ry * rw + rx] >= 0 where the source pixel
+// (ry, rx) of the rectangle (the tile plus its halo) is in view and updated (3x3, stride 1: the footprint of tile pixel
+// (ly, lx) is rectangle rows ly .. ly + 2, columns lx .. lx + 2) - no flag loads of its own.
+// pub_seg >= 0: the block also ranks list segment pub_seg (256 consecutive window indices), whose tap masks vm_p the
+// caller has requested with the rectangle's flags; pub_off = this thread's position in that segment's compute list or
+// -1, sh[8 .. 11] the entries of the segment per wave.  Nothing is written to global memory here: the wave's later
+// loads would queue behind those stores (tile_effects_2d does it once the tile's own loads are done).
+__device__ __forceinline__ int tile_prologue_2d(const EdgeDev& e, int wy0, int wx0, int th, int tw, const int* s_pix, int rw,
+                                                int pub_seg, unsigned vm_p, int& pub_off, int* s_wy, int* s_wx, int* sh) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) sh[4] = 0;
+    const int ly = tid / tw, lx = tid - ly * tw;
+    const int wy = wy0 + ly, wx = wx0 + lx;
+    const bool in_tile = ly < th && wy < e.Hp && wx < e.Wp;
+    const bool in_seg = pub_seg >= 0 && pub_seg * kSegPixels + tid < e.Hp * e.Wp;
+    unsigned vm = 0;
+    if (in_tile) {
+        const int* r = s_pix + ly * rw + lx;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) vm |= (unsigned)(r[(t / 3) * rw + t % 3] >= 0) << t;
+    }
+    const bool has = vm != 0, hasp = in_seg && vm_p != 0;
+    const unsigned long long bal = __ballot(has), balp = __ballot(hasp);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (lane == 0) { sh[wave] = __popcll(bal); sh[8 + wave] = __popcll(balp); }
+    __syncthreads();
+    int off = __popcll(bal & below), offp = __popcll(balp & below);
+    for (int i = 0; i < wave; ++i) { off += sh[i]; offp += sh[8 + i]; }
+    const int cnt = sh[0] + sh[1] + sh[2] + sh[3];
+    if (has) {
+        s_wy[off] = wy;
+        s_wx[off] = wx;
+    }
+    pub_off = hasp ? offp : -1;
+    int taps = __popc(vm);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) taps += __shfl_xor(taps, o);
+    if (lane == 0 && taps) atomicAdd(&sh[4], taps);
+    __syncthreads();
+    return cnt;
+}
+
+// What a tile leaves behind besides its sums, after tile_prologue_2d: the touched marks of its `tot` entries and the
+// multiply-accumulate count (touch), the compute list of segment pub_seg and its counts.  No barrier.
+__device__ __forceinline__ void tile_effects_2d(const EdgeDev& e, int tot, bool touch, int pub_seg, int pub_off,
+                                                const int* s_wy, const int* s_wx, const int* sh) {
+    const int tid = threadIdx.x;
+    if (touch) {
+        for (int r = tid; r < tot; r += 256) mark_touched(e, s_wy[r], s_wx[r]);
+        if (tid == 0) add_macs(e, sh[4], 0);
+    }
+    if (pub_seg >= 0) {
+        if (pub_off >= 0) e.clist[pub_seg * kSegPixels + pub_off] = pub_seg * kSegPixels + tid;
+        if (tid == 0) {                                    // single writer per segment: no atomics
+            const int n = sh[8] + sh[9] + sh[10] + sh[11];
+            e.ccnt[pub_seg] = n;
+            e.cacc[pub_seg] += (unsigned long long)n;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Halo-staged MFMA convolution: KS x KS, stride 1, fp16, weights in the packed
+// order [tap][cin/16][cout][16] (k_pack_weights).
+// A tile is one NSUB-th of a list segment -- the entries among SUB = kSegPixels
+// / NSUB consecutive indices of the padded window -- x BN couts.  Every input
+// pixel those entries read lies in a small rectangle of the source (the rows
+// the index range spans plus KS-1, full width if it spans more than one row).
+// Per KC-channel chunk that rectangle is staged ONCE in LDS -- zero rows for
+// pixels out of view or not updated, which is all the masking the taps need --
+// and all KS*KS taps multiply out of it: the deltas are fetched once instead
+// of once per tap.  The weights never touch LDS: the four waves are WMV
+// (row-tile groups) x WK (K split); a wave multiplies its row tiles x TN 32x32
+// accumulators over every WK-th 16-channel block of every tap and loads
+// exactly the fragments it needs, 1 KiB contiguous each, several steps ahead.
+// The body of a chunk is straight-line code (static taps, static register
+// rings), so the loads of the next steps and of the next chunk stay in flight
+// behind the matrix instructions; two tiles per compute unit cover each
+// other's barriers.  The K-split partial sums are added in a fixed order
+// through LDS, so the result does not depend on timing; P is then updated with
+// 16-byte accesses.
+// ---------------------------------------------------------------------------
+template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1)>
+struct HaloCfg {
+    static constexpr int SUB = kSegPixels / NSUB;    // indices (and at most entries) per tile
+    static_assert(WMV * WK == 4 && WMV * TM * 32 == SUB && SUB % 64 == 0, "4 waves cover one tile");
+    static constexpr int BN = 32 * TN;
+    static constexpr int KB = KC / 16;               // 16-channel blocks per chunk
+    static_assert(KB % WK == 0, "every K wave takes the same number of blocks per tap");
+    static constexpr int MB = KB / WK;               // blocks per tap and wave
+    static constexpr int NS = KS * KS * MB;          // steps per chunk and wave
+    static constexpr int RING = RING_;               // weight-fragment sets in flight; divides NS, so the
+                                                     // ring carries over from chunk to chunk.  Above 3 the
+                                                     // registers go to the ring and the next chunk of the
+                                                     // rectangle is fetched at the chunk boundary instead of
+                                                     // being prefetched into registers during the chunk
+    static_assert(NS % RING == 0, "static ring slots");
+    static constexpr int CPR = KC / 8;               // 16-byte pieces per staged pixel
+    static constexpr int NLD = NLD_;                 // pieces per thread and chunk
+    static constexpr int CAP = NLD * 256 / CPR;      // staged pixels
+    static constexpr int LDK = KC + 8;               // staged row, halves (16 bytes of padding)
+    static constexpr int LDC = BN + 4;               // accumulator row, floats
+    static constexpr int HALO_BYTES = CAP * LDK * 2;
+    static constexpr int C_BYTES = SUB * LDC * 4;
+    static constexpr int MAIN_BYTES = HALO_BYTES > C_BYTES ? HALO_BYTES : C_BYTES;
+    static constexpr int SMEM = MAIN_BYTES + CAP * 4;   // + source pixel index of every staged position
+    static constexpr int LPS = (NLD + NS / 2 - 1) / (NS / 2);   // staging loads per step (first steps of a chunk)
+    static constexpr int NLS = (NLD + LPS - 1) / LPS;
+    static_assert(NLS <= NS, "staging loads fit the steps of a chunk");
+    static constexpr int MINB = MINB_;               // tiles per compute unit the registers are budgeted for
+};
+
+// T2D: the tiles are th x tw rectangles of the padded window (th * tw <= SUB) instead of index ranges: the staged rectangle
+// is the tile plus its KS - 1 halo whatever the width of the window, so wide rows fit and narrow ones stage less.
+template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
+__device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsigned nblk, int NT, int work_items, int th, int tw) {
+    using Cfg = HaloCfg<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_>;
+    constexpr int SUB = Cfg::SUB, BN = Cfg::BN, KB = Cfg::KB, MB = Cfg::MB, NS = Cfg::NS, CPR = Cfg::CPR, NLD = Cfg::NLD,
+                  LDK = Cfg::LDK, LDC = Cfg::LDC;
+    extern __shared__ __align__(16) unsigned char smem[];
+    f16* halo = reinterpret_cast<f16*>(smem);            // [CAP][LDK] during the K loop
+    float* sC = reinterpret_cast<float*>(smem);          // [SUB][LDC] after it
+    int* s_pix = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);
+    __shared__ int s_wy[SUB], s_wx[SUB];
+    __shared__ int sh[12];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: scalar branches below
+    const int wm = wave % WMV, wk = wave / WMV;
+    const int r32 = lane & 31, kh = lane >> 5;
+    const int tiles_x = T2D ? (e.Wp + tw - 1) / tw : 1;
+    const int ntiles = T2D ? tiles_x * ((e.Hp + th - 1) / th) : edge_segments(e) * NSUB;
+    const int nchunks = e.Cin / KC;
+    const int nwin = e.Hp * e.Wp;
+    // (the host checks that both tensors are smaller than 2 GiB)
+    const rsrc_t drs = make_rsrc(e.delta, (unsigned)e.sH * (unsigned)e.sW * (unsigned)e.Cin * 2u);
+    const rsrc_t wrs = make_rsrc(e.wp, (unsigned)(KS * KS) * (unsigned)e.Cin * (unsigned)e.Cout * 2u);
+    const unsigned tap_stride = (unsigned)(e.Cin / 16) * (unsigned)e.Cout * 32u;   // packed weights: bytes per tap
+    const unsigned blk_stride = (unsigned)e.Cout * 32u;                            //                 per 16-channel block
+
+    unsigned warm = 0;
+    if constexpr (T2D) {
+        // the blocks of a cout tile touch that tile's weights, a line each, before anything else: the fragments of the
+        // K loop then come from the L2 of their XCD instead of following each other to memory
+        const unsigned nt0 = blk % NT, sharers = nblk / NT > 0 ? nblk / NT : 1, rank = blk / NT;
+        const unsigned kb = e.Cin / 16, lpf = BN * 32 / 128, nlines = KS * KS * kb * lpf;
+        for (unsigned l = rank * 256 + tid; l < nlines; l += sharers * 256) {
+            const unsigned f = l / lpf, ln = l - f * lpf;
+            const unsigned off = (f / kb) * tap_stride + (f % kb) * blk_stride + nt0 * BN * 32 + ln * 128;
+            warm ^= (unsigned)__builtin_amdgcn_raw_buffer_load_b32(wrs, (int)off, 0, 0);
+        }
+    }
+    carry_source_compaction(e, sh, blk, nblk);
+
+    for (int u = (int)blk; u < work_items; u += (int)nblk) {
+        const int nt = u % NT, mt = u / NT;              // u % 8 picks the XCD: few cout tiles per XCD
+        if (mt >= ntiles) continue;
+        const int n0 = nt * BN;
+        __syncthreads();                                  // previous tile is done with LDS
+        int tot, wyA, wyB, cxA, cxB;                      // entries; window rows and source columns the tile spans
+        constexpr int NRF = (Cfg::CAP + 255) / 256;       // rectangle positions per thread
+        int rpix[NRF];                                    // T2D: source pixel of this thread's positions, -1 outside the view
+        unsigned rflag[NRF];                              //      and its flags, requested together with those of the prologue
+        int pub_seg = -1, pub_off = -1;
+        if constexpr (T2D) {
+            const int ty = mt / tiles_x, tx = mt - ty * tiles_x;
+            wyA = ty * th;
+            wyB = (wyA + th < e.Hp ? wyA + th : e.Hp) - 1;
+            cxA = tx * tw - e.bx0;
+            cxB = (tx * tw + tw < e.Wp ? tx * tw + tw : e.Wp) - 1 - e.bx0;
+            const int ry0 = wyA - e.by0 - e.pad, rx0 = cxA - e.pad, rw = cxB - cxA + KS, rn = (wyB - wyA + KS) * rw;
+#pragma unroll
+            for (int j = 0; j < NRF; ++j) {
+                const int pos = tid + 256 * j;
+                const int ry = pos / rw, iy = ry0 + ry, ix = rx0 + pos - ry * rw;
+                const bool ok = pos < rn && iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW;
+                rpix[j] = ok ? iy * e.sW + ix : -1;
+                rflag[j] = e.sflags[ok ? rpix[j] : 0];
+            }
+            // every list segment is published by one of the first tiles (there are at least as many tiles as segments):
+            // the flags of its footprints travel with those of the rectangle
+            pub_seg = nt == 0 && mt < edge_segments(e) ? mt : -1;
+            unsigned vm_p = 0;
+            if (pub_seg >= 0) {
+                const int p = pub_seg * kSegPixels + tid, qy = p / e.Wp, qx = p - qy * e.Wp;
+                const bool in_seg = p < nwin;              // (threads beyond the window read the flags of pixel (0, 0): unused)
+                vm_p = tap_mask(e, in_seg ? qy - e.by0 : 0, in_seg ? qx - e.bx0 : 0);
+            }
+            // the rectangle: source pixel of every position, -1 where it is out of view or not updated
+#pragma unroll
+            for (int j = 0; j < NRF; ++j) {
+                const int pos = tid + 256 * j;
+                if (pos < rn) s_pix[pos] = rpix[j] >= 0 && (rflag[j] & kFlagM) ? rpix[j] : -1;
+            }
+            __syncthreads();
+            tot = tile_prologue_2d(e, ty * th, tx * tw, th, tw, s_pix, rw, pub_seg, vm_p, pub_off, s_wy, s_wx, sh);
+            if (tot <= 0) tile_effects_2d(e, 0, false, pub_seg, pub_off, s_wy, s_wx, sh);
+        } else {
+            const int seg = mt / NSUB, sub_lo = (mt % NSUB) * SUB;
+            tot = tile_prologue_sub(e, seg, sub_lo, SUB, nt == 0 && sub_lo == 0, nt == 0, s_wy, s_wx, sh);
+            // the source rectangle this index range reads (block-uniform)
+            const int a = seg * kSegPixels + sub_lo;
+            const int last = (a + SUB < nwin ? a + SUB : nwin) - 1;
+            wyA = a / e.Wp; wyB = last / e.Wp;
+            cxA = wyA == wyB ? a - wyA * e.Wp - e.bx0 : -e.bx0;
+            cxB = wyA == wyB ? last - wyA * e.Wp - e.bx0 : e.Wp - 1 - e.bx0;
+        }
+        if (tot <= 0) continue;
+        if (!T2D && tid == 0 && nt == 0) add_macs(e, sh[4], 0);
+        const int iy0 = wyA - e.by0 - e.pad, ix0 = cxA - e.pad;
+        const int RW = cxB - cxA + KS, npos = (wyB - wyA + KS) * RW;       // npos <= CAP: checked by the host
+        if constexpr (!T2D) {                             // (rectangular tiles: s_pix was filled ahead of the prologue)
+            for (int pos = tid; pos < npos; pos += 256) {
+                const int ry = pos / RW, rx = pos - ry * RW;
+                const int iy = iy0 + ry, ix = ix0 + rx;
+                const bool ok = iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW && (e.sflags[iy * e.sW + ix] & kFlagM);
+                s_pix[pos] = ok ? iy * e.sW + ix : -1;
+            }
+            __syncthreads();
+        }
+        const int nrt = (tot + 31) >> 5;                  // live 32-entry row tiles of the tile
+        const int mylive = nrt > wm ? (nrt - wm + WMV - 1) / WMV : 0;      // of this wave: row tiles wm, wm + WMV, ...
+
+        // staging: piece q = tid + 256 j is 16 bytes of staged pixel q / CPR (q / CPR < CAP: inside the buffer).
+        // Dead pieces (outside the rectangle, out of view, not updated) are loaded from beyond the end of the
+        // delta map, which a buffer load answers with zeros, and stored like the others: no predicates.
+        f16x8 hreg[NLD];
+        unsigned hsrc[NLD];                               // byte offsets into the delta map
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            const int q = tid + 256 * j, pos = q / CPR;
+            const int pix = pos < npos ? s_pix[pos] : -1;
+            hsrc[j] = pix >= 0 ? ((unsigned)pix * (unsigned)e.Cin + (q % CPR) * 8) * 2u : 0x80000000u;
+        }
+        auto halo_store = [&]() {
+#pragma unroll
+            for (int j = 0; j < NLD; ++j) {
+                const int q = tid + 256 * j;
+                *reinterpret_cast<f16x8*>(halo + (q / CPR) * LDK + (q % CPR) * 8) = hreg[j];
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) hreg[j] = buf_load16(drs, hsrc[j], 0u);
+        halo_store();
+
+        f32x16 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        int rowoff[TM];                                   // this lane's staged row per row tile (halves)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int r = (i * WMV + wm) * 32 + r32;
+            rowoff[i] = kh * 8 + wk * 16 + (r < tot ? ((s_wy[r] - e.by0 - e.pad - iy0) * RW + (s_wx[r] - e.bx0 - e.pad - ix0)) * LDK : 0);
+        }
+        const unsigned wlane = (unsigned)(r32 * 16 + kh * 8) * 2u;                      // this lane's bytes within a fragment
+        const unsigned wwave = ((unsigned)wk * (unsigned)e.Cout + (unsigned)n0) * 32u;   // this wave's K block and cout tile
+        __syncthreads();
+
+        // The K loop for L live row tiles of this wave.  Step i of a chunk: tap i / MB,
+        // 16-channel block wk + WK * (i % MB) of the chunk.
+        auto kloop = [&](auto lc) {
+            constexpr int L = decltype(lc)::value;
+            constexpr int D = Cfg::RING;
+            constexpr int FBR = TM > 4 ? 2 : 3;                      // sets of staged-row fragments in flight
+            f16x8 fa[D][TN], fb[FBR][L > 0 ? L : 1];
+            auto load_a = [&](int slot, int c, int i) {              // i may run into the next chunk
+                const int cc = i < NS ? c : (c + 1 < nchunks ? c + 1 : c), ii = i < NS ? i : i - NS;
+                const unsigned src = wwave + (unsigned)(ii / MB) * tap_stride + (unsigned)(cc * KB + WK * (ii % MB)) * blk_stride;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fa[slot][j] = buf_load16(wrs, wlane, src + (unsigned)j * 32u * 32u);
+            };
+            auto load_b = [&](int slot, int i) {
+                const int tap = i / MB;
+                const f16* hb = halo + ((tap / KS) * RW + tap % KS) * LDK + WK * (i % MB) * 16;
+#pragma unroll
+                for (int t = 0; t < L; ++t) fb[slot][t] = *reinterpret_cast<const f16x8*>(hb + rowoff[t]);
+            };
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i) load_a(i, 0, i);
+            for (int c = 0; c < nchunks; ++c) {
+                const int cn = c + 1 < nchunks ? c + 1 : c;          // the last chunk re-reads itself: no branch
+                const unsigned hc = (unsigned)cn * KC * 2u;
+#pragma unroll
+                for (int i = 0; i < FBR - 1; ++i) load_b(i, i);
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    if (Cfg::RING <= 3 && i < Cfg::NLS) { // staging loads of the next chunk, a few per step
+#pragma unroll
+                        for (int j = i * Cfg::LPS; j < (i + 1) * Cfg::LPS && j < NLD; ++j)
+                            hreg[j] = buf_load16(drs, hsrc[j], hc);
+                    }
+                    load_a((i + D - 1) % D, c, i + D - 1);
+                    if (i + FBR - 1 < NS) load_b((i + FBR - 1) % FBR, i + FBR - 1);
+#pragma unroll
+                    for (int t = 0; t < L; ++t)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i % D][j], fb[i % FBR][t], acc[t][j], 0, 0, 0);
+                    // the loads just issued (for later steps) stay ahead of these MFMAs and are
+                    // spread between them: one LDS read, one global load, a quarter of the MFMAs
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                       // one LDS read
+                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                       // one global load
+                        __builtin_amdgcn_sched_group_barrier(0x008, (L * TN + 3) / 4, 0);        // a quarter of the MFMAs
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();                          // everyone is done reading the staged chunk
+                if (c + 1 < nchunks) {
+                    if constexpr (Cfg::RING > 3) {        // deep weight ring: the registers go to it, the next chunk is
+                                                          // fetched here (the weight loads of its first steps are in flight)
+#pragma unroll
+                        for (int j = 0; j < NLD; ++j) hreg[j] = buf_load16(drs, hsrc[j], hc);
+                    }
+                    halo_store();
+                    __syncthreads();
+                }
+            }
+        };
+        switch (mylive) {
+            case 0: kloop(std::integral_constant<int, 0>{}); break;
+            case 1: kloop(std::integral_constant<int, 1>{}); break;
+            case 2: kloop(std::integral_constant<int, TM >= 2 ? 2 : TM>{}); break;
+            case 3: kloop(std::integral_constant<int, (TM > 4 ? 4 : TM >= 3 ? 3 : TM)>{}); break;    // rounded up: dead tiles are not stored
+            case 4: kloop(std::integral_constant<int, (TM >= 4 ? 4 : TM)>{}); break;
+            default: kloop(std::integral_constant<int, TM>{}); break;
+        }
+
+        // K-split partial sums -> LDS [entry][cout].  Every element is added up in a fixed
+        // order of the K waves: with four K waves over all rows, wave w takes quarter
+        // (w + p) % 4 of the rows in phase p (all waves busy in every phase); otherwise
+        // the K waves take turns.
+        auto put = [&](int i, bool add) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                float* dst = sC + ((i * WMV + wm) * 32 + r32) * LDC + j * 32 + 4 * kh;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+                    if (add) {
+                        const float4 o = *reinterpret_cast<const float4*>(dst + 8 * g);
+                        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+                    }
+                    *reinterpret_cast<float4*>(dst + 8 * g) = v;
+                }
+            }
+        };
+        if constexpr (WK == 4 && WMV == 1 && TM % 4 == 0) {
+#pragma unroll
+            for (int ph = 0; ph < 4; ++ph) {
+                const int q = (wk + ph) & 3;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    if (i / (TM / 4) == q && i < mylive) put(i, ph > 0);
+                __syncthreads();
+            }
+        } else {
+#pragma unroll
+            for (int kq = 0; kq < WK; ++kq) {
+                if (wk == kq) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        if (i < mylive) put(i, kq > 0);
+                }
+                __syncthreads();
+            }
+        }
+        // P <- P + sum: all reads of P go out first (their latency is paid once), then the stores
+        constexpr int TPR = BN / 8;                        // threads per entry, 8 couts each
+        constexpr int RPP = 256 / TPR, NPASS = (SUB + RPP - 1) / RPP;
+        const int c8 = (tid % TPR) * 8;
+        f16x8 pold[NPASS];
+        f16* pp[NPASS];
+#pragma unroll
+        for (int t = 0; t < NPASS; ++t) {
+            const int row = tid / TPR + t * RPP;
+            const int rr = row < tot ? row : 0;             // dead rows read entry 0 and store nothing
+            pp[t] = (f16*)e.P + pdst_offset(e, s_wy[rr], s_wx[rr]) + n0 + c8;
+            pold[t] = *reinterpret_cast<const f16x8*>(pp[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < NPASS; ++t) {
+            const int row = tid / TPR + t * RPP;
+            if (row < tot) {
+                const float4 v0 = *reinterpret_cast<const float4*>(sC + row * LDC + c8);
+                const float4 v1 = *reinterpret_cast<const float4*>(sC + row * LDC + c8 + 4);
+                const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                f16x8 o = pold[t];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) o[q] = (f16)((float)o[q] + v[q]);
+                *reinterpret_cast<f16x8*>(pp[t]) = o;
+            }
+        }
+        if constexpr (T2D) tile_effects_2d(e, tot, nt == 0, pub_seg, pub_off, s_wy, s_wx, sh);
+    }
+    if (warm == 0x9e3779b9u && work_items < 0) e.ccnt[0] = 0;     // (keeps the loads above)
+}
+
+}  // namespace mdcnn

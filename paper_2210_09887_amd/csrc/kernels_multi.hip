@@ -1,0 +1,72 @@
+// Convolutions of several independent edges in one launch: the branches of a multi-resolution network between two fusion
+// points.  Each is a launch of 12 to 110 blocks that takes the latency of one tile (about 12 us, whatever its size), so one
+// after the other they leave the chip idle and cost the host a launch each; on streams of their own every crossing costs
+// an event.  A block finds its edge by its number and runs the tile its edge would run alone: the results are the same bits.
+#include <atomic>
+
+#include "conv_tiles.h"
+
+namespace mdcnn {
+
+__global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
+    int j = 0;
+    while (j + 1 < m.n && blockIdx.x >= m.job[j + 1].block0) ++j;
+    const ConvJob& jb = m.job[j];
+    const unsigned blk = blockIdx.x - jb.block0;
+    if (blk >= jb.blocks) return;                         // (the numbers between two edges, up to a multiple of 8)
+    const ConvVid& v = m.vid[j * gridDim.z + blockIdx.z];
+    EdgeDev e = jb.e;
+    auto at = [](auto*& p, long long d) {
+        if (p) p = (std::remove_reference_t<decltype(p)>)((uintptr_t)p + (uintptr_t)d);
+    };
+    at(e.delta, v.sd); at(e.sflags, v.sd); at(e.pub_list, v.sd); at(e.pub_lcnt, v.sd); at(e.pub_lacc, v.sd); at(e.scounters, v.sd);
+    at(e.P, v.dd); at(e.dflags, v.dd); at(e.clist, v.dd); at(e.ccnt, v.dd); at(e.cacc, v.dd); at(e.dcounters, v.dd);
+    e.p_oy = v.p_oy;
+    e.p_ox = v.p_ox;
+    const int NT = jb.NT, items = jb.items, p0 = jb.p0, p1 = jb.p1;
+    const unsigned nblk = jb.blocks;
+#define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
+    case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
+        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, NT, items, p0, p1);                      \
+        break;
+#define TILED(WM, WN, TM, TN, KC)                                                                                         \
+    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, NT, items, p0); break;
+    switch (jb.body) {
+        HALO(2, 2, 2, 2, 1, 32, 3, 3, true)
+        HALO(2, 2, 2, 2, 1, 64, 6, 6, true)
+        HALO(2, 2, 2, 2, 2, 64, 6, 6, true)
+        HALO(4, 2, 2, 1, 1, 32, 2, 9, true)
+        HALO(4, 1, 4, 2, 1, 64, 4, 9, true)
+        HALO(4, 1, 4, 2, 2, 64, 4, 9, true)
+        HALO(4, 2, 2, 1, 1, 32, 6, 9, false)
+        HALO(4, 1, 4, 2, 1, 64, 9, 9, false)
+        HALO(4, 1, 4, 2, 2, 64, 9, 9, false)
+        HALO(2, 2, 2, 2, 2, 64, 11, 6, false)
+        TILED(2, 2, 1, 1, 32) TILED(2, 2, 1, 1, 64) TILED(2, 2, 1, 1, 128)
+        TILED(4, 1, 1, 1, 32) TILED(4, 1, 1, 1, 64) TILED(4, 1, 1, 1, 128)
+        TILED(2, 2, 2, 1, 32) TILED(2, 2, 2, 1, 64) TILED(2, 2, 2, 1, 128)
+        TILED(2, 2, 1, 2, 32) TILED(2, 2, 1, 2, 64) TILED(2, 2, 1, 2, 128)
+        default: break;
+    }
+#undef HALO
+#undef TILED
+}
+
+hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_t st) {
+    unsigned blocks = 0;
+    for (int j = 0; j < m.n; ++j) {
+        m.job[j].block0 = blocks;
+        blocks += (m.job[j].blocks + 7u) & ~7u;
+    }
+    static std::atomic<bool> attr_set{false};
+    if (smem > 32768 && !attr_set.load(std::memory_order_acquire)) {
+        const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv_multi), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        if (err != hipSuccess) { (void)hipGetLastError(); return err; }    // do not leave it for the next call to report
+        attr_set.store(true, std::memory_order_release);
+    }
+    if (smem > 80u * 1024u) return hipErrorInvalidValue;
+    k_conv_multi<<<dim3(blocks, 1, (unsigned)videos), dim3(256), smem, st>>>(m);
+    return hipGetLastError();
+}
+
+}  // namespace mdcnn

@@ -2,6 +2,8 @@
 // pixels, delta + truncation + mask (input and inner sites), view-ordered
 // readout.  (Compaction lives with its consumer, the convolution kernels.)
 // gfx950 only: 64-wide wavefronts, ballot/popcount compaction, 16-byte accesses.
+#include <type_traits>
+
 #include "mdcnn_internal.h"
 
 namespace mdcnn {
@@ -56,7 +58,7 @@ __device__ __forceinline__ size_t skip_offset(const SkipDev& k, int vy, int vx, 
 // new padded window outside the kept rectangle get P = bias (the activation
 // adds it later on); pixels of the new view outside the kept rectangle get
 // A = 0 and flag N (sites with crops: state "unseen" in their ring S and a zero
-// previous pooling output).  Per-frame counters are cleared here.
+// previous pooling output).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void decode_new(int Wn, int Hn, int y0, int y1, int x0, int x1, int idx, int& y, int& x) {
     const int top = y0 * Wn;
@@ -468,6 +470,51 @@ static hipError_t step1_t(const Args& a, const SiteDev& s, int n, unsigned extra
 
 hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
     return bt.s[0].dtype == MDCNN_F16 ? step1_t<f16>(bt, bt.s[0], n, 0u, st) : step1_t<float>(bt, bt.s[0], n, 0u, st);
+}
+
+// Step 1 of several sites that do not depend on each other (see k_conv_multi): one 16-byte chunk per lane, fp16.
+__global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
+    int j = 0;
+    while (j + 1 < m.n && blockIdx.x >= m.job[j + 1].block0) ++j;
+    const Step1Job& jb = m.job[j];
+    const Step1Vid& v = m.vid[j * gridDim.z + blockIdx.z];
+    SiteDev s = jb.s;
+    SkipDev k = jb.skip;
+    auto at = [](auto*& p, long long d) {
+        if (p) p = (std::remove_reference_t<decltype(p)>)((uintptr_t)p + (uintptr_t)d);
+    };
+    at(s.A, v.sd); at(s.P, v.sd); at(s.flags, v.sd); at(s.delta, v.sd);
+    s.a_oy = v.a_oy; s.a_ox = v.a_ox; s.p_oy = v.p_oy; s.p_ox = v.p_ox; s.cy = v.cy; s.cx = v.cx;
+    at(k.P, v.kd); at(k.dflags, v.kd);
+    k.p_oy = v.k_oy; k.p_ox = v.k_ox;
+    const unsigned blk = blockIdx.x - jb.block0;
+    const f16* const X = nullptr;
+    switch (jb.G) {
+        case 1: step1_block<f16, 1, 1>(s, k, X, nullptr, blk); break;
+        case 2: step1_block<f16, 2, 1>(s, k, X, nullptr, blk); break;
+        case 4: step1_block<f16, 4, 1>(s, k, X, nullptr, blk); break;
+        case 8: step1_block<f16, 8, 1>(s, k, X, nullptr, blk); break;
+        case 16: step1_block<f16, 16, 1>(s, k, X, nullptr, blk); break;
+        case 32: step1_block<f16, 32, 1>(s, k, X, nullptr, blk); break;
+        default: step1_block<f16, 64, 1>(s, k, X, nullptr, blk); break;
+    }
+}
+
+bool step1_multi_applies(const SiteDev& s) {
+    int G = 0, CH = 0;
+    return s.dtype == MDCNN_F16 && s.kind == MDCNN_SITE_PREACT && step1_shape(s.C, V16<f16>::N, G, CH) && CH == 1;
+}
+
+hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
+    unsigned blocks = 0;
+    for (int j = 0; j < m.n; ++j) {
+        int CH = 0;
+        if (!step1_shape(m.job[j].s.C, V16<f16>::N, m.job[j].G, CH) || CH != 1) return hipErrorInvalidValue;
+        m.job[j].block0 = blocks;
+        blocks += step1_blocks_of(m.job[j].s);
+    }
+    k_step1_multi<<<dim3(blocks, 1, (unsigned)videos), dim3(256), 0, st>>>(m);
+    return hipGetLastError();
 }
 
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st) {

@@ -184,13 +184,28 @@ struct PipePlan {
     int stream_of(int frame, int call) const { return mode ? frame % streams : seg_of_call[(size_t)call]; }
 };
 
+// Launches of a frame when independent ones are put together (k_step1_multi, k_conv_multi): rounds of operations of one
+// kind that do not depend on each other, in an order that keeps the sequence of writers of every site.
+struct RoundOp {
+    int site, edge;            // edge < 0: step 1 of the site (-1), or the compaction-only launch of its forward call (-2)
+    int skip;                  // step 1: edge whose residual add it does, or -1
+    bool first;                // the edge that also compacts the source's update mask
+};
+struct RoundPlan {
+    int key = -1;              // g_fuse_skip the plan was made for
+    int n_ops = 0;
+    std::vector<std::vector<RoundOp>> rounds;
+    bool shorter(int of, int than) const { return (int)rounds.size() * of < n_ops * than; }
+};
+
 struct mdcnn_net {
     std::vector<mdcnn_buffer*> sites;
     std::vector<int> esrc, edst;
     std::vector<mdcnn_conv_desc> edges;
     size_t out_bytes;
     Plan plan;
-    PipePlan pipe;
+    RoundPlan rounds;
+    PipePlan pipe, pipe_rounds;
 };
 
 namespace {
@@ -313,6 +328,30 @@ mdcnn_status validate_forward(const mdcnn_buffer* in, const void* frame, const u
 // fuse_skip: index of an identity edge whose add is done by the step-1 kernel (its
 // destination is touched there and the edge gets no launch of its own), or -1.
 // riders (n == 1 only): jobs[riders[0 .. n_riders)] are run by spare blocks of the step-1 launch.
+// Fills in step 1 of site `in` for one video; skip_dst: destination of a residual add it does, or nullptr.
+void set_step1(Step1Batch& sb, int b, const mdcnn_buffer* in, const mdcnn_buffer* skip_dst, const void* X, const uint8_t* forced) {
+    sb.s[b] = in->dev;
+    sb.X[b] = X;
+    sb.forced[b] = forced;
+    SkipDev& k = sb.skip[b];
+    k = SkipDev{};
+    if (!skip_dst) return;
+    k.P = skip_dst->dev.P;
+    k.dflags = skip_dst->d.kind == MDCNN_SITE_OUTPUT ? nullptr : skip_dst->dev.flags;
+    k.Hp = skip_dst->L.Hp; k.Wp = skip_dst->L.Wp; k.by0 = skip_dst->d.border[0]; k.bx0 = skip_dst->d.border[2];
+    k.p_oy = skip_dst->dev.p_oy; k.p_ox = skip_dst->dev.p_ox;
+}
+EdgeDev compact_only(const mdcnn_buffer* in) {             // a forward call without an edge of its own
+    EdgeDev e{};
+    e.sflags = in->dev.flags; e.sH = in->d.H; e.sW = in->d.W;
+    e.scounters = in->dev.counters;
+    e.k = -1;
+    return e;
+}
+void set_source_list(EdgeDev& e, const mdcnn_buffer* in) {
+    e.pub_list = in->dev.list; e.pub_lcnt = in->dev.lcnt; e.pub_lacc = in->dev.lacc;
+}
+
 // Streams and events of one multi-stream frame.  Every wait is on an event that was recorded
 // earlier in the same call, so no stream can wait for something that never happens.
 constexpr int kMaxStreams = 4;
@@ -355,20 +394,8 @@ mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* fram
                         const int* riders = nullptr, int n_riders = 0, const ListScratch* ls = nullptr) {
     static thread_local Step1Batch sb;                     // 3.4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
-    for (int b = 0; b < n; ++b) {
-        sb.s[b] = ins[b]->dev;
-        sb.X[b] = frames ? frames[b] : nullptr;
-        sb.forced[b] = forced ? forced[b] : nullptr;
-        sb.skip[b] = SkipDev{};
-        if (fuse_skip >= 0) {
-            const mdcnn_buffer* d = outs[b][fuse_skip];
-            SkipDev& k = sb.skip[b];
-            k.P = d->dev.P;
-            k.dflags = d->d.kind == MDCNN_SITE_OUTPUT ? nullptr : d->dev.flags;
-            k.Hp = d->L.Hp; k.Wp = d->L.Wp; k.by0 = d->d.border[0]; k.bx0 = d->d.border[2];
-            k.p_oy = d->dev.p_oy; k.p_ox = d->dev.p_ox;
-        }
-    }
+    for (int b = 0; b < n; ++b)
+        set_step1(sb, b, ins[b], fuse_skip >= 0 ? outs[b][fuse_skip] : nullptr, frames ? frames[b] : nullptr, forced ? forced[b] : nullptr);
     hipError_t err;
     if (ins[0]->d.truncation_free) {
         // step 1 happened in the producer's launch; initialisation jobs that would have ridden along get a launch of their own
@@ -410,17 +437,13 @@ mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* fram
         return MDCNN_OK;
     };
     auto with_source_list = [&](EdgeDev& e, const mdcnn_buffer* in) {
-        e.pub_list = in->dev.list; e.pub_lcnt = in->dev.lcnt; e.pub_lacc = in->dev.lacc;
+        set_source_list(e, in);
         if (ls) { e.pub_list = ls->list; e.pub_lcnt = ls->lcnt; e.pub_lacc = ls->lacc; }
     };
     if (n_edges == 0 || (n_edges == 1 && fuse_skip == 0)) {
         for (int b = 0; b < n; ++b) {
-            EdgeDev e{};
-            e.sflags = ins[b]->dev.flags; e.sH = ins[b]->d.H; e.sW = ins[b]->d.W;
-            e.scounters = ins[b]->dev.counters;
-            with_source_list(e, ins[b]);
-            e.k = -1;
-            eb.d[b] = e;
+            eb.d[b] = compact_only(ins[b]);
+            with_source_list(eb.d[b], ins[b]);
         }
         return launch_edge(-1);
     }
@@ -532,6 +555,67 @@ void make_plan(const mdcnn_net* net, int ns, Plan& plan) {
     for (const PlanNode& nd : plan.nodes) plan.streams = nd.stream + 1 > plan.streams ? nd.stream + 1 : plan.streams;
 }
 
+// Rounds of a frame.  Every launch reads its source site and reads and writes its destination site (step 1: its own site
+// and the destination of a fused skip); it can go as soon as the operations before it in program order that conflict with
+// it have gone, so writers of one site keep their order and the sums of P theirs.  A round takes every operation of one
+// kind that can go, the kind being the one the last round was not of (branches that have come out of step by a launch
+// fall into step again).
+void make_rounds(const mdcnn_net* net, RoundPlan& rp) {
+    struct Op { RoundOp op; int kind; std::vector<int> after; bool done; };
+    std::vector<Op> ops;
+    const int n_sites = (int)net->sites.size(), n_edges = (int)net->edges.size();
+    std::vector<int> lastw((size_t)n_sites, -1);
+    std::vector<std::vector<int>> readers((size_t)n_sites);    // since the last writer
+    auto add = [&](RoundOp op, int kind, int read, std::initializer_list<int> writes) {
+        Op o{op, kind, {}, false};
+        const int id = (int)ops.size();
+        if (read >= 0 && lastw[(size_t)read] >= 0) o.after.push_back(lastw[(size_t)read]);
+        for (int w : writes) {
+            if (w < 0) continue;
+            if (lastw[(size_t)w] >= 0) o.after.push_back(lastw[(size_t)w]);
+            for (int r : readers[(size_t)w]) o.after.push_back(r);
+        }
+        if (read >= 0) readers[(size_t)read].push_back(id);
+        for (int w : writes)
+            if (w >= 0) { lastw[(size_t)w] = id; readers[(size_t)w].clear(); }
+        ops.push_back(std::move(o));
+    };
+    int e0 = 0;
+    for (int i = 0; i < n_sites; ++i) {
+        if (net->sites[(size_t)i]->d.kind == MDCNN_SITE_OUTPUT) continue;
+        int e1 = e0;
+        while (e1 < n_edges && net->esrc[(size_t)e1] == i) ++e1;
+        const int fuse = fused_skip(net, e0, e1);
+        // (a truncation-free site has no step 1: its producer did it)
+        if (!net->sites[(size_t)i]->d.truncation_free)
+            add({i, -1, fuse >= 0 ? e0 + fuse : -1, false}, 0, -1, {i, fuse >= 0 ? net->edst[(size_t)(e0 + fuse)] : -1});
+        bool first = true;
+        for (int e = e0; e < e1; ++e) {
+            if (e - e0 == fuse) continue;
+            add({i, e, -1, first}, 1, i, {net->edst[(size_t)e]});
+            first = false;
+        }
+        if (first) add({i, -2, -1, true}, 1, i, {});
+        e0 = e1;
+    }
+    rp.rounds.clear();
+    rp.n_ops = (int)ops.size();
+    int left = rp.n_ops, last_kind = 1;
+    while (left) {
+        std::vector<int> ready[2];
+        for (int k = 0; k < (int)ops.size(); ++k) {
+            if (ops[(size_t)k].done) continue;
+            bool ok = true;
+            for (int d : ops[(size_t)k].after) ok &= ops[(size_t)d].done;
+            if (ok) ready[ops[(size_t)k].kind].push_back(k);
+        }
+        const int kind = !ready[1 - last_kind].empty() ? 1 - last_kind : last_kind;
+        rp.rounds.emplace_back();
+        for (int k : ready[kind]) { rp.rounds.back().push_back(ops[(size_t)k].op); ops[(size_t)k].done = true; --left; }
+        last_kind = kind;
+    }
+}
+
 // Length of a plan in launches, if every launch took one unit of time and a wait for another
 // stream one more (measured: such a wait costs about as much as a small launch).  These
 // launches are bound by their latency, not by the size of the GPU, so this is the time a frame
@@ -554,6 +638,21 @@ double plan_length(const Plan& plan) {
 void choose_plan(const mdcnn_net* net, int streams, Plan& plan) {
     make_plan(net, streams ? streams : kMaxStreams, plan);
     if (!streams && plan_length(plan) > 0.8 * (double)plan.nodes.size()) make_plan(net, 1, plan);
+}
+
+// Whether frames of a network run in rounds: left to itself (MDCNN_OPT_STREAMS = 0) the library puts independent launches
+// together, instead of spreading them over streams, wherever there are any - frames in flight (`overlap`) only where
+// that shortens the frame by a fifth: the frames beside it fill the gaps as well, and what initialises sites gets launches
+// of its own.  (The profiling mode times every launch by itself.)
+// 384 x 288 HRNet-like network: a frame 1 213 -> 657 us (178 launches -> 76), frames in flight 647 -> 266 us, 8 videos 1 914 ->
+// 1 420 us; ResNet-18-style network (a projection beside the first convolution of a block, 3 launches of 37): 518 -> 476 us.
+bool use_rounds(mdcnn_net* net, bool overlap = false) {
+    if (g_streams != 0 || g_profile || net->sites[0]->d.dtype != MDCNN_F16) return false;
+    if (net->rounds.key != g_fuse_skip) {
+        make_rounds(net, net->rounds);
+        net->rounds.key = g_fuse_skip;
+    }
+    return overlap ? net->rounds.shorter(5, 4) : net->rounds.shorter(1, 1);
 }
 
 // The library's own streams (per host thread, default priority, made on first use) and events.
@@ -683,6 +782,83 @@ size_t crop_pixels(const mdcnn_buffer* b) {                // sites without crop
 }
 bool whole_view(const mdcnn_buffer* b) { return crop_pixels(b) == (size_t)b->d.H * b->d.W; }
 
+// One round of a plan for n videos (n <= kMaxBatch): sites[b] are the sites of video b as the frame sees them.
+// Operations the multi-edge kernels do not take get a launch each.
+mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets, int n, const std::vector<mdcnn_buffer* const*>& sites,
+                       const void* const* frames, const uint8_t* const* forced, hipStream_t st) {
+    static thread_local Step1Batch sb;                     // 3.4 to 4 KiB each: kept off the stack
+    static thread_local EdgeBatch eb;
+    static thread_local Step1Multi sm;
+    static thread_local ConvMulti cm;
+    const mdcnn_net* net = nets[0];
+    sm.n = cm.n = 0;
+    unsigned smem = 0;
+    auto dist = [](const void* p, const void* q) { return (long long)((intptr_t)p - (intptr_t)q); };
+    hipError_t err = hipSuccess;
+    int cls = 0;
+    auto flush_step1 = [&] {
+        if (sm.n && err == hipSuccess) err = launch_step1_multi(sm, n, st);
+        sm.n = 0;
+    };
+    auto flush_conv = [&] {
+        if (cm.n && err == hipSuccess) err = launch_conv_multi(cm, n, smem, st);
+        cm.n = 0;
+        smem = 0;
+    };
+    for (const RoundOp& op : round) {
+        if (op.edge == -1) {
+            const mdcnn_buffer* in0 = sites[0][op.site];
+            const int sd = op.skip >= 0 ? net->edst[(size_t)op.skip] : -1;
+            for (int b = 0; b < n; ++b)
+                set_step1(sb, b, sites[(size_t)b][op.site], sd >= 0 ? sites[(size_t)b][sd] : nullptr, op.site == 0 && frames ? frames[b] : nullptr,
+                          op.site == 0 && forced ? forced[b] : nullptr);
+            if (round.size() == 1 || !step1_multi_applies(in0->dev)) {
+                err = launch_step1(sb, n, st);
+            } else {
+                if (sm.n == kMaxMultiJobs || (sm.n + 1) * n > kMaxStep1Vids) flush_step1();
+                Step1Job& j = sm.job[sm.n];
+                j.s = sb.s[0];
+                j.skip = sb.skip[0];
+                for (int b = 0; b < n; ++b) {
+                    const SiteDev& s = sb.s[b];
+                    sm.vid[sm.n * n + b] = Step1Vid{dist(s.A, j.s.A), dist(sb.skip[b].P, j.skip.P), s.a_oy, s.a_ox, s.p_oy, s.p_ox,
+                                                    sb.skip[b].p_oy, sb.skip[b].p_ox, s.cy, s.cx};
+                }
+                ++sm.n;
+            }
+        } else {
+            ConvPick pick{};
+            pick.body = -1;
+            bool same_weights = true;
+            for (int b = 0; b < n; ++b) {
+                const mdcnn_buffer* in = sites[(size_t)b][op.site];
+                if (op.edge < 0) eb.d[b] = compact_only(in);
+                else eb.d[b] = make_edge(in, sites[(size_t)b][net->edst[(size_t)op.edge]], nets[b]->edges[(size_t)op.edge]);
+                if (op.first) set_source_list(eb.d[b], in);
+                same_weights &= eb.d[b].w == eb.d[0].w && eb.d[b].wp == eb.d[0].wp;
+            }
+            const int dtype = sites[0][op.site]->d.dtype;
+            if (round.size() > 1 && same_weights) err = launch_conv(eb, n, dtype, g_conv_path, st, &cls, &pick);
+            if (err == hipSuccess && pick.body < 0) {
+                err = launch_conv(eb, n, dtype, g_conv_path, st, &cls);
+            } else if (err == hipSuccess) {
+                if (cm.n == kMaxMultiJobs || (cm.n + 1) * n > kMaxConvVids) flush_conv();
+                ConvJob& j = cm.job[cm.n];
+                j.e = eb.d[0];
+                j.body = pick.body; j.NT = pick.NT; j.items = pick.items; j.p0 = pick.p0; j.p1 = pick.p1; j.blocks = pick.blocks;
+                for (int b = 0; b < n; ++b)
+                    cm.vid[cm.n * n + b] = ConvVid{dist(eb.d[b].delta, j.e.delta), dist(eb.d[b].P, j.e.P), eb.d[b].p_oy, eb.d[b].p_ox};
+                smem = pick.smem > smem ? pick.smem : smem;
+                ++cm.n;
+            }
+        }
+        if (err != hipSuccess) break;
+    }
+    flush_step1();
+    flush_conv();
+    return err == hipSuccess ? MDCNN_OK : fail(MDCNN_ERR_HIP, "launch of a round: %s", hipGetErrorString(err));
+}
+
 // Shift, forward over all non-terminal sites, readout: for n streams at once.
 mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frames, const uint8_t* const* forced,
                          const int* dty, const int* dtx, void* const* outs_dev, void* stream, int* did_full_reset) {
@@ -708,7 +884,8 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     // them after the shift and joins them before the readout, so to the caller the call is in
     // stream order as before
     Sched sched, *sc = nullptr;
-    if (g_streams != 1) {
+    const bool rounds = use_rounds(net);
+    if (g_streams != 1 && !rounds) {
         const int key = g_streams * 2 + g_fuse_skip;
         if (net->plan.key != key) {
             choose_plan(net, g_streams, net->plan);
@@ -747,7 +924,15 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     mdcnn_buffer* ins[kMaxBatch];
     const mdcnn_conv_desc* edges[kMaxBatch];
     mdcnn_buffer* const* outs[kMaxBatch];
-    for (int i = 0; i < (int)net->sites.size(); ++i) {
+    if (rounds) {
+        std::vector<mdcnn_buffer* const*> sites((size_t)n);
+        for (int b = 0; b < n; ++b) sites[(size_t)b] = nets[b]->sites.data();
+        for (const std::vector<RoundOp>& round : net->rounds.rounds) {
+            mdcnn_status rc = run_round(round, nets, n, sites, frames, forced, st);
+            if (rc) return rc;
+        }
+    }
+    for (int i = 0; !rounds && i < (int)net->sites.size(); ++i) {
         if (net->sites[i]->d.kind == MDCNN_SITE_OUTPUT) continue;
         int e1 = e0;
         while (e1 < n_edges && net->esrc[e1] == i) ++e1;
@@ -866,6 +1051,44 @@ void make_pipe_plan(const mdcnn_net* net, int group_calls, int streams, int mode
         if (pp.forward[(size_t)c] && pp.event_of_call[(size_t)c - 1] < 0) pp.event_of_call[(size_t)c - 1] = pp.n_events++;
 }
 
+// The same for a frame that runs in rounds: "call" c is round c, every frame runs on one stream (mode 1).  The last thing a
+// frame does to a site is the last round with an operation that touches it (the readout for an OUTPUT site).
+void make_pipe_rounds(const mdcnn_net* net, int group_rounds, int streams, PipePlan& pp) {
+    const int n_sites = (int)net->sites.size(), n = (int)net->rounds.rounds.size();
+    pp = PipePlan{};
+    pp.key = (group_rounds * 8 + streams) * 2 + net->rounds.key;
+    pp.streams = streams;
+    pp.mode = 1;
+    auto touched = [&](const RoundOp& op, auto&& f) {
+        f(op.site);
+        if (op.edge >= 0) f(net->edst[(size_t)op.edge]);
+        if (op.skip >= 0) f(net->edst[(size_t)op.skip]);
+    };
+    std::vector<int> last((size_t)n_sites, n);
+    for (int c = 0; c < n; ++c)
+        for (const RoundOp& op : net->rounds.rounds[(size_t)c])
+            touched(op, [&](int s) { if (net->sites[(size_t)s]->d.kind != MDCNN_SITE_OUTPUT) last[(size_t)s] = c; });
+    pp.seg_of_call.assign((size_t)n + 1, 0);
+    pp.forward.assign((size_t)n, 0);
+    pp.event_of_call.assign((size_t)n + 1, -1);
+    std::vector<char> filled((size_t)n_sites, 0);
+    for (int c0 = 0; c0 < n; c0 += group_rounds) {
+        PipeGroup g{c0, c0 + group_rounds < n ? c0 + group_rounds : n, {}, -1};
+        auto fill = [&](int s) {
+            if (filled[(size_t)s]) return;
+            filled[(size_t)s] = 1;
+            g.fill.push_back(s);
+            g.wait_call = last[(size_t)s] > g.wait_call ? last[(size_t)s] : g.wait_call;
+        };
+        for (int c = g.call0; c < g.call1; ++c)
+            for (const RoundOp& op : net->rounds.rounds[(size_t)c]) touched(op, fill);
+        if (g.call1 == n)
+            for (int s = 0; s < n_sites; ++s) fill(s);         // sites nothing leads to are still initialised
+        if (g.wait_call >= 0 && pp.event_of_call[(size_t)g.wait_call] < 0) pp.event_of_call[(size_t)g.wait_call] = pp.n_events++;
+        pp.groups.push_back(g);
+    }
+}
+
 constexpr int kMaxFrames = 4096;
 constexpr int kDefaultDepth = 4;
 constexpr int kMinLaunchesInFlight = 16;   // launches of a frame from which on the default is kDefaultDepth streams
@@ -899,12 +1122,15 @@ mdcnn_status check_mask_params(const mdcnn_mask_params* prm, int Hc, int Wc, siz
 // most: every group costs an event and a wait per frame, and a long network (config 4: 85 calls) is
 // bound by those, while a short one needs the frames to follow each other closely (measured: config 3,
 // 18 calls, 3.3 k frames/s with groups of 1 and 2.8 k with groups of 4; config 4 1.45 k and 1.6 k).
-int pipe_group(const mdcnn_net* net) {
+int pipe_group(int n_calls) {
     if (g_pipe_group) return g_pipe_group;
-    int n_calls = 0;
-    for (const mdcnn_buffer* b : net->sites) n_calls += b->d.kind != MDCNN_SITE_OUTPUT;
     const int g = (n_calls + 10) / 20;
     return g < 1 ? 1 : g > 4 ? 4 : g;
+}
+int pipe_group(const mdcnn_net* net) {
+    int n_calls = 0;
+    for (const mdcnn_buffer* b : net->sites) n_calls += b->d.kind != MDCNN_SITE_OUTPUT;
+    return pipe_group(n_calls);
 }
 
 // What the issue of one frame needs, fixed before anything is issued: the sites as they stand after the
@@ -929,10 +1155,16 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
                        const int* dty, const int* dtx, const int* crops, const FrontEnd* fe, void* const* outs_dev, int depth,
                        hipStream_t user, int* did_full_reset) {
     mdcnn_net* const net = nets[0];
-    const int group = pipe_group(net), key = (group * 8 + depth) * 2 + g_pipe_mode;
-    if (net->pipe.key != key) make_pipe_plan(net, group, depth, g_pipe_mode, net->pipe);
-    const PipePlan& pp = net->pipe;
-    const int n_calls = (int)pp.call_site.size(), n_sites = (int)net->sites.size(), ring = 3;
+    const bool rounds = g_pipe_mode == 1 && use_rounds(net, true);
+    const int group = rounds ? pipe_group((int)net->rounds.rounds.size()) : pipe_group(net);
+    const int key = (group * 8 + depth) * 2 + (rounds ? net->rounds.key : g_pipe_mode);
+    PipePlan& pp_kept = rounds ? net->pipe_rounds : net->pipe;
+    if (pp_kept.key != key) {
+        if (rounds) make_pipe_rounds(net, group, depth, pp_kept);
+        else make_pipe_plan(net, group, depth, g_pipe_mode, pp_kept);
+    }
+    const PipePlan& pp = pp_kept;
+    const int n_calls = (int)pp.forward.size(), n_sites = (int)net->sites.size(), ring = 3;
     // events: ring x n_events for the plan, then one per stream for fork and join
     const size_t ev_sync = (size_t)ring * pp.n_events;
     hipError_t err = aux_prepare(depth, ev_sync + kMaxStreams);
@@ -1010,7 +1242,7 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
     std::vector<char> wanted((size_t)n_calls + 1, 0);
     for (size_t gi = 0; gi < pp.groups.size(); ++gi) {
         const PipeGroup& g = pp.groups[gi];
-        const int carrier = gi ? pp.groups[gi - 1].call1 - 1 : 0;
+        const int carrier = gi && !rounds ? pp.groups[gi - 1].call1 - 1 : 0;
         if (g.wait_call >= 0 && (pp.mode == 1 || pp.seg_of_call[(size_t)g.wait_call] != pp.seg_of_call[(size_t)carrier])) wanted[(size_t)g.wait_call] = 1;
     }
     for (int c = 1; c < n_calls; ++c)
@@ -1052,19 +1284,32 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
             }
             return hipStreamWaitEvent(s[mine], ev_prev[pp.event_of_call[(size_t)g.wait_call]], 0);
         };
+        std::vector<mdcnn_buffer*> flat;
+        std::vector<mdcnn_buffer* const*> sites_of;
+        if (rounds) {
+            for (mdcnn_buffer& b : w.sites) flat.push_back(&b);
+            for (int v = 0; v < nb; ++v) sites_of.push_back(flat.data() + (size_t)v * n_sites);
+        }
         for (size_t gi = 0; gi < pp.groups.size(); ++gi) {
             const PipeGroup& g = pp.groups[gi];
-            if (gi == 0) {
+            if (gi == 0 || rounds) {
                 err = wait_for(g, 0);
                 if (err == hipSuccess) err = launch_fills(g.fill, s[pp.stream_of(f, 0)]);
                 if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: shift launch: %s", f, hipGetErrorString(err));
-                if (fe) {                                      // the input site is initialised: its mask for this frame
+                if (fe && gi == 0) {                           // the input site is initialised: its mask for this frame
                     mdcnn_status rc = mdcnn_input_mask(&w.sites[0], frames[f], fe->roi ? fe->roi[f] : nullptr, fe->prm, fe->masks[f],
                                                        fe->mask_bytes, s[pp.stream_of(f, 0)]);
                     if (rc) return rc;
                 }
             }
-            for (int c = g.call0; c < g.call1; ++c) {
+            for (int c = g.call0; c < g.call1 && rounds; ++c) {
+                const void* const* X = frames + (size_t)f * nb;
+                const uint8_t* const* fm = fe ? (const uint8_t* const*)fe->masks + f : forced ? forced + (size_t)f * nb : nullptr;
+                mdcnn_status rc = run_round(net->rounds.rounds[(size_t)c], nets, nb, sites_of, X, fm, s[pp.stream_of(f, c)]);
+                if (rc) return rc;
+                if (issued(c) != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: event: %s", f, hipGetErrorString(err));
+            }
+            for (int c = g.call0; c < g.call1 && !rounds; ++c) {
                 hipStream_t st = s[pp.stream_of(f, c)];
                 if (c > 0 && pp.forward[(size_t)c] && depth > 1) {            // the calls so far ran on another stream
                     err = hipStreamWaitEvent(st, ev_mine[pp.event_of_call[(size_t)c - 1]], 0);

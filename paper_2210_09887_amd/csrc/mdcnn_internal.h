@@ -22,7 +22,6 @@ constexpr int kStateDirty = 2;    // touched by a producer while outside the cro
 // (unsigned long long*)counters), zeroed when the buffer is first reset.
 constexpr int kCntUpdated = 0;      // pixels updated this frame
 constexpr int kCntCandidates = 1;   // pixels visited by step 1 this frame
-constexpr int kNumPerFrame = 8;
 constexpr int kAccUpdated = 4;      // sum of update counts
 constexpr int kAccCandidates = 5;   // sum of candidate counts
 constexpr int kAccMacs = 6;         // multiply-accumulates of the MFMA kernels into this site (valid taps x Cin x Cout)
@@ -31,6 +30,7 @@ constexpr int kAccMacsPlain = 8;    // multiply-accumulates of the plain-FMA ker
 // The two multiply-accumulate sums are kept as 8 partial sums each (slot + 8 * {1, 2} + block % 8)
 // so that the statistics atomics of a launch do not all hit one address.
 constexpr int kAccMacsSpread = 16;  // [16, 24): MFMA partials, [24, 32): plain partials
+constexpr int kNumPerFrame = 8;
 constexpr int kNumCounters = 64;
 
 // Lists are compacted per segment of kSegPixels consecutive linear indices:
@@ -191,9 +191,80 @@ hipError_t launch_shift_fill(const FillBatch& fb, hipStream_t st);
 hipError_t launch_step1(const Step1Batch& b, int n, hipStream_t st);
 // fills in fill_blocks and the jobs' block_begin
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
+// Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
+// half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
+constexpr int kMultiHaloBodies = 10, kMultiTiledBodies = 12;
+constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc, int nld, int ring, bool t2d) {
+    const int c[kMultiHaloBodies][9] = {
+        {2, 2, 2, 2, 1, 32, 3, 3, 1}, {2, 2, 2, 2, 1, 64, 6, 6, 1}, {2, 2, 2, 2, 2, 64, 6, 6, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1},
+        {4, 1, 4, 2, 1, 64, 4, 9, 1}, {4, 1, 4, 2, 2, 64, 4, 9, 1}, {4, 2, 2, 1, 1, 32, 6, 9, 0}, {4, 1, 4, 2, 1, 64, 9, 9, 0},
+        {4, 1, 4, 2, 2, 64, 9, 9, 0}, {2, 2, 2, 2, 2, 64, 11, 6, 0}};
+    for (int i = 0; i < kMultiHaloBodies; ++i)
+        if (c[i][0] == nsub && c[i][1] == wmv && c[i][2] == wk && c[i][3] == tm && c[i][4] == tn && c[i][5] == kc && c[i][6] == nld &&
+            c[i][7] == ring && (c[i][8] != 0) == t2d)
+            return i;
+    return -1;
+}
+constexpr int multi_tiled_body(int wm, int wn, int tm, int tn, int kc, int pipe) {
+    const int c[4][4] = {{2, 2, 1, 1}, {4, 1, 1, 1}, {2, 2, 2, 1}, {2, 2, 1, 2}};
+    for (int i = 0; i < 4; ++i)
+        if (pipe == 1 && c[i][0] == wm && c[i][1] == wn && c[i][2] == tm && c[i][3] == tn)
+            return kMultiHaloBodies + 3 * i + (kc == 32 ? 0 : kc == 64 ? 1 : 2);
+    return -1;
+}
+// How launch_conv would run an edge; body < 0: not with one of those configurations.
+struct ConvPick {
+    int body, NT, items;
+    int p0, p1;               // halo tiles: th, tw; gather tiles: xcd_map
+    unsigned blocks, smem;
+};
+
+// Several edges that do not depend on each other in one launch.  The videos of a batch have their sites at different
+// addresses and ring origins and everything else in common, so a job carries the descriptor of the first video and a
+// video what differs: the distance of its source and destination memory and the origin of the destination's P.
+constexpr int kMaxMultiJobs = 6, kMaxConvVids = 96, kMaxStep1Vids = 48;
+struct ConvJob {
+    EdgeDev e;
+    int body, NT, items, p0, p1;
+    unsigned blocks, block0;  // its blocks of the grid: [block0, block0 + blocks), block0 a multiple of 8 (XCDs)
+};
+struct ConvVid {
+    long long sd, dd;
+    int p_oy, p_ox;
+};
+struct ConvMulti {
+    ConvJob job[kMaxMultiJobs];
+    ConvVid vid[kMaxConvVids];    // job j, video b: vid[j * videos + b]
+    int n;
+};
+static_assert(sizeof(ConvMulti) <= 4000, "kernel arguments stay below 4 KiB");
+hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_t st);      // fills in block0
+
+// The same for step 1 of several sites (no INPUT sites: those take a frame).
+struct Step1Job {
+    SiteDev s;
+    SkipDev skip;
+    int G;                    // lanes per pixel (one 16-byte chunk each)
+    unsigned block0;
+};
+struct Step1Vid {
+    long long sd, kd;
+    int a_oy, a_ox, p_oy, p_ox, k_oy, k_ox;
+    unsigned cy, cx;
+};
+struct Step1Multi {
+    Step1Job job[kMaxMultiJobs];
+    Step1Vid vid[kMaxStep1Vids];
+    int n;
+};
+static_assert(sizeof(Step1Multi) <= 4000, "kernel arguments stay below 4 KiB");
+bool step1_multi_applies(const SiteDev& s);
+hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);
+
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls
-hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, hipStream_t st, int* cls);
+// pick: nothing is launched; *pick says with which configuration of k_conv_multi the edge would run, if with one
+hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, hipStream_t st, int* cls, ConvPick* pick = nullptr);
 // convolution tile straight from global memory (kernels_direct.hip): shapes it takes, launch
 bool direct_applies(const EdgeDev& e, int dtype);
 hipError_t launch_conv_direct(const EdgeBatch& eb, int nb, int dtype, hipStream_t st);
