@@ -171,9 +171,8 @@ __device__ __forceinline__ void fill_items(const FillJob& j, unsigned lb) {
 
 // Block lb of the initialisation job j.
 __device__ __forceinline__ void fill_block(const FillJob& j, unsigned lb) {
-    if (lb == 0 && j.reset_counters && (int)threadIdx.x < (j.reset_counters == 2 ? kNumCounters : kNumPerFrame))
-        j.counters[threadIdx.x] = 0;
-    if (lb == 0 && j.reset_counters == 2) {                // first reset: clear the per-segment running sums
+    if (lb == 0 && j.reset_counters) {                     // first reset: clear the counters, the lists' counts and running sums
+        if ((int)threadIdx.x < kNumCounters) j.counters[threadIdx.x] = 0;
         for (int i = threadIdx.x; i < j.n_lacc; i += 256) { j.lacc[i] = 0ull; j.lcnt[i] = 0; }
         for (int i = threadIdx.x; i < j.n_cacc; i += 256) { j.cacc[i] = 0ull; j.ccnt[i] = 0; }
     }

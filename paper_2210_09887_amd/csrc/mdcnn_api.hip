@@ -736,7 +736,7 @@ mdcnn_status shift_jobs(mdcnn_buffer* const* bufs, int n, int dty, int dtx, std:
         };
         j.nP = j.P ? outside(j.Hp, j.Wp, j.py0, j.py1, j.px0, j.px1) : 0;
         j.nA = j.A ? outside(j.H, j.W, j.ay0, j.ay1, j.ax0, j.ax1) : 0;
-        j.reset_counters = b->fresh ? 2 : 1;             // per-frame counters start at zero every frame
+        j.reset_counters = b->fresh ? 1 : 0;
         j.per_block = full ? kFillItemsPerBlockFull : kFillItemsPerBlockStrip;
         jobs[(size_t)i] = j;
         if (full) {
@@ -765,6 +765,7 @@ hipError_t launch_fill_jobs(const FillJob* jobs, const int* which, int count, hi
     };
     for (int k = 0; k < count; ++k) {
         FillJob j = jobs[which ? which[k] : k];
+        if (fill_blocks(j) == 0) continue;
         j.block_begin = fb.total_blocks;
         fb.j[fb.n++] = j;
         fb.total_blocks += fill_blocks(j);

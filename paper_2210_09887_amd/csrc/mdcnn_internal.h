@@ -17,9 +17,9 @@ constexpr int kFlagC = 8;   // was a candidate of step 1 this frame (statistics)
 constexpr int kStateUnseen = 1;   // allocated, no frame has covered the pixel yet
 constexpr int kStateDirty = 2;    // touched by a producer while outside the crop
 
-// counters[] of a site (int32 slots, device).  Slots [0, 8) are per-frame values
-// zeroed by every camera shift; 64-bit running sums follow (index into
-// (unsigned long long*)counters), zeroed when the buffer is first reset.
+// counters[] of a site (int32 slots, device).  Slots [0, 8) are per-frame values of the
+// statistics view, filled in where it is read; 64-bit running sums follow (index into
+// (unsigned long long*)counters).  All are zeroed when the buffer is first reset.
 constexpr int kCntUpdated = 0;      // pixels updated this frame
 constexpr int kCntCandidates = 1;   // pixels visited by step 1 this frame
 constexpr int kAccUpdated = 4;      // sum of update counts
@@ -30,7 +30,6 @@ constexpr int kAccMacsPlain = 8;    // multiply-accumulates of the plain-FMA ker
 // The two multiply-accumulate sums are kept as 8 partial sums each (slot + 8 * {1, 2} + block % 8)
 // so that the statistics atomics of a launch do not all hit one address.
 constexpr int kAccMacsSpread = 16;  // [16, 24): MFMA partials, [24, 32): plain partials
-constexpr int kNumPerFrame = 8;
 constexpr int kNumCounters = 64;
 
 // Lists are compacted per segment of kSegPixels consecutive linear indices:
@@ -103,7 +102,7 @@ struct FillJob {
     int ay0, ay1, ax0, ax1;     // kept rows / cols of the view
     int nP, nA;                 // pixels to initialise in P / in A
     int dtype;
-    int reset_counters;         // 1: per-frame slots, 2: all (first reset)
+    int reset_counters;         // 1: first reset of the site, clear its counters and lists
     int per_block;              // items a block initialises
     unsigned block_begin;       // first block of the launch that works on this job
 };
@@ -117,11 +116,11 @@ struct FillBatch {
 // number of blocks; after a camera shift a block's time is latency (bias loads, ring arithmetic per item), so
 // the strips get more, smaller blocks.
 constexpr int kFillItemsPerBlockFull = 2048, kFillItemsPerBlockStrip = 512;
-inline unsigned fill_blocks(const FillJob& j) {   // blocks a job takes in a launch (at least one: it clears the counters)
+inline unsigned fill_blocks(const FillJob& j) {   // blocks a job takes in a launch (none if nothing was unveiled)
     const int vec = j.dtype == MDCNN_F16 ? 8 : 4;
     const long long items = (long long)(j.nP + j.nA) * (j.C % vec == 0 ? j.C / vec : j.C);
     const long long blocks = (items + j.per_block - 1) / j.per_block;
-    return (unsigned)(blocks < 1 ? 1 : blocks);
+    return (unsigned)(blocks < 1 && j.reset_counters ? 1 : blocks);
 }
 static_assert(sizeof(FillBatch) <= 4000, "kernel arguments stay below 4 KiB");
 
