@@ -71,6 +71,14 @@ __device__ __forceinline__ unsigned tap_mask(const EdgeDev& e, int cy, int cx) {
     return m;
 }
 
+// a / d for 0 <= a <= 2^24 + 2^23, r = 1 / d within a rounding (rcp_of): the quotient of the floats is off by one at most.  A
+// tenth of the instructions of an integer division, of which the start of a tile has one per index it decodes.
+__device__ __forceinline__ float rcp_of(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ __forceinline__ int fast_div(int a, int d, float r) {
+    const int q = (int)((float)a * r), rem = a - q * d;
+    return q + (rem >= d ? 1 : 0) - (rem < 0 ? 1 : 0);
+}
+
 // Number of list segments an edge walks: upsampling edges walk the source
 // pixels (view order), all others the destination's padded window.
 __device__ __forceinline__ int edge_segments(const EdgeDev& e) {
@@ -192,6 +200,71 @@ __device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* s
         }
     }
     __syncthreads();
+}
+
+// By-products of an edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
+// the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
+// count.  One wave per list segment, no barriers; a tile that made them itself had their loads ahead of its own and its
+// loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K loop, now 1.3.
+template <int KS>
+__device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, unsigned nblk) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int HW = e.sH * e.sW, n = e.Hp * e.Wp;
+    const int nsrc = e.pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, nseg = nsrc + (n + kSegPixels - 1) / kSegPixels;
+    const float rw = rcp_of(e.Wp);
+    for (int s = (int)blk * 4 + wave; s < nseg; s += (int)nblk * 4) {
+        if (s < nsrc) {
+            unsigned f[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int p = s * kSegPixels + k * 64 + lane;
+                f[k] = e.sflags[p < HW ? p : 0];
+                if (p >= HW) f[k] = 0u;
+            }
+            int tot = 0, cand = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned long long bm = __ballot(f[k] & kFlagM);
+                if (f[k] & kFlagM) e.pub_list[s * kSegPixels + tot + __popcll(bm & below)] = s * kSegPixels + k * 64 + lane;
+                tot += __popcll(bm);
+                cand += __popcll(__ballot(f[k] & kFlagC));
+            }
+            if (lane == 0) {                               // single writer per segment: no atomics
+                e.pub_lcnt[2 * s] = tot;
+                e.pub_lcnt[2 * s + 1] = cand;
+                e.pub_lacc[2 * s] += (unsigned long long)tot;
+                e.pub_lacc[2 * s + 1] += (unsigned long long)cand;
+            }
+            continue;
+        }
+        const int seg = s - nsrc;
+        unsigned vm[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int p = seg * kSegPixels + k * 64 + lane, wy = fast_div(p, e.Wp, rw), wx = p - wy * e.Wp;
+            vm[k] = tap_mask_k<KS>(e, p < n ? wy - e.by0 : 0, p < n ? wx - e.bx0 : 0);
+            if (p >= n) vm[k] = 0;
+        }
+        int tot = 0, taps = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned long long b = __ballot(vm[k] != 0);
+            if (vm[k]) {
+                const int p = seg * kSegPixels + k * 64 + lane, wy = fast_div(p, e.Wp, rw);
+                e.clist[seg * kSegPixels + tot + __popcll(b & below)] = p;
+                mark_pixel(e, wy, p - wy * e.Wp);
+            }
+            tot += __popcll(b);
+            taps += __popc(vm[k]);
+        }
+        taps = wave_sum(taps);
+        if (lane == 0) {
+            e.ccnt[seg] = tot;
+            e.cacc[seg] += (unsigned long long)tot;
+            add_macs(e, taps, 0);
+        }
+    }
 }
 
 // Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a

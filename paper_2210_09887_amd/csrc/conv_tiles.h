@@ -327,66 +327,36 @@ __device__ __forceinline__ int tile_prologue_sub(const EdgeDev& e, int seg, int 
 
 // Variant of tile_prologue for tiles that are th x tw rectangles of the padded window (th * tw <= 256, top-left
 // corner (wy0, wx0)): thread t looks at tile pixel (t / tw, t % tw); the live ones are ranked in that order.
-// Returns their number; rows s_wy / s_wx are filled for them, sh[4] = valid taps of the tile.
+// Returns their number; rows s_wy / s_wx are filled for them.
 // The tap mask of a tile pixel is read off the tile's staged rectangle: s_pix[ry * rw + rx] >= 0 where the source pixel
 // (ry, rx) of the rectangle (the tile plus its halo) is in view and updated (3x3, stride 1: the footprint of tile pixel
-// (ly, lx) is rectangle rows ly .. ly + 2, columns lx .. lx + 2) - no flag loads of its own.
-// pub_seg >= 0: the block also ranks list segment pub_seg (256 consecutive window indices), whose tap masks vm_p the
-// caller has requested with the rectangle's flags; pub_off = this thread's position in that segment's compute list or
-// -1, sh[8 .. 11] the entries of the segment per wave.  Nothing is written to global memory here: the wave's later
-// loads would queue behind those stores (tile_effects_2d does it once the tile's own loads are done).
+// (ly, lx) is rectangle rows ly .. ly + 2, columns lx .. lx + 2) - no flag loads of its own.  Nothing is written to global
+// memory: what a tile leaves behind besides its sums is done by other blocks (publish_edge).
 __device__ __forceinline__ int tile_prologue_2d(const EdgeDev& e, int wy0, int wx0, int th, int tw, const int* s_pix, int rw,
-                                                int pub_seg, unsigned vm_p, int& pub_off, int* s_wy, int* s_wx, int* sh) {
+                                                int* s_wy, int* s_wx, int* sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) sh[4] = 0;
-    const int ly = tid / tw, lx = tid - ly * tw;
+    const int ly = fast_div(tid, tw, rcp_of(tw)), lx = tid - ly * tw;
     const int wy = wy0 + ly, wx = wx0 + lx;
-    const bool in_tile = ly < th && wy < e.Hp && wx < e.Wp;
-    const bool in_seg = pub_seg >= 0 && pub_seg * kSegPixels + tid < e.Hp * e.Wp;
-    unsigned vm = 0;
-    if (in_tile) {
+    bool has = false;
+    if (ly < th && wy < e.Hp && wx < e.Wp) {
         const int* r = s_pix + ly * rw + lx;
+        int any = -1;                                      // negative as long as no tap is live
 #pragma unroll
-        for (int t = 0; t < 9; ++t) vm |= (unsigned)(r[(t / 3) * rw + t % 3] >= 0) << t;
+        for (int t = 0; t < 9; ++t) any &= r[(t / 3) * rw + t % 3] | 0x7fffffff;
+        has = any >= 0;
     }
-    const bool has = vm != 0, hasp = in_seg && vm_p != 0;
-    const unsigned long long bal = __ballot(has), balp = __ballot(hasp);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    if (lane == 0) { sh[wave] = __popcll(bal); sh[8 + wave] = __popcll(balp); }
+    const unsigned long long bal = __ballot(has);
+    if (lane == 0) sh[wave] = __popcll(bal);
     __syncthreads();
-    int off = __popcll(bal & below), offp = __popcll(balp & below);
-    for (int i = 0; i < wave; ++i) { off += sh[i]; offp += sh[8 + i]; }
-    const int cnt = sh[0] + sh[1] + sh[2] + sh[3];
+    int off = __popcll(bal & ((1ull << lane) - 1ull));
+    for (int i = 0; i < wave; ++i) off += sh[i];
     if (has) {
         s_wy[off] = wy;
         s_wx[off] = wx;
     }
-    pub_off = hasp ? offp : -1;
-    int taps = __popc(vm);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) taps += __shfl_xor(taps, o);
-    if (lane == 0 && taps) atomicAdd(&sh[4], taps);
+    const int cnt = sh[0] + sh[1] + sh[2] + sh[3];
     __syncthreads();
     return cnt;
-}
-
-// What a tile leaves behind besides its sums, after tile_prologue_2d: the touched marks of its `tot` entries and the
-// multiply-accumulate count (touch), the compute list of segment pub_seg and its counts.  No barrier.
-__device__ __forceinline__ void tile_effects_2d(const EdgeDev& e, int tot, bool touch, int pub_seg, int pub_off,
-                                                const int* s_wy, const int* s_wx, const int* sh) {
-    const int tid = threadIdx.x;
-    if (touch) {
-        for (int r = tid; r < tot; r += 256) mark_touched(e, s_wy[r], s_wx[r]);
-        if (tid == 0) add_macs(e, sh[4], 0);
-    }
-    if (pub_seg >= 0) {
-        if (pub_off >= 0) e.clist[pub_seg * kSegPixels + pub_off] = pub_seg * kSegPixels + tid;
-        if (tid == 0) {                                    // single writer per segment: no atomics
-            const int n = sh[8] + sh[9] + sh[10] + sh[11];
-            e.ccnt[pub_seg] = n;
-            e.cacc[pub_seg] += (unsigned long long)n;
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -443,7 +413,7 @@ struct HaloCfg {
 // T2D: the tiles are th x tw rectangles of the padded window (th * tw <= SUB) instead of index ranges: the staged rectangle
 // is the tile plus its KS - 1 halo whatever the width of the window, so wide rows fit and narrow ones stage less.
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
-__device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsigned nblk, int NT, int work_items, int th, int tw) {
+__device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsigned nblk, unsigned npub, int NT, int work_items, int th, int tw) {
     using Cfg = HaloCfg<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_>;
     constexpr int SUB = Cfg::SUB, BN = Cfg::BN, KB = Cfg::KB, MB = Cfg::MB, NS = Cfg::NS, CPR = Cfg::CPR, NLD = Cfg::NLD,
                   LDK = Cfg::LDK, LDC = Cfg::LDC;
@@ -452,7 +422,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
     float* sC = reinterpret_cast<float*>(smem);          // [SUB][LDC] after it
     int* s_pix = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);
     __shared__ int s_wy[SUB], s_wx[SUB];
-    __shared__ int sh[12];
+    __shared__ int sh[8];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: scalar branches below
@@ -470,17 +440,24 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
 
     unsigned warm = 0;
     if constexpr (T2D) {
+        if (blk < npub) {
+            publish_edge<KS>(e, blk, npub);
+            return;
+        }
+        blk -= npub;
+        nblk -= npub;
         // the blocks of a cout tile touch that tile's weights, a line each, before anything else: the fragments of the
         // K loop then come from the L2 of their XCD instead of following each other to memory
         const unsigned nt0 = blk % NT, sharers = nblk / NT > 0 ? nblk / NT : 1, rank = blk / NT;
         const unsigned kb = e.Cin / 16, lpf = BN * 32 / 128, nlines = KS * KS * kb * lpf;
         for (unsigned l = rank * 256 + tid; l < nlines; l += sharers * 256) {
-            const unsigned f = l / lpf, ln = l - f * lpf;
-            const unsigned off = (f / kb) * tap_stride + (f % kb) * blk_stride + nt0 * BN * 32 + ln * 128;
+            const unsigned f = l / lpf, ln = l - f * lpf, t = (unsigned)fast_div((int)f, (int)kb, rcp_of((int)kb));
+            const unsigned off = t * tap_stride + (f - t * kb) * blk_stride + nt0 * BN * 32 + ln * 128;
             warm ^= (unsigned)__builtin_amdgcn_raw_buffer_load_b32(wrs, (int)off, 0, 0);
         }
+    } else {
+        carry_source_compaction(e, sh, blk, nblk);
     }
-    carry_source_compaction(e, sh, blk, nblk);
 
     for (int u = (int)blk; u < work_items; u += (int)nblk) {
         const int nt = u % NT, mt = u / NT;              // u % 8 picks the XCD: few cout tiles per XCD
@@ -489,9 +466,6 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
         __syncthreads();                                  // previous tile is done with LDS
         int tot, wyA, wyB, cxA, cxB;                      // entries; window rows and source columns the tile spans
         constexpr int NRF = (Cfg::CAP + 255) / 256;       // rectangle positions per thread
-        int rpix[NRF];                                    // T2D: source pixel of this thread's positions, -1 outside the view
-        unsigned rflag[NRF];                              //      and its flags, requested together with those of the prologue
-        int pub_seg = -1, pub_off = -1;
         if constexpr (T2D) {
             const int ty = mt / tiles_x, tx = mt - ty * tiles_x;
             wyA = ty * th;
@@ -499,32 +473,25 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             cxA = tx * tw - e.bx0;
             cxB = (tx * tw + tw < e.Wp ? tx * tw + tw : e.Wp) - 1 - e.bx0;
             const int ry0 = wyA - e.by0 - e.pad, rx0 = cxA - e.pad, rw = cxB - cxA + KS, rn = (wyB - wyA + KS) * rw;
+            const float rrw = rcp_of(rw);
+            // the rectangle: source pixel of every position, -1 where it is out of view or not updated
+            int rpix[NRF];
+            unsigned rflag[NRF];
 #pragma unroll
             for (int j = 0; j < NRF; ++j) {
                 const int pos = tid + 256 * j;
-                const int ry = pos / rw, iy = ry0 + ry, ix = rx0 + pos - ry * rw;
+                const int ry = fast_div(pos, rw, rrw), iy = ry0 + ry, ix = rx0 + pos - ry * rw;
                 const bool ok = pos < rn && iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW;
                 rpix[j] = ok ? iy * e.sW + ix : -1;
                 rflag[j] = e.sflags[ok ? rpix[j] : 0];
             }
-            // every list segment is published by one of the first tiles (there are at least as many tiles as segments):
-            // the flags of its footprints travel with those of the rectangle
-            pub_seg = nt == 0 && mt < edge_segments(e) ? mt : -1;
-            unsigned vm_p = 0;
-            if (pub_seg >= 0) {
-                const int p = pub_seg * kSegPixels + tid, qy = p / e.Wp, qx = p - qy * e.Wp;
-                const bool in_seg = p < nwin;              // (threads beyond the window read the flags of pixel (0, 0): unused)
-                vm_p = tap_mask(e, in_seg ? qy - e.by0 : 0, in_seg ? qx - e.bx0 : 0);
-            }
-            // the rectangle: source pixel of every position, -1 where it is out of view or not updated
 #pragma unroll
             for (int j = 0; j < NRF; ++j) {
                 const int pos = tid + 256 * j;
                 if (pos < rn) s_pix[pos] = rpix[j] >= 0 && (rflag[j] & kFlagM) ? rpix[j] : -1;
             }
             __syncthreads();
-            tot = tile_prologue_2d(e, ty * th, tx * tw, th, tw, s_pix, rw, pub_seg, vm_p, pub_off, s_wy, s_wx, sh);
-            if (tot <= 0) tile_effects_2d(e, 0, false, pub_seg, pub_off, s_wy, s_wx, sh);
+            tot = tile_prologue_2d(e, ty * th, tx * tw, th, tw, s_pix, rw, s_wy, s_wx, sh);
         } else {
             const int seg = mt / NSUB, sub_lo = (mt % NSUB) * SUB;
             tot = tile_prologue_sub(e, seg, sub_lo, SUB, nt == 0 && sub_lo == 0, nt == 0, s_wy, s_wx, sh);
@@ -726,7 +693,6 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 *reinterpret_cast<f16x8*>(pp[t]) = o;
             }
         }
-        if constexpr (T2D) tile_effects_2d(e, tot, nt == 0, pub_seg, pub_off, s_wy, s_wx, sh);
     }
     if (warm == 0x9e3779b9u && work_items < 0) e.ccnt[0] = 0;     // (keeps the loads above)
 }

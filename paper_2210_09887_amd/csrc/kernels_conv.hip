@@ -38,8 +38,8 @@ __global__ __launch_bounds__(256) void k_conv_mfma_tiled(EdgeBatch eb, int NT, i
     tiled_body<WM, WN, TM, TN, KC, PIPE>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, NT, work_items, xcd_map);
 }
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
-__global__ __launch_bounds__(256, MINB_) void k_conv_halo(EdgeBatch eb, int NT, int work_items, int th, int tw) {
-    halo_body<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_, T2D>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, NT, work_items, th, tw);
+__global__ __launch_bounds__(256, MINB_) void k_conv_halo(EdgeBatch eb, unsigned npub, int NT, int work_items, int th, int tw) {
+    halo_body<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_, T2D>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, npub, NT, work_items, th, tw);
 }
 
 // Weights [tap][cout][cin] -> [tap][cin/16][cout][16]: the 32 couts x 16 cin
@@ -954,7 +954,7 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
     unsigned g = cap_blocks(items, 4096);
     g = (g + 7u) & ~7u;                                    // whole rounds over the 8 XCDs
     if (pick) {
-        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), NT, (int)items, xcd, 0, g, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), NT, (int)items, xcd, 0, 0u, g, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_mfma_tiled<WM, WN, TM, TN, KC, PIPE>;
@@ -1022,8 +1022,9 @@ static hipError_t launch_halo_t(const EdgeBatch& eb, int nb, long long nseg, hip
     const int NT = e.Cout / Cfg::BN;
     const long long tiles = T2D ? (long long)((e.Hp + th - 1) / th) * ((e.Wp + tw - 1) / tw) : nseg * NSUB;
     const long long items = tiles * NT;
+    const unsigned npub = T2D ? publish_blocks(e) : 0u, blocks = cap_blocks(items, 16384) + npub;
     if (pick) {
-        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), NT, (int)items, th, tw, cap_blocks(items, 16384), (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), NT, (int)items, th, tw, npub, blocks, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_halo<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, MINB, T2D>;
@@ -1033,7 +1034,7 @@ static hipError_t launch_halo_t(const EdgeBatch& eb, int nb, long long nseg, hip
         if (err != hipSuccess) { (void)hipGetLastError(); return err; }    // do not leave it for the next call to report
         attr_set.store(true, std::memory_order_release);
     }
-    kern<<<dim3(cap_blocks(items, 16384), 1, nb), dim3(256), Cfg::SMEM, st>>>(eb, NT, (int)items, th, tw);
+    kern<<<dim3(blocks, 1, nb), dim3(256), Cfg::SMEM, st>>>(eb, npub, NT, (int)items, th, tw);
     return hipGetLastError();
 }
 

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     const unsigned nblk = jb.blocks;
 #define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
     case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
-        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, NT, items, p0, p1);                      \
+        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, jb.npub, NT, items, p0, p1);             \
         break;
 #define TILED(WM, WN, TM, TN, KC)                                                                                         \
     case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, NT, items, p0); break;

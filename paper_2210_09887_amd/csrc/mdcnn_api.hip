@@ -846,7 +846,7 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 if (cm.n == kMaxMultiJobs || (cm.n + 1) * n > kMaxConvVids) flush_conv();
                 ConvJob& j = cm.job[cm.n];
                 j.e = eb.d[0];
-                j.body = pick.body; j.NT = pick.NT; j.items = pick.items; j.p0 = pick.p0; j.p1 = pick.p1; j.blocks = pick.blocks;
+                j.body = pick.body; j.NT = pick.NT; j.items = pick.items; j.p0 = pick.p0; j.p1 = pick.p1; j.npub = pick.npub; j.blocks = pick.blocks;
                 for (int b = 0; b < n; ++b)
                     cm.vid[cm.n * n + b] = ConvVid{dist(eb.d[b].delta, j.e.delta), dist(eb.d[b].P, j.e.P), eb.d[b].p_oy, eb.d[b].p_ox};
                 smem = pick.smem > smem ? pick.smem : smem;

@@ -156,6 +156,13 @@ struct EdgeDev {
     int s_aoy, s_aox, s_relu, d_aoy, d_aox, op;
 };
 constexpr int kOpTruncFree = 3;
+// Blocks of a launch that publish the lists of an edge (publish_edge): two segments per wave, at most 64 blocks.
+inline unsigned publish_blocks(const EdgeDev& e) {
+    const long long segs = (e.pub_list ? ((long long)e.sH * e.sW + kSegPixels - 1) / kSegPixels : 0) +
+                           ((long long)e.Hp * e.Wp + kSegPixels - 1) / kSegPixels;
+    const long long b = (segs + 7) / 8;
+    return (unsigned)(b < 1 ? 1 : b > 64 ? 64 : b);
+}
 
 // Several independent streams (same network, own buffers and camera paths) share
 // one launch: blockIdx.z picks the stream.  The descriptors travel as kernel
@@ -215,7 +222,7 @@ constexpr int multi_tiled_body(int wm, int wn, int tm, int tn, int kc, int pipe)
 struct ConvPick {
     int body, NT, items;
     int p0, p1;               // halo tiles: th, tw; gather tiles: xcd_map
-    unsigned blocks, smem;
+    unsigned npub, blocks, smem;      // blocks of the edge, the first npub of which publish its lists
 };
 
 // Several edges that do not depend on each other in one launch.  The videos of a batch have their sites at different
@@ -225,7 +232,7 @@ constexpr int kMaxMultiJobs = 6, kMaxConvVids = 96, kMaxStep1Vids = 48;
 struct ConvJob {
     EdgeDev e;
     int body, NT, items, p0, p1;
-    unsigned blocks, block0;  // its blocks of the grid: [block0, block0 + blocks), block0 a multiple of 8 (XCDs)
+    unsigned npub, blocks, block0;  // its blocks of the grid: [block0, block0 + blocks), block0 a multiple of 8 (XCDs)
 };
 struct ConvVid {
     long long sd, dd;
