@@ -32,7 +32,8 @@ struct TiledCfg {
     static constexpr int STAGE_HALVES = (BM + BN) * LDK;
     static constexpr int SLAB_BYTES = PIPE * STAGE_HALVES * 2;
     static constexpr int C_BYTES = BM * LDC * 4;
-    static constexpr int SMEM = SLAB_BYTES > C_BYTES ? SLAB_BYTES : C_BYTES;
+    static constexpr int MAIN_BYTES = SLAB_BYTES > C_BYTES ? SLAB_BYTES : C_BYTES;
+    static constexpr int SMEM = MAIN_BYTES + (4 * BM + 8) * 4;      // + the entries' rows and a few counts
     static constexpr int TPS = kSegPixels / BM;    // tiles per list segment
 };
 
@@ -63,9 +64,9 @@ __device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsig
     extern __shared__ __align__(16) unsigned char smem[];
     f16* slab = reinterpret_cast<f16*>(smem);            // PIPE x { [BM][LDK] deltas, [BN][LDK] weights }
     float* sC = reinterpret_cast<float*>(smem);          // [BM][LDC] after the K loop
-    __shared__ int s_base[BM], s_wy[BM], s_wx[BM];
-    __shared__ unsigned s_vm[BM];
-    __shared__ int sh[8];
+    int* const s_base = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);
+    int *const s_wy = s_base + BM, *const s_wx = s_wy + BM, *const sh = s_wx + BM;
+    unsigned* const s_vm = reinterpret_cast<unsigned*>(sh + 8);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
@@ -402,8 +403,12 @@ struct HaloCfg {
     static constexpr int LDC = BN + 4;               // accumulator row, floats
     static constexpr int HALO_BYTES = CAP * LDK * 2;
     static constexpr int C_BYTES = SUB * LDC * 4;
-    static constexpr int MAIN_BYTES = HALO_BYTES > C_BYTES ? HALO_BYTES : C_BYTES;
-    static constexpr int SMEM = MAIN_BYTES + CAP * 4;   // + source pixel index of every staged position
+    // K-split partial sums: a buffer per K wave where that leaves room for two tiles per compute unit (one barrier, the
+    // thread that updates P adds them up), else the waves take turns adding to one (a barrier per wave)
+    static constexpr bool PARTS = WK > 1 && WK * C_BYTES <= 72 * 1024;
+    static constexpr int SUM_BYTES = PARTS ? WK * C_BYTES : C_BYTES;
+    static constexpr int MAIN_BYTES = HALO_BYTES > SUM_BYTES ? HALO_BYTES : SUM_BYTES;
+    static constexpr int SMEM = MAIN_BYTES + (CAP + 2 * SUB + 8) * 4;   // + source pixel of every staged position, entries, counts
     static constexpr int LPS = (NLD + NS / 2 - 1) / (NS / 2);   // staging loads per step (first steps of a chunk)
     static constexpr int NLS = (NLD + LPS - 1) / LPS;
     static_assert(NLS <= NS, "staging loads fit the steps of a chunk");
@@ -417,12 +422,16 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
     using Cfg = HaloCfg<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_>;
     constexpr int SUB = Cfg::SUB, BN = Cfg::BN, KB = Cfg::KB, MB = Cfg::MB, NS = Cfg::NS, CPR = Cfg::CPR, NLD = Cfg::NLD,
                   LDK = Cfg::LDK, LDC = Cfg::LDC;
+    constexpr bool PARTS = Cfg::PARTS;
+    // Quarter-segment rectangles, which a launch has few of: what a tile can ask for before it knows what it needs goes out
+    // at once - the first weight fragments, the rows of the rectangle whether updated or not, then the pending rows - so
+    // that its round trips to memory overlap.  (Larger tiles fill the chip: there the same only adds traffic and registers.)
+    constexpr bool EARLY = T2D && NSUB == 4, EARLY_P = EARLY;
     extern __shared__ __align__(16) unsigned char smem[];
     f16* halo = reinterpret_cast<f16*>(smem);            // [CAP][LDK] during the K loop
     float* sC = reinterpret_cast<float*>(smem);          // [SUB][LDC] after it
     int* s_pix = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);
-    __shared__ int s_wy[SUB], s_wx[SUB];
-    __shared__ int sh[8];
+    int *const s_wy = s_pix + Cfg::CAP, *const s_wx = s_wy + SUB, *const sh = s_wx + SUB;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: scalar branches below
@@ -448,12 +457,14 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
         nblk -= npub;
         // the blocks of a cout tile touch that tile's weights, a line each, before anything else: the fragments of the
         // K loop then come from the L2 of their XCD instead of following each other to memory
+        if constexpr (!EARLY) {
         const unsigned nt0 = blk % NT, sharers = nblk / NT > 0 ? nblk / NT : 1, rank = blk / NT;
         const unsigned kb = e.Cin / 16, lpf = BN * 32 / 128, nlines = KS * KS * kb * lpf;
         for (unsigned l = rank * 256 + tid; l < nlines; l += sharers * 256) {
             const unsigned f = l / lpf, ln = l - f * lpf, t = (unsigned)fast_div((int)f, (int)kb, rcp_of((int)kb));
             const unsigned off = t * tap_stride + (f - t * kb) * blk_stride + nt0 * BN * 32 + ln * 128;
             warm ^= (unsigned)__builtin_amdgcn_raw_buffer_load_b32(wrs, (int)off, 0, 0);
+        }
         }
     } else {
         carry_source_compaction(e, sh, blk, nblk);
@@ -463,8 +474,22 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
         const int nt = u % NT, mt = u / NT;              // u % 8 picks the XCD: few cout tiles per XCD
         if (mt >= ntiles) continue;
         const int n0 = nt * BN;
+        const unsigned wlane = (unsigned)(r32 * 16 + kh * 8) * 2u;                      // this lane's bytes within a fragment
+        const unsigned wwave = ((unsigned)wk * (unsigned)e.Cout + (unsigned)n0) * 32u;   // this wave's K block and cout tile
+        f16x8 fa[Cfg::RING][TN];                          // weight fragments in flight
+        auto load_a = [&](int slot, int c, int i) {       // step i of chunk c; i may run into the next chunk
+            const int cc = i < NS ? c : (c + 1 < nchunks ? c + 1 : c), ii = i < NS ? i : i - NS;
+            const unsigned src = wwave + (unsigned)(ii / MB) * tap_stride + (unsigned)(cc * KB + WK * (ii % MB)) * blk_stride;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fa[slot][j] = buf_load16(wrs, wlane, src + (unsigned)j * 32u * 32u);
+        };
+        if constexpr (EARLY) {
+#pragma unroll
+            for (int i = 0; i < Cfg::RING - 1; ++i) load_a(i, 0, i);
+        }
         __syncthreads();                                  // previous tile is done with LDS
         int tot, wyA, wyB, cxA, cxB;                      // entries; window rows and source columns the tile spans
+        f16x8 hreg[NLD];                                  // rows of the rectangle on their way to LDS
         constexpr int NRF = (Cfg::CAP + 255) / 256;       // rectangle positions per thread
         if constexpr (T2D) {
             const int ty = mt / tiles_x, tx = mt - ty * tiles_x;
@@ -484,6 +509,15 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 const bool ok = pos < rn && iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW;
                 rpix[j] = ok ? iy * e.sW + ix : -1;
                 rflag[j] = e.sflags[ok ? rpix[j] : 0];
+            }
+            if constexpr (EARLY) {
+#pragma unroll
+                for (int j = 0; j < NLD; ++j) {
+                    const int q = tid + 256 * j, pos = q / CPR;
+                    const int ry = fast_div(pos, rw, rrw), iy = ry0 + ry, ix = rx0 + pos - ry * rw;
+                    const bool ok = pos < rn && iy >= 0 && iy < e.sH && ix >= 0 && ix < e.sW;
+                    hreg[j] = buf_load16(drs, ok ? ((unsigned)(iy * e.sW + ix) * (unsigned)e.Cin + (q % CPR) * 8) * 2u : 0x80000000u, 0u);
+                }
             }
 #pragma unroll
             for (int j = 0; j < NRF; ++j) {
@@ -521,7 +555,6 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
         // staging: piece q = tid + 256 j is 16 bytes of staged pixel q / CPR (q / CPR < CAP: inside the buffer).
         // Dead pieces (outside the rectangle, out of view, not updated) are loaded from beyond the end of the
         // delta map, which a buffer load answers with zeros, and stored like the others: no predicates.
-        f16x8 hreg[NLD];
         unsigned hsrc[NLD];                               // byte offsets into the delta map
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
@@ -537,7 +570,13 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             }
         };
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) hreg[j] = buf_load16(drs, hsrc[j], 0u);
+        for (int j = 0; j < NLD; ++j) {
+            if constexpr (EARLY) {
+                if (hsrc[j] == 0x80000000u) hreg[j] = f16x8{};      // requested above, but not updated
+            } else {
+                hreg[j] = buf_load16(drs, hsrc[j], 0u);
+            }
+        }
         halo_store();
 
         f32x16 acc[TM][TN];
@@ -553,9 +592,24 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             const int r = (i * WMV + wm) * 32 + r32;
             rowoff[i] = kh * 8 + wk * 16 + (r < tot ? ((s_wy[r] - e.by0 - e.pad - iy0) * RW + (s_wx[r] - e.bx0 - e.pad - ix0)) * LDK : 0);
         }
-        const unsigned wlane = (unsigned)(r32 * 16 + kh * 8) * 2u;                      // this lane's bytes within a fragment
-        const unsigned wwave = ((unsigned)wk * (unsigned)e.Cout + (unsigned)n0) * 32u;   // this wave's K block and cout tile
         __syncthreads();
+
+        // the pending rows this thread updates: all reads go out together (before the K loop where registers allow)
+        constexpr int TPR = BN / 8;                        // threads per entry, 8 couts each
+        constexpr int RPP = 256 / TPR, NPASS = (SUB + RPP - 1) / RPP;
+        const int c8 = (tid % TPR) * 8;
+        f16x8 pold[NPASS];
+        f16* pp[NPASS];
+        auto load_p = [&] {
+#pragma unroll
+            for (int t = 0; t < NPASS; ++t) {
+                const int row = tid / TPR + t * RPP;
+                const int rr = row < tot ? row : 0;         // dead rows read entry 0 and store nothing
+                pp[t] = (f16*)e.P + pdst_offset(e, s_wy[rr], s_wx[rr]) + n0 + c8;
+                pold[t] = *reinterpret_cast<const f16x8*>(pp[t]);
+            }
+        };
+        if constexpr (EARLY_P) load_p();
 
         // The K loop for L live row tiles of this wave.  Step i of a chunk: tap i / MB,
         // 16-channel block wk + WK * (i % MB) of the chunk.
@@ -563,21 +617,17 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             constexpr int L = decltype(lc)::value;
             constexpr int D = Cfg::RING;
             constexpr int FBR = TM > 4 ? 2 : 3;                      // sets of staged-row fragments in flight
-            f16x8 fa[D][TN], fb[FBR][L > 0 ? L : 1];
-            auto load_a = [&](int slot, int c, int i) {              // i may run into the next chunk
-                const int cc = i < NS ? c : (c + 1 < nchunks ? c + 1 : c), ii = i < NS ? i : i - NS;
-                const unsigned src = wwave + (unsigned)(ii / MB) * tap_stride + (unsigned)(cc * KB + WK * (ii % MB)) * blk_stride;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) fa[slot][j] = buf_load16(wrs, wlane, src + (unsigned)j * 32u * 32u);
-            };
+            f16x8 fb[FBR][L > 0 ? L : 1];
             auto load_b = [&](int slot, int i) {
                 const int tap = i / MB;
                 const f16* hb = halo + ((tap / KS) * RW + tap % KS) * LDK + WK * (i % MB) * 16;
 #pragma unroll
                 for (int t = 0; t < L; ++t) fb[slot][t] = *reinterpret_cast<const f16x8*>(hb + rowoff[t]);
             };
+            if constexpr (!EARLY) {
 #pragma unroll
-            for (int i = 0; i < D - 1; ++i) load_a(i, 0, i);
+                for (int i = 0; i < D - 1; ++i) load_a(i, 0, i);
+            }
             for (int c = 0; c < nchunks; ++c) {
                 const int cn = c + 1 < nchunks ? c + 1 : c;          // the last chunk re-reads itself: no branch
                 const unsigned hc = (unsigned)cn * KC * 2u;
@@ -619,7 +669,8 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 }
             }
         };
-        switch (mylive) {
+        if constexpr (EARLY) kloop(std::integral_constant<int, TM>{});     // (a second loop body would not share the ring's registers)
+        else switch (mylive) {
             case 0: kloop(std::integral_constant<int, 0>{}); break;
             case 1: kloop(std::integral_constant<int, 1>{}); break;
             case 2: kloop(std::integral_constant<int, TM >= 2 ? 2 : TM>{}); break;
@@ -628,14 +679,13 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             default: kloop(std::integral_constant<int, TM>{}); break;
         }
 
-        // K-split partial sums -> LDS [entry][cout].  Every element is added up in a fixed
-        // order of the K waves: with four K waves over all rows, wave w takes quarter
-        // (w + p) % 4 of the rows in phase p (all waves busy in every phase); otherwise
-        // the K waves take turns.
+        if constexpr (!EARLY_P) load_p();
+        // K-split partial sums -> LDS [entry][cout], a buffer per K wave or added up in turns; either way every element
+        // is added up in the order of the K waves.
         auto put = [&](int i, bool add) {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                float* dst = sC + ((i * WMV + wm) * 32 + r32) * LDC + j * 32 + 4 * kh;
+                float* dst = sC + (PARTS ? wk * SUB * LDC : 0) + ((i * WMV + wm) * 32 + r32) * LDC + j * 32 + 4 * kh;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
@@ -647,15 +697,11 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 }
             }
         };
-        if constexpr (WK == 4 && WMV == 1 && TM % 4 == 0) {
+        if constexpr (PARTS) {
 #pragma unroll
-            for (int ph = 0; ph < 4; ++ph) {
-                const int q = (wk + ph) & 3;
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    if (i / (TM / 4) == q && i < mylive) put(i, ph > 0);
-                __syncthreads();
-            }
+            for (int i = 0; i < TM; ++i)
+                if (i < mylive) put(i, false);
+            __syncthreads();
         } else {
 #pragma unroll
             for (int kq = 0; kq < WK; ++kq) {
@@ -667,26 +713,20 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 __syncthreads();
             }
         }
-        // P <- P + sum: all reads of P go out first (their latency is paid once), then the stores
-        constexpr int TPR = BN / 8;                        // threads per entry, 8 couts each
-        constexpr int RPP = 256 / TPR, NPASS = (SUB + RPP - 1) / RPP;
-        const int c8 = (tid % TPR) * 8;
-        f16x8 pold[NPASS];
-        f16* pp[NPASS];
-#pragma unroll
-        for (int t = 0; t < NPASS; ++t) {
-            const int row = tid / TPR + t * RPP;
-            const int rr = row < tot ? row : 0;             // dead rows read entry 0 and store nothing
-            pp[t] = (f16*)e.P + pdst_offset(e, s_wy[rr], s_wx[rr]) + n0 + c8;
-            pold[t] = *reinterpret_cast<const f16x8*>(pp[t]);
-        }
+        // P <- P + sum
 #pragma unroll
         for (int t = 0; t < NPASS; ++t) {
             const int row = tid / TPR + t * RPP;
             if (row < tot) {
-                const float4 v0 = *reinterpret_cast<const float4*>(sC + row * LDC + c8);
-                const float4 v1 = *reinterpret_cast<const float4*>(sC + row * LDC + c8 + 4);
-                const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                float v[8];
+#pragma unroll
+                for (int kq = 0; kq < (PARTS ? WK : 1); ++kq) {
+                    const float* src = sC + kq * SUB * LDC + row * LDC + c8;
+                    const float4 v0 = *reinterpret_cast<const float4*>(src), v1 = *reinterpret_cast<const float4*>(src + 4);
+                    const float part[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) v[q] = kq ? v[q] + part[q] : part[q];
+                }
                 f16x8 o = pold[t];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) o[q] = (f16)((float)o[q] + v[q]);

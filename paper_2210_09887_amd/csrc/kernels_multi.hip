@@ -38,10 +38,6 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
         HALO(4, 2, 2, 1, 1, 32, 2, 9, true)
         HALO(4, 1, 4, 2, 1, 64, 4, 9, true)
         HALO(4, 1, 4, 2, 2, 64, 4, 9, true)
-        HALO(4, 2, 2, 1, 1, 32, 6, 9, false)
-        HALO(4, 1, 4, 2, 1, 64, 9, 9, false)
-        HALO(4, 1, 4, 2, 2, 64, 9, 9, false)
-        HALO(2, 2, 2, 2, 2, 64, 11, 6, false)
         TILED(2, 2, 1, 1, 32) TILED(2, 2, 1, 1, 64) TILED(2, 2, 1, 1, 128)
         TILED(4, 1, 1, 1, 32) TILED(4, 1, 1, 1, 64) TILED(4, 1, 1, 1, 128)
         TILED(2, 2, 2, 1, 32) TILED(2, 2, 2, 1, 64) TILED(2, 2, 2, 1, 128)

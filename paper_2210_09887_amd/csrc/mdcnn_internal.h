@@ -199,12 +199,11 @@ hipError_t launch_step1(const Step1Batch& b, int n, hipStream_t st);
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
 // half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
-constexpr int kMultiHaloBodies = 10, kMultiTiledBodies = 12;
+constexpr int kMultiHaloBodies = 6, kMultiTiledBodies = 12;
 constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc, int nld, int ring, bool t2d) {
     const int c[kMultiHaloBodies][9] = {
         {2, 2, 2, 2, 1, 32, 3, 3, 1}, {2, 2, 2, 2, 1, 64, 6, 6, 1}, {2, 2, 2, 2, 2, 64, 6, 6, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1},
-        {4, 1, 4, 2, 1, 64, 4, 9, 1}, {4, 1, 4, 2, 2, 64, 4, 9, 1}, {4, 2, 2, 1, 1, 32, 6, 9, 0}, {4, 1, 4, 2, 1, 64, 9, 9, 0},
-        {4, 1, 4, 2, 2, 64, 9, 9, 0}, {2, 2, 2, 2, 2, 64, 11, 6, 0}};
+        {4, 1, 4, 2, 1, 64, 4, 9, 1}, {4, 1, 4, 2, 2, 64, 4, 9, 1}};
     for (int i = 0; i < kMultiHaloBodies; ++i)
         if (c[i][0] == nsub && c[i][1] == wmv && c[i][2] == wk && c[i][3] == tm && c[i][4] == tn && c[i][5] == kc && c[i][6] == nld &&
             c[i][7] == ring && (c[i][8] != 0) == t2d)
