@@ -71,14 +71,6 @@ __device__ __forceinline__ unsigned tap_mask(const EdgeDev& e, int cy, int cx) {
     return m;
 }
 
-// a / d for 0 <= a <= 2^24 + 2^23, r = 1 / d within a rounding (rcp_of): the quotient of the floats is off by one at most.  A
-// tenth of the instructions of an integer division, of which the start of a tile has one per index it decodes.
-__device__ __forceinline__ float rcp_of(int d) { return __builtin_amdgcn_rcpf((float)d); }
-__device__ __forceinline__ int fast_div(int a, int d, float r) {
-    const int q = (int)((float)a * r), rem = a - q * d;
-    return q + (rem >= d ? 1 : 0) - (rem < 0 ? 1 : 0);
-}
-
 // Number of list segments an edge walks: upsampling edges walk the source
 // pixels (view order), all others the destination's padded window.
 __device__ __forceinline__ int edge_segments(const EdgeDev& e) {

@@ -1040,7 +1040,7 @@ static hipError_t launch_halo_t(const EdgeBatch& eb, int nb, long long nseg, hip
 
 // Rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 // (ties: the smaller halo).  False if none fits.
-bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out) {
+static bool search_tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out) {
     long long best = -1, best_halo = 0;
     for (int th = 1; th <= sub && th <= Hp; ++th) {
         int tw = sub / th < Wp ? sub / th : Wp;
@@ -1054,6 +1054,23 @@ bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, 
     }
     if (best < 0) return false;
     *tiles_out = best;
+    return true;
+}
+// The search takes some microseconds and every launch asks up to three times: the answers are kept per host thread, a few
+// hundred at most (a network has a handful of window sizes).
+bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out) {
+    struct Entry { int Hp = -1, Wp, k, sub, cap, th, tw; bool fits; long long tiles; };
+    static thread_local Entry table[256];
+    const unsigned h = (unsigned)Hp * 2654435761u ^ (unsigned)Wp * 2246822519u ^ (unsigned)(sub * 8 + k) * 3266489917u ^ (unsigned)cap * 668265263u;
+    Entry& t = table[(h >> 16) % 256];
+    if (t.Hp != Hp || t.Wp != Wp || t.k != k || t.sub != sub || t.cap != cap) {
+        t = Entry{Hp, Wp, k, sub, cap, 0, 0, false, 0};
+        t.fits = search_tile_2d(Hp, Wp, k, sub, cap, &t.th, &t.tw, &t.tiles);
+    }
+    if (!t.fits) return false;
+    *th_out = t.th;
+    *tw_out = t.tw;
+    *tiles_out = t.tiles;
     return true;
 }
 

@@ -60,111 +60,97 @@ __device__ __forceinline__ size_t skip_offset(const SkipDev& k, int vy, int vx, 
 // A = 0 and flag N (sites with crops: state "unseen" in their ring S and a zero
 // previous pooling output).
 // ---------------------------------------------------------------------------
+// Pixel idx of those outside the kept rectangle (rows above it, rows below it, the two sides).
 __device__ __forceinline__ void decode_new(int Wn, int Hn, int y0, int y1, int x0, int x1, int idx, int& y, int& x) {
     const int top = y0 * Wn;
     const int bot = (Hn - y1) * Wn;
-    if (idx < top) {
-        y = idx / Wn; x = idx - y * Wn;
-    } else if (idx < top + bot) {
-        const int j = idx - top;
-        const int q = j / Wn;
-        y = y1 + q; x = j - q * Wn;
+    if (idx < top + bot) {
+        const int q = fast_div(idx, Wn, rcp_of(Wn));
+        x = idx - q * Wn;
+        y = q < y0 ? q : q - y0 + y1;
     } else {
         const int j = idx - top - bot;
         const int mw = x0 + (Wn - x1);
-        const int q = j / mw;
+        const int q = fast_div(j, mw, rcp_of(mw));
         const int c = j - q * mw;
         y = y0 + q;
         x = c < x0 ? c : x1 + (c - x0);
     }
 }
 
-template <typename T, int VEC>
+// An item is VEC channels of a pixel; the view's pixels are one item each if only their flags are set.
+template <typename T, int VEC, typename I>
 __device__ __forceinline__ void fill_items(const FillJob& j, unsigned lb) {
-    const int chunks = j.C / VEC;
-    const long long total = (long long)(j.nP + j.nA) * chunks;
-    // a full reset (empty kept rectangles) needs no ring arithmetic
+    const unsigned chunks = (unsigned)(j.C / VEC), achunks = j.flags_only ? 1u : chunks;
+    const I nPc = (I)j.nP * chunks, total = nPc + (I)j.nA * achunks;
+    // a full reset (empty kept rectangles) needs no ring arithmetic: any order covers the rings
     const bool full = j.py0 == j.py1 && j.px0 == j.px1 && j.ay0 == j.ay1 && j.ax0 == j.ax1 && j.py0 == 0 && j.ay0 == 0;
-    const long long begin = (long long)lb * j.per_block;
-    long long end = begin + j.per_block;
-    if (end > total) end = total;
+    const I begin = (I)lb * (unsigned)j.per_block, end = begin + (unsigned)j.per_block < total ? begin + (unsigned)j.per_block : total;
     uint8_t* const Sr = j.s_off ? (uint8_t*)j.A + (size_t)j.s_off * 256 : nullptr;   // rings like A
     T* const Yr = j.y_off ? (T*)((char*)j.A + (size_t)j.y_off * 256) : nullptr;
-    if constexpr (VEC > 1) {
-        // Full reset with a power-of-two number of 16-byte chunks per pixel (<= 256): the
-        // rings are filled front to back, a thread keeps its channel chunk over the whole
-        // loop (block starts and the stride of 256 are multiples of `chunks`), so the loop
-        // body is one store: no divisions, no bias loads.
-        if (full && (chunks & (chunks - 1)) == 0 && chunks <= 256 && total < (1ll << 31)) {
-            const unsigned nPc = (unsigned)j.nP * chunks, e32 = (unsigned)end;
-            const int c0 = (int)(threadIdx.x & (chunks - 1)) * VEC;
-            int sh = 0;
-            while ((1 << sh) < chunks) ++sh;
-            float bv[VEC], zv[VEC];
+    const bool pow2 = (chunks & (chunks - 1)) == 0;
+    const int sh = 31 - __builtin_clz(chunks);
+    const bool bias16 = VEC > 1 && ((uintptr_t)j.bias & 15) == 0;
+    auto bias_of = [&](unsigned c0, float* v) {
+        if (!j.bias) {
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) { bv[i] = j.bias ? j.bias[c0 + i] : 0.f; zv[i] = 0.f; }
-            for (unsigned idx = (unsigned)begin + threadIdx.x; idx < e32; idx += 256) {
-                if (idx < nPc) {
-                    V16<T>::store((T*)j.P + (size_t)idx * VEC, bv);
-                } else {
-                    const unsigned ia = idx - nPc;
-                    V16<T>::store((T*)j.A + (size_t)ia * VEC, zv);
-                    if (Yr) V16<T>::store(Yr + (size_t)ia * VEC, zv);
-                    if (c0 == 0) {
-                        j.flags[ia >> sh] = (uint8_t)kFlagN;
-                        if (Sr) Sr[ia >> sh] = (uint8_t)kStateUnseen;
-                    }
-                }
+            for (int i = 0; i < VEC; ++i) v[i] = 0.f;
+        } else if (bias16) {
+#pragma unroll
+            for (int i = 0; i < VEC; i += 4) {
+                const float4 b = *reinterpret_cast<const float4*>(j.bias + c0 + i);
+                v[i] = b.x;
+                if constexpr (VEC > 1) { v[i + 1] = b.y; v[i + 2] = b.z; v[i + 3] = b.w; }
             }
-            return;
+        } else {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) v[i] = j.bias[c0 + i];
         }
-    }
-    for (long long idx = begin + threadIdx.x; idx < end; idx += 256) {
-        const int pix = (int)(idx / chunks);
-        const int c0 = (int)(idx - (long long)pix * chunks) * VEC;
-        if (pix < j.nP) {
-            size_t poff = (size_t)pix;                     // everything is new: any order covers the ring
+    };
+    auto put = [&](T* p, const float* v) {
+        if constexpr (VEC > 1) V16<T>::store(p, v);
+        else p[0] = (T)v[0];
+    };
+    float zv[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) zv[i] = 0.f;
+    // With a power-of-two number of chunks per pixel (<= 256) a thread keeps its channels over the whole loop (block starts
+    // and the stride of 256 are multiples of `chunks`): no bias loads in it.
+    const bool keeps = pow2 && chunks <= 256 && (unsigned)j.per_block % 256 == 0;
+    float bv[VEC];
+    if (keeps) bias_of((threadIdx.x & (chunks - 1)) * VEC, bv);
+    for (I idx = begin + threadIdx.x; idx < end; idx += 256) {
+        if (idx < nPc) {
+            const unsigned pix = (unsigned)(pow2 ? idx >> sh : idx / chunks), c0 = (unsigned)(idx - (I)pix * chunks) * VEC;
+            size_t poff = (size_t)pix;
             if (!full) {
                 int wy, wx;
-                decode_new(j.Wp, j.Hp, j.py0, j.py1, j.px0, j.px1, pix, wy, wx);
+                decode_new(j.Wp, j.Hp, j.py0, j.py1, j.px0, j.px1, (int)pix, wy, wx);
                 const int py = wrap(j.p_oy + wy, j.Hp), px = wrap(j.p_ox + wx, j.Wp);
                 poff = (size_t)py * j.Wp + px;
             }
-            T* p = (T*)j.P + poff * j.C + c0;
-            if constexpr (VEC > 1) {
-                float v[VEC];
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) v[i] = j.bias ? j.bias[c0 + i] : 0.f;
-                V16<T>::store(p, v);
-            } else {
-                p[0] = (T)(j.bias ? j.bias[c0] : 0.f);
-            }
-        } else {
-            const int ap = pix - j.nP;
-            size_t aoff = (size_t)ap;
-            int vlin = ap;                                 // view-linear index for the flag
-            if (!full) {
-                int vy, vx;
-                decode_new(j.W, j.H, j.ay0, j.ay1, j.ax0, j.ax1, ap, vy, vx);
-                const int ay = wrap(j.a_oy + vy, j.H), ax = wrap(j.a_ox + vx, j.W);
-                aoff = (size_t)ay * j.W + ax;
-                vlin = vy * j.W + vx;
-            }
-            T* p = (T*)j.A + aoff * j.C + c0;
-            if constexpr (VEC > 1) {
-                float v[VEC];
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) v[i] = 0.f;
-                V16<T>::store(p, v);
-                if (Yr) V16<T>::store(Yr + aoff * j.C + c0, v);
-            } else {
-                p[0] = (T)0.f;
-                if (Yr) Yr[aoff * j.C + c0] = (T)0.f;
-            }
-            if (c0 == 0) {
-                j.flags[vlin] = (uint8_t)kFlagN;
-                if (Sr) Sr[aoff] = (uint8_t)kStateUnseen;
-            }
+            if (!keeps) bias_of(c0, bv);
+            put((T*)j.P + poff * j.C + c0, bv);
+            continue;
+        }
+        const I ia = idx - nPc;
+        const unsigned ap = (unsigned)(j.flags_only ? ia : pow2 ? ia >> sh : ia / chunks), c0 = j.flags_only ? 0u : (unsigned)(ia - (I)ap * chunks) * VEC;
+        size_t aoff = (size_t)ap;
+        int vlin = (int)ap;                                // view-linear index for the flag
+        if (!full) {
+            int vy, vx;
+            decode_new(j.W, j.H, j.ay0, j.ay1, j.ax0, j.ax1, (int)ap, vy, vx);
+            const int ay = wrap(j.a_oy + vy, j.H), ax = wrap(j.a_ox + vx, j.W);
+            aoff = (size_t)ay * j.W + ax;
+            vlin = vy * j.W + vx;
+        }
+        if (!j.flags_only) {
+            put((T*)j.A + aoff * j.C + c0, zv);
+            if (Yr) put(Yr + aoff * j.C + c0, zv);
+        }
+        if (c0 == 0) {
+            j.flags[vlin] = (uint8_t)kFlagN;
+            if (Sr) Sr[aoff] = (uint8_t)kStateUnseen;
         }
     }
 }
@@ -176,11 +162,15 @@ __device__ __forceinline__ void fill_block(const FillJob& j, unsigned lb) {
         for (int i = threadIdx.x; i < j.n_lacc; i += 256) { j.lacc[i] = 0ull; j.lcnt[i] = 0; }
         for (int i = threadIdx.x; i < j.n_cacc; i += 256) { j.cacc[i] = 0ull; j.ccnt[i] = 0; }
     }
-    if (j.dtype == MDCNN_F16) {
-        if (j.C % 8 == 0) fill_items<f16, 8>(j, lb); else fill_items<f16, 1>(j, lb);
-    } else {
-        if (j.C % 4 == 0) fill_items<float, 4>(j, lb); else fill_items<float, 1>(j, lb);
-    }
+    auto go = [&](auto idx) {                              // (item numbers of the largest sites take 64 bits)
+        using I = decltype(idx);
+        if (j.dtype == MDCNN_F16) {
+            if (j.C % 8 == 0) fill_items<f16, 8, I>(j, lb); else fill_items<f16, 1, I>(j, lb);
+        } else {
+            if (j.C % 4 == 0) fill_items<float, 4, I>(j, lb); else fill_items<float, 1, I>(j, lb);
+        }
+    };
+    if (((long long)j.nP + j.nA) * j.C < (1ll << 31)) go(0u); else go(0ull);
 }
 
 __global__ __launch_bounds__(256) void k_shift_fill(FillBatch fb) {
@@ -229,9 +219,14 @@ __device__ __forceinline__ bool crop_state(const SiteDev& s, int pix, bool write
     return inside;
 }
 
+// A pixel of the view that the camera shift has just brought in.
+__device__ __forceinline__ bool unveiled(const FillJob& j, int vy, int vx) {
+    return vy < j.ay0 || vy >= j.ay1 || vx < j.ax0 || vx >= j.ax1;
+}
+
 template <typename T, int G, int CH>
 __device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& skip, const T* __restrict__ X,
-                                            const uint8_t* __restrict__ forced, unsigned blk) {
+                                            const uint8_t* __restrict__ forced, unsigned blk, const FillJob* own = nullptr) {
     constexpr int VEC = V16<T>::N;
     constexpr int PPB = 256 / G;
     const int tid = threadIdx.x;
@@ -248,6 +243,7 @@ __device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& ski
         cand = inside && (is_input || forced != nullptr || (fl & (kFlagN | kFlagU)));
         if (cand) {
             const int vy = pix / s.W, vx = pix - vy * s.W;
+            if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
             T* Ap = (T*)s.A + a_offset(s, vy, vx);
             T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
             const T* Xp = is_input ? X + (size_t)xpix * s.C : nullptr;
@@ -257,7 +253,12 @@ __device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& ski
             for (int j = 0; j < CH; ++j) {
                 const int c0 = (lp + j * G) * VEC;
                 float a[VEC], t[VEC];
-                V16<T>::load(Ap + c0, a);
+                if (fl & kFlagN) {                         // nothing accumulated yet (and perhaps not even set to zero)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) a[i] = 0.f;
+                } else {
+                    V16<T>::load(Ap + c0, a);
+                }
                 if (is_input) {
                     V16<T>::load(Xp + c0, t);
 #pragma unroll
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(256) void k_step1(Step1Batch bt) {
 template <typename T, int G, int CH>
 __global__ __launch_bounds__(256) void k_step1_fill(Step1Fill a) {
     if (blockIdx.x >= a.fill_blocks) {
-        step1_block<T, G, CH>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks);
+        step1_block<T, G, CH>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks, a.has_own ? &a.own : nullptr);
         return;
     }
     int ji = 0;
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256) void k_step1_fill(Step1Fill a) {
 // Any channel count: one lane per pixel, scalar accesses.
 template <typename T>
 __device__ __forceinline__ void step1_scalar_block(const SiteDev& s, const SkipDev& skip, const T* __restrict__ X,
-                                                   const uint8_t* __restrict__ forced, unsigned blk) {
+                                                   const uint8_t* __restrict__ forced, unsigned blk, const FillJob* own = nullptr) {
     const int tid = threadIdx.x;
     const int pix = (int)blk * 256 + tid;
     const int HW = s.H * s.W;
@@ -344,12 +345,13 @@ __device__ __forceinline__ void step1_scalar_block(const SiteDev& s, const SkipD
         cand = inside && (is_input || forced != nullptr || (fl & (kFlagN | kFlagU)));
         if (cand) {
             const int vy = pix / s.W, vx = pix - vy * s.W;
+            if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
             T* Ap = (T*)s.A + a_offset(s, vy, vx);
             T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
             const T* Xp = is_input ? X + (size_t)xpix * s.C : nullptr;
             float mx = 0.f;
             for (int c = 0; c < s.C; ++c) {
-                float a = (float)Ap[c], o;
+                float a = fl & kFlagN ? 0.f : (float)Ap[c], o;
                 if (is_input) {
                     o = (float)Xp[c] - a;
                 } else {
@@ -365,7 +367,7 @@ __device__ __forceinline__ void step1_scalar_block(const SiteDev& s, const SkipD
                 T* Sp = skip.P ? (T*)skip.P + skip_offset(skip, vy, vx, s.C) : nullptr;
                 if (Sp && skip.dflags) skip.dflags[pix] |= (uint8_t)kFlagU;
                 for (int c = 0; c < s.C; ++c) {
-                    float a = (float)Ap[c];
+                    float a = fl & kFlagN ? 0.f : (float)Ap[c];
                     if (is_input) {
                         float x = (float)Xp[c];
                         Ap[c] = (T)x;
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(256) void k_step1_scalar(Step1Batch bt) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_step1_scalar_fill(Step1Fill a) {
     if (blockIdx.x >= a.fill_blocks) {
-        step1_scalar_block<T>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks);
+        step1_scalar_block<T>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks, a.has_own ? &a.own : nullptr);
         return;
     }
     int ji = 0;

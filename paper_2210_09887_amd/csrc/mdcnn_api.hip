@@ -195,6 +195,12 @@ struct RoundPlan {
     int key = -1;              // g_fuse_skip the plan was made for
     int n_ops = 0;
     std::vector<std::vector<RoundOp>> rounds;
+    // How the sites of a single video are initialised after a camera shift: site 0 by its own step 1 if that is the first
+    // launch (own0), as many others as fit by spare blocks of the same launch (fills), the rest by a launch ahead of it
+    // (head).  (Spread over the step-1 launches of the frame, each just before the site is needed, they were slower:
+    // every such launch waits for the strips' round trips; ResNet-18-style frame 455 -> 464 us.)
+    std::vector<int> fills, head;
+    bool own0 = false;
     bool shorter(int of, int than) const { return (int)rounds.size() * of < n_ops * than; }
 };
 
@@ -407,6 +413,7 @@ mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* fram
         // initialisation jobs of other sites, which nothing in this launch touches, ride along
         static thread_local Step1Fill sf;
         sf.s = sb.s[0]; sf.skip = sb.skip[0]; sf.X = sb.X[0]; sf.forced = sb.forced[0];
+        sf.has_own = 0;
         sf.n = n_riders;
         for (int k = 0; k < n_riders; ++k) sf.j[k] = jobs[riders[k]];
         err = timed(kClsStep1, st, [&] { return launch_step1_fill(sf, st); });
@@ -614,6 +621,15 @@ void make_rounds(const mdcnn_net* net, RoundPlan& rp) {
         for (int k : ready[kind]) { rp.rounds.back().push_back(ops[(size_t)k].op); ops[(size_t)k].done = true; --left; }
         last_kind = kind;
     }
+    rp.fills.clear();
+    rp.head.clear();
+    const std::vector<RoundOp>* r0 = rp.rounds.empty() ? nullptr : &rp.rounds[0];
+    rp.own0 = r0 && r0->size() == 1 && (*r0)[0].edge == -1 && (*r0)[0].site == 0;
+    for (int s = rp.own0 ? 1 : 0; s < n_sites; ++s) {
+        const bool busy = rp.own0 && (*r0)[0].skip >= 0 && net->edst[(size_t)(*r0)[0].skip] == s;      // step 1 adds to it
+        if (rp.own0 && !busy && (int)rp.fills.size() < kMaxRiders) rp.fills.push_back(s);
+        else rp.head.push_back(s);
+    }
 }
 
 // Length of a plan in launches, if every launch took one unit of time and a wait for another
@@ -647,12 +663,15 @@ void choose_plan(const mdcnn_net* net, int streams, Plan& plan) {
 // 384 x 288 HRNet-like network: a frame 1 213 -> 657 us (178 launches -> 76), frames in flight 647 -> 266 us, 8 videos 1 914 ->
 // 1 420 us; ResNet-18-style network (a projection beside the first convolution of a block, 3 launches of 37): 518 -> 476 us.
 bool use_rounds(mdcnn_net* net, bool overlap = false) {
-    if (g_streams != 0 || g_profile || net->sites[0]->d.dtype != MDCNN_F16) return false;
+    if (g_streams != 0 || g_profile) return false;
     if (net->rounds.key != g_fuse_skip) {
         make_rounds(net, net->rounds);
         net->rounds.key = g_fuse_skip;
     }
-    return overlap ? net->rounds.shorter(5, 4) : net->rounds.shorter(1, 1);
+    // (fp32 launches are not put together, a network with branches keeps its streams; frames one by one run in rounds of
+    // one launch each otherwise, for what that saves in initialisation launches)
+    const bool f16 = net->sites[0]->d.dtype == MDCNN_F16;
+    return overlap ? f16 && net->rounds.shorter(5, 4) : f16 || !net->rounds.shorter(5, 4);
 }
 
 // The library's own streams (per host thread, default priority, made on first use) and events.
@@ -754,6 +773,15 @@ mdcnn_status shift_jobs(mdcnn_buffer* const* bufs, int n, int dty, int dtx, std:
     return MDCNN_OK;
 }
 
+// For the initialisation of a whole frame: where a frame follows that visits every newly unveiled pixel of a site and gives
+// it an accumulated value (step 1 emits them all and takes zero for what they held), only the flags are set.  Not for
+// sites with crops (a later frame may be the one that covers the pixel), truncation-free sites (their producer reads A)
+// and sites somebody else reads before step 1 (`read0`: site 0, by the mask front end).  Halves what a reset writes.
+void frame_follows(mdcnn_buffer* const* bufs, std::vector<FillJob>& jobs, bool read0) {
+    for (size_t i = 0; i < jobs.size(); ++i)
+        jobs[i].flags_only = jobs[i].nA > 0 && !bufs[i]->d.crops && !bufs[i]->d.truncation_free && !(read0 && i == 0);
+}
+
 // Launches jobs[which[0 .. count)] (which == nullptr: jobs[0 .. count)), kMaxFillJobs to a launch.
 hipError_t launch_fill_jobs(const FillJob* jobs, const int* which, int count, hipStream_t st) {
     FillBatch fb{};
@@ -786,7 +814,8 @@ bool whole_view(const mdcnn_buffer* b) { return crop_pixels(b) == (size_t)b->d.H
 // One round of a plan for n videos (n <= kMaxBatch): sites[b] are the sites of video b as the frame sees them.
 // Operations the multi-edge kernels do not take get a launch each.
 mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets, int n, const std::vector<mdcnn_buffer* const*>& sites,
-                       const void* const* frames, const uint8_t* const* forced, hipStream_t st) {
+                       const void* const* frames, const uint8_t* const* forced, hipStream_t st, const FillJob* jobs = nullptr,
+                       const std::vector<int>* fills = nullptr) {
     static thread_local Step1Batch sb;                     // 3.4 to 4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
     static thread_local Step1Multi sm;
@@ -813,7 +842,16 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
             for (int b = 0; b < n; ++b)
                 set_step1(sb, b, sites[(size_t)b][op.site], sd >= 0 ? sites[(size_t)b][sd] : nullptr, op.site == 0 && frames ? frames[b] : nullptr,
                           op.site == 0 && forced ? forced[b] : nullptr);
-            if (round.size() == 1 || !step1_multi_applies(in0->dev)) {
+            if (jobs) {                                    // the first launch of a frame of one video, with what it initialises
+                static thread_local Step1Fill sf;
+                sf.s = sb.s[0]; sf.skip = sb.skip[0]; sf.X = sb.X[0]; sf.forced = sb.forced[0];
+                sf.n = 0;
+                for (int s : *fills)
+                    if (fill_blocks(jobs[s]) > 0) sf.j[sf.n++] = jobs[s];
+                sf.has_own = fill_blocks(jobs[op.site]) > 0;
+                if (sf.has_own) sf.own = jobs[op.site];
+                err = sf.n || sf.has_own ? launch_step1_fill(sf, st) : launch_step1(sb, n, st);
+            } else if (round.size() == 1 || !step1_multi_applies(in0->dev)) {
                 err = launch_step1(sb, n, st);
             } else {
                 if (sm.n == kMaxMultiJobs || (sm.n + 1) * n > kMaxStep1Vids) flush_step1();
@@ -874,18 +912,33 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
                 for (mdcnn_buffer* s : nets[b]->sites) s->fresh = true;
         }
     } unfinished{nets, n};
-    for (int b = 0; b < n; ++b) {
-        mdcnn_status rc = mdcnn_shift_camera(nets[b]->sites.data(), (int)nets[b]->sites.size(), dty[b], dtx[b], stream,
-                                             did_full_reset ? did_full_reset + b : nullptr);
-        if (rc) return rc;
-    }
     mdcnn_net* net = nets[0];
+    const bool rounds = use_rounds(net);
+    static thread_local std::vector<FillJob> jobs;
+    const bool ride = rounds && n == 1 && net->rounds.own0 && !net->sites[0]->d.crops && !net->sites[0]->fresh;
+    if (ride) {                                            // the initialisation goes with the launches of the frame
+        bool full = false;
+        mdcnn_status rc = shift_jobs(net->sites.data(), (int)net->sites.size(), dty[0], dtx[0], jobs, &full);
+        if (rc) return rc;
+        if (did_full_reset) did_full_reset[0] = full ? 1 : 0;
+        frame_follows(net->sites.data(), jobs, false);
+        const hipError_t err = launch_fill_jobs(jobs.data(), net->rounds.head.data(), (int)net->rounds.head.size(), st);
+        if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "shift launch: %s", hipGetErrorString(err));
+    }
+    for (int b = 0; b < n && !ride; ++b) {
+        bool full = false;
+        mdcnn_status rc = shift_jobs(nets[b]->sites.data(), (int)nets[b]->sites.size(), dty[b], dtx[b], jobs, &full);
+        if (rc) return rc;
+        if (did_full_reset) did_full_reset[b] = full ? 1 : 0;
+        frame_follows(nets[b]->sites.data(), jobs, false);
+        const hipError_t err = launch_fill_jobs(jobs.data(), nullptr, (int)jobs.size(), st);
+        if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "shift launch: %s", hipGetErrorString(err));
+    }
     const int n_edges = (int)net->edges.size();
     // independent branches of the network on streams of their own; the caller's stream forks into
     // them after the shift and joins them before the readout, so to the caller the call is in
     // stream order as before
     Sched sched, *sc = nullptr;
-    const bool rounds = use_rounds(net);
     if (g_streams != 1 && !rounds) {
         const int key = g_streams * 2 + g_fuse_skip;
         if (net->plan.key != key) {
@@ -928,8 +981,8 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     if (rounds) {
         std::vector<mdcnn_buffer* const*> sites((size_t)n);
         for (int b = 0; b < n; ++b) sites[(size_t)b] = nets[b]->sites.data();
-        for (const std::vector<RoundOp>& round : net->rounds.rounds) {
-            mdcnn_status rc = run_round(round, nets, n, sites, frames, forced, st);
+        for (size_t r = 0; r < net->rounds.rounds.size(); ++r) {
+            mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills);
             if (rc) return rc;
         }
     }
@@ -1211,6 +1264,7 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
                 mdcnn_status rc = shift_jobs(nv->sites.data(), n_sites, dty[fv], dtx[fv], jobs, &full);
                 if (rc) return rc;
                 if (did_full_reset) did_full_reset[fv] = full ? 1 : 0;
+                frame_follows(nv->sites.data(), jobs, fe != nullptr);
                 if (crops) {                                   // (nb == 1)
                     rc = mdcnn_set_crop(nv->sites.data(), n_sites, crops[4 * f], crops[4 * f + 1], crops[4 * f + 2], crops[4 * f + 3]);
                     if (rc) return rc;

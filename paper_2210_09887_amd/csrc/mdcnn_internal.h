@@ -9,6 +9,15 @@
 
 namespace mdcnn {
 
+// a / d for a >= 0, r = 1 / d within a rounding (rcp_of): below 2^24 the quotient of the floats is off by one at most.  A
+// tenth of the instructions of an integer division, of which the start of a tile has one per index it decodes.
+__device__ __forceinline__ float rcp_of(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ __forceinline__ int fast_div(int a, int d, float r) {
+    if (a >= 1 << 24) return a / d;
+    const int q = (int)((float)a * r), rem = a - q * d;
+    return q + (rem >= d ? 1 : 0) - (rem < 0 ? 1 : 0);
+}
+
 constexpr int kFlagN = 1;   // newly unveiled this frame
 constexpr int kFlagU = 2;   // touched by a producer this frame
 constexpr int kFlagM = 4;   // updated (emitted a delta) this frame
@@ -104,9 +113,11 @@ struct FillJob {
     int dtype;
     int reset_counters;         // 1: first reset of the site, clear its counters and lists
     int per_block;              // items a block initialises
+    int flags_only;             // 1: the view's new pixels get their flag N and nothing else - the frame that follows replaces
+                                // their accumulated values without reading them
     unsigned block_begin;       // first block of the launch that works on this job
 };
-constexpr int kMaxFillJobs = 21;
+constexpr int kMaxFillJobs = 20;
 struct FillBatch {
     FillJob j[kMaxFillJobs];
     int n;
@@ -118,7 +129,8 @@ struct FillBatch {
 constexpr int kFillItemsPerBlockFull = 2048, kFillItemsPerBlockStrip = 512;
 inline unsigned fill_blocks(const FillJob& j) {   // blocks a job takes in a launch (none if nothing was unveiled)
     const int vec = j.dtype == MDCNN_F16 ? 8 : 4;
-    const long long items = (long long)(j.nP + j.nA) * (j.C % vec == 0 ? j.C / vec : j.C);
+    const int chunks = j.C % vec == 0 ? j.C / vec : j.C;
+    const long long items = (long long)j.nP * chunks + (long long)j.nA * (j.flags_only ? 1 : chunks);
     const long long blocks = (items + j.per_block - 1) / j.per_block;
     return (unsigned)(blocks < 1 && j.reset_counters ? 1 : blocks);
 }
@@ -177,12 +189,16 @@ struct Step1Batch {
 };
 // One site's step 1 and, in the same launch, initialisation jobs of OTHER sites that nothing in this
 // launch touches (blocks [0, fill_blocks) of the grid; the site's own blocks follow).
-constexpr int kMaxRiders = 6;
+// own: the site's own initialisation (an INPUT site without crops, not its first reset), done by step 1 itself - a pixel
+// outside the kept rectangle of the view counts as newly unveiled and its accumulated value as zero.
+constexpr int kMaxRiders = 18;
 struct Step1Fill {
     SiteDev s;
     SkipDev skip;
     const void* X;
     const uint8_t* forced;
+    FillJob own;
+    int has_own;
     FillJob j[kMaxRiders];
     int n;
     unsigned fill_blocks;
