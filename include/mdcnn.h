@@ -486,7 +486,7 @@ typedef enum {
                              /* 3 auto but never the packed-weights kernel                */
     MDCNN_OPT_PROFILE = 1,   /* 1: bracket every kernel launch with a pair of HIP events  */
     MDCNN_OPT_CONV_TILE = 2, /* tuning: 0 auto, 1..14 force a tile shape of the fp16 MFMA kernel; */
-                             /* fp32 3x3 layers: 1 / 2 / 4 waves share the taps of a tile         */
+                             /* fp32 3x3 layers of 16 channels: 1 / 2 / 4 waves share the taps     */
     MDCNN_OPT_CONV_PIPE = 3, /* tuning: 0 auto, 1 / 2 prefetch depth of the MFMA kernel    */
     MDCNN_OPT_CONV_XCD = 4,  /* tuning: 1 (default) tie cout tiles to XCDs, 0 plain order  */
     MDCNN_OPT_CONV_KC = 5,   /* tuning: 0 auto, 64 cap the K step at 64 channels           */

@@ -15,8 +15,8 @@
 //                       channel chunk in LDS, packed weights straight into MFMA fragments
 //   k_conv_mfma_tiled : LDS-tiled gather-GEMM on the CDNA4 matrix cores (fp16 in, fp32 acc)
 //   k_conv_mfma_f16   : MFMA without LDS staging (fallback for Cin % 32 != 0)
-//   k_conv_mfma_f32   : fp32 layers of up to 64 channels, weights in LDS (fp32 matrix instruction)
-//   k_conv_direct     : operands straight from global memory (conv_direct.h): all other fp32 layers with
+//   k_conv_mfma_f32   : small fp32 layers, weights in LDS (fp32 matrix instruction)
+//   k_conv_f32        : weights and delta rows staged in LDS (conv_f32.h): all other fp32 layers with
 //                       Cin % 8 == 0 and Cout 16 or a multiple of 32
 //   k_conv_small      : 3-channel 3x3 stems, plain FMA
 //   k_conv_ldsw       : plain FMA with the weights resident in LDS (fp32 nets)
@@ -1229,7 +1229,8 @@ static hipError_t launch_mfma_f32_ks(const EdgeBatch& eb, int nb, long long nseg
         return launch_mfma_f32_inst<KK, CIN, 1>(eb, nb, nseg, st);
     } else {
         // two waves share the taps of a 64-entry tile unless 128-entry tiles already give every compute unit four
-        // blocks (config 2, 66 and 17 segments: 10.5 k frames/s with one wave per tile, 11.7 k with two, 10.4 k with four)
+        // blocks (measured on 32- and 64-channel layers of 66 and 17 segments: 10.5 k frames/s of a small network with one wave
+        // per tile, 11.7 k with two, 10.4 k with four)
         const long long nts = (e.Cout + 31) / 32;
         int ks = nseg * 2 * nts >= 1024 ? 1 : 2;
         if (g_tile == 1 || g_tile == 2 || g_tile == 4) ks = g_tile;
@@ -1241,13 +1242,11 @@ static hipError_t launch_mfma_f32_ks(const EdgeBatch& eb, int nb, long long nseg
 static hipError_t launch_mfma_f32(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, bool* done) {
     const EdgeDev& e = eb.d[0];
     *done = false;
-    if (e.up || (e.k != 1 && e.k != 3) || (e.Cin != 16 && e.Cin != 32 && e.Cin != 64) || (e.Cout % 32 != 0 && e.Cout != 16) || e.Cout > 1024 ||
+    if (e.up || (e.k != 1 && e.k != 3) || (e.Cin != 16 && (e.k == 3 || (e.Cin != 32 && e.Cin != 64))) || (e.Cout % 32 != 0 && e.Cout != 16) || e.Cout > 1024 ||
         (long long)e.sH * e.sW * e.Cin >= (1ll << 29) || (long long)e.k * e.k * e.Cin * e.Cout >= (1ll << 29))
         return hipSuccess;
     *done = true;
-    if (e.k == 3)
-        return e.Cin == 16 ? launch_mfma_f32_ks<3, 16>(eb, nb, nseg, st)
-             : e.Cin == 32 ? launch_mfma_f32_ks<3, 32>(eb, nb, nseg, st) : launch_mfma_f32_ks<3, 64>(eb, nb, nseg, st);
+    if (e.k == 3) return launch_mfma_f32_ks<3, 16>(eb, nb, nseg, st);
     return e.Cin == 16 ? launch_mfma_f32_ks<1, 16>(eb, nb, nseg, st)
          : e.Cin == 32 ? launch_mfma_f32_ks<1, 32>(eb, nb, nseg, st) : launch_mfma_f32_ks<1, 64>(eb, nb, nseg, st);
 }
@@ -1320,11 +1319,13 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, hi
         return hipGetLastError();
     }
     if (dtype == MDCNN_F32 && (conv_path == 0 || conv_path == 3) && g_f32_mfma) {
+        // 1x1 layers of up to 64 channels and 3x3 layers of 16, whose weights k_conv_mfma_f32 keeps in LDS (1x1, 32 to 64
+        // channels at 128 x 128: 7.5 us, 9.0 with k_conv_f32); k_conv_f32 for the rest, 3x3 layers of 32 and 64 channels among
+        // them (64 at 128 x 128: 20 us, 35 with the weights in LDS; 32: 13 and 14.5)
         bool done = false;
         const hipError_t err = launch_mfma_f32(eb, nb, nseg, st, &done);
         if (done) { *cls = kClsConvMfma; return err; }
-        // every other layer whose rows are whole K blocks (the weights of a wide layer do not fit the LDS)
-        if (direct_applies(e, dtype)) { *cls = kClsConvMfma; return launch_conv_direct(eb, nb, dtype, st); }
+        if (f32_applies(e)) { *cls = kClsConvMfma; return launch_conv_f32(eb, nb, st); }
     }
     if ((conv_path == 0 || conv_path == 3) && g_f32_mfma && e.k == 3 && e.Cin == 3 && e.Cout % 32 == 0 && e.Cout <= 1024 && !e.up &&
         (long long)e.sH * e.sW * 3 < (1ll << 29)) {

@@ -286,9 +286,9 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);
 // returns the kernel class that was launched in *cls
 // pick: nothing is launched; *pick says with which configuration of k_conv_multi the edge would run, if with one
 hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, hipStream_t st, int* cls, ConvPick* pick = nullptr);
-// convolution tile straight from global memory (kernels_direct.hip): shapes it takes, launch
-bool direct_applies(const EdgeDev& e, int dtype);
-hipError_t launch_conv_direct(const EdgeBatch& eb, int nb, int dtype, hipStream_t st);
+// fp32 layers on the matrix cores (kernels_f32.hip): shapes it takes, launch
+bool f32_applies(const EdgeDev& e);
+hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st);
 extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // convolution tuning knobs
 // host-only: the rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);

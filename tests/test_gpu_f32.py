@@ -1,5 +1,5 @@
-"""Convolution tiles that read their operands straight from global memory (fp32 layers of many channels),
-against the oracle on ragged windows, partial cout tiles, strides and upsampling edges."""
+"""The convolution tile of the fp32 layers, against the oracle on ragged windows, partial chunks and cout tiles, odd numbers
+of steps, strides and upsampling edges."""
 import numpy as np
 import pytest
 
@@ -22,22 +22,24 @@ def frames_of(net, seed, n=3):
 
 
 @pytest.mark.parametrize("cin,cout,H,W,k,stride", [
-    (128, 32, 8, 8, 3, 1),         # one tile and a bit: the 10 x 10 window in 8 x 4 tiles
-    (8, 32, 5, 37, 3, 1),          # one K block per tap: waves share the taps
-    (24, 96, 33, 18, 3, 1),        # three blocks per tap, three cout tiles
+    (128, 32, 8, 8, 3, 1),         # one tile and a bit: the 10 x 10 window in tiles of up to 32 pixels
+    (8, 32, 5, 37, 3, 1),          # a quarter of a chunk: one wave multiplies
+    (24, 96, 33, 18, 3, 1),        # three quarters of a chunk, three cout tiles
     (72, 16, 30, 22, 1, 1),        # half a cout tile
     (128, 128, 48, 40, 3, 2),      # stride 2
-    (40, 64, 90, 100, 5, 1),       # 25 taps; enough pixels for the larger tiles
+    (40, 64, 90, 100, 5, 1),       # 25 taps; a chunk and a quarter
     (512, 64, 11, 9, 3, 1),        # a long K loop
+    (32, 32, 41, 29, 3, 1),        # one chunk: an odd number of steps
+    (64, 96, 3, 75, 3, 1),         # two chunks; a window narrower than a tile is high
 ])
-def test_fp32_layers_straight_from_memory(cin, cout, H, W, k, stride):
+def test_fp32_layers(cin, cout, H, W, k, stride):
     import gpu_harness as G
     H, W = H * stride, W * stride
     net = tiny_net("f32", H, W, (cin, cout), k=k, stride=stride, theta=0.05, seed=cin + cout, total_stride=stride)
     G.teacher_forced(net, frames_of(net, cin * 10 + cout), [(0, 0), (0, 0), (1, -1)])
 
 
-def test_fp32_upsampling_edge_straight_from_memory():
+def test_fp32_upsampling_edge():
     import gpu_harness as G
     net = NetSpec("up", "f32", 36, 52, 4)
     b = _Builder(net, np.random.default_rng(3), 0.1)

@@ -7,7 +7,7 @@ import torch
 
 from inputs import build_net, build_sequence
 from inputs.nets import NetSpec, _Builder, random_dag_net
-from test_gpu_direct import frames_of
+from test_gpu_f32 import frames_of
 from test_gpu_streams import run, same
 
 pytestmark = pytest.mark.gpu
