@@ -505,7 +505,7 @@ typedef enum {
                              /* groups let a frame follow the one before it more closely, at one more event   */
                              /* and wait per group and frame.  0 (default): about twenty groups per frame,    */
                              /* four calls per group at most                                                 */
-    MDCNN_OPT_PIPE_THREADS = 12, /* mdcnn_frames: 1 (default) in mode 1, runs of at least 4 x depth frames are    */
+    MDCNN_OPT_PIPE_THREADS = 12, /* mdcnn_frames: 1 (default) in mode 1, runs of three frames or more are         */
                              /* issued by one host thread per stream (started and joined inside the call; a   */
                              /* frame is issued after the events it waits for have been recorded); 0: the     */
                              /* calling thread issues everything                                             */

@@ -10,6 +10,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -1419,10 +1420,12 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
         return MDCNN_OK;
     };
 
-    // One issuing thread per stream where whole frames go to streams and the run is long enough to pay for
-    // starting them; the profiling mode keeps its event lists on the calling thread.  Frame 0 is issued first
-    // and alone: it takes every kernel of the network through its first launch on this thread.
-    const bool threads = g_pipe_threads && pp.mode == 1 && depth > 1 && n_frames >= 4 * depth && !g_profile;
+    // One issuing thread per stream where whole frames go to streams, from three frames on (issuing a frame takes one thread
+    // about as long as the GPU needs for it; starting the threads takes less: ResNet-18-style network, 4 frames of 256 x 256
+    // 931 -> 797 us, 12 of 720 x 1280 boxes 3350 -> 2719 us, HRNet-like network, 3 / 8 frames 1376 / 3421 -> 1099 / 2149 us; two
+    // frames: no difference); the profiling mode keeps its event lists on the calling thread.  Frame 0 is issued first and
+    // alone: it takes every kernel of the network through its first launch on this thread.
+    const bool threads = g_pipe_threads && pp.mode == 1 && depth > 1 && n_frames >= 3 && !g_profile;
     mdcnn_status rc = MDCNN_OK;
     if (!threads) {
         for (int f = 0; f < n_frames && rc == MDCNN_OK; ++f) rc = issue_frame(f, false);
@@ -1433,9 +1436,15 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
             (void)hipGetDevice(&device);
             std::vector<mdcnn_status> st_of((size_t)depth, MDCNN_OK);
             std::vector<std::string> msg_of((size_t)depth);
-            auto worker = [&](int k) {
+            std::vector<std::thread> pool;
+            pool.reserve((size_t)depth);
+            // thread k issues the frames of stream k; the calling thread those of stream 0 and of the streams whose thread
+            // could not be started (`own` and up), in the order of the frames
+            auto worker = [&](int k, int own) {
                 if (k) (void)hipSetDevice(device);
-                for (int f = k ? k : depth; f < n_frames; f += depth) {
+                for (int f = 1; f < n_frames; ++f) {
+                    const int stream = f % depth;
+                    if (stream != k && (k || stream < own)) continue;
                     if (shared.abort.load(std::memory_order_relaxed)) break;
                     const mdcnn_status r = issue_frame(f, true);
                     if (r != MDCNN_OK) {
@@ -1446,9 +1455,12 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
                     }
                 }
             };
-            std::vector<std::thread> pool;
-            for (int k = 1; k < depth; ++k) pool.emplace_back(worker, k);
-            worker(0);
+            int own = 1;
+            try {
+                for (; own < depth && own < n_frames; ++own) pool.emplace_back(worker, own, depth);
+            } catch (const std::system_error&) {
+            }
+            worker(0, own);
             for (std::thread& t : pool) t.join();
             for (int k = 0; k < depth && rc == MDCNN_OK; ++k)
                 if (st_of[(size_t)k] != MDCNN_OK) rc = fail(st_of[(size_t)k], "%s", msg_of[(size_t)k].c_str());
