@@ -423,11 +423,24 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
 // footprint row are nine consecutive values.  A block owns 128 list entries and
 // one tile of 32 couts (blockIdx.y), a wave 32 entries; a lane fetches its 14
 // values with single-element buffer loads that all go out together (a tap
-// outside the entry's mask reads beyond the tensor: zero).
+// outside the entry's mask reads beyond the tensor: zero).  The lists, touched
+// marks and counts are left to the last npub blocks (publish_edge): a stem's
+// source has four times the pixels of its destination, and every tile used to
+// compact its share of them, a round trip and two barriers per segment, before
+// its own loads: 512 x 512 frames and 64 couts 15.4 -> 14.1 us, 384 x 288
+// 12.4 -> 10.3, 256 x 256 fp32 and 32 couts 9.3 -> 7.6; boxes of 720 x 1280
+// frames 29.5 either way.  What bounds it: the round trips of a tile, flags,
+// deltas and pending rows.  (64 couts to a block with P updated through LDS in
+// whole rows has half the blocks and is slower: 15.9 us, 33 on the boxes.)
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb) {
+__global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb, unsigned npub) {
     const EdgeDev& e = eb.d[blockIdx.z];                  // blockIdx.z: stream of the batch
+    const unsigned nblk = gridDim.x - npub;
+    if (blockIdx.x >= nblk) {
+        if (blockIdx.y == 0) publish_edge<3>(e, blockIdx.x - nblk, npub);
+        return;
+    }
     constexpr int BM = 128, KH = 14;
     __shared__ float sW[2 * KH * 32];                       // [k][32 couts], row 27 zero
     __shared__ int s_base[BM], s_wy[BM], s_wx[BM];
@@ -438,21 +451,18 @@ __global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb) {
     const int p32 = lane & 31, h = lane >> 5;
     const int nt = blockIdx.y;
     const T* __restrict__ w = (const T*)e.w;
-    carry_source_compaction(e, sh);
     for (int i = tid; i < 28 * 32; i += 256) {              // weights [tap][cout][3] -> LDS [k = 3 tap + ci][cout of the tile]
         const int k = i >> 5, co = i & 31;
         sW[i] = k < 27 ? (float)w[((k / 3) * e.Cout + nt * 32 + co) * 3 + k % 3] : 0.f;
     }
     const rsrc_t drs = make_rsrc(e.delta, (unsigned)e.sH * (unsigned)e.sW * 3u * (unsigned)sizeof(T));
-    long long block_taps = 0;                               // statistics (thread 0 of the blocks of cout tile 0)
     constexpr int TPS = kSegPixels / BM;
     const int MT = edge_segments(e) * TPS;
-    for (int tile = blockIdx.x; tile < MT; tile += gridDim.x) {
+    for (int tile = blockIdx.x; tile < MT; tile += (int)nblk) {
         const int seg = tile / TPS, first = (tile - seg * TPS) * BM;
         __syncthreads();
-        const int tot = tile_prologue(e, seg, first, BM, nt == 0 && first == 0, nt == 0, s_base, s_wy, s_wx, s_vm, sh);
+        const int tot = tile_prologue(e, seg, first, BM, false, false, s_base, s_wy, s_wx, s_vm, sh);
         if (first >= tot) continue;                         // block-uniform
-        if (tid == 0 && nt == 0) block_taps += sh[4];
         if (first + wave * 32 >= tot) continue;             // no entry for this wave (no barrier until the next tile)
         const int pl = wave * 32 + p32;
         const bool act = first + pl < tot;
@@ -501,7 +511,6 @@ __global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb) {
             }
         }
     }
-    if (tid == 0) add_macs(e, block_taps, 0);               // statistics: one atomic per block
 }
 
 // ---------------------------------------------------------------------------
@@ -1355,9 +1364,9 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, hi
     if ((conv_path == 0 || conv_path == 3) && g_f32_mfma && e.k == 3 && e.Cin == 3 && e.Cout % 32 == 0 && e.Cout <= 1024 && !e.up &&
         (long long)e.sH * e.sW * 3 < (1ll << 29)) {
         *cls = kClsConvMfma;
-        const unsigned g = cap_blocks(nseg * (kSegPixels / 128), 2048);
-        if (dtype == MDCNN_F16) k_conv_stem_mfma<f16><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb);
-        else k_conv_stem_mfma<float><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb);
+        const unsigned npub = publish_blocks(e, 512), g = cap_blocks(nseg * (kSegPixels / 128), 2048) + npub;
+        if (dtype == MDCNN_F16) k_conv_stem_mfma<f16><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb, npub);
+        else k_conv_stem_mfma<float><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb, npub);
         return hipGetLastError();
     }
     *cls = kClsConvPlain;
