@@ -479,18 +479,19 @@ __global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
     while (j + 1 < m.n && blockIdx.x >= m.job[j + 1].block0) ++j;
     const Step1Job& jb = m.job[j];
     const Step1Vid& v = m.vid[j * gridDim.z + blockIdx.z];
-    SiteDev s = jb.s;
-    SkipDev k = jb.skip;
-    auto at = [](auto*& p, long long d) {
-        if (p) p = (std::remove_reference_t<decltype(p)>)((uintptr_t)p + (uintptr_t)d);
-    };
-    at(s.A, v.sd); at(s.P, v.sd); at(s.flags, v.sd); at(s.delta, v.sd);
-    s.a_oy = v.a_oy; s.a_ox = v.a_ox; s.p_oy = v.p_oy; s.p_ox = v.p_ox; s.cy = v.cy; s.cx = v.cx;
-    at(k.P, v.kd); at(k.dflags, v.kd);
-    k.p_oy = v.k_oy; k.p_ox = v.k_ox;
+    auto at = [](auto* p, long long d) { return p ? (decltype(p))((uintptr_t)p + (uintptr_t)d) : nullptr; };
+    SiteDev s{};
+    s.kind = MDCNN_SITE_PREACT;
+    s.A = at(jb.A, v.sd); s.P = at(jb.P, v.sd); s.delta = at(jb.delta, v.sd); s.flags = at(jb.flags, v.sd);
+    s.H = jb.H; s.W = jb.W; s.C = jb.C; s.Hp = jb.Hp; s.Wp = jb.Wp; s.by0 = jb.by0; s.bx0 = jb.bx0; s.relu = jb.relu;
+    s.theta = v.theta; s.s_off = jb.s_off; s.cy = v.cy; s.cx = v.cx;
+    s.a_oy = v.a_oy; s.a_ox = v.a_ox; s.p_oy = v.p_oy; s.p_ox = v.p_ox;
+    SkipDev k{};
+    k.P = at(jb.skip_P, v.kd); k.dflags = at(jb.skip_flags, v.kd);
+    k.Hp = jb.skip_Hp; k.Wp = jb.skip_Wp; k.by0 = jb.skip_by0; k.bx0 = jb.skip_bx0; k.p_oy = v.k_oy; k.p_ox = v.k_ox;
     const unsigned blk = blockIdx.x - jb.block0;
     const f16* const X = nullptr;
-    switch (jb.G) {
+    switch (s.C / V16<f16>::N) {                           // lanes per pixel
         case 1: step1_block<f16, 1, 1>(s, k, X, nullptr, blk); break;
         case 2: step1_block<f16, 2, 1>(s, k, X, nullptr, blk); break;
         case 4: step1_block<f16, 4, 1>(s, k, X, nullptr, blk); break;
@@ -509,10 +510,12 @@ bool step1_multi_applies(const SiteDev& s) {
 hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
     unsigned blocks = 0;
     for (int j = 0; j < m.n; ++j) {
-        int CH = 0;
-        if (!step1_shape(m.job[j].s.C, V16<f16>::N, m.job[j].G, CH) || CH != 1) return hipErrorInvalidValue;
-        m.job[j].block0 = blocks;
-        blocks += step1_blocks_of(m.job[j].s);
+        Step1Job& jb = m.job[j];
+        int G = 0, CH = 0;
+        if (!step1_shape(jb.C, V16<f16>::N, G, CH) || CH != 1) return hipErrorInvalidValue;
+        const int ppb = 256 / G;
+        jb.block0 = blocks;
+        blocks += (unsigned)((jb.H * jb.W + ppb - 1) / ppb);
     }
     k_step1_multi<<<dim3(blocks, 1, (unsigned)videos), dim3(256), 0, st>>>(m);
     return hipGetLastError();

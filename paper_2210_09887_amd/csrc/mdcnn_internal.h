@@ -261,17 +261,23 @@ struct ConvMulti {
 static_assert(sizeof(ConvMulti) <= 4000, "kernel arguments stay below 4 KiB");
 hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_t st);      // fills in block0
 
-// The same for step 1 of several sites (no INPUT sites: those take a frame).
+// The same for step 1 of several sites (PREACT sites only: an INPUT site takes a frame).  The job holds what networks of
+// equal shape have in common and the addresses of the first video, everything else is the video's own.
 struct Step1Job {
-    SiteDev s;
-    SkipDev skip;
-    int G;                    // lanes per pixel (one 16-byte chunk each)
+    void *A, *P, *delta;
+    uint8_t* flags;
+    void* skip_P;             // destination of the residual add, nullptr: none
+    uint8_t* skip_flags;
+    int H, W, C, Hp, Wp, by0, bx0, relu;
+    int skip_Hp, skip_Wp, skip_by0, skip_bx0;
+    unsigned s_off;
     unsigned block0;
 };
 struct Step1Vid {
-    long long sd, kd;
+    long long sd, kd;         // distance of the site's memory, of the memory of the residual add's destination
     int a_oy, a_ox, p_oy, p_ox, k_oy, k_ox;
     unsigned cy, cx;
+    float theta;
 };
 struct Step1Multi {
     Step1Job job[kMaxMultiJobs];
