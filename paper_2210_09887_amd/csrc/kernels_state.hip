@@ -484,7 +484,7 @@ __global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
     s.kind = MDCNN_SITE_PREACT;
     s.A = at(jb.A, v.sd); s.P = at(jb.P, v.sd); s.delta = at(jb.delta, v.sd); s.flags = at(jb.flags, v.sd);
     s.H = jb.H; s.W = jb.W; s.C = jb.C; s.Hp = jb.Hp; s.Wp = jb.Wp; s.by0 = jb.by0; s.bx0 = jb.bx0; s.relu = jb.relu;
-    s.theta = v.theta; s.s_off = jb.s_off; s.cy = v.cy; s.cx = v.cx;
+    s.theta = v.theta; s.s_off = v.s_off; s.cy = v.cy; s.cx = v.cx;
     s.a_oy = v.a_oy; s.a_ox = v.a_ox; s.p_oy = v.p_oy; s.p_ox = v.p_ox;
     SkipDev k{};
     k.P = at(jb.skip_P, v.kd); k.dflags = at(jb.skip_flags, v.kd);

@@ -860,12 +860,12 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 const SiteDev& s0 = sb.s[0];
                 const SkipDev& k0 = sb.skip[0];
                 j = Step1Job{s0.A, s0.P, s0.delta, s0.flags, k0.P, k0.dflags, s0.H, s0.W, s0.C, s0.Hp, s0.Wp, s0.by0, s0.bx0, s0.relu,
-                             k0.Hp, k0.Wp, k0.by0, k0.bx0, s0.s_off, 0u};
+                             k0.Hp, k0.Wp, k0.by0, k0.bx0, 0u};
                 for (int b = 0; b < n; ++b) {
                     const SiteDev& s = sb.s[b];
                     const SkipDev& k = sb.skip[b];
                     sm.vid[sm.n * n + b] = Step1Vid{dist(s.A, s0.A), dist(k.P, k0.P), s.a_oy, s.a_ox, s.p_oy, s.p_ox, k.p_oy, k.p_ox,
-                                                    s.cy, s.cx, s.theta};
+                                                    s.s_off, s.cy, s.cx, s.theta};
                 }
                 ++sm.n;
             }

@@ -270,13 +270,12 @@ struct Step1Job {
     uint8_t* skip_flags;
     int H, W, C, Hp, Wp, by0, bx0, relu;
     int skip_Hp, skip_Wp, skip_by0, skip_bx0;
-    unsigned s_off;
     unsigned block0;
 };
 struct Step1Vid {
     long long sd, kd;         // distance of the site's memory, of the memory of the residual add's destination
     int a_oy, a_ox, p_oy, p_ox, k_oy, k_ox;
-    unsigned cy, cx;
+    unsigned s_off, cy, cx;   // (where the state ring lies depends on what else the site keeps)
     float theta;
 };
 struct Step1Multi {

@@ -95,3 +95,29 @@ def test_a_threshold_per_video(entry):
     alone, together = run_alone_and_together([with_thresholds(net, f) for f in (1.0, 0.25, 4.0)], entry)
     assert any(not np.array_equal(x, y) for x, y in zip(alone[1][0], alone[1][1]))      # the thresholds matter
     same(alone, together)
+
+
+@pytest.mark.parametrize("keeping", [(0, 2), (1,)])
+def test_pooling_output_kept_by_some_of_the_videos(keeping, monkeypatch):
+    """Sites that keep a previous pooling output (here without a pooling edge) have their crop state further back in their
+    memory: every video's own offset counts."""
+    from paper_2210_09887_amd import binding as B
+    from paper_2210_09887_amd.runtime import GpuNet
+    nbytes = B.mdcnn_buffer_bytes
+    net = network()
+    sizes = []
+
+    def make(b, spec, **kw):
+        def sized(d):
+            if d.kind == B.MDCNN_SITE_PREACT:
+                d.pool_prev = int(b in keeping)
+            return nbytes(d)
+        with monkeypatch.context() as m:
+            m.setattr(B, "mdcnn_buffer_bytes", sized)
+            g = GpuNet(spec, **kw)
+        sizes.append(sum(t.numel() for t in g.mem))
+        return g
+
+    alone, together = run_alone_and_together([net] * 3, "crop", make)
+    assert len(set(sizes)) == 2                             # the layouts do differ
+    same(alone, together)
