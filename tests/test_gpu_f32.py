@@ -49,3 +49,52 @@ def test_fp32_upsampling_edge():
     b.conv(x, s, 5, 4, pad=2)
     b.conv(s, y, 1, 1, pad=0, up=2)
     G.teacher_forced(net, frames_of(net, 1), [(0, 0), (0, 1), (0, 0)])
+
+
+def kernel_of_last_site(net, X):
+    """Which kind of kernel counted the products of a frame into the network's output site."""
+    import gpu_harness as G
+    from paper_2210_09887_amd.runtime import GpuNet
+    g = GpuNet(net)
+    try:
+        g.frame(G.dev(X))
+        t = g.totals()["per_site"]
+        n = [int(t[k][-1]) for k in ("macs_mfma", "macs_plain")]
+        assert sum(v > 0 for v in n) == 1, n
+        return "mfma" if n[0] else "plain"
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("cin,cout,H,W,k,kernel", [
+    (8, 16, 24, 32, 1, "plain"),        # 128 products per pixel: plain from 768 pixels on
+    (8, 16, 24, 31, 1, "mfma"),
+    (8, 16, 70, 94, 3, "plain"),        # 1152 products, a padded window of 72 x 96
+    (8, 16, 70, 93, 3, "mfma"),
+    (128, 64, 192, 256, 1, "plain"),    # 8192 products: the most there may be, 49152 pixels
+    (128, 64, 191, 257, 1, "mfma"),
+    (72, 128, 240, 240, 1, "mfma"),     # 9216 products: more than 32 KiB of weights
+    (8, 544, 164, 164, 1, "mfma"),      # more couts than the plain kernel takes
+])
+def test_small_layers_on_large_windows(cin, cout, H, W, k, kernel):
+    """Both sides of the line between k_conv_f32 and the plain kernel with its weights in LDS."""
+    import gpu_harness as G
+    net = tiny_net("f32", H, W, (cin, cout), k=k, theta=0.05, seed=cin + cout)
+    frames = frames_of(net, cin + cout, 2)
+    assert kernel_of_last_site(net, frames[0]) == kernel
+    G.teacher_forced(net, frames, [(0, 0), (1, -1)])
+
+
+@pytest.mark.parametrize("rows,kernel", [(24, "plain"), (23, "mfma")])
+def test_small_upsampling_edges_on_large_views(rows, kernel):
+    import gpu_harness as G
+    net = NetSpec("up", "f32", 2 * rows, 64, 2)
+    b = _Builder(net, np.random.default_rng(4), 0.1)
+    x = b.site("in", 8, 1, "input", False, 0.05)
+    s = b.site("low", 8, 2, theta=0.02)
+    y = b.site("out", 16, 1, "output", False, 0.0)
+    b.conv(x, s, 3, 2)
+    b.conv(s, y, 1, 1, pad=0, up=1)
+    frames = frames_of(net, 2)
+    assert kernel_of_last_site(net, frames[0]) == kernel
+    G.teacher_forced(net, frames, [(0, 0), (0, 1), (0, 0)])
