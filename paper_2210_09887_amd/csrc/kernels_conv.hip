@@ -1355,7 +1355,11 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, hi
     if (dtype == MDCNN_F32 && (conv_path == 0 || conv_path == 3) && g_f32_mfma) {
         // 1x1 layers of up to 64 channels and 3x3 layers of 16, whose weights k_conv_mfma_f32 keeps in LDS (1x1, 32 to 64
         // channels at 128 x 128: 7.5 us, 9.0 with k_conv_f32); k_conv_f32 for the rest, 3x3 layers of 32 and 64 channels among
-        // them (64 at 128 x 128: 20 us, 35 with the weights in LDS; 32: 13 and 14.5)
+        // them (64 at 128 x 128: 20 us, 35 with the weights in LDS; 32 at 64 x 64: 11.8 and 13.3.  On large windows 32 channels
+        // are ahead with the weights in LDS while most pixels are updated - frames in a row of a one-layer network, 512 x 512:
+        // 107 us, 146 with k_conv_f32; 128 x 128: 21 and 24 - and behind where updates come in clusters, which this kernel
+        // passes over by tiles: a fifth of the frame 90 and 68 us, 256 x 256 38 and 29; five-layer network, 512 x 512 frames,
+        // 105 and 99)
         bool done = false;
         const hipError_t err = launch_mfma_f32(eb, nb, nseg, st, &done);
         if (done) { *cls = kClsConvMfma; return err; }

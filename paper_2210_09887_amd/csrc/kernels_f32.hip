@@ -29,19 +29,23 @@ hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Rows of whole 32-byte blocks, tensors a 32-bit byte offset reaches - but for layers of few products on a large window,
+// Rows of whole 32-byte blocks, tensors a 32-bit byte offset reaches - but for layers of very few products on a large window,
 // which the plain kernel with the weights in LDS (k_conv_ldsw) does sooner: this tile costs its flag, weight and row round
-// trips whether a pixel takes 128 products or 8192, and a large window has many tiles.  All pixels updated, this kernel /
-// the plain one, in us: 1x1, 8 -> 16 channels at 64 x 64: 9.7 / 8.4, 256 x 256: 32.6 / 14.5, 512 x 512: 107 / 23; 72 -> 32 at
-// 128 x 128: 14.9 / 13.1, 256 x 256: 34.3 / 22.3; 3x3, 8 -> 64 at 180 x 180: 29.3 / 28.7, 512 x 512: 146 / 115; 1x1, 64 -> 32
-// into 2 x 2 pixels at 256 x 256: 36.2 / 26.0.  On the other side of the line: 1x1, 72 -> 64 at 128 x 128: 15.0 / 17.0; 3x3,
-// 8 -> 16 at 64 x 64: 12.0 / 13.7; and above 32 KiB of weights the plain kernel has too few blocks: 3x3, 72 -> 16 at 256 x 256:
-// 53.9 / 79.6, 40 -> 32: 45.6 / 85.1.  Near the line either may be ahead by a tenth (with few pixels updated the plain one by
-// a fifth).  The choice is made by one video's layer: a video of a batch gives the bits it gives alone.
+// trips whether a pixel takes 128 products or 8192, and a large window has many tiles.  Where updates come in clusters it
+// leaves most tiles at once and the line lies lower than it does for dense frames.  Frames in a row of a one-layer network,
+// this kernel / the plain one, in us, all pixels updated and clusters of 24 x 24 pixels on a fifth of the frame:
+//   1x1,  8 -> 16, 512 x 512: 120 / 36, 61 / 29;   256 x 256: 38 / 21, 25 / 17;   128 x 128: 19.7 / 16.5, 16.5 / 16.6
+//   1x1, 24 -> 32, 512 x 512: 145 / 72, 72 / 60;   224 x 224: 36 / 29, 23 / 22;   128 x 128: 20.2 / 18.6, 16.8 / 16.5
+//   1x1, 96 -> 16, 512 x 512: 184 / 110, 88 / 72;  224 x 224: 43 / 31, 26 / 24;   128 x 128 (past the line): 22.9 / 21.6, 18.5 / 19.0
+//   3x3,  8 -> 16, 512 x 512: 127 / 51, 56 / 45;   180 x 180: 29 / 22, 20 / 20;   128 x 128 (past): 22.8 / 20.1, 18.0 / 19.0
+//   more products (past): 3x3, 8 -> 32, 512 x 512: 132 / 80, 61 / 74; 8 -> 64: 168 / 138, 101 / 132; 24 -> 16, 256 x 256: 48 / 39, 27 / 30
+// Into 2 x 2 pixels the plain kernel writes from fewer blocks and needs four times the window (launches alone): 64 -> 16 from 256 x 256
+// pixels 36 / 20, 20 / 14; past the line 8 -> 64 from 128 x 128: 16.7 / 17.8, 11.0 / 11.8, 24 -> 32: 15.5 / 14.0, 10.6 / 11.7.
+// The choice is made by one video's layer: a video of a batch gives the bits it gives alone.
 bool f32_applies(const EdgeDev& e) {
     const long long lim = 1ll << 31, products = (long long)e.k * e.k * e.Cin * e.Cout;
     const long long pixels = e.up ? (long long)e.sH * e.sW : (long long)e.Hp * e.Wp;
-    if (e.Cout <= 512 && products <= 8192 && 6 * products <= pixels) return false;
+    if (products <= 2048 && (e.up ? 64 : 16) * products <= pixels) return false;
     return e.k >= 1 && e.k <= 5 && !e.op && e.Cin % 8 == 0 && (e.Cout % 32 == 0 || e.Cout == 16) &&
            (long long)e.sH * e.sW * e.Cin * 4 < lim && (long long)e.Hp * e.Wp * e.Cout * 4 < lim && products * 4 < lim;
 }

@@ -67,14 +67,14 @@ def kernel_of_last_site(net, X):
 
 
 @pytest.mark.parametrize("cin,cout,H,W,k,kernel", [
-    (8, 16, 24, 32, 1, "plain"),        # 128 products per pixel: plain from 768 pixels on
-    (8, 16, 24, 31, 1, "mfma"),
-    (8, 16, 70, 94, 3, "plain"),        # 1152 products, a padded window of 72 x 96
-    (8, 16, 70, 93, 3, "mfma"),
-    (128, 64, 192, 256, 1, "plain"),    # 8192 products: the most there may be, 49152 pixels
-    (128, 64, 191, 257, 1, "mfma"),
-    (72, 128, 240, 240, 1, "mfma"),     # 9216 products: more than 32 KiB of weights
-    (8, 544, 164, 164, 1, "mfma"),      # more couts than the plain kernel takes
+    (8, 16, 32, 64, 1, "plain"),        # 128 products per pixel: plain from 2048 pixels on
+    (8, 16, 32, 63, 1, "mfma"),
+    (8, 16, 126, 142, 3, "plain"),      # 1152 products, a padded window of 128 x 144
+    (8, 16, 126, 141, 3, "mfma"),
+    (128, 16, 128, 256, 1, "plain"),    # 2048 products: the most there may be, 32768 pixels
+    (128, 16, 127, 258, 1, "mfma"),
+    (8, 256, 181, 182, 1, "plain"),     # the most couts
+    (72, 32, 200, 200, 1, "mfma"),      # 2304 products
 ])
 def test_small_layers_on_large_windows(cin, cout, H, W, k, kernel):
     """Both sides of the line between k_conv_f32 and the plain kernel with its weights in LDS."""
@@ -85,10 +85,10 @@ def test_small_layers_on_large_windows(cin, cout, H, W, k, kernel):
     G.teacher_forced(net, frames, [(0, 0), (1, -1)])
 
 
-@pytest.mark.parametrize("rows,kernel", [(24, "plain"), (23, "mfma")])
+@pytest.mark.parametrize("rows,kernel", [(64, "plain"), (63, "mfma")])
 def test_small_upsampling_edges_on_large_views(rows, kernel):
     import gpu_harness as G
-    net = NetSpec("up", "f32", 2 * rows, 64, 2)
+    net = NetSpec("up", "f32", 2 * rows, 256, 2)
     b = _Builder(net, np.random.default_rng(4), 0.1)
     x = b.site("in", 8, 1, "input", False, 0.05)
     s = b.site("low", 8, 2, theta=0.02)
