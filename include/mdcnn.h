@@ -326,7 +326,8 @@ mdcnn_status mdcnn_frame_batch_crop(mdcnn_net* const* nets, int n_streams,
  * before has finished with it: two launches on one site are either on one stream or
  * ordered by an event.  The initialisation of a camera shift is split by groups of
  * calls for this and done by spare blocks of the delta launches (MDCNN_OPT_PIPE_GROUP,
- * mdcnn_frames_plan).
+ * mdcnn_frames_plan); where independent launches of the network go out as one, it is split
+ * by groups of such launches and each group has a launch of its own (mdcnn_frames_rounds).
  * These launches are bound by their latency, not by the size of the GPU, so overlapping
  * frames raises the frame rate of a single video the way a batch does for several; the
  * latency of a frame does not improve.
@@ -383,7 +384,9 @@ mdcnn_status mdcnn_frames_crop(mdcnn_net* net, int n_frames, const void* const* 
                                const int* crops, void* const* outs_dev, const size_t* out_bytes,
                                int depth, void* stream, int* did_full_reset);
 
-/* Host-only.  The plan mdcnn_frames follows for `net` on `depth` streams (0: default).
+/* Host-only.  The plan by forward calls for `net` on `depth` streams (0: default):
+ * mdcnn_frames, mdcnn_frames_crop, mdcnn_frames_masked and mdcnn_frames_batch follow it
+ * unless they put independent launches of the network together (mdcnn_frames_rounds).
  * The forward calls of a frame (non-terminal sites in order) are numbered 0 ..
  * *n_calls - 1; the readout counts as call *n_calls.  stream_of_call[c] (c <= *n_calls):
  * the stream of call c in every frame (MDCNN_OPT_PIPE_MODE 0; -1 in mode 1, where frame
@@ -403,6 +406,28 @@ mdcnn_status mdcnn_frames_crop(mdcnn_net* net, int n_frames, const void* const* 
 mdcnn_status mdcnn_frames_plan(mdcnn_net* net, int depth, int* first_call, int* wait_call,
                                int* init_call, int cap_groups, int* group_of_site, int cap_sites,
                                int* stream_of_call, int cap_calls, int* n_groups, int* n_calls);
+
+/* Host-only.  The plan of the same calls for a network whose independent launches they put
+ * together, with the options in force now (MDCNN_OPT_STREAMS 0, MDCNN_OPT_PIPE_MODE 1, no
+ * profiling mode, fp16, and the frame gets shorter by a fifth or more, counted in
+ * launches); *n_rounds is 0 and nothing else is written for a network that follows
+ * mdcnn_frames_plan.  A frame is *n_rounds rounds of operations of one kind that do not
+ * depend on each other, taken in order on stream f % depth; the readout counts as round
+ * *n_rounds.  Operation k belongs to round op_round[k] (ascending): op_edge[k] >= 0: that
+ * edge, whose source is site op_site[k]; -1: the delta step of the site, which also adds
+ * the residual skip op_skip[k] (an edge, -1: none); -2: the compaction of the site's own
+ * list.  Operations that touch one site, at least one of them writing it, keep the order
+ * of mdcnn_frame_plan.  The rounds are cut into groups of MDCNN_OPT_PIPE_GROUP: group g
+ * starts with round first_round[g], and the sites it is the first to touch (group_of_site)
+ * are initialised by a launch of their own just before that round, after round
+ * wait_round[g] of the frame BEFORE has finished.  The arrays are caller-owned with room
+ * for cap_ops / cap_groups / cap_sites entries and may be NULL; *n_ops and *n_groups are
+ * optional, *n_rounds is not.
+ * Errors: MDCNN_ERR_SIZE if an array is too small or depth out of range. */
+mdcnn_status mdcnn_frames_rounds(mdcnn_net* net, int depth, int* op_round, int* op_site, int* op_edge,
+                                 int* op_skip, int cap_ops, int* first_round, int* wait_round,
+                                 int cap_groups, int* group_of_site, int cap_sites, int* n_ops,
+                                 int* n_groups, int* n_rounds);
 
 /* Optional post-processing of the input update mask.  Writes, for the frame
  * `frame_dev` (not yet passed to a forward call), the mask that the threshold
@@ -501,7 +526,7 @@ typedef enum {
                              /* residual skip (identity edge) instead of a launch of its own; */
                              /* such an edge then adds nothing to the compute-list statistics  */
                              /* of its destination.  0: one launch per edge                  */
-    MDCNN_OPT_PIPE_GROUP = 10, /* mdcnn_frames: forward calls per group of the frame pipeline (1..64): smaller */
+    MDCNN_OPT_PIPE_GROUP = 10, /* mdcnn_frames: forward calls (rounds) per group of the frame pipeline (1..64): smaller */
                              /* groups let a frame follow the one before it more closely, at one more event   */
                              /* and wait per group and frame.  0 (default): about twenty groups per frame,    */
                              /* four calls per group at most                                                 */

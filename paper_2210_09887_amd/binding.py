@@ -30,7 +30,7 @@ STATUS_NAMES = {0: "OK", 1: "ERR_NULL", 2: "ERR_SHAPE", 3: "ERR_DTYPE", 4: "ERR_
 
 EXPORTS = ["mdcnn_conv_border", "mdcnn_conv_tiles", "mdcnn_buffer_bytes", "mdcnn_create_buffer", "mdcnn_destroy_buffer",
            "mdcnn_shift_camera", "mdcnn_set_crop", "mdcnn_layer_forward", "mdcnn_layer_forward_noalloc", "mdcnn_net_create", "mdcnn_net_destroy",
-           "mdcnn_frame", "mdcnn_frame_crop", "mdcnn_frame_batch", "mdcnn_frame_batch_crop", "mdcnn_frame_plan", "mdcnn_frames", "mdcnn_frames_batch", "mdcnn_frames_crop", "mdcnn_frames_masked", "mdcnn_frames_plan", "mdcnn_input_mask", "mdcnn_read_view", "mdcnn_write_view", "mdcnn_set_option", "mdcnn_profile_read", "mdcnn_profile_read_launches", "mdcnn_bench_copy", "mdcnn_bench_mfma",
+           "mdcnn_frame", "mdcnn_frame_crop", "mdcnn_frame_batch", "mdcnn_frame_batch_crop", "mdcnn_frame_plan", "mdcnn_frames", "mdcnn_frames_batch", "mdcnn_frames_crop", "mdcnn_frames_masked", "mdcnn_frames_plan", "mdcnn_frames_rounds", "mdcnn_input_mask", "mdcnn_read_view", "mdcnn_write_view", "mdcnn_set_option", "mdcnn_profile_read", "mdcnn_profile_read_launches", "mdcnn_bench_copy", "mdcnn_bench_mfma",
            "mdcnn_pack_weights", "mdcnn_last_error", "mdcnn_version"]
 
 
@@ -91,6 +91,7 @@ def lib():
         L.mdcnn_frames_masked.argtypes = [vp, C.c_int, C.POINTER(vp), C.POINTER(vp), C.POINTER(mdcnn_mask_params), C.POINTER(vp), sz, ip, ip,
                                           C.POINTER(vp), sz, C.c_int, vp, ip]
         L.mdcnn_frames_plan.argtypes = [vp, C.c_int, ip, ip, ip, C.c_int, ip, C.c_int, ip, C.c_int, ip, ip]
+        L.mdcnn_frames_rounds.argtypes = [vp, C.c_int, ip, ip, ip, ip, C.c_int, ip, ip, C.c_int, ip, C.c_int, ip, ip, ip]
         L.mdcnn_input_mask.argtypes = [vp, vp, vp, C.POINTER(mdcnn_mask_params), vp, sz, vp]
         L.mdcnn_read_view.argtypes = [vp, C.c_int, vp, sz, vp]
         L.mdcnn_write_view.argtypes = [vp, C.c_int, vp, sz, vp]
@@ -335,6 +336,21 @@ def mdcnn_frames_plan(net: int, n_sites: int, depth: int = 0):
     _check(lib().mdcnn_frames_plan(net, int(depth), a, b, c, n.value, g, n_sites, so, nc.value + 1, None, None))
     return dict(first_call=list(a), wait_call=list(b), init_call=list(c), group_of_site=list(g), stream_of_call=list(so),
                 n_calls=nc.value)
+
+
+def mdcnn_frames_rounds(net: int, n_sites: int, depth: int = 0):
+    """Rounds of a frame of `net` as a dict, None if it follows mdcnn_frames_plan: `ops` [(round, site, edge, skip)] (edge -1:
+    delta step, -2: compaction), per group `first_round` and `wait_round` (round of the frame before it waits for),
+    `group_of_site`, `n_rounds`."""
+    no, ng, nr = C.c_int(), C.c_int(), C.c_int()
+    _check(lib().mdcnn_frames_rounds(net, int(depth), None, None, None, None, 0, None, None, 0, None, 0, C.byref(no), C.byref(ng), C.byref(nr)))
+    if not nr.value:
+        return None
+    r, s, e, k = ((C.c_int * no.value)() for _ in range(4))
+    a, b = (C.c_int * ng.value)(), (C.c_int * ng.value)()
+    g = (C.c_int * n_sites)(*([-1] * n_sites))
+    _check(lib().mdcnn_frames_rounds(net, int(depth), r, s, e, k, no.value, a, b, ng.value, g, n_sites, None, None, C.byref(nr)))
+    return dict(ops=list(zip(r, s, e, k)), first_round=list(a), wait_round=list(b), group_of_site=list(g), n_rounds=nr.value)
 
 
 def mdcnn_input_mask(buf: int, frame_ptr: int, roi_ptr, prm: mdcnn_mask_params, mask_ptr: int, mask_bytes: int, stream: int = 0):

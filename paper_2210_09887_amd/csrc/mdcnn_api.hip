@@ -675,6 +675,8 @@ bool use_rounds(mdcnn_net* net, bool overlap = false) {
     return overlap ? f16 && net->rounds.shorter(5, 4) : f16 || !net->rounds.shorter(5, 4);
 }
 
+bool frames_in_rounds(mdcnn_net* net) { return g_pipe_mode == 1 && use_rounds(net, true); }     // frames in flight
+
 // The library's own streams (per host thread, default priority, made on first use) and events.
 struct Aux {
     hipStream_t s[kMaxStreams - 1] = {};
@@ -1213,7 +1215,7 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
                        const int* dty, const int* dtx, const int* crops, const FrontEnd* fe, void* const* outs_dev, int depth,
                        hipStream_t user, int* did_full_reset) {
     mdcnn_net* const net = nets[0];
-    const bool rounds = g_pipe_mode == 1 && use_rounds(net, true);
+    const bool rounds = frames_in_rounds(net);
     const int group = rounds ? pipe_group((int)net->rounds.rounds.size()) : pipe_group(net);
     const int key = (group * 8 + depth) * 2 + (rounds ? net->rounds.key : g_pipe_mode);
     PipePlan& pp_kept = rounds ? net->pipe_rounds : net->pipe;
@@ -2044,6 +2046,43 @@ mdcnn_status mdcnn_frames_plan(mdcnn_net* net, int depth, int* first_call, int* 
     for (int c = 0; stream_of_call && c <= nc; ++c) stream_of_call[c] = pp.mode ? -1 : pp.seg_of_call[(size_t)c];
     if (n_groups) *n_groups = n;
     if (n_calls) *n_calls = nc;
+    return MDCNN_OK;
+}
+
+mdcnn_status mdcnn_frames_rounds(mdcnn_net* net, int depth, int* op_round, int* op_site, int* op_edge, int* op_skip, int cap_ops,
+                                 int* first_round, int* wait_round, int cap_groups, int* group_of_site, int cap_sites, int* n_ops,
+                                 int* n_groups, int* n_rounds) {
+    if (!net || !n_rounds) return fail(MDCNN_ERR_NULL, "net / n_rounds is NULL");
+    if (depth < 0 || depth > kMaxStreams) return fail(MDCNN_ERR_SIZE, "frames_rounds: 0 <= depth <= %d", kMaxStreams);
+    *n_rounds = 0;
+    if (n_ops) *n_ops = 0;
+    if (n_groups) *n_groups = 0;
+    if (!frames_in_rounds(net)) return MDCNN_OK;
+    const RoundPlan& rp = net->rounds;
+    PipePlan pp;
+    make_pipe_rounds(net, pipe_group((int)rp.rounds.size()), depth ? depth : kDefaultDepth, pp);
+    const int n = (int)pp.groups.size(), n_sites = (int)net->sites.size();
+    if ((op_round || op_site || op_edge || op_skip) && cap_ops < rp.n_ops) return fail(MDCNN_ERR_SIZE, "frames_rounds: %d operations, room for %d", rp.n_ops, cap_ops);
+    if ((first_round || wait_round) && cap_groups < n) return fail(MDCNN_ERR_SIZE, "frames_rounds: %d groups, room for %d", n, cap_groups);
+    if (group_of_site && cap_sites < n_sites) return fail(MDCNN_ERR_SIZE, "frames_rounds: %d sites, room for %d", n_sites, cap_sites);
+    int k = 0;
+    for (size_t r = 0; r < rp.rounds.size(); ++r)
+        for (const RoundOp& op : rp.rounds[r]) {
+            if (op_round) op_round[k] = (int)r;
+            if (op_site) op_site[k] = op.site;
+            if (op_edge) op_edge[k] = op.edge;
+            if (op_skip) op_skip[k] = op.skip;
+            ++k;
+        }
+    for (int g = 0; g < n; ++g) {
+        if (first_round) first_round[g] = pp.groups[(size_t)g].call0;
+        if (wait_round) wait_round[g] = pp.groups[(size_t)g].wait_call;
+        if (group_of_site)
+            for (int site : pp.groups[(size_t)g].fill) group_of_site[site] = g;
+    }
+    *n_rounds = (int)rp.rounds.size();
+    if (n_ops) *n_ops = rp.n_ops;
+    if (n_groups) *n_groups = n;
     return MDCNN_OK;
 }
 

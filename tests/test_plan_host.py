@@ -194,6 +194,109 @@ def test_frames_in_flight_never_share_a_site(name, group, depth, mode):
             B.mdcnn_destroy_buffer(b)
 
 
+@pytest.mark.parametrize("name", ["hrnet", "hrnet_full"] + [f"dag{seed}" for seed in range(1, 12, 2)])
+@pytest.mark.parametrize("group,depth", [(0, 0), (1, 4), (2, 2), (5, 3), (64, 4), (1, 1)])
+def test_rounds_of_frames_in_flight_never_share_a_site(name, group, depth):
+    """Networks whose independent launches mdcnn_frames puts together do not follow mdcnn_frames_plan but the rounds of
+    mdcnn_frames_rounds.  Every launch of the frame is in exactly one round, no two of a round touch a site that one of them
+    writes, launches on one site keep their program order, and with four frames laid out as the library issues them
+    (initialisation of a group, its rounds, the readout; frame f on stream f % depth) everything that touches a site is
+    ordered."""
+    spec = NETS[name]()
+    net, bufs = host_net(spec)
+    B.mdcnn_set_option(B.MDCNN_OPT_PIPE_GROUP, group)
+    try:
+        p = B.mdcnn_frames_rounds(net, len(spec.sites), depth)
+        if p is None:
+            assert not name.startswith("hrnet")
+            return
+        depth = depth or 4
+        want = launches_of(spec)
+
+        def touches(site, edge, skip):
+            if edge == -1:
+                return set(), {site} | ({spec.edges[skip].dst} if skip >= 0 else set())
+            assert edge == -2 or spec.edges[edge].src == site
+            return {site}, {site} if edge == -2 else {spec.edges[edge].dst}
+
+        key = lambda t: (sorted(t[0]), sorted(t[1]))
+        ops = [(r, touches(s, e, k)) for r, s, e, k in p["ops"]]
+        assert sorted(key(t) for _, t in ops) == sorted(key(t) for t in want)
+        assert len(p["ops"]) == len(set(p["ops"]))
+        rounds = [r for r, _ in ops]
+        assert rounds == sorted(rounds) and set(rounds) == set(range(p["n_rounds"])) and p["n_rounds"] < len(ops)
+        for r in range(p["n_rounds"]):
+            kinds = {e == -1 for q, _, e, _ in p["ops"] if q == r}
+            assert len(kinds) == 1                                            # one kind of launch per round
+        # program order of two launches that touch a site: the round of the earlier one comes first
+        program = []                                                          # (round, touched) in program order
+        left = list(ops)
+        for t in want:
+            hit = next(o for o in left if key(o[1]) == key(t))                # (equal ones come in the order of their rounds)
+            left.remove(hit)
+            program.append(hit)
+        for b, (rb, (readb, writeb)) in enumerate(program):
+            for ra, (reada, writea) in program[:b]:
+                if (writea & (readb | writeb)) or (reada & writeb):
+                    assert ra < rb, f"launch {b} and one before it touch {(writea & (readb | writeb)) | (reada & writeb)}: rounds {ra} and {rb}"
+        first, wait, gos = p["first_round"], p["wait_round"], p["group_of_site"]
+        assert first[0] == 0 and first == sorted(set(first)) and all(0 <= g < len(first) for g in gos)
+        if group:
+            assert first == list(range(0, p["n_rounds"], group))
+        outputs = {i for i, s in enumerate(spec.sites) if s.kind == "output"}
+        touched = [set().union(*(t[0] | t[1] for q, t in ops if q == r)) for r in range(p["n_rounds"])] + [outputs]
+        steps = []                                                            # (frame, round or None, sites, waits)
+        for f in range(4):
+            for r in range(p["n_rounds"] + 1):
+                if r in first and r < p["n_rounds"]:
+                    g = first.index(r)
+                    waits = [(f - 1, wait[g])] if f and wait[g] >= 0 and depth > 1 else []
+                    steps.append((f, None, {i for i, gg in enumerate(gos) if gg == g}, waits))
+                steps.append((f, r, touched[r], []))
+        index = {(f, r): k for k, (f, r, _, _) in enumerate(steps) if r is not None}
+        reach = ordered_before([f % depth for f, _, _, _ in steps], [[index[w] for w in ws] for _, _, _, ws in steps])
+        for b, (fb, rb, sb, _) in enumerate(steps):
+            for a in range(b):
+                fa, ra, sa, _ = steps[a]
+                if sa & sb:
+                    assert a in reach[b], f"frame {fa} round {ra} and frame {fb} round {rb} touch {sa & sb} unordered"
+        for i in range(len(spec.sites)):
+            assert [r for f, r, t, _ in steps if f == 0 and i in t][0] is None, f"site {i} is used before it is initialised"
+    finally:
+        B.mdcnn_set_option(B.MDCNN_OPT_PIPE_GROUP, 0)
+        B.mdcnn_net_destroy(net)
+        for b in bufs:
+            B.mdcnn_destroy_buffer(b)
+
+
+def test_which_networks_run_in_rounds():
+    for name, option, value, rounds in [("hrnet", None, 0, True), ("resnet", None, 0, False), ("cnn5", None, 0, False),
+                                        ("hrnet", B.MDCNN_OPT_STREAMS, 1, False), ("hrnet", B.MDCNN_OPT_PIPE_MODE, 0, False)]:
+        spec = NETS[name]()
+        net, bufs = host_net(spec)
+        try:
+            if option is not None:
+                B.mdcnn_set_option(option, value)
+            assert (B.mdcnn_frames_rounds(net, len(spec.sites)) is not None) == rounds, (name, option)
+        finally:
+            B.mdcnn_set_option(B.MDCNN_OPT_STREAMS, 0)
+            B.mdcnn_set_option(B.MDCNN_OPT_PIPE_MODE, 1)
+            B.mdcnn_net_destroy(net)
+            for b in bufs:
+                B.mdcnn_destroy_buffer(b)
+    spec = NETS["hrnet"]()
+    net, bufs = host_net(spec)
+    try:
+        with pytest.raises(B.MdcnnError):
+            B.mdcnn_frames_rounds(net, len(spec.sites), 5)
+        with pytest.raises(B.MdcnnError):
+            B.mdcnn_frames_rounds(net, len(spec.sites) - 1)
+    finally:
+        B.mdcnn_net_destroy(net)
+        for b in bufs:
+            B.mdcnn_destroy_buffer(b)
+
+
 def test_rectangular_tiles_cover_the_window_within_their_limits():
     """mdcnn_conv_tiles (host only): the tile the halo-staged kernel would take.  It holds no more pixels than allowed,
     its footprint no more than the staging buffer does, it is not larger than the window, no other rectangle within the
