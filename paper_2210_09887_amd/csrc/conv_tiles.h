@@ -426,7 +426,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
     // Quarter-segment rectangles, which a launch has few of: what a tile can ask for before it knows what it needs goes out
     // at once - the first weight fragments, the rows of the rectangle whether updated or not, then the pending rows - so
     // that its round trips to memory overlap.  (Larger tiles fill the chip: there the same only adds traffic and registers.)
-    constexpr bool EARLY = T2D && NSUB == 4, EARLY_P = EARLY;
+    constexpr bool EARLY = T2D && NSUB == 4;
     extern __shared__ __align__(16) unsigned char smem[];
     f16* halo = reinterpret_cast<f16*>(smem);            // [CAP][LDK] during the K loop
     float* sC = reinterpret_cast<float*>(smem);          // [SUB][LDC] after it
@@ -609,7 +609,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
                 pold[t] = *reinterpret_cast<const f16x8*>(pp[t]);
             }
         };
-        if constexpr (EARLY_P) load_p();
+        if constexpr (EARLY) load_p();
 
         // The K loop for L live row tiles of this wave.  Step i of a chunk: tap i / MB,
         // 16-channel block wk + WK * (i % MB) of the chunk.
@@ -679,7 +679,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
             default: kloop(std::integral_constant<int, TM>{}); break;
         }
 
-        if constexpr (!EARLY_P) load_p();
+        if constexpr (!EARLY) load_p();
         // K-split partial sums -> LDS [entry][cout], a buffer per K wave or added up in turns; either way every element
         // is added up in the order of the K waves.
         auto put = [&](int i, bool add) {

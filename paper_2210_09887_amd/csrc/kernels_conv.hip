@@ -4,12 +4,12 @@
 //   P_dst[q] <- P_dst[q] + y[q]        (border pixels included: they are stashed)
 // Output-stationary: one owner per output pixel, fixed summation order, so the
 // result does not depend on scheduling.  Weights are w[tap][cout][cin].
-// There is no separate list kernel: every block compacts the segment of the
-// compute list it works on itself, from the source's update mask (kSegPixels
-// indices per segment, one per thread, ballot + popcount ranks); a tile is
-// (segment, offset inside the segment).  The first tile of a segment also writes
-// the segment to the destination's compute list, the copy the ABI exposes, and
-// the first edge of a forward call compacts the source's update mask into L.
+// There is no separate list kernel: every block finds the entries of its own tile from the source's update mask.  A tile
+// of the gather kernels is a piece of a list segment (kSegPixels indices, one per thread, ballot + popcount ranks); the
+// block of a segment's first piece also writes the segment to the destination's compute list, the copy the ABI exposes,
+// and every block of the first edge of a forward call compacts its share of the source's update mask into L before its
+// tiles.  The halo-staged kernel (rectangles of the padded window) and the 3-channel stem leave both to a few blocks of
+// their own (publish_edge), k_conv_f32 writes segment n with its n-th rectangle and does L after its tiles.
 //
 //   k_conv_halo       : 3x3 stride-1 fp16 layers: source rectangle of a tile staged once per
 //                       channel chunk in LDS, packed weights straight into MFMA fragments
@@ -17,9 +17,9 @@
 //   k_conv_mfma_f16   : MFMA without LDS staging (fallback for Cin % 32 != 0)
 //   k_conv_mfma_f32   : small fp32 layers, weights in LDS (fp32 matrix instruction)
 //   k_conv_f32        : weights and delta rows staged in LDS (conv_f32.h): all other fp32 layers with
-//                       Cin % 8 == 0 and Cout 16 or a multiple of 32
+//                       Cin % 8 == 0 and Cout 16 or a multiple of 32, but for the smallest (f32_applies)
 //   k_conv_small      : 3-channel 3x3 stems, plain FMA
-//   k_conv_ldsw       : plain FMA with the weights resident in LDS (fp32 nets)
+//   k_conv_ldsw       : plain FMA with the weights resident in LDS (fp32 layers of few products, other shapes)
 //   k_conv_plain      : plain FMA, any dtype / channel count
 //   k_identity        : residual skip, P_dst[q] += delta[q] (when it is not fused into step 1)
 //   k_pool            : max pooling in delta form against a previous-output ring
@@ -974,7 +974,7 @@ static unsigned cap_blocks(long long b, long long cap) {
 
 // Tuning knobs (mdcnn_set_option): forced tile shape, pipeline depth, XCD mapping.
 int g_tile = 0, g_pipe = 0, g_xcd = 1, g_kc = 0;
-int g_f32_mfma = 1;     // 1: fp32 layers go to the matrix cores where k_conv_mfma_f32 applies, 0: plain FMA kernels
+int g_f32_mfma = 1;     // 1: fp32 layers (k_conv_mfma_f32, k_conv_f32) and 3-channel stems go to the matrix cores where they apply, 0: plain FMA kernels
 
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
 static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick) {
@@ -1045,8 +1045,8 @@ static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_ent
     return launch_tiled_p<4, 1, 1, 1, KC>(eb, nb, max_entries, st, pick);                                             // 128 x 32
 }
 
-int g_halo = 1;          // 0: never use the halo-staged kernel, 2: force 32-cout tiles, 3: tiles are index ranges only,
-                         // 4: as 1
+int g_halo = 1;          // 0: never use the halo-staged kernel, 2: force 32-cout tiles, 3: tiles are index ranges instead of
+                         // rectangles (launch_halo_n), 4: as 1
 int g_halo_sub = 0;      // 0: auto, 1 / 2 / 4: tiles per list segment of the halo-staged kernel
 
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD, int RING = 3, int MINB = (NSUB >= 2 ? 2 : 1), bool T2D = false>
@@ -1158,7 +1158,8 @@ static long long halo_worst(const EdgeDev& e, int sub) {
     return (span + e.k - 1) * (width - 1 + e.k);
 }
 
-// Halo-staged kernel if the rectangle a tile can read fits the staging buffer
+// Tiles that are index ranges of the padded window (MDCNN_OPT_CONV_HALO = 3 only: rectangles fit every window and are
+// ahead; the tests compare the two bit for bit), where the rectangle of pixels a range can read fits the staging buffer
 // (the fewer channels per chunk, the more pixels fit; below 32 channels per chunk
 // -- rows wider than about 250 pixels -- the tiled kernel is faster).
 // *done = false: not applicable.
@@ -1195,14 +1196,12 @@ static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, hipSt
     if (!g_halo || !e.wp || e.k != 3 || e.stride != 1 || e.up != 0 || e.Cin % 16 || e.Cout % 32) return hipSuccess;
     if ((long long)e.sH * e.sW * e.Cin >= (1ll << 30) || (long long)e.k * e.k * e.Cin * e.Cout >= (1ll << 30))
         return hipSuccess;                                                     // 32-bit byte offsets into deltas and weights
-    // rectangular tiles where they fit (windows of a few list segments used to stay on index ranges, whose tiles stage whole
-    // rows; with the by-products made by other blocks and the round trips of a small tile overlapped the rectangles are
-    // faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512 channels 22 -> 17 us a launch)
-    if (g_halo != 3) {
-        const hipError_t err = e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
-        if (err != hipSuccess || *done) return err;
-    }
-    return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
+    // Rectangular tiles (one of up to 64 pixels fits every window).  Windows of a few list segments used to stay on index
+    // ranges, whose tiles stage whole rows; with the by-products made by other blocks and the round trips of a small tile
+    // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512
+    // channels 22 -> 17 us a launch.
+    if (g_halo != 3) return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
+    return e.Cout % 64 == 0 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
 }
 
 hipError_t launch_pack_weights(const void* src, void* dst, int taps, int Cout, int Cin, hipStream_t st) {

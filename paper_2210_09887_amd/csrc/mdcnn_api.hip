@@ -329,12 +329,6 @@ mdcnn_status validate_forward(const mdcnn_buffer* in, const void* frame, const u
     return MDCNN_OK;
 }
 
-// One forward call for `n` streams of the same network at once (n <= kMaxBatch;
-// the caller has checked that all streams have the same shapes): stream b goes
-// from ins[b] along edges[b][0 .. n_edges) to outs[b][0 .. n_edges).
-// fuse_skip: index of an identity edge whose add is done by the step-1 kernel (its
-// destination is touched there and the edge gets no launch of its own), or -1.
-// riders (n == 1 only): jobs[riders[0 .. n_riders)] are run by spare blocks of the step-1 launch.
 // Fills in step 1 of site `in` for one video; skip_dst: destination of a residual add it does, or nullptr.
 void set_step1(Step1Batch& sb, int b, const mdcnn_buffer* in, const mdcnn_buffer* skip_dst, const void* X, const uint8_t* forced) {
     sb.s[b] = in->dev;
@@ -395,6 +389,12 @@ struct ListScratch {
     std::vector<int*> clist, ccnt; std::vector<unsigned long long*> cacc;    // per edge
 };
 
+// One forward call for `n` streams of the same network at once (n <= kMaxBatch;
+// the caller has checked that all streams have the same shapes): stream b goes
+// from ins[b] along edges[b][0 .. n_edges) to outs[b][0 .. n_edges).
+// fuse_skip: index of an identity edge whose add is done by the step-1 kernel (its
+// destination is touched there and the edge gets no launch of its own), or -1.
+// riders (n == 1 only): jobs[riders[0 .. n_riders)] are run by spare blocks of the step-1 launch.
 mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* frames, const uint8_t* const* forced,
                         const mdcnn_conv_desc* const* edges, mdcnn_buffer* const* const* outs, int n_edges,
                         hipStream_t st, int fuse_skip = -1, Sched* sc = nullptr, const FillJob* jobs = nullptr,
