@@ -121,3 +121,20 @@ def test_pooling_output_kept_by_some_of_the_videos(keeping, monkeypatch):
     alone, together = run_alone_and_together([net] * 3, "crop", make)
     assert len(set(sizes)) == 2                             # the layouts do differ
     same(alone, together)
+
+
+@pytest.mark.parametrize("entry", ["frame", "frames"])
+def test_weights_of_their_own(entry):
+    """Videos that do not share their weights (the second runs another model of the same shape)."""
+    from paper_2210_09887_amd.runtime import GpuNet
+    net, other = network(), network()
+    for e in other.edges:
+        if e.w is not None:
+            e.w = (e.w[..., ::-1] * np.float16(0.75)).astype(net.np_dtype)
+
+    def make(b, spec, share_weights=None, **kw):
+        return GpuNet(spec, share_weights=share_weights if b == 2 else None, **kw)
+
+    alone, together = run_alone_and_together([net, other, net], entry, make)
+    assert any(not np.array_equal(x, y) for x, y in zip(alone[1][0], alone[1][1]))
+    same(alone, together)
