@@ -23,6 +23,8 @@ region of --steps frames.  Besides the throughput the line carries
   per_layer      -- the same per layer: the convolution launches into every site and
                     the delta launch of every site, with their own bound
                     max(bytes / HBM peak, flops / matrix peak);
+                    (both of launches one to a site or edge, as the instrumented pass
+                    makes them; ordinary fp16 frames put independent ones together)
   measured_peaks -- what a plain copy kernel and a loop of matrix-core instructions
                     reach on this machine, and the fractions against those;
   frame_at_a_time-- one mdcnn_frame call per frame (the latency of a frame), with the
@@ -645,7 +647,7 @@ def main():
                                + (", truncation-free sites: " + ",".join(s.name for s in net.sites if s.trunc_free) if a.truncation_free else "")
                                + (f", density {a.density}" if cfg == 5 else ""),
                    "input": [net.H, net.W, net.sites[0].C], "sites": len(net.sites), "edges": len(net.edges),
-                   "launches_per_frame": len(B.mdcnn_frame_plan(g.net, 1)[0]) + 2,
+                   "launches_per_frame": len(B.mdcnn_frame_plan(g.net, 1)[0]) + 2,       # one to a site or edge
                    "state_bytes": int(sum(m.numel() for m in g.mem)),
                    "resets_in_timed_steps": resets_timed, "mean_update_density": round(float(np.mean(dens)), 4),
                    "input_update_density": round(dens[0], 4), "frames_in_flight": in_flight, "entry_point": entry},
