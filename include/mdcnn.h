@@ -510,6 +510,8 @@ typedef enum {
     MDCNN_OPT_CONV_PATH = 0, /* 0 auto; fallbacks for testing: 1 plain FMA, 2 MFMA w/o LDS, */
                              /* 3 auto but never the packed-weights kernel                */
     MDCNN_OPT_PROFILE = 1,   /* 1: bracket every kernel launch with a pair of HIP events  */
+                             /* (launches that otherwise go out as one, see               */
+                             /* MDCNN_OPT_STREAMS, then go out one to a site or edge)     */
     MDCNN_OPT_CONV_TILE = 2, /* tuning: 0 auto, 1..14 force a tile shape of the fp16 MFMA kernel; */
                              /* fp32 3x3 layers of 16 channels: 1 / 2 / 4 waves share the taps     */
     MDCNN_OPT_CONV_PIPE = 3, /* tuning: 0 auto, 1 / 2 prefetch depth of the MFMA kernel    */
