@@ -194,67 +194,110 @@ __device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* s
     __syncthreads();
 }
 
-// By-products of an edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
+// Update flags of the 3 x 3 footprint of output (cy, cx) as a bit mask, in two steps so that the loads of several pixels go
+// out together: a row of three flags is one (unaligned) word, which may reach three bytes past the flags of the site, into
+// the padding or the region behind them.
+__device__ __forceinline__ void tap_rows_load(const EdgeDev& e, int cy, int cx, unsigned (&w)[3]) {
+    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int iy = y0 + r, at = iy * e.sW + x0;            // before the first flag: the word starts at flag 0 (tap_rows_mask)
+        const bool ok = iy >= 0 && iy < e.sH && x0 < e.sW;
+        __builtin_memcpy(&w[r], e.sflags + (ok && at > 0 ? at : 0), 4);
+    }
+}
+__device__ __forceinline__ unsigned tap_rows_mask(const EdgeDev& e, int cy, int cx, const unsigned (&w)[3]) {
+    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
+    unsigned cols = 0, m = 0;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) cols |= x0 + t >= 0 && x0 + t < e.sW ? 1u << t : 0u;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int iy = y0 + r, at = iy * e.sW + x0;
+        const unsigned v = at < 0 && at > -4 ? w[r] << (-8 * at) : w[r];
+        const unsigned b = (v >> 2) & 0x010101u;               // kFlagM == 4
+        if (iy >= 0 && iy < e.sH) m |= ((b | b >> 7 | b >> 14) & cols) << (3 * r);
+    }
+    return m;
+}
+
+// By-products of a 3 x 3 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
 // the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
-// count.  One wave per list segment, no barriers; a tile that made them itself had their loads ahead of its own and its
-// loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K loop, now 1.3.
-template <int KS>
+// count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
+// its own and its loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K
+// loop, now 1.3.  All loads of the two segments go out together, a row of the footprint is one word, and a mark is a byte
+// store - a pixel has one owner, so nobody else writes its flag meanwhile - where an atomic OR went past the L2 of its XCD:
+// the blocks of a 258 x 258 window were done 12.8 us into the launch, after its tiles, now 5.2 (64 channels, 256 x 256);
+// ResNet-18-style 512 x 512 frame 434 -> 425 us, HRNet-like 384 x 288 frame 632 -> 611, 8 videos of it 1273 -> 1229.
 __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, unsigned nblk) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned long long below = (1ull << lane) - 1ull;
     const int HW = e.sH * e.sW, n = e.Hp * e.Wp;
-    const int nsrc = e.pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, nseg = nsrc + (n + kSegPixels - 1) / kSegPixels;
+    const int nsrc = e.pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = (n + kSegPixels - 1) / kSegPixels;
+    const int units = nsrc > ndst ? nsrc : ndst;
     const float rw = rcp_of(e.Wp);
-    for (int s = (int)blk * 4 + wave; s < nseg; s += (int)nblk * 4) {
+    for (int s = (int)blk * 4 + wave; s < units; s += (int)nblk * 4) {
+        unsigned f[4], w[4][3], df[4];
+        int cy[4], cx[4], at[4];                               // at: the pixel's flag in the destination, -1 outside the view
+        unsigned long long lacc[2] = {0, 0}, cacc = 0;
         if (s < nsrc) {
-            unsigned f[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int p = s * kSegPixels + k * 64 + lane;
                 f[k] = e.sflags[p < HW ? p : 0];
-                if (p >= HW) f[k] = 0u;
             }
+            if (lane == 0) { lacc[0] = e.pub_lacc[2 * s]; lacc[1] = e.pub_lacc[2 * s + 1]; }
+        }
+        if (s < ndst) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int p = s * kSegPixels + k * 64 + lane, q = p < n ? p : 0, wy = fast_div(q, e.Wp, rw);
+                cy[k] = wy - e.by0;
+                cx[k] = q - wy * e.Wp - e.bx0;
+                tap_rows_load(e, cy[k], cx[k], w[k]);
+                at[k] = e.dflags && p < n && cy[k] >= 0 && cy[k] < e.dH && cx[k] >= 0 && cx[k] < e.dW ? cy[k] * e.dW + cx[k] : -1;
+                df[k] = at[k] >= 0 ? e.dflags[at[k]] : 0u;
+            }
+            if (lane == 0) cacc = e.cacc[s];
+        }
+        if (s < nsrc) {
             int tot = 0, cand = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
+                const int p = s * kSegPixels + k * 64 + lane;
+                if (p >= HW) f[k] = 0u;
                 const unsigned long long bm = __ballot(f[k] & kFlagM);
-                if (f[k] & kFlagM) e.pub_list[s * kSegPixels + tot + __popcll(bm & below)] = s * kSegPixels + k * 64 + lane;
+                if (f[k] & kFlagM) e.pub_list[s * kSegPixels + tot + __popcll(bm & below)] = p;
                 tot += __popcll(bm);
                 cand += __popcll(__ballot(f[k] & kFlagC));
             }
-            if (lane == 0) {                               // single writer per segment: no atomics
+            if (lane == 0) {                                   // single writer per segment: no atomics
                 e.pub_lcnt[2 * s] = tot;
                 e.pub_lcnt[2 * s + 1] = cand;
-                e.pub_lacc[2 * s] += (unsigned long long)tot;
-                e.pub_lacc[2 * s + 1] += (unsigned long long)cand;
+                e.pub_lacc[2 * s] = lacc[0] + (unsigned long long)tot;
+                e.pub_lacc[2 * s + 1] = lacc[1] + (unsigned long long)cand;
             }
-            continue;
         }
-        const int seg = s - nsrc;
-        unsigned vm[4];
+        if (s < ndst) {
+            int tot = 0, taps = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int p = seg * kSegPixels + k * 64 + lane, wy = fast_div(p, e.Wp, rw), wx = p - wy * e.Wp;
-            vm[k] = tap_mask_k<KS>(e, p < n ? wy - e.by0 : 0, p < n ? wx - e.bx0 : 0);
-            if (p >= n) vm[k] = 0;
-        }
-        int tot = 0, taps = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const unsigned long long b = __ballot(vm[k] != 0);
-            if (vm[k]) {
-                const int p = seg * kSegPixels + k * 64 + lane, wy = fast_div(p, e.Wp, rw);
-                e.clist[seg * kSegPixels + tot + __popcll(b & below)] = p;
-                mark_pixel(e, wy, p - wy * e.Wp);
+            for (int k = 0; k < 4; ++k) {
+                const int p = s * kSegPixels + k * 64 + lane;
+                const unsigned vm = p < n ? tap_rows_mask(e, cy[k], cx[k], w[k]) : 0u;
+                const unsigned long long b = __ballot(vm != 0);
+                if (vm) {
+                    e.clist[s * kSegPixels + tot + __popcll(b & below)] = p;
+                    if (at[k] >= 0) e.dflags[at[k]] = (uint8_t)(df[k] | kFlagU);
+                }
+                tot += __popcll(b);
+                taps += __popc(vm);
             }
-            tot += __popcll(b);
-            taps += __popc(vm[k]);
-        }
-        taps = wave_sum(taps);
-        if (lane == 0) {
-            e.ccnt[seg] = tot;
-            e.cacc[seg] += (unsigned long long)tot;
-            add_macs(e, taps, 0);
+            taps = wave_sum(taps);
+            if (lane == 0) {
+                e.ccnt[s] = tot;
+                e.cacc[s] = cacc + (unsigned long long)tot;
+                add_macs(e, taps, 0);
+            }
         }
     }
 }

@@ -450,7 +450,8 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
     unsigned warm = 0;
     if constexpr (T2D) {
         if (blk < npub) {
-            publish_edge<KS>(e, blk, npub);
+            static_assert(KS == 3, "publish_edge reads rows of three");
+            publish_edge(e, blk, npub);
             return;
         }
         blk -= npub;

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb, unsigned n
     const EdgeDev& e = eb.d[blockIdx.z];                  // blockIdx.z: stream of the batch
     const unsigned nblk = gridDim.x - npub;
     if (blockIdx.x >= nblk) {
-        if (blockIdx.y == 0) publish_edge<3>(e, blockIdx.x - nblk, npub);
+        if (blockIdx.y == 0) publish_edge(e, blockIdx.x - nblk, npub);
         return;
     }
     constexpr int BM = 128, KH = 14;
