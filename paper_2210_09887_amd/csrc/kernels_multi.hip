@@ -9,12 +9,11 @@
 namespace mdcnn {
 
 __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
-    int j = 0;
-    while (j + 1 < m.n && blockIdx.x >= m.job[j + 1].block0) ++j;
+    unsigned blk;
+    const int j = m.blocks.find(blockIdx.x, &blk);
     const ConvJob& jb = m.job[j];
-    const unsigned blk = blockIdx.x - jb.block0;
     if (blk >= jb.blocks) return;                         // (the numbers between two edges, up to a multiple of 8)
-    const ConvVid& v = m.vid[j * gridDim.z + blockIdx.z];
+    const ConvVid& v = m.vid[j * m.videos + (int)blockIdx.z];
     EdgeDev e = jb.e;
     auto at = [](auto*& p, long long d) {
         if (p) p = (std::remove_reference_t<decltype(p)>)((uintptr_t)p + (uintptr_t)d);
@@ -49,11 +48,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
 }
 
 hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_t st) {
-    unsigned blocks = 0;
-    for (int j = 0; j < m.n; ++j) {
-        m.job[j].block0 = blocks;
-        blocks += (m.job[j].blocks + 7u) & ~7u;
-    }
+    m.blocks.clear();
+    m.videos = videos;
+    for (int j = 0; j < m.n; ++j) m.blocks.add(j, (m.job[j].blocks + 7u) & ~7u);
     static std::atomic<bool> attr_set{false};
     if (smem > 32768 && !attr_set.load(std::memory_order_acquire)) {
         const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(k_conv_multi), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
@@ -61,7 +58,7 @@ hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_
         attr_set.store(true, std::memory_order_release);
     }
     if (smem > 80u * 1024u) return hipErrorInvalidValue;
-    k_conv_multi<<<dim3(blocks, 1, (unsigned)videos), dim3(256), smem, st>>>(m);
+    k_conv_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), smem, st>>>(m);
     return hipGetLastError();
 }
 

@@ -174,15 +174,14 @@ __device__ __forceinline__ void fill_block(const FillJob& j, unsigned lb) {
 }
 
 __global__ __launch_bounds__(256) void k_shift_fill(FillBatch fb) {
-    int ji = 0;
-    while (ji + 1 < fb.n && blockIdx.x >= fb.j[ji + 1].block_begin) ++ji;
-    const FillJob& j = fb.j[ji];
-    fill_block(j, blockIdx.x - j.block_begin);
+    unsigned lb;
+    const int j = fb.blocks.find(blockIdx.x, &lb);
+    fill_block(fb.j[j], lb);
 }
 
 hipError_t launch_shift_fill(const FillBatch& fb, hipStream_t st) {
-    if (fb.n == 0 || fb.total_blocks == 0) return hipSuccess;
-    k_shift_fill<<<dim3(fb.total_blocks), dim3(256), 0, st>>>(fb);
+    if (fb.n == 0 || fb.blocks.total == 0) return hipSuccess;
+    k_shift_fill<<<dim3(fb.blocks.total), dim3(256), 0, st>>>(fb);
     return hipGetLastError();
 }
 
@@ -315,17 +314,17 @@ __global__ __launch_bounds__(256) void k_step1(Step1Batch bt) {
     step1_block<T, G, CH>(bt.s[blockIdx.z], bt.skip[blockIdx.z], (const T*)bt.X[blockIdx.z], bt.forced[blockIdx.z], blockIdx.x);
 }
 
-// One site, and in the same launch the initialisation jobs of other sites: the first fill_blocks
+// One site, and in the same launch the initialisation jobs of other sites: the first
 // blocks of the grid, so that they start with the launch and not in its tail.
 template <typename T, int G, int CH>
 __global__ __launch_bounds__(256) void k_step1_fill(Step1Fill a) {
-    if (blockIdx.x >= a.fill_blocks) {
-        step1_block<T, G, CH>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks, a.has_own ? &a.own : nullptr);
+    if (blockIdx.x >= a.blocks.total) {
+        step1_block<T, G, CH>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.blocks.total, a.has_own ? &a.own : nullptr);
         return;
     }
-    int ji = 0;
-    while (ji + 1 < a.n && blockIdx.x >= a.j[ji + 1].block_begin) ++ji;
-    fill_block(a.j[ji], blockIdx.x - a.j[ji].block_begin);
+    unsigned lb;
+    const int j = a.blocks.find(blockIdx.x, &lb);
+    fill_block(a.j[j], lb);
 }
 
 // Any channel count: one lane per pixel, scalar accesses.
@@ -394,13 +393,13 @@ __global__ __launch_bounds__(256) void k_step1_scalar(Step1Batch bt) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_step1_scalar_fill(Step1Fill a) {
-    if (blockIdx.x >= a.fill_blocks) {
-        step1_scalar_block<T>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.fill_blocks, a.has_own ? &a.own : nullptr);
+    if (blockIdx.x >= a.blocks.total) {
+        step1_scalar_block<T>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.blocks.total, a.has_own ? &a.own : nullptr);
         return;
     }
-    int ji = 0;
-    while (ji + 1 < a.n && blockIdx.x >= a.j[ji + 1].block_begin) ++ji;
-    fill_block(a.j[ji], blockIdx.x - a.j[ji].block_begin);
+    unsigned lb;
+    const int j = a.blocks.find(blockIdx.x, &lb);
+    fill_block(a.j[j], lb);
 }
 
 // Split C/VEC chunks into G lanes x CH chunks per lane (G a power of two <= 64,
@@ -475,10 +474,10 @@ hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
 
 // Step 1 of several sites that do not depend on each other (see k_conv_multi): one 16-byte chunk per lane, fp16.
 __global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
-    int j = 0;
-    while (j + 1 < m.n && blockIdx.x >= m.job[j + 1].block0) ++j;
+    unsigned blk;
+    const int j = m.blocks.find(blockIdx.x, &blk);
     const Step1Job& jb = m.job[j];
-    const Step1Vid& v = m.vid[j * gridDim.z + blockIdx.z];
+    const Step1Vid& v = m.vid[j * m.videos + (int)blockIdx.z];
     auto at = [](auto* p, long long d) { return p ? (decltype(p))((uintptr_t)p + (uintptr_t)d) : nullptr; };
     SiteDev s{};
     s.kind = MDCNN_SITE_PREACT;
@@ -489,7 +488,6 @@ __global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
     SkipDev k{};
     k.P = at(jb.skip_P, v.kd); k.dflags = at(jb.skip_flags, v.kd);
     k.Hp = jb.skip_Hp; k.Wp = jb.skip_Wp; k.by0 = jb.skip_by0; k.bx0 = jb.skip_bx0; k.p_oy = v.k_oy; k.p_ox = v.k_ox;
-    const unsigned blk = blockIdx.x - jb.block0;
     const f16* const X = nullptr;
     switch (s.C / V16<f16>::N) {                           // lanes per pixel
         case 1: step1_block<f16, 1, 1>(s, k, X, nullptr, blk); break;
@@ -508,28 +506,24 @@ bool step1_multi_applies(const SiteDev& s) {
 }
 
 hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
-    unsigned blocks = 0;
+    m.blocks.clear();
+    m.videos = videos;
     for (int j = 0; j < m.n; ++j) {
-        Step1Job& jb = m.job[j];
+        const Step1Job& jb = m.job[j];
         int G = 0, CH = 0;
         if (!step1_shape(jb.C, V16<f16>::N, G, CH) || CH != 1) return hipErrorInvalidValue;
         const int ppb = 256 / G;
-        jb.block0 = blocks;
-        blocks += (unsigned)((jb.H * jb.W + ppb - 1) / ppb);
+        m.blocks.add(j, (unsigned)((jb.H * jb.W + ppb - 1) / ppb));
     }
-    k_step1_multi<<<dim3(blocks, 1, (unsigned)videos), dim3(256), 0, st>>>(m);
+    k_step1_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m);
     return hipGetLastError();
 }
 
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st) {
     if (a.n < 0 || a.n > kMaxRiders) return hipErrorInvalidValue;
-    unsigned extra = 0;
-    for (int k = 0; k < a.n; ++k) {
-        a.j[k].block_begin = extra;
-        extra += fill_blocks(a.j[k]);
-    }
-    a.fill_blocks = extra;
-    return a.s.dtype == MDCNN_F16 ? step1_t<f16>(a, a.s, 1, extra, st) : step1_t<float>(a, a.s, 1, extra, st);
+    a.blocks.clear();
+    for (int k = 0; k < a.n; ++k) a.blocks.add(k, fill_blocks(a.j[k]));
+    return a.s.dtype == MDCNN_F16 ? step1_t<f16>(a, a.s, 1, a.blocks.total, st) : step1_t<float>(a, a.s, 1, a.blocks.total, st);
 }
 
 // ---------------------------------------------------------------------------

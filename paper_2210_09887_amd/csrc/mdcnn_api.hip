@@ -705,8 +705,8 @@ hipError_t aux_prepare(int streams, size_t events) {
 }
 
 // Host part of a camera shift: decides between growth and full reset, moves the buffers and
-// makes the initialisation job of every buffer (jobs[i] for bufs[i]; block_begin is left to the
-// launch).  Nothing is launched.
+// makes the initialisation job of every buffer (jobs[i] for bufs[i]).  Nothing is
+// launched.
 mdcnn_status shift_jobs(mdcnn_buffer* const* bufs, int n, int dty, int dtx, std::vector<FillJob>& jobs, bool* full_out) {
     if (!bufs || n < 1) return fail(MDCNN_ERR_NULL, "no buffers");
     for (int i = 0; i < n; ++i) {
@@ -788,18 +788,18 @@ void frame_follows(mdcnn_buffer* const* bufs, std::vector<FillJob>& jobs, bool r
 // Launches jobs[which[0 .. count)] (which == nullptr: jobs[0 .. count)), kMaxFillJobs to a launch.
 hipError_t launch_fill_jobs(const FillJob* jobs, const int* which, int count, hipStream_t st) {
     FillBatch fb{};
+    fb.blocks.clear();
     auto flush = [&]() -> hipError_t {
         hipError_t err = timed(kClsShift, st, [&] { return launch_shift_fill(fb, st); });
         fb.n = 0;
-        fb.total_blocks = 0;
+        fb.blocks.clear();
         return err;
     };
     for (int k = 0; k < count; ++k) {
-        FillJob j = jobs[which ? which[k] : k];
+        const FillJob& j = jobs[which ? which[k] : k];
         if (fill_blocks(j) == 0) continue;
-        j.block_begin = fb.total_blocks;
+        fb.blocks.add(fb.n, fill_blocks(j));
         fb.j[fb.n++] = j;
-        fb.total_blocks += fill_blocks(j);
         if (fb.n == kMaxFillJobs) {
             hipError_t err = flush();
             if (err != hipSuccess) return err;
@@ -862,7 +862,7 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 const SiteDev& s0 = sb.s[0];
                 const SkipDev& k0 = sb.skip[0];
                 j = Step1Job{s0.A, s0.P, s0.delta, s0.flags, k0.P, k0.dflags, s0.H, s0.W, s0.C, s0.Hp, s0.Wp, s0.by0, s0.bx0, s0.relu,
-                             k0.Hp, k0.Wp, k0.by0, k0.bx0, 0u};
+                             k0.Hp, k0.Wp, k0.by0, k0.bx0};
                 for (int b = 0; b < n; ++b) {
                     const SiteDev& s = sb.s[b];
                     const SkipDev& k = sb.skip[b];
