@@ -85,10 +85,16 @@ __device__ __forceinline__ void add_macs(const EdgeDev& e, long long taps, int w
         atomicAdd(reinterpret_cast<unsigned long long*>(e.dcounters) + kAccMacsSpread + 8 * which + (blockIdx.x & 7),
                   (unsigned long long)taps * (unsigned long long)(e.Cin * e.Cout));
 }
+// Sum over the wave, in every lane: DPP moves (row_shr 1, 2, 4, 8, then row_bcast 15 and 31), a tenth of the latency of shuffles
+// through LDS.
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Marks a window pixel as touched, if it is in the view: an atomic OR on the word that holds the flag byte, its result
@@ -194,114 +200,6 @@ __device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* s
     __syncthreads();
 }
 
-// Update flags of the 3 x 3 footprint of output (cy, cx) as a bit mask, in two steps so that the loads of several pixels go
-// out together: a row of three flags is one (unaligned) word, which may reach three bytes past the flags of the site, into
-// the padding or the region behind them.
-__device__ __forceinline__ void tap_rows_load(const EdgeDev& e, int cy, int cx, unsigned (&w)[3]) {
-    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int iy = y0 + r, at = iy * e.sW + x0;            // before the first flag: the word starts at flag 0 (tap_rows_mask)
-        const bool ok = iy >= 0 && iy < e.sH && x0 < e.sW;
-        __builtin_memcpy(&w[r], e.sflags + (ok && at > 0 ? at : 0), 4);
-    }
-}
-__device__ __forceinline__ unsigned tap_rows_mask(const EdgeDev& e, int cy, int cx, const unsigned (&w)[3]) {
-    const int y0 = cy * e.stride - e.pad, x0 = cx * e.stride - e.pad;
-    unsigned cols = 0, m = 0;
-#pragma unroll
-    for (int t = 0; t < 3; ++t) cols |= x0 + t >= 0 && x0 + t < e.sW ? 1u << t : 0u;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int iy = y0 + r, at = iy * e.sW + x0;
-        const unsigned v = at < 0 && at > -4 ? w[r] << (-8 * at) : w[r];
-        const unsigned b = (v >> 2) & 0x010101u;               // kFlagM == 4
-        if (iy >= 0 && iy < e.sH) m |= ((b | b >> 7 | b >> 14) & cols) << (3 * r);
-    }
-    return m;
-}
-
-// By-products of a 3 x 3 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
-// the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
-// count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
-// its own and its loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K
-// loop, now 1.3.  All loads of the two segments go out together, a row of the footprint is one word, and a mark is a byte
-// store - a pixel has one owner, so nobody else writes its flag meanwhile - where an atomic OR went past the L2 of its XCD:
-// the blocks of a 258 x 258 window were done 12.8 us into the launch, after its tiles, now 5.2 (64 channels, 256 x 256);
-// ResNet-18-style 512 x 512 frame 434 -> 425 us, HRNet-like 384 x 288 frame 632 -> 611, 8 videos of it 1273 -> 1229.
-__device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, unsigned nblk) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    const int HW = e.sH * e.sW, n = e.Hp * e.Wp;
-    const int nsrc = e.pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = (n + kSegPixels - 1) / kSegPixels;
-    const int units = nsrc > ndst ? nsrc : ndst;
-    const float rw = rcp_of(e.Wp);
-    for (int s = (int)blk * 4 + wave; s < units; s += (int)nblk * 4) {
-        unsigned f[4], w[4][3], df[4];
-        int cy[4], cx[4], at[4];                               // at: the pixel's flag in the destination, -1 outside the view
-        unsigned long long lacc[2] = {0, 0}, cacc = 0;
-        if (s < nsrc) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int p = s * kSegPixels + k * 64 + lane;
-                f[k] = e.sflags[p < HW ? p : 0];
-            }
-            if (lane == 0) { lacc[0] = e.pub_lacc[2 * s]; lacc[1] = e.pub_lacc[2 * s + 1]; }
-        }
-        if (s < ndst) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int p = s * kSegPixels + k * 64 + lane, q = p < n ? p : 0, wy = fast_div(q, e.Wp, rw);
-                cy[k] = wy - e.by0;
-                cx[k] = q - wy * e.Wp - e.bx0;
-                tap_rows_load(e, cy[k], cx[k], w[k]);
-                at[k] = e.dflags && p < n && cy[k] >= 0 && cy[k] < e.dH && cx[k] >= 0 && cx[k] < e.dW ? cy[k] * e.dW + cx[k] : -1;
-                df[k] = at[k] >= 0 ? e.dflags[at[k]] : 0u;
-            }
-            if (lane == 0) cacc = e.cacc[s];
-        }
-        if (s < nsrc) {
-            int tot = 0, cand = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int p = s * kSegPixels + k * 64 + lane;
-                if (p >= HW) f[k] = 0u;
-                const unsigned long long bm = __ballot(f[k] & kFlagM);
-                if (f[k] & kFlagM) e.pub_list[s * kSegPixels + tot + __popcll(bm & below)] = p;
-                tot += __popcll(bm);
-                cand += __popcll(__ballot(f[k] & kFlagC));
-            }
-            if (lane == 0) {                                   // single writer per segment: no atomics
-                e.pub_lcnt[2 * s] = tot;
-                e.pub_lcnt[2 * s + 1] = cand;
-                e.pub_lacc[2 * s] = lacc[0] + (unsigned long long)tot;
-                e.pub_lacc[2 * s + 1] = lacc[1] + (unsigned long long)cand;
-            }
-        }
-        if (s < ndst) {
-            int tot = 0, taps = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int p = s * kSegPixels + k * 64 + lane;
-                const unsigned vm = p < n ? tap_rows_mask(e, cy[k], cx[k], w[k]) : 0u;
-                const unsigned long long b = __ballot(vm != 0);
-                if (vm) {
-                    e.clist[s * kSegPixels + tot + __popcll(b & below)] = p;
-                    if (at[k] >= 0) e.dflags[at[k]] = (uint8_t)(df[k] | kFlagU);
-                }
-                tot += __popcll(b);
-                taps += __popc(vm);
-            }
-            taps = wave_sum(taps);
-            if (lane == 0) {
-                e.ccnt[s] = tot;
-                e.cacc[s] = cacc + (unsigned long long)tot;
-                add_macs(e, taps, 0);
-            }
-        }
-    }
-}
-
 // Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a
 // scalar byte offset, so a wave spends one vector register on all the addresses of a tensor instead of a
 // 64-bit pointer per load (reads past `bytes` return zero instead of faulting).
@@ -313,6 +211,106 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, unsigned bytes) {
 __device__ __forceinline__ f16x8 buf_load16(rsrc_t r, unsigned lane_bytes, unsigned wave_bytes) {
     const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)wave_bytes, 0);
     return __builtin_bit_cast(f16x8, v);
+}
+
+// By-products of a 3 x 3 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
+// the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
+// count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
+// its own and its loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K
+// loop, now 1.3.  All loads of the two segments go out together, a row of the footprint is one unaligned word, and a mark is
+// a byte store - a pixel has one owner, so nobody else writes its flag meanwhile - where an atomic OR went past the L2 of its
+// XCD.  What bounds it is the number of instructions: one that needs the result of the one before it starts 8 cycles later.  The
+// blocks of a 258 x 258 window were done 12.8 us into the launch, after its tiles, now 4.8; of a 66 x 66 window 6.3, now 2.5.
+__device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, unsigned nblk) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const uint8_t* sflags = e.sflags;
+    uint8_t* dflags = e.dflags;
+    int *pub_list = e.pub_list, *pub_lcnt = e.pub_lcnt, *clist = e.clist, *ccnt = e.ccnt;
+    unsigned long long *pub_lacc = e.pub_lacc, *cacc = e.cacc;
+    int sH = e.sH, sW = e.sW, dH = e.dH, dW = e.dW, Hp = e.Hp, Wp = e.Wp, by0 = e.by0, bx0 = e.bx0, stride = e.stride, pad = e.pad;
+    asm volatile("" : "+s"(sflags), "+s"(dflags), "+s"(pub_list), "+s"(pub_lcnt), "+s"(clist), "+s"(ccnt), "+s"(pub_lacc), "+s"(cacc), "+s"(sH), "+s"(sW), "+s"(dH));
+    asm volatile("" : "+s"(dW), "+s"(Hp), "+s"(Wp), "+s"(by0), "+s"(bx0), "+s"(stride), "+s"(pad));     // read in one go
+    const int HW = sH * sW, n = Hp * Wp;
+    const int nsrc = pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = (n + kSegPixels - 1) / kSegPixels;
+    const int units = nsrc > ndst ? nsrc : ndst;
+    const float rw = rcp_of(Wp);
+    // Flags of the source from the word before the first on (whatever is there, it is masked); a row outside the source is read
+    // from beyond the end, which gives zeros, and so is a mark's byte outside the destination's view.
+    const rsrc_t frs = make_rsrc(sflags, (unsigned)HW), wrs = make_rsrc(sflags - 4, (unsigned)HW + 7u), mrs = make_rsrc(dflags, dflags ? (unsigned)(dH * dW) : 0u);
+    constexpr unsigned kOutside = 0x80000000u;
+    for (int s = (int)blk * 4 + wave; s < units; s += (int)nblk * 4) {
+        const int p0 = s * kSegPixels + lane;
+        unsigned f[4], w[4][3], df[4], at[4], cols[4];         // at: the pixel's flag in the destination; cols: flag M of the columns in the source
+        unsigned long long lsum[2] = {0, 0}, csum = 0;
+        if (s < nsrc) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = __builtin_amdgcn_raw_buffer_load_b8(frs, p0 + k * 64, 0, 0);
+            if (lane == 0) { lsum[0] = pub_lacc[2 * s]; lsum[1] = pub_lacc[2 * s + 1]; }
+        }
+        if (s < ndst) {
+            const int ry = (s * kSegPixels) / Wp, rx = s * kSegPixels - ry * Wp + lane;        // row of the segment's first pixel
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int x = rx + k * 64;                     // (fast_div below 2^24: a window has fewer columns)
+                int q = (int)((float)x * rw);
+                const int rem = x - q * Wp;
+                q += (rem >= Wp ? 1 : 0) - (rem < 0 ? 1 : 0);
+                const int cy = ry + q - by0, cx = x - q * Wp - bx0;
+                const int iy = cy * stride - pad, ix = cx * stride - pad;
+                const bool in = p0 + k * 64 < n;
+                cols[k] = 0;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) cols[k] |= in && (unsigned)(ix + t) < (unsigned)sW ? (unsigned)kFlagM << (8 * t) : 0u;
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+                    w[k][r] = __builtin_amdgcn_raw_buffer_load_b32(wrs, (unsigned)(iy + r) < (unsigned)sH && cols[k] ? (iy + r) * sW + ix + 4 : (int)kOutside, 0, 0);
+                at[k] = in && (unsigned)cy < (unsigned)dH && (unsigned)cx < (unsigned)dW ? (unsigned)(cy * dW + cx) : kOutside;
+                df[k] = __builtin_amdgcn_raw_buffer_load_b8(mrs, (int)at[k], 0, 0);
+            }
+            if (lane == 0) csum = cacc[s];
+        }
+        if (s < nsrc) {
+            int tot = 0, cand = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned long long bm = __ballot(f[k] & kFlagM);
+                if (f[k] & kFlagM) pub_list[s * kSegPixels + tot + __popcll(bm & below)] = p0 + k * 64;
+                tot += __popcll(bm);
+                cand += __popcll(__ballot(f[k] & kFlagC));
+            }
+            if (lane == 0) {                                   // single writer per segment: no atomics
+                pub_lcnt[2 * s] = tot;
+                pub_lcnt[2 * s + 1] = cand;
+                pub_lacc[2 * s] = lsum[0] + (unsigned long long)tot;
+                pub_lacc[2 * s + 1] = lsum[1] + (unsigned long long)cand;
+            }
+        }
+        if (s < ndst) {
+            int tot = 0, taps = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                unsigned any = 0;
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    any |= w[k][r] & cols[k];
+                    taps += __popc(w[k][r] & cols[k]);
+                }
+                const unsigned long long b = __ballot(any != 0);
+                if (any) {
+                    clist[s * kSegPixels + tot + __popcll(b & below)] = p0 + k * 64;
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(df[k] | kFlagU), mrs, (int)at[k], 0, 0);     // outside: dropped
+                }
+                tot += __popcll(b);
+            }
+            taps = wave_sum(taps);
+            if (lane == 0) {
+                ccnt[s] = tot;
+                cacc[s] = csum + (unsigned long long)tot;
+                add_macs(e, taps, 0);
+            }
+        }
+    }
 }
 
 }  // namespace mdcnn

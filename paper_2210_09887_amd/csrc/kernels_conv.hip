@@ -28,6 +28,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "conv_rect.h"
 #include "conv_tiles.h"
 
 namespace mdcnn {
@@ -40,6 +41,11 @@ __global__ __launch_bounds__(256) void k_conv_mfma_tiled(EdgeBatch eb, int NT, i
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
 __global__ __launch_bounds__(256, MINB_) void k_conv_halo(EdgeBatch eb, unsigned npub, int NT, int work_items, int th, int tw) {
     halo_body<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_, T2D>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, npub, NT, work_items, th, tw);
+}
+
+template <typename Cfg>
+__global__ __launch_bounds__(256, Cfg::MINB) void k_conv_rect(TileGrid g, unsigned blocks, EdgeBatch eb) {
+    rect_body<Cfg>(eb.d[blockIdx.z], blockIdx.x, blocks, g);
 }
 
 // Weights [tap][cout][cin] -> [tap][cin/16][cout][16]: the 32 couts x 16 cin
@@ -988,7 +994,7 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
     unsigned g = cap_blocks(items, 4096);
     g = (g + 7u) & ~7u;                                    // whole rounds over the 8 XCDs
     if (pick) {
-        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), NT, (int)items, xcd, 0, 0u, g, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), (int)items, TileGrid{0u, NT, xcd, 0, 0, 0u, 0u}, g, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_mfma_tiled<WM, WN, TM, TN, KC, PIPE>;
@@ -1058,7 +1064,7 @@ static hipError_t launch_halo_t(const EdgeBatch& eb, int nb, long long nseg, hip
     const long long items = tiles * NT;
     const unsigned npub = T2D ? publish_blocks(e) : 0u, blocks = cap_blocks(items, 16384) + npub;
     if (pick) {
-        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), NT, (int)items, th, tw, npub, blocks, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), (int)items, TileGrid{npub, NT, th, tw, 0, 0u, 0u}, blocks, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_halo<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, MINB, T2D>;
@@ -1108,22 +1114,112 @@ bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, 
     return true;
 }
 
-// Rectangular tiles.  The tile size follows the number of tiles of ONE stream, whatever the batch - the K split of a
-// tile fixes the order of the sums, and a stream in a batch must give the bits it gives alone: whole segments if that
-// gives every compute unit a tile, else the smallest split that gives half of them one.  A whole-segment tile keeps its
-// four waves on rows (no K split: 64 accumulator registers, two tiles per compute unit); it is what the 64-channel
-// layers with rows wider than a segment use.  With many streams to a launch whole segments are the faster choice
-// everywhere (ResNet-18-style network, 16 videos: 4.1 k frames/s against 3.9 k; one video: 3.5 k against 3.7 k): a caller
-// who serves batches sets MDCNN_OPT_CONV_HALO_SUB to 1.  128-channel chunks (half the chunk boundaries) were measured
-// too: no faster alone or in a batch, so chunks stay at 64 channels.
+// Rectangle of at most m pixels, 14 columns and rows - 2 rows for the tiles of conv_rect.h, with the fewest tiles over an
+// Hp x Wp window (ties: the smaller halo).  Asked for by every launch: the answers are kept per host thread, as tile_2d's.
+static void rect_tile(int Hp, int Wp, int m, int rows, int* th_out, int* tw_out, long long* tiles_out) {
+    struct Entry { int Hp = -1, Wp, m, th, tw; long long tiles; };
+    static thread_local Entry table[256];
+    const unsigned h = (unsigned)Hp * 2654435761u ^ (unsigned)Wp * 2246822519u ^ (unsigned)m * 3266489917u;
+    Entry& t = table[(h >> 16) % 256];
+    if (t.Hp != Hp || t.Wp != Wp || t.m != m) {
+        t = Entry{Hp, Wp, m, 0, 0, -1};
+        long long halo = 0;
+        for (int tw = 1; tw <= 14 && tw <= Wp; ++tw) {
+            int th = m / tw < rows - 2 ? m / tw : rows - 2;
+            if (th > Hp) th = Hp;
+            const int down = (Hp + th - 1) / th, across = (Wp + tw - 1) / tw;
+            th = (Hp + down - 1) / down;                   // the lowest tile with as many rows of tiles
+            const long long n = (long long)down * across, hl = (long long)(th + 2) * (tw + 2);
+            if (t.tiles < 0 || n < t.tiles || (n == t.tiles && hl < halo)) { t.tiles = n; halo = hl; t.th = th; t.tw = tw; }
+        }
+    }
+    *th_out = t.th;
+    *tw_out = t.tw;
+    *tiles_out = t.tiles;
+}
+template <typename Cfg>
+static long long rect_tiles(const EdgeDev& e) {
+    int th, tw;
+    long long tiles;
+    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, &th, &tw, &tiles);
+    return tiles * (e.Cout / Cfg::BN);
+}
+template <typename Cfg>
+static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done) {
+    const EdgeDev& e = eb.d[0];
+    int th, tw;
+    long long tiles;
+    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, &th, &tw, &tiles);
+    const int NT = e.Cout / Cfg::BN, tiles_x = (e.Wp + tw - 1) / tw;
+    *done = (double)tiles * NT * NT < 4e9 && (double)tiles * tiles_x < 4e9;      // (the reciprocals are exact below 2^32)
+    if (!*done) return hipSuccess;
+    const unsigned npub = publish_blocks(e), blocks = (unsigned)(tiles * NT) + npub;
+    const TileGrid g{npub, NT, th, tw, tiles_x, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)tiles_x)};
+    if (pick) {
+        *pick = ConvPick{multi_rect_body(Cfg::M, Cfg::TN), (int)(tiles * NT), g, blocks, (unsigned)Cfg::SMEM};
+        return hipSuccess;
+    }
+    auto kern = k_conv_rect<Cfg>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::SMEM);
+        if (err != hipSuccess) { (void)hipGetLastError(); return err; }    // do not leave it for the next call to report
+        attr_set.store(true, std::memory_order_release);
+    }
+    kern<<<dim3(blocks, 1, nb), dim3(256), Cfg::SMEM, st>>>(g, blocks, eb);
+    return hipGetLastError();
+}
+
+// Which tile.  Alone on the GPU a launch takes as long as the compute unit with the most tiles, one or two of them, and a tile
+// as long as its K loop (per entry, Cin + what the epilogue takes); in a full GPU - several tiles per compute unit, or the
+// frames beside this one, four in flight - it is the sum of the tiles and 2 us of each (12500 in these units) that nothing
+// covers.  Tiles of 160 entries have a compute unit for themselves and an epilogue that takes 1.3 us more.  Measured alone, 64 /
+// 96 / 160 entries: 512 -> 512 channels on a 66 x 66 window 30.9 / 25.2 / 23.2 us (29.9 with the kernel before), 256 -> 256
+// 12.5 / 10.6 / 15.2 (13.3), 128 -> 128 on 130 x 130 14.2 / 11.2 / 12.3 (12.8); 16 videos, 96 / 128 / 160 entries: 293 / 264
+// / 308 us (279), 84 / 78 / 100 (81), 95 / 91 / 129 (96).  64 channels on large windows: 256-entry tiles without a K split,
+// two to a compute unit, 12.4 us on 258 x 258 against 17.7 with 160-entry tiles, 16 videos 111 (13.6 and 118 before).
+template <int TN>
+static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream_t st, ConvPick* pick, bool* done) {
+    const EdgeDev& e = eb.d[0];
+    using T = RectTiles<TN>;
+    int m = 0;
+    if (g_halo_sub) {
+        m = g_halo_sub == 4 ? 64 : g_halo_sub == 2 ? 128 : e.Cin == 64 ? 256 : 160;
+    } else if (e.Cin == 64 && rect_tiles<typename T::T96>(e) > 512) {
+        m = 256;
+    } else {
+        const long long of[4] = {rect_tiles<typename T::T64>(e), rect_tiles<typename T::T96>(e), rect_tiles<typename T::T128>(e), rect_tiles<typename T::T160>(e)};
+        double best = 0;
+        for (int i = 0; i < (alone && !pick ? 4 : 3); ++i) {
+            const int px = 64 + 32 * i;
+            const double per_cu = (double)(of[i] * nb * (alone ? 1 : 4)) / 256;
+            const bool full = per_cu > 2;
+            const double cost = (full ? per_cu : per_cu <= 1 ? 1 : 2) * ((double)px * (e.Cin + 78) + (full ? 12500 : px == 160 ? 8000 : 0));
+            if (m == 0 || cost <= best) { best = cost; m = px; }
+        }
+    }
+    switch (m) {
+        case 64: return launch_rect_t<typename T::T64>(eb, nb, st, pick, done);
+        case 96: return launch_rect_t<typename T::T96>(eb, nb, st, pick, done);
+        case 128: return launch_rect_t<typename T::T128>(eb, nb, st, pick, done);
+        case 160: return launch_rect_t<typename T::T160>(eb, nb, st, pick, done);
+        default: return launch_rect_t<typename T::T256>(eb, nb, st, pick, done);
+    }
+}
+
+// Rectangular tiles of the layers whose input channels are a multiple of 32 and not of 64.  The tile size follows the number
+// of tiles of ONE stream, whatever the batch - the K split of a tile fixes the order of the sums, and a stream in a batch must
+// give the bits it gives alone: whole segments if that gives every compute unit a tile, else the smallest split that gives
+// half of them one.  A whole-segment tile keeps its four waves on rows (no K split: 64 accumulator registers, two tiles per
+// compute unit).
 template <int TN>
 static hipError_t launch_halo_2d(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done) {
     const EdgeDev& e = eb.d[0];
     const int NT = e.Cout / (32 * TN);
-    const bool c64 = e.Cin % 64 == 0, c32 = e.Cin % 32 == 0;
     int th = 0, tw = 0;
     long long tiles = 0;
-    *done = true;
+    *done = e.Cin % 32 == 0;
+    if (!*done) return hipSuccess;
     const int first = g_halo_sub ? g_halo_sub : 1;
     for (int nsub = first; nsub <= 4; nsub *= 2) {
         const int sub = kSegPixels / nsub;
@@ -1131,20 +1227,13 @@ static hipError_t launch_halo_2d(const EdgeBatch& eb, int nb, hipStream_t st, Co
         // (a forced split is taken as it is)
         if (!g_halo_sub && nsub < 4 && tile_2d(e.Hp, e.Wp, e.k, sub, 1 << 20, &th, &tw, &tiles) && tiles * NT < (nsub == 1 ? 256 : 128)) continue;
         if (nsub == 1) {
-            if (c64 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<1, 4, 1, 2, TN, 64, 11, 3>::CAP, &th, &tw, &tiles))
-                return launch_halo_t<1, 4, 1, 2, TN, 64, 11, 6, 2, true>(eb, nb, 0, st, pick, th, tw);
-            if (c32 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<1, 4, 1, 2, TN, 32, 6, 3>::CAP, &th, &tw, &tiles))
+            if (tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<1, 4, 1, 2, TN, 32, 6, 3>::CAP, &th, &tw, &tiles))
                 return launch_halo_t<1, 4, 1, 2, TN, 32, 6, 3, 2, true>(eb, nb, 0, st, pick, th, tw);
         } else if (nsub == 2) {
-            if (c64 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<2, 2, 2, 2, TN, 64, 6, 3>::CAP, &th, &tw, &tiles))
-                return launch_halo_t<2, 2, 2, 2, TN, 64, 6, 6, 2, true>(eb, nb, 0, st, pick, th, tw);
-            if (c32 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<2, 2, 2, 2, TN, 32, 3, 3>::CAP, &th, &tw, &tiles))
+            if (tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<2, 2, 2, 2, TN, 32, 3, 3>::CAP, &th, &tw, &tiles))
                 return launch_halo_t<2, 2, 2, 2, TN, 32, 3, 3, 2, true>(eb, nb, 0, st, pick, th, tw);
-        } else {
-            if (c64 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<4, 1, 4, 2, TN, 64, 4, 3>::CAP, &th, &tw, &tiles))
-                return launch_halo_t<4, 1, 4, 2, TN, 64, 4, 9, 2, true>(eb, nb, 0, st, pick, th, tw);
-            if (c32 && tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<4, 2, 2, 1, TN, 32, 2, 3>::CAP, &th, &tw, &tiles))
-                return launch_halo_t<4, 2, 2, 1, TN, 32, 2, 9, 2, true>(eb, nb, 0, st, pick, th, tw);
+        } else if (tile_2d(e.Hp, e.Wp, e.k, sub, HaloCfg<4, 2, 2, 1, TN, 32, 2, 3>::CAP, &th, &tw, &tiles)) {
+            return launch_halo_t<4, 2, 2, 1, TN, 32, 2, 9, 2, true>(eb, nb, 0, st, pick, th, tw);
         }
     }
     *done = false;
@@ -1179,7 +1268,7 @@ static hipError_t launch_halo_n(const EdgeBatch& eb, int nb, long long nseg, hip
             if (c64 && worst <= HaloCfg<1, 2, 2, 4, TN, 64, 16, 3>::CAP) return launch_halo_t<1, 2, 2, 4, TN, 64, 16>(eb, nb, nseg, st, pick);
             if (c32 && worst <= HaloCfg<1, 2, 2, 4, TN, 32, 12, 3>::CAP) return launch_halo_t<1, 2, 2, 4, TN, 32, 12>(eb, nb, nseg, st, pick);
         } else if (nsub == 2) {
-            if (c64 && worst <= HaloCfg<2, 2, 2, 2, TN, 64, 11, 3>::CAP) return launch_halo_t<2, 2, 2, 2, TN, 64, 11, 6>(eb, nb, nseg, st, pick);
+            if (c64 && worst <= HaloCfg<2, 1, 4, 4, TN, 64, 11, 3>::CAP) return launch_halo_t<2, 1, 4, 4, TN, 64, 11>(eb, nb, nseg, st, pick);
             if (c32 && worst <= HaloCfg<2, 2, 2, 2, TN, 32, 9, 3>::CAP) return launch_halo_t<2, 2, 2, 2, TN, 32, 9>(eb, nb, nseg, st, pick);
         } else {
             if (c64 && worst <= HaloCfg<4, 1, 4, 2, TN, 64, 9, 3>::CAP) return launch_halo_t<4, 1, 4, 2, TN, 64, 9, 9>(eb, nb, nseg, st, pick);
@@ -1190,7 +1279,7 @@ static hipError_t launch_halo_n(const EdgeBatch& eb, int nb, long long nseg, hip
     return hipSuccess;
 }
 
-static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, ConvPick* pick, bool* done) {
+static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool alone, hipStream_t st, ConvPick* pick, bool* done) {
     const EdgeDev& e = eb.d[0];
     *done = false;
     if (!g_halo || !e.wp || e.k != 3 || e.stride != 1 || e.up != 0 || e.Cin % 16 || e.Cout % 32) return hipSuccess;
@@ -1200,6 +1289,8 @@ static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, hipSt
     // ranges, whose tiles stage whole rows; with the by-products made by other blocks and the round trips of a small tile
     // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512
     // channels 22 -> 17 us a launch.
+    if (g_halo != 3 && e.Cin % 64 == 0)
+        return e.Cout % 64 == 0 && g_halo != 2 ? launch_rect<2>(eb, nb, alone, st, pick, done) : launch_rect<1>(eb, nb, alone, st, pick, done);
     if (g_halo != 3) return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
     return e.Cout % 64 == 0 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
 }
@@ -1284,7 +1375,7 @@ static hipError_t launch_mfma_f32(const EdgeBatch& eb, int nb, long long nseg, h
          : e.Cin == 32 ? launch_mfma_f32_ks<1, 32>(eb, nb, nseg, st) : launch_mfma_f32_ks<1, 64>(eb, nb, nseg, st);
 }
 
-hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, hipStream_t st, int* cls, ConvPick* pick) {
+hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick) {
     const EdgeDev& e = eb.d[0];                            // geometry and weights layout are the same for all streams
     const long long max_entries = e.up ? (long long)e.sH * e.sW : (long long)e.Hp * e.Wp;
     const long long nseg = (max_entries + kSegPixels - 1) / kSegPixels;
@@ -1332,7 +1423,7 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, hi
     const bool mfma_ok = dtype == MDCNN_F16 && conv_path != 1 && e.Cin % 16 == 0 && e.Cout % 32 == 0;
     if (mfma_ok && conv_path == 0) {
         bool done = false;
-        const hipError_t err = launch_halo(eb, nb, nseg, st, pick, &done);
+        const hipError_t err = launch_halo(eb, nb, nseg, alone, st, pick, &done);
         if (done) { *cls = kClsConvMfma; return err; }
     }
     // (the tiled kernel addresses deltas and weights with 32-bit byte offsets)

@@ -4,6 +4,7 @@
 // an event.  A block finds its edge by its number and runs the tile its edge would run alone: the results are the same bits.
 #include <atomic>
 
+#include "conv_rect.h"
 #include "conv_tiles.h"
 
 namespace mdcnn {
@@ -22,27 +23,27 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     at(e.P, v.dd); at(e.dflags, v.dd); at(e.clist, v.dd); at(e.ccnt, v.dd); at(e.cacc, v.dd); at(e.dcounters, v.dd);
     e.p_oy = v.p_oy;
     e.p_ox = v.p_ox;
-    const int NT = jb.NT, items = jb.items, p0 = jb.p0, p1 = jb.p1;
+    const int NT = jb.g.NT, items = jb.items, p0 = jb.g.p0, p1 = jb.g.p1;
     const unsigned nblk = jb.blocks;
+#define RECT(M, TN)                                                                                                       \
+    case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M>(e, blk, nblk, jb.g); break;
 #define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
     case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
-        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, jb.npub, NT, items, p0, p1);             \
+        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, jb.g.npub, NT, items, p0, p1);           \
         break;
 #define TILED(WM, WN, TM, TN, KC)                                                                                         \
     case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, NT, items, p0); break;
     switch (jb.body) {
+        RECT(64, 1) RECT(64, 2) RECT(96, 1) RECT(96, 2) RECT(128, 1) RECT(128, 2)
         HALO(2, 2, 2, 2, 1, 32, 3, 3, true)
-        HALO(2, 2, 2, 2, 1, 64, 6, 6, true)
-        HALO(2, 2, 2, 2, 2, 64, 6, 6, true)
         HALO(4, 2, 2, 1, 1, 32, 2, 9, true)
-        HALO(4, 1, 4, 2, 1, 64, 4, 9, true)
-        HALO(4, 1, 4, 2, 2, 64, 4, 9, true)
         TILED(2, 2, 1, 1, 32) TILED(2, 2, 1, 1, 64) TILED(2, 2, 1, 1, 128)
         TILED(4, 1, 1, 1, 32) TILED(4, 1, 1, 1, 64) TILED(4, 1, 1, 1, 128)
         TILED(2, 2, 2, 1, 32) TILED(2, 2, 2, 1, 64) TILED(2, 2, 2, 1, 128)
         TILED(2, 2, 1, 2, 32) TILED(2, 2, 1, 2, 64) TILED(2, 2, 1, 2, 128)
         default: break;
     }
+#undef RECT
 #undef HALO
 #undef TILED
 }

@@ -398,7 +398,7 @@ struct ListScratch {
 mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* frames, const uint8_t* const* forced,
                         const mdcnn_conv_desc* const* edges, mdcnn_buffer* const* const* outs, int n_edges,
                         hipStream_t st, int fuse_skip = -1, Sched* sc = nullptr, const FillJob* jobs = nullptr,
-                        const int* riders = nullptr, int n_riders = 0, const ListScratch* ls = nullptr) {
+                        const int* riders = nullptr, int n_riders = 0, const ListScratch* ls = nullptr, bool alone = true) {
     static thread_local Step1Batch sb;                     // 3.4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
     for (int b = 0; b < n; ++b)
@@ -435,7 +435,7 @@ mdcnn_status do_forward(int n, mdcnn_buffer* const* ins, const void* const* fram
             if (!t.start || !t.stop) return fail(MDCNN_ERR_HIP, "cannot create profiling events");
             (void)hipEventRecord(t.start, st);
         }
-        err = launch_conv(eb, n, ins[0]->d.dtype, g_conv_path, st, &cls);
+        err = launch_conv(eb, n, ins[0]->d.dtype, g_conv_path, alone, st, &cls);
         if (g_profile) {
             (void)hipEventRecord(t.stop, st);
             t.cls = cls;
@@ -817,7 +817,7 @@ bool whole_view(const mdcnn_buffer* b) { return crop_pixels(b) == (size_t)b->d.H
 // One round of a plan for n videos (n <= kMaxBatch): sites[b] are the sites of video b as the frame sees them.
 // Operations the multi-edge kernels do not take get a launch each.
 mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets, int n, const std::vector<mdcnn_buffer* const*>& sites,
-                       const void* const* frames, const uint8_t* const* forced, hipStream_t st, const FillJob* jobs = nullptr,
+                       const void* const* frames, const uint8_t* const* forced, hipStream_t st, bool alone, const FillJob* jobs = nullptr,
                        const std::vector<int>* fills = nullptr) {
     static thread_local Step1Batch sb;                     // 3.4 to 4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
@@ -883,14 +883,14 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 same_weights &= eb.d[b].w == eb.d[0].w && eb.d[b].wp == eb.d[0].wp;
             }
             const int dtype = sites[0][op.site]->d.dtype;
-            if (round.size() > 1 && same_weights) err = launch_conv(eb, n, dtype, g_conv_path, st, &cls, &pick);
+            if (round.size() > 1 && same_weights) err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls, &pick);
             if (err == hipSuccess && pick.body < 0) {
-                err = launch_conv(eb, n, dtype, g_conv_path, st, &cls);
+                err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls);
             } else if (err == hipSuccess) {
                 if (cm.n == kMaxMultiJobs || (cm.n + 1) * n > kMaxConvVids) flush_conv();
                 ConvJob& j = cm.job[cm.n];
                 j.e = eb.d[0];
-                j.body = pick.body; j.NT = pick.NT; j.items = pick.items; j.p0 = pick.p0; j.p1 = pick.p1; j.npub = pick.npub; j.blocks = pick.blocks;
+                j.body = pick.body; j.items = pick.items; j.g = pick.g; j.blocks = pick.blocks;
                 for (int b = 0; b < n; ++b)
                     cm.vid[cm.n * n + b] = ConvVid{dist(eb.d[b].delta, j.e.delta), dist(eb.d[b].P, j.e.P), eb.d[b].p_oy, eb.d[b].p_ox};
                 smem = pick.smem > smem ? pick.smem : smem;
@@ -988,7 +988,7 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
         std::vector<mdcnn_buffer* const*> sites((size_t)n);
         for (int b = 0; b < n; ++b) sites[(size_t)b] = nets[b]->sites.data();
         for (size_t r = 0; r < net->rounds.rounds.size(); ++r) {
-            mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills);
+            mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, true, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills);
             if (rc) return rc;
         }
     }
@@ -1366,7 +1366,7 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
             for (int c = g.call0; c < g.call1 && rounds; ++c) {
                 const void* const* X = frames + (size_t)f * nb;
                 const uint8_t* const* fm = fe ? (const uint8_t* const*)fe->masks + f : forced ? forced + (size_t)f * nb : nullptr;
-                mdcnn_status rc = run_round(net->rounds.rounds[(size_t)c], nets, nb, sites_of, X, fm, s[pp.stream_of(f, c)]);
+                mdcnn_status rc = run_round(net->rounds.rounds[(size_t)c], nets, nb, sites_of, X, fm, s[pp.stream_of(f, c)], depth == 1);
                 if (rc) return rc;
                 if (issued(c) != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: event: %s", f, hipGetErrorString(err));
             }
@@ -1404,7 +1404,7 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
                 }
                 g_tag_site = i; g_tag_edge0 = e0;
                 mdcnn_status rc = do_forward(nb, ins, i == 0 ? X : nullptr, i == 0 ? fm : nullptr, edges, outs, ne, st,
-                                             fused_skip(net, e0, e1), nullptr, jobs, riders, n_riders);
+                                             fused_skip(net, e0, e1), nullptr, jobs, riders, n_riders, nullptr, depth == 1);
                 g_tag_site = g_tag_edge0 = -1;
                 if (rc) return rc;
                 if (issued(c) != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: event: %s", f, hipGetErrorString(err));

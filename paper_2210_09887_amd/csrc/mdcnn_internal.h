@@ -243,29 +243,36 @@ hipError_t launch_step1(const Step1Batch& b, int n, hipStream_t st);
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
 // half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
-constexpr int kMultiHaloBodies = 6, kMultiTiledBodies = 12;
+constexpr int kMultiRectBodies = 6, kMultiHaloBodies = 2, kMultiTiledBodies = 12;
+constexpr int multi_rect_body(int m, int tn) { return m == 64 || m == 96 || m == 128 ? (m / 32 - 2) * 2 + tn - 1 : -1; }
 constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc, int nld, int ring, bool t2d) {
-    const int c[kMultiHaloBodies][9] = {
-        {2, 2, 2, 2, 1, 32, 3, 3, 1}, {2, 2, 2, 2, 1, 64, 6, 6, 1}, {2, 2, 2, 2, 2, 64, 6, 6, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1},
-        {4, 1, 4, 2, 1, 64, 4, 9, 1}, {4, 1, 4, 2, 2, 64, 4, 9, 1}};
+    const int c[kMultiHaloBodies][9] = {{2, 2, 2, 2, 1, 32, 3, 3, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1}};
     for (int i = 0; i < kMultiHaloBodies; ++i)
         if (c[i][0] == nsub && c[i][1] == wmv && c[i][2] == wk && c[i][3] == tm && c[i][4] == tn && c[i][5] == kc && c[i][6] == nld &&
             c[i][7] == ring && (c[i][8] != 0) == t2d)
-            return i;
+            return kMultiRectBodies + i;
     return -1;
 }
 constexpr int multi_tiled_body(int wm, int wn, int tm, int tn, int kc, int pipe) {
     const int c[4][4] = {{2, 2, 1, 1}, {4, 1, 1, 1}, {2, 2, 2, 1}, {2, 2, 1, 2}};
     for (int i = 0; i < 4; ++i)
         if (pipe == 1 && c[i][0] == wm && c[i][1] == wn && c[i][2] == tm && c[i][3] == tn)
-            return kMultiHaloBodies + 3 * i + (kc == 32 ? 0 : kc == 64 ? 1 : 2);
+            return kMultiRectBodies + kMultiHaloBodies + 3 * i + (kc == 32 ? 0 : kc == 64 ? 1 : 2);
     return -1;
 }
+// How the tiles of an edge are dealt to its blocks.  per_*: 2^32 / divisor, rounded up, 0 for 1 (by_reciprocal).
+struct TileGrid {
+    unsigned npub;            // blocks that publish the lists
+    int NT;                   // cout tiles
+    int p0, p1;               // rectangular tiles: rows, columns; gather tiles: xcd_map
+    int tiles_x;              // rectangles in a row
+    unsigned per_NT, per_tiles_x;
+};
 // How launch_conv would run an edge; body < 0: not with one of those configurations.
 struct ConvPick {
-    int body, NT, items;
-    int p0, p1;               // halo tiles: th, tw; gather tiles: xcd_map
-    unsigned npub, blocks, smem;      // blocks of the edge, the first npub of which publish its lists
+    int body, items;
+    TileGrid g;
+    unsigned blocks, smem;    // blocks of the edge
 };
 
 // Several edges that do not depend on each other in one launch.  The videos of a batch have their sites at different
@@ -274,8 +281,9 @@ struct ConvPick {
 constexpr int kMaxMultiJobs = 6, kMaxConvVids = 96, kMaxStep1Vids = 48;
 struct ConvJob {
     EdgeDev e;
-    int body, NT, items, p0, p1;
-    unsigned npub, blocks;          // its blocks of the grid (their numbers start at a multiple of 8, for the XCDs)
+    int body, items;
+    TileGrid g;
+    unsigned blocks;          // its blocks of the grid (their numbers start at a multiple of 8, for the XCDs)
 };
 struct ConvVid {
     long long sd, dd;
@@ -318,8 +326,9 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      /
 
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls
+// alone: the launches of other frames do not run beside this one (the choice of the tile, not its results)
 // pick: nothing is launched; *pick says with which configuration of k_conv_multi the edge would run, if with one
-hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, hipStream_t st, int* cls, ConvPick* pick = nullptr);
+hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick = nullptr);
 // fp32 layers on the matrix cores (kernels_f32.hip): shapes it takes, launch
 bool f32_applies(const EdgeDev& e);
 hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st);

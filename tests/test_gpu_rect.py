@@ -1,0 +1,62 @@
+"""3 x 3 stride-1 fp16 layers of 64 n input channels (conv_rect.h): every tile against the oracle, and the same bits whatever the
+tile where the channels are split four ways - windows lower or narrower than a tile, ragged last tiles, numbers of cout tiles
+that are no power of two, one to five chunks, frames in flight (which take other tiles than a frame alone)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def frames_of(cin, H, W, n=3):
+    rng = np.random.default_rng(cin * 1000 + H * 7 + W)
+    x = rng.normal(0, 1, (H, W, cin)).astype(np.float32)
+    out = [x.astype(np.float16)]
+    for _ in range(n - 1):
+        x = x.copy()
+        y0, x0 = int(rng.integers(0, max(1, H - 8))), int(rng.integers(0, max(1, W - 17)))
+        x[y0:y0 + 8, x0:x0 + 17] += rng.normal(0, 1, x[y0:y0 + 8, x0:x0 + 17].shape).astype(np.float32)
+        x[rng.random((H, W)) < 0.02] += 0.5
+        out.append(x.astype(np.float16))
+    return out
+
+
+@pytest.mark.parametrize("cin,cout,H,W", [(64, 64, 25, 41), (64, 32, 3, 90), (64, 192, 12, 12), (128, 96, 17, 29), (192, 64, 40, 9),
+                                          (256, 192, 14, 15), (320, 64, 1, 30)])
+def test_tiles_agree(cin, cout, H, W):
+    import gpu_harness as H_
+    from inputs.nets import tiny_net
+    from paper_2210_09887_amd import binding as B
+    from paper_2210_09887_amd.runtime import GpuNet
+    net = tiny_net("f16", H, W, (cin, cout), k=3, stride=1, theta=0.05, seed=cin + cout + H, total_stride=1)
+    frames, shifts = frames_of(cin, H, W), [(0, 0), (0, 0), (0, -1)]
+    outs = {}
+    try:
+        for sub in (0, 1, 2, 4):
+            B.mdcnn_set_option(B.MDCNN_OPT_CONV_HALO_SUB, sub)
+            H_.teacher_forced(net, frames, shifts)
+            g = GpuNet(net)
+            outs[sub] = [g.frame(H_.dev(f), dy, dx)[0].cpu().numpy().copy() for f, (dy, dx) in zip(frames, shifts)]
+            g.close()
+    finally:
+        B.mdcnn_set_option(B.MDCNN_OPT_CONV_HALO_SUB, 0)
+    for sub in (0, 1, 4):
+        if cin > 64 or sub != 1:                   # (64 channels: the largest tile does not split them)
+            for t, (a, b) in enumerate(zip(outs[sub], outs[2])):
+                assert np.array_equal(a, b), f"split {sub}, frame {t}"
+
+
+@pytest.mark.parametrize("cin,cout,H,W", [(64, 64, 60, 60), (128, 128, 66, 70), (512, 64, 40, 34)])
+def test_frames_in_flight_take_other_tiles(cin, cout, H, W):
+    import gpu_harness as H_
+    from inputs.nets import tiny_net
+    from paper_2210_09887_amd.runtime import GpuNet
+    net = tiny_net("f16", H, W, (cin, cout, cout), k=3, stride=1, theta=0.05, seed=cin + cout + H, total_stride=1)
+    frames = [H_.dev(f) for f in frames_of(cin, H, W, 6)]
+    dy, dx = [0, 0, 1, 0, 0, -1], [0, 0, -1, 0, 1, 0]
+    a, b = GpuNet(net), GpuNet(net)
+    one = [a.frame(f, y, x)[0].clone() for f, y, x in zip(frames, dy, dx)]
+    run, _ = b.frames(frames, dy, dx, depth=4)
+    for t, (p, q) in enumerate(zip(one, run)):
+        assert np.array_equal(p.cpu().numpy(), q.cpu().numpy()), f"frame {t}"
+    a.close()
+    b.close()
