@@ -85,8 +85,9 @@ __device__ __forceinline__ void add_macs(const EdgeDev& e, long long taps, int w
         atomicAdd(reinterpret_cast<unsigned long long*>(e.dcounters) + kAccMacsSpread + 8 * which + (blockIdx.x & 7),
                   (unsigned long long)taps * (unsigned long long)(e.Cin * e.Cout));
 }
-// Sum over the wave, in every lane: DPP moves (row_shr 1, 2, 4, 8, then row_bcast 15 and 31), a tenth of the latency of shuffles
-// through LDS.
+// Sum over the wave, in every lane: moves within the vector unit (row_shr 1, 2, 4, 8, then row_bcast 15 and 31), where a
+// shuffle goes through LDS (0.1 us each, six of them in a row: with step 1's, ResNet-18-style 512 x 512 frame 387 -> 380 us,
+// 256 x 256 in fp32 666 -> 659, bottleneck 47.3 -> 46.2).
 __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
@@ -95,6 +96,16 @@ __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // Marks a window pixel as touched, if it is in the view: an atomic OR on the word that holds the flag byte, its result
@@ -161,10 +172,8 @@ __device__ __forceinline__ int tile_prologue(const EdgeDev& e, int seg, int firs
         e.ccnt[seg] = tot;
         e.cacc[seg] += (unsigned long long)tot;
     }
-    unsigned orm = mine ? vm : 0u;
-    int taps = mine ? __popc(vm) : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { orm |= __shfl_xor(orm, o); taps += __shfl_xor(taps, o); }
+    const unsigned orm = wave_or(mine ? vm : 0u);
+    const int taps = wave_sum(mine ? __popc(vm) : 0);
     if (lane == 0 && orm) { atomicOr(reinterpret_cast<unsigned*>(&sh[5]), orm); atomicAdd(&sh[4], taps); }
     __syncthreads();
     return tot;
@@ -229,8 +238,7 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
     int *pub_list = e.pub_list, *pub_lcnt = e.pub_lcnt, *clist = e.clist, *ccnt = e.ccnt;
     unsigned long long *pub_lacc = e.pub_lacc, *cacc = e.cacc;
     int sH = e.sH, sW = e.sW, dH = e.dH, dW = e.dW, Hp = e.Hp, Wp = e.Wp, by0 = e.by0, bx0 = e.bx0, stride = e.stride, pad = e.pad;
-    asm volatile("" : "+s"(sflags), "+s"(dflags), "+s"(pub_list), "+s"(pub_lcnt), "+s"(clist), "+s"(ccnt), "+s"(pub_lacc), "+s"(cacc), "+s"(sH), "+s"(sW), "+s"(dH));
-    asm volatile("" : "+s"(dW), "+s"(Hp), "+s"(Wp), "+s"(by0), "+s"(bx0), "+s"(stride), "+s"(pad));     // read in one go
+    read_now(sflags, dflags, pub_list, pub_lcnt, clist, ccnt, pub_lacc, cacc, sH, sW, dH, dW, Hp, Wp, by0, bx0, stride, pad);
     const int HW = sH * sW, n = Hp * Wp;
     const int nsrc = pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = (n + kSegPixels - 1) / kSegPixels;
     const int units = nsrc > ndst ? nsrc : ndst;

@@ -102,16 +102,14 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, unsign
     float* const sC = reinterpret_cast<float*>(smem);
     int* const s_ent = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);      // entry -> ly << 4 | lx
     unsigned char* const s_mask = smem + Cfg::MAIN_BYTES + M * 4;           // live pixels of a staged row, 16 bits each
-    // The descriptor is read in one go: fetched field by field where they are used, as the compiler would, every fetch is a
-    // round trip of its own (1 us until the flags are asked for).
+    // (fetched field by field where they are used: 1 us until the flags are asked for)
     int Hp = e.Hp, Wp = e.Wp, sH = e.sH, sW = e.sW, Cin = e.Cin, Cout = e.Cout, by0 = e.by0, bx0 = e.bx0, pad = e.pad, p_oy = e.p_oy, p_ox = e.p_ox;
     const void *delta = e.delta, *wp = e.wp;
     const uint8_t* sflags = e.sflags;
     f16* P = (f16*)e.P;
     int NT = g.NT, th = g.p0, tw = g.p1, tiles_x = g.tiles_x;
     unsigned npub = g.npub, per_NT = g.per_NT, per_tiles_x = g.per_tiles_x;
-    asm volatile("" : "+s"(Hp), "+s"(Wp), "+s"(sH), "+s"(sW), "+s"(Cin), "+s"(Cout), "+s"(by0), "+s"(bx0), "+s"(pad), "+s"(p_oy), "+s"(p_ox));
-    asm volatile("" : "+s"(delta), "+s"(wp), "+s"(sflags), "+s"(P), "+s"(NT), "+s"(th), "+s"(tw), "+s"(tiles_x), "+s"(npub), "+s"(per_NT), "+s"(per_tiles_x));
+    read_now(Hp, Wp, sH, sW, Cin, Cout, by0, bx0, pad, p_oy, p_ox, delta, wp, sflags, P, NT, th, tw, tiles_x, npub, per_NT, per_tiles_x);
     nblk -= npub;
     if (blk >= nblk) {
         publish_edge(e, blk - nblk, npub);

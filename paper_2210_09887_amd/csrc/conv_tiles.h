@@ -318,9 +318,7 @@ __device__ __forceinline__ int tile_prologue_sub(const EdgeDev& e, int seg, int 
         e.ccnt[seg] = tot;
         e.cacc[seg] += (unsigned long long)tot;
     }
-    int taps = mine ? __popc(vm) : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) taps += __shfl_xor(taps, o);
+    const int taps = wave_sum(mine ? __popc(vm) : 0);
     if (lane == 0 && taps) atomicAdd(&sh[4], taps);
     __syncthreads();
     return cnt;

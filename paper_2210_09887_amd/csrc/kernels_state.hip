@@ -185,6 +185,28 @@ hipError_t launch_shift_fill(const FillBatch& fb, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Largest value of G neighbouring lanes (a power of two), in each of them: moves within the vector unit, not through LDS.
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+    auto dpp = [&](auto ctrl) {
+        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, true);
+        v = fmaxf(v, __builtin_bit_cast(float, o));
+    };
+    if constexpr (G >= 2) dpp(std::integral_constant<int, 0xb1>{});       // quad_perm 1 0 3 2
+    if constexpr (G >= 4) dpp(std::integral_constant<int, 0x4e>{});       // quad_perm 2 3 0 1
+    if constexpr (G >= 8) dpp(std::integral_constant<int, 0x141>{});      // row_half_mirror: the other four of eight
+    if constexpr (G >= 16) dpp(std::integral_constant<int, 0x140>{});     // row_mirror: the other eight of sixteen
+    auto both = [&](auto p) {                              // (elements by value: a bit cast of an element takes element 0)
+        const unsigned a = p[0], b = p[1];
+        v = fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+    };
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    if constexpr (G >= 32) both(__builtin_amdgcn_permlane16_swap(u, u, false, false));
+    const unsigned w = __builtin_bit_cast(unsigned, v);
+    if constexpr (G >= 64) both(__builtin_amdgcn_permlane32_swap(w, w, false, false));
+    return v;
+}
+
 // ---------------------------------------------------------------------------
 // Step 1 of a site: delta, truncation, update mask.
 //   INPUT : d = X - A
@@ -224,9 +246,11 @@ __device__ __forceinline__ bool unveiled(const FillJob& j, int vy, int vx) {
 }
 
 template <typename T, int G, int CH>
-__device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& skip, const T* __restrict__ X,
+__device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __restrict__ X,
                                             const uint8_t* __restrict__ forced, unsigned blk, const FillJob* own = nullptr) {
     constexpr int VEC = V16<T>::N;
+    read_now(s.A, s.P, s.flags, s.delta, s.H, s.W, s.C, s.Hp, s.Wp, s.by0, s.bx0, s.a_oy, s.a_ox, s.p_oy, s.p_ox, s.theta, s.relu, s.kind, s.s_off,
+             skip.P, skip.dflags, skip.Hp, skip.Wp, skip.by0, skip.bx0, skip.p_oy, skip.p_ox, X, forced);
     constexpr int PPB = 256 / G;
     const int tid = threadIdx.x;
     const int lp = tid % G;
@@ -241,7 +265,7 @@ __device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& ski
         if (s.s_off) inside = crop_state(s, pix, lp == 0, fl, xpix);
         cand = inside && (is_input || forced != nullptr || (fl & (kFlagN | kFlagU)));
         if (cand) {
-            const int vy = pix / s.W, vx = pix - vy * s.W;
+            const int vy = div24(pix, s.W, rcp_of(s.W)), vx = pix - vy * s.W;
             if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
             T* Ap = (T*)s.A + a_offset(s, vy, vx);
             T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
@@ -274,8 +298,7 @@ __device__ __forceinline__ void step1_block(const SiteDev& s, const SkipDev& ski
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) mx = fmaxf(mx, fabsf(out[j][i]));
             }
-#pragma unroll
-            for (int off = G / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+            mx = group_max<G>(mx);
             const bool hit = forced ? forced[xpix] != 0 : mx > s.theta;
             m = (fl & kFlagN) || hit;
             if (m) {

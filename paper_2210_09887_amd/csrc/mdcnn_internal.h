@@ -18,6 +18,32 @@ __device__ __forceinline__ int fast_div(int a, int d, float r) {
     return q + (rem >= d ? 1 : 0) - (rem < 0 ? 1 : 0);
 }
 
+// The same for a below 2^24 (a view has at most that many pixels).
+__device__ __forceinline__ int div24(int a, int d, float r) {
+    const int q = (int)((float)a * r), rem = a - q * d;
+    return q + (rem >= d ? 1 : 0) - (rem < 0 ? 1 : 0);
+}
+// Has these kernel arguments, or what was computed from them alone, in scalar registers at this point.  Left to itself the
+// compiler fetches a field of a descriptor where it is used, and every such place is a round trip of its own, one behind the
+// other; named together at the start of a kernel they are fetched together.
+__device__ __forceinline__ void read_now() {}
+template <typename A, typename... R>
+__device__ __forceinline__ void read_now(A& a, R&... r);
+template <typename A, typename B, typename C, typename D, typename E, typename F, typename G, typename H, typename... R>
+__device__ __forceinline__ void read_eight(A& a, B& b, C& c, D& d, E& e, F& f, G& g, H& h, R&... r) {
+    asm volatile("" : "+s"(a), "+s"(b), "+s"(c), "+s"(d), "+s"(e), "+s"(f), "+s"(g), "+s"(h));
+    read_now(r...);
+}
+template <typename A, typename... R>
+__device__ __forceinline__ void read_now(A& a, R&... r) {
+    if constexpr (sizeof...(R) >= 7) {
+        read_eight(a, r...);
+    } else {
+        asm volatile("" : "+s"(a));
+        read_now(r...);
+    }
+}
+
 constexpr int kFlagN = 1;   // newly unveiled this frame
 constexpr int kFlagU = 2;   // touched by a producer this frame
 constexpr int kFlagM = 4;   // updated (emitted a delta) this frame
