@@ -13,6 +13,19 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ int wrapc(int v, int n) { return v >= n ? v - n : v; }
 
+// Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a
+// scalar byte offset, so a wave spends one vector register on all the addresses of a tensor instead of a
+// 64-bit pointer per load (reads past `bytes` return zero instead of faulting).
+using rsrc_t = __amdgpu_buffer_rsrc_t;
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ f16x8 buf_load16(rsrc_t r, unsigned lane_bytes, unsigned wave_bytes) {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)wave_bytes, 0);
+    return __builtin_bit_cast(f16x8, v);
+}
+
 __device__ __forceinline__ size_t pdst_offset(const EdgeDev& e, int wy, int wx) {
     int py = wrapc(e.p_oy + wy, e.Hp), px = wrapc(e.p_ox + wx, e.Wp);
     return ((size_t)py * e.Wp + px) * e.Cout;
@@ -22,10 +35,11 @@ __device__ __forceinline__ size_t pdst_offset(const EdgeDev& e, int wy, int wx) 
 // frame and the top-left destination window pixel (wy, wx).
 __device__ __forceinline__ void decode_entry(const EdgeDev& e, int idx, int& cy, int& cx, int& wy, int& wx) {
     if (e.up) {                       // entry = updated source pixel (1x1 conv)
-        cy = idx / e.sW; cx = idx - cy * e.sW;
+        cy = div24(idx, e.sW, rcp_of(e.sW)); cx = idx - cy * e.sW;
         wy = (cy << e.up) + e.by0; wx = (cx << e.up) + e.bx0;
-    } else {                          // entry = destination padded-window pixel
-        wy = idx / e.Wp; wx = idx - wy * e.Wp;
+    } else {                          // entry = destination padded-window pixel (borders may take a window past 2^24 pixels)
+        wy = (long long)e.Hp * e.Wp < 1 << 24 ? div24(idx, e.Wp, rcp_of(e.Wp)) : idx / e.Wp;
+        wx = idx - wy * e.Wp;
         cy = wy - e.by0; cx = wx - e.bx0;
     }
 }
@@ -49,10 +63,37 @@ __device__ __forceinline__ unsigned tap_mask_k(const EdgeDev& e, int cy, int cx)
     return m;
 }
 
+// The same for three by three, a row of three flags at a time: one word, which need not be aligned and may start or end beyond
+// the flags of the site (the regions before and behind them in its memory; those bits are masked).  Rows outside the source
+// are read from beyond the end of everything, which gives zeros.
+struct Taps3 {
+    unsigned w[3], cols;              // flag M of the columns inside the source, a byte each
+};
+__device__ __forceinline__ rsrc_t taps3_rsrc(const uint8_t* sflags, int HW) { return make_rsrc(sflags - 4, (unsigned)HW + 7u); }
+__device__ __forceinline__ void taps3_load(rsrc_t rs, int sH, int sW, int iy, int ix, bool in, Taps3& t) {    // (iy, ix): the top left tap
+    t.cols = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) t.cols |= in && (unsigned)(ix + c) < (unsigned)sW ? (unsigned)kFlagM << (8 * c) : 0u;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        t.w[r] = __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)(iy + r) < (unsigned)sH && t.cols ? (iy + r) * sW + ix + 4 : (int)0x80000000u, 0, 0);
+}
+__device__ __forceinline__ unsigned tap_mask3(const EdgeDev& e, int cy, int cx) {
+    Taps3 t;
+    taps3_load(taps3_rsrc(e.sflags, e.sH * e.sW), e.sH, e.sW, cy * e.stride - e.pad, cx * e.stride - e.pad, true, t);
+    unsigned m = 0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const unsigned b = (t.w[r] & t.cols) >> 2;         // kFlagM == 4
+        m |= ((b | b >> 7 | b >> 14) & 7u) << (3 * r);
+    }
+    return m;
+}
+
 __device__ __forceinline__ unsigned tap_mask(const EdgeDev& e, int cy, int cx) {
     switch (e.k) {
         case 1: return tap_mask_k<1>(e, cy, cx);
-        case 3: return tap_mask_k<3>(e, cy, cx);
+        case 3: return tap_mask3(e, cy, cx);
         case 5: return tap_mask_k<5>(e, cy, cx);
         default: break;
     }
@@ -209,20 +250,7 @@ __device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* s
     __syncthreads();
 }
 
-// Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a
-// scalar byte offset, so a wave spends one vector register on all the addresses of a tensor instead of a
-// 64-bit pointer per load (reads past `bytes` return zero instead of faulting).
-using rsrc_t = __amdgpu_buffer_rsrc_t;
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ rsrc_t make_rsrc(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ f16x8 buf_load16(rsrc_t r, unsigned lane_bytes, unsigned wave_bytes) {
-    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, (int)wave_bytes, 0);
-    return __builtin_bit_cast(f16x8, v);
-}
-
-// By-products of a 3 x 3 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
+// By-products of a 3 x 3 or 1 x 1 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
 // the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
 // count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
 // its own and its loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K
@@ -237,19 +265,19 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
     uint8_t* dflags = e.dflags;
     int *pub_list = e.pub_list, *pub_lcnt = e.pub_lcnt, *clist = e.clist, *ccnt = e.ccnt;
     unsigned long long *pub_lacc = e.pub_lacc, *cacc = e.cacc;
-    int sH = e.sH, sW = e.sW, dH = e.dH, dW = e.dW, Hp = e.Hp, Wp = e.Wp, by0 = e.by0, bx0 = e.bx0, stride = e.stride, pad = e.pad;
-    read_now(sflags, dflags, pub_list, pub_lcnt, clist, ccnt, pub_lacc, cacc, sH, sW, dH, dW, Hp, Wp, by0, bx0, stride, pad);
+    int sH = e.sH, sW = e.sW, dH = e.dH, dW = e.dW, Hp = e.Hp, Wp = e.Wp, by0 = e.by0, bx0 = e.bx0, stride = e.stride, pad = e.pad, ks = e.k, up = e.up;
+    read_now(sflags, dflags, pub_list, pub_lcnt, clist, ccnt, pub_lacc, cacc, sH, sW, dH, dW, Hp, Wp, by0, bx0, stride, pad, ks, up);
     const int HW = sH * sW, n = Hp * Wp;
-    const int nsrc = pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = (n + kSegPixels - 1) / kSegPixels;
+    const int nsrc = pub_list ? (HW + kSegPixels - 1) / kSegPixels : 0, ndst = up ? 0 : (n + kSegPixels - 1) / kSegPixels;      // (an upsampling edge has no compute list, its tiles mark what they touch)
     const int units = nsrc > ndst ? nsrc : ndst;
     const float rw = rcp_of(Wp);
-    // Flags of the source from the word before the first on (whatever is there, it is masked); a row outside the source is read
-    // from beyond the end, which gives zeros, and so is a mark's byte outside the destination's view.
-    const rsrc_t frs = make_rsrc(sflags, (unsigned)HW), wrs = make_rsrc(sflags - 4, (unsigned)HW + 7u), mrs = make_rsrc(dflags, dflags ? (unsigned)(dH * dW) : 0u);
+    // (a mark's byte outside the destination's view is read from beyond the end and its store dropped)
+    const rsrc_t frs = make_rsrc(sflags, (unsigned)HW), wrs = taps3_rsrc(sflags, HW), mrs = make_rsrc(dflags, dflags ? (unsigned)(dH * dW) : 0u);
     constexpr unsigned kOutside = 0x80000000u;
     for (int s = (int)blk * 4 + wave; s < units; s += (int)nblk * 4) {
         const int p0 = s * kSegPixels + lane;
-        unsigned f[4], w[4][3], df[4], at[4], cols[4];         // at: the pixel's flag in the destination; cols: flag M of the columns in the source
+        unsigned f[4], df[4], at[4];                           // at: the pixel's flag in the destination
+        Taps3 w[4];
         unsigned long long lsum[2] = {0, 0}, csum = 0;
         if (s < nsrc) {
 #pragma unroll
@@ -267,12 +295,13 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
                 const int cy = ry + q - by0, cx = x - q * Wp - bx0;
                 const int iy = cy * stride - pad, ix = cx * stride - pad;
                 const bool in = p0 + k * 64 < n;
-                cols[k] = 0;
-#pragma unroll
-                for (int t = 0; t < 3; ++t) cols[k] |= in && (unsigned)(ix + t) < (unsigned)sW ? (unsigned)kFlagM << (8 * t) : 0u;
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-                    w[k][r] = __builtin_amdgcn_raw_buffer_load_b32(wrs, (unsigned)(iy + r) < (unsigned)sH && cols[k] ? (iy + r) * sW + ix + 4 : (int)kOutside, 0, 0);
+                if (ks == 3) {
+                    taps3_load(wrs, sH, sW, iy, ix, in, w[k]);
+                } else {
+                    w[k].cols = kFlagM;
+                    w[k].w[1] = w[k].w[2] = 0;
+                    w[k].w[0] = __builtin_amdgcn_raw_buffer_load_b8(frs, in && (unsigned)iy < (unsigned)sH && (unsigned)ix < (unsigned)sW ? iy * sW + ix : (int)kOutside, 0, 0);
+                }
                 at[k] = in && (unsigned)cy < (unsigned)dH && (unsigned)cx < (unsigned)dW ? (unsigned)(cy * dW + cx) : kOutside;
                 df[k] = __builtin_amdgcn_raw_buffer_load_b8(mrs, (int)at[k], 0, 0);
             }
@@ -301,8 +330,8 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
                 unsigned any = 0;
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
-                    any |= w[k][r] & cols[k];
-                    taps += __popc(w[k][r] & cols[k]);
+                    any |= w[k].w[r] & w[k].cols;
+                    taps += __popc(w[k].w[r] & w[k].cols);
                 }
                 const unsigned long long b = __ballot(any != 0);
                 if (any) {

@@ -54,9 +54,19 @@ __device__ __forceinline__ void map_tile(int u, int NT, int xcd_map, int& m, int
 // PIPE = 1: one LDS buffer, loads one step ahead (two barriers per step).
 // PIPE = 2: two LDS buffers and two register stages, loads two steps ahead
 //           (one barrier per step).
-// blk, nblk: this block's number among the blocks that work on the edge (the grid may hold blocks of other edges too).
+// blk, nblk: this block's number among the blocks that work on the edge (the grid may hold blocks of other edges too).  The last
+// g.npub of them make the by-products (1x1 and 3x3 layers; for others every tile makes them itself).
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
-__device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsigned nblk, int NT, int work_items, int xcd_map) {
+__device__ __forceinline__ void tiled_body(EdgeDev e, unsigned blk, unsigned nblk, TileGrid g, int work_items) {
+    int NT = g.NT, xcd_map = g.p0;
+    read_now(e.delta, e.sflags, e.sH, e.sW, e.Cin, e.P, e.dflags, e.dH, e.dW, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up,
+             NT, xcd_map, g.npub, work_items);
+    const bool published = e.k == 1 || e.k == 3;
+    nblk -= g.npub;
+    if (blk >= nblk) {
+        publish_edge(e, blk - nblk, g.npub);
+        return;
+    }
     using Cfg = TiledCfg<WM, WN, TM, TN, KC, PIPE>;
     constexpr int BM = Cfg::BM, BN = Cfg::BN, LDK = Cfg::LDK, LDC = Cfg::LDC, CPR = Cfg::CPR, TPS = Cfg::TPS;
     constexpr int NB = (BM * CPR + 255) / 256, NA = (BN * CPR + 255) / 256;
@@ -76,7 +86,7 @@ __device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsig
     const rsrc_t drs = make_rsrc(e.delta, (unsigned)e.sH * (unsigned)e.sW * (unsigned)e.Cin * 2u);
     const rsrc_t wrs = make_rsrc(e.w, (unsigned)(e.k * e.k) * (unsigned)e.Cin * (unsigned)e.Cout * 2u);
 
-    carry_source_compaction(e, sh, blk, nblk);
+    if (!published) carry_source_compaction(e, sh, blk, nblk);
 
     // The f x f pixels an entry of an upsampling edge adds to are dealt to f * f / 4 items, which all make the entry's sums
     // (a 1x1 convolution: a step or two): in one block they were up to 64 read-add-write round trips in a row (12 x 9 source
@@ -90,12 +100,12 @@ __device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsig
         const int seg = mt / TPS, first = (mt - seg * TPS) * BM;
         const int n0 = nt * BN;
         __syncthreads();                                  // previous tile is done with LDS
-        const int tot = tile_prologue(e, seg, first, BM, nt == 0 && first == 0 && !e.up, nt == 0 && !e.up,
+        const int tot = tile_prologue(e, seg, first, BM, nt == 0 && first == 0 && !e.up && !published, nt == 0 && !e.up && !published,
                                       s_base, s_wy, s_wx, s_vm, sh);
         const int live = tot - first < BM ? tot - first : BM;     // entries of this tile (block-uniform)
         if (live <= 0) continue;
         const unsigned tilemask = (unsigned)sh[5];
-        if (tid == 0 && nt == 0 && part == 0) add_macs(e, sh[4], 0);    // statistics: one atomic per tile
+        if (tid == 0 && nt == 0 && part == 0 && (e.up || !published)) add_macs(e, sh[4], 0);    // statistics: one atomic per tile
 
         f32x16 acc[TM][TN];
 #pragma unroll
@@ -448,7 +458,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
     unsigned warm = 0;
     if constexpr (T2D) {
         if (blk < npub) {
-            static_assert(KS == 3, "publish_edge reads rows of three");
+            static_assert(KS == 3, "publish_edge takes 3 x 3 and 1 x 1 edges");
             publish_edge(e, blk, npub);
             return;
         }

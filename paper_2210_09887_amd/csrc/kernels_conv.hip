@@ -35,8 +35,8 @@ namespace mdcnn {
 
 // One edge per launch (blockIdx.z: stream of the batch); the tiles are those of conv_tiles.h.
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
-__global__ __launch_bounds__(256) void k_conv_mfma_tiled(EdgeBatch eb, int NT, int work_items, int xcd_map) {
-    tiled_body<WM, WN, TM, TN, KC, PIPE>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, NT, work_items, xcd_map);
+__global__ __launch_bounds__(256) void k_conv_mfma_tiled(TileGrid g, unsigned blocks, int work_items, EdgeBatch eb) {
+    tiled_body<WM, WN, TM, TN, KC, PIPE>(eb.d[blockIdx.z], blockIdx.x, blocks, g, work_items);
 }
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
 __global__ __launch_bounds__(256, MINB_) void k_conv_halo(EdgeBatch eb, unsigned npub, int NT, int work_items, int th, int tw) {
@@ -993,8 +993,10 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
     const long long items = (xcd ? 8 * ((MT + 8 / NT - 1) / (8 / NT)) : MT * NT) * (e.up > 1 ? 1 << (2 * e.up - 2) : 1);
     unsigned g = cap_blocks(items, 4096);
     g = (g + 7u) & ~7u;                                    // whole rounds over the 8 XCDs
+    const TileGrid tg{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, NT, xcd, 0, 0, 0u, 0u};
+    g += tg.npub;
     if (pick) {
-        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), (int)items, TileGrid{0u, NT, xcd, 0, 0, 0u, 0u}, g, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), (int)items, tg, g, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_mfma_tiled<WM, WN, TM, TN, KC, PIPE>;
@@ -1005,7 +1007,7 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
         if (err != hipSuccess) { (void)hipGetLastError(); return err; }    // do not leave it for the next call to report
         attr_set.store(true, std::memory_order_release);
     }
-    kern<<<dim3(g, 1, nb), dim3(256), Cfg::SMEM, st>>>(eb, NT, (int)items, xcd);
+    kern<<<dim3(g, 1, nb), dim3(256), Cfg::SMEM, st>>>(tg, g, (int)items, eb);
     return hipGetLastError();
 }
 

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
         halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, jb.g.npub, NT, items, p0, p1);           \
         break;
 #define TILED(WM, WN, TM, TN, KC)                                                                                         \
-    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, NT, items, p0); break;
+    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, jb.g, items); break;
     switch (jb.body) {
         RECT(64, 1) RECT(64, 2) RECT(96, 1) RECT(96, 2) RECT(128, 1) RECT(128, 2)
         HALO(2, 2, 2, 2, 1, 32, 3, 3, true)

@@ -225,7 +225,8 @@ constexpr int kOpTruncFree = 3;
 // Blocks of a launch that publish the lists of an edge (publish_edge): a segment of either list per wave, at most `cap` blocks.
 inline unsigned publish_blocks(const EdgeDev& e, int cap = 128) {
     const long long nsrc = e.pub_list ? ((long long)e.sH * e.sW + kSegPixels - 1) / kSegPixels : 0;
-    const long long ndst = ((long long)e.Hp * e.Wp + kSegPixels - 1) / kSegPixels;
+    const long long ndst = e.up ? 0 : ((long long)e.Hp * e.Wp + kSegPixels - 1) / kSegPixels;
+    if (nsrc + ndst == 0) return 0;
     const long long b = ((nsrc > ndst ? nsrc : ndst) + 3) / 4;
     return (unsigned)(b < 1 ? 1 : b > cap ? cap : b);
 }
