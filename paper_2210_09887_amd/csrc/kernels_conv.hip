@@ -1027,8 +1027,10 @@ static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_ent
     auto blocks = [&](int bm, int bn) { return ((max_entries + bm - 1) / bm) * (e.Cout / bn); };
     int tile = g_tile;
     if (tile == 0) {
-        // the largest tile that still yields about one block per compute unit
-        const long long want = 224;
+        // the largest tile that still yields about one block per compute unit; a 1x1 edge that shares its launch leaves the
+        // places to the other one (two blocks to a compute unit, and a block more than that starts when the first are done:
+        // 3x3 and 1x1, 64 -> 128 channels on 130 x 130 pixels, 536 blocks 18.0 us, 403 blocks 16.0)
+        const long long want = pick && e.k == 1 ? 112 : 224;
         if (e.Cout % 128 == 0 && blocks(128, 128) >= want) tile = 4;
         else if (e.Cout % 128 == 0 && blocks(64, 128) >= want) tile = 5;
         else if (e.Cout % 64 == 0) tile = blocks(256, 64) >= want ? 1 : blocks(128, 64) >= want ? 2 : 3;
@@ -1196,7 +1198,8 @@ static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream
             const int px = 64 + 32 * i;
             const double per_cu = (double)(of[i] * nb * (alone ? 1 : 4)) / 256;
             const bool full = per_cu > 2;
-            const double cost = (full ? per_cu : per_cu <= 1 ? 1 : 2) * ((double)px * (e.Cin + 78) + (full ? 12500 : px == 160 ? 8000 : 0));
+            double cost = (full ? per_cu : per_cu <= 1 ? 1 : 2) * ((double)px * (e.Cin + 78) + (full ? 12500 : px == 160 ? 8000 : 0));
+            if (pick && of[i] * nb > 352) cost *= 1.4;     // beside the blocks of other edges: some would wait for a place
             if (m == 0 || cost <= best) { best = cost; m = px; }
         }
     }

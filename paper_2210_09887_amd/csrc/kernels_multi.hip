@@ -41,6 +41,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
         TILED(4, 1, 1, 1, 32) TILED(4, 1, 1, 1, 64) TILED(4, 1, 1, 1, 128)
         TILED(2, 2, 2, 1, 32) TILED(2, 2, 2, 1, 64) TILED(2, 2, 2, 1, 128)
         TILED(2, 2, 1, 2, 32) TILED(2, 2, 1, 2, 64) TILED(2, 2, 1, 2, 128)
+        TILED(2, 2, 2, 2, 32) TILED(2, 2, 2, 2, 64) TILED(2, 2, 2, 2, 128)
         default: break;
     }
 #undef RECT

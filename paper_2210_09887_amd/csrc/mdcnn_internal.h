@@ -270,7 +270,7 @@ hipError_t launch_step1(const Step1Batch& b, int n, hipStream_t st);
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
 // half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
-constexpr int kMultiRectBodies = 6, kMultiHaloBodies = 2, kMultiTiledBodies = 12;
+constexpr int kMultiRectBodies = 6, kMultiHaloBodies = 2, kMultiTiledBodies = 15;
 constexpr int multi_rect_body(int m, int tn) { return m == 64 || m == 96 || m == 128 ? (m / 32 - 2) * 2 + tn - 1 : -1; }
 constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc, int nld, int ring, bool t2d) {
     const int c[kMultiHaloBodies][9] = {{2, 2, 2, 2, 1, 32, 3, 3, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1}};
@@ -281,8 +281,8 @@ constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc,
     return -1;
 }
 constexpr int multi_tiled_body(int wm, int wn, int tm, int tn, int kc, int pipe) {
-    const int c[4][4] = {{2, 2, 1, 1}, {4, 1, 1, 1}, {2, 2, 2, 1}, {2, 2, 1, 2}};
-    for (int i = 0; i < 4; ++i)
+    const int c[5][4] = {{2, 2, 1, 1}, {4, 1, 1, 1}, {2, 2, 2, 1}, {2, 2, 1, 2}, {2, 2, 2, 2}};
+    for (int i = 0; i < 5; ++i)
         if (pipe == 1 && c[i][0] == wm && c[i][1] == wn && c[i][2] == tm && c[i][3] == tn)
             return kMultiRectBodies + kMultiHaloBodies + 3 * i + (kc == 32 ? 0 : kc == 64 ? 1 : 2);
     return -1;
