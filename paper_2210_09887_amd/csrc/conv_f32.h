@@ -59,7 +59,7 @@ constexpr unsigned kBeyond = 0x80000000u;            // a byte offset past every
 // Tile with top left index-space pixel (y0, x0) - the padded window, or the source view of an upsampling edge - and first
 // cout n0.  Block-uniform; called by all 256 threads; smem: kF32Smem floats, s_vm: kF32Px words, s_or: 4 words.  The caller
 // has a barrier before the call.
-__device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int th, int tw, int n0, float* smem, unsigned* s_vm, unsigned* s_or) {
+__device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int th, int tw, int n0, bool published, float* smem, unsigned* s_vm, unsigned* s_or) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
@@ -183,7 +183,7 @@ __device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int t
                 }
         }
     }
-    if (n0 == 0 && wave == 0) {                                  // by the first cout tile: touched marks, statistics
+    if (n0 == 0 && wave == 0 && !published) {                    // by the first cout tile: touched marks, statistics
         const unsigned m = tid < kF32Px ? s_vm[tid] : 0u;
         if (m) {
             int iy, ix;

@@ -282,8 +282,14 @@ __global__ __launch_bounds__(256) void k_conv_ldsw(EdgeBatch eb, int groups, int
 // has no branches.
 // ---------------------------------------------------------------------------
 template <int KK, int CIN, int KS>
-__global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
-    const EdgeDev& e = eb.d[blockIdx.z];                  // blockIdx.z: stream of the batch
+__global__ __launch_bounds__(256) void k_conv_mfma_f32(unsigned npub, unsigned blocks, EdgeBatch eb) {
+    EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
+    const unsigned nblk = blocks - npub;
+    if (blockIdx.x >= nblk) {
+        if (blockIdx.y == 0) publish_edge(e, blockIdx.x - nblk, npub);
+        return;
+    }
+    read_now(e.delta, e.sflags, e.sH, e.sW, e.P, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up, e.op);
     extern __shared__ __align__(16) unsigned char smem[];
     float* sW = reinterpret_cast<float*>(smem);             // [tap][CIN][32]
     constexpr int TAPS = KK * KK, HALF = CIN / 2, NP = HALF / 4, PGS = 4 / KS, BM = PGS * 32, NQ = (TAPS + KS - 1) / KS;
@@ -299,7 +305,6 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
     const int nt = blockIdx.y;                              // cout tile
     const int ncout = e.Cout - nt * 32 < 32 ? e.Cout - nt * 32 : 32;      // 16 for a 16-cout layer: the other rows of the tile are not stored
     const float* __restrict__ w = (const float*)e.w;
-    carry_source_compaction(e, sh);
     // weights [tap][cout][cin] -> LDS [tap][cin][32], eight 16-byte reads of a thread in flight.  The first eight are
     // requested here and stored after the prologue of the block's first tile, whose flag reads they travel with.
     constexpr int pieces = CIN / 4, WU = 8, wtotal = TAPS * pieces * 32;
@@ -331,13 +336,12 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
     request(tid, raw0, dst0);
     bool weights_in = false;
     const rsrc_t drs = make_rsrc(e.delta, (unsigned)e.sH * (unsigned)e.sW * (unsigned)CIN * 4u);
-    long long block_taps = 0;                               // statistics (thread 0 of the blocks of cout tile 0)
     constexpr int TPS = kSegPixels / BM;                    // tiles per segment
     const int MT = edge_segments(e) * TPS;
-    for (int tile = blockIdx.x; tile < MT; tile += gridDim.x) {
+    for (int tile = blockIdx.x; tile < MT; tile += (int)nblk) {
         const int seg = tile / TPS, first = (tile - seg * TPS) * BM;
         __syncthreads();
-        const int tot = tile_prologue(e, seg, first, BM, nt == 0 && first == 0, nt == 0, s_base, s_wy, s_wx, s_vm, sh);
+        const int tot = tile_prologue(e, seg, first, BM, false, false, s_base, s_wy, s_wx, s_vm, sh);
         if (!weights_in) {                                  // first tile of the block (block-uniform)
             store(raw0, dst0);
             for (int i0 = tid + 256 * WU; i0 < wtotal; i0 += 256 * WU) {
@@ -350,7 +354,6 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
             __syncthreads();
         }
         if (first >= tot) continue;                         // block-uniform
-        if (tid == 0 && nt == 0) block_taps += sh[4];
         const bool wave_on = first + pg * 32 < tot;         // wave-uniform: the group has entries
         const int pl = pg * 32 + p32;
         const bool act = first + pl < tot;
@@ -417,7 +420,6 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
             }
         }
     }
-    if (tid == 0) add_macs(e, block_taps, 0);               // statistics: one atomic per block
 }
 
 // ---------------------------------------------------------------------------
@@ -440,13 +442,14 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(EdgeBatch eb) {
 // whole rows has half the blocks and is slower: 15.9 us, 33 on the boxes.)
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void k_conv_stem_mfma(EdgeBatch eb, unsigned npub) {
-    const EdgeDev& e = eb.d[blockIdx.z];                  // blockIdx.z: stream of the batch
-    const unsigned nblk = gridDim.x - npub;
+__global__ __launch_bounds__(256) void k_conv_stem_mfma(unsigned npub, unsigned blocks, EdgeBatch eb) {
+    EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
+    const unsigned nblk = blocks - npub;
     if (blockIdx.x >= nblk) {
         if (blockIdx.y == 0) publish_edge(e, blockIdx.x - nblk, npub);
         return;
     }
+    read_now(e.delta, e.sflags, e.sH, e.sW, e.P, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up, e.op);
     constexpr int BM = 128, KH = 14;
     __shared__ float sW[2 * KH * 32];                       // [k][32 couts], row 27 zero
     __shared__ int s_base[BM], s_wy[BM], s_wx[BM];
@@ -1347,8 +1350,8 @@ static hipError_t launch_mfma_f32_inst(const EdgeBatch& eb, int nb, long long ns
     const long long tiles = nseg * (kSegPixels / (32 * (4 / KS)));
     // weights are staged once per block: a bounded number of persistent blocks
     const long long cap = (smem > 49152 ? 512 : 1024) / nts;
-    const unsigned g = cap_blocks(tiles, cap > 0 ? cap : 1);
-    kern<<<dim3(g, nts, nb), dim3(256), smem, st>>>(eb);
+    const unsigned npub = publish_blocks(e), g = cap_blocks(tiles, cap > 0 ? cap : 1) + npub;
+    kern<<<dim3(g, nts, nb), dim3(256), smem, st>>>(npub, g, eb);
     return hipGetLastError();
 }
 template <int KK, int CIN>
@@ -1464,8 +1467,8 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bo
         (long long)e.sH * e.sW * 3 < (1ll << 29)) {
         *cls = kClsConvMfma;
         const unsigned npub = publish_blocks(e, 512), g = cap_blocks(nseg * (kSegPixels / 128), 2048) + npub;
-        if (dtype == MDCNN_F16) k_conv_stem_mfma<f16><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb, npub);
-        else k_conv_stem_mfma<float><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(eb, npub);
+        if (dtype == MDCNN_F16) k_conv_stem_mfma<f16><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(npub, g, eb);
+        else k_conv_stem_mfma<float><<<dim3(g, e.Cout / 32, nb), dim3(256), 0, st>>>(npub, g, eb);
         return hipGetLastError();
     }
     *cls = kClsConvPlain;

@@ -3,19 +3,27 @@
 
 namespace mdcnn {
 
-__global__ __launch_bounds__(256, 2) void k_conv_f32(EdgeBatch eb, int NT, int tiles_x, int tiles, int th, int tw) {
-    const EdgeDev& e = eb.d[blockIdx.z];                  // blockIdx.z: stream of the batch
+__global__ __launch_bounds__(256, 2) void k_conv_f32(TileGrid g, int tiles, unsigned blocks, EdgeBatch eb) {
+    EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
     __shared__ __align__(16) float smem[kF32Smem];
     __shared__ unsigned s_vm[kF32Px], s_or[4];
     __shared__ int sh[8];
-    const int nseg = e.up ? 0 : edge_segments(e);         // (an upsampling edge publishes no compute list)
-    for (int u = blockIdx.x; u < tiles * NT; u += gridDim.x) {
-        const int nt = u % NT, mt = u / NT, ty = mt / tiles_x, tx = mt - ty * tiles_x;
-        __syncthreads();                                  // previous tile is done with LDS
-        f32_tile(e, ty * th, tx * tw, th, tw, nt * kF32Co, smem, s_vm, s_or);
-        if (nt == 0 && mt < nseg) publish_segment(e, mt, sh);      // (there are at least as many tiles as segments)
+    const unsigned nblk = blocks - g.npub;
+    if (blockIdx.x >= nblk) {
+        publish_edge(e, blockIdx.x - nblk, g.npub);
+        return;
     }
-    carry_source_compaction(e, sh);
+    read_now(e.delta, e.sflags, e.sH, e.sW, e.Cin, e.P, e.dflags, e.dH, e.dW, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up);
+    const bool published = (e.k == 1 || e.k == 3) && !e.up;      // by blocks of their own (the source's list: whenever k is 1 or 3)
+    const int nseg = e.up ? 0 : edge_segments(e);         // (an upsampling edge publishes no compute list)
+    for (int u = (int)blockIdx.x; u < tiles * g.NT; u += (int)nblk) {
+        const int mt = fast_div(u, g.NT, rcp_of(g.NT)), nt = u - mt * g.NT, ty = fast_div(mt, g.tiles_x, rcp_of(g.tiles_x)), tx = mt - ty * g.tiles_x;
+        __syncthreads();                                  // previous tile is done with LDS
+        f32_tile(e, __builtin_amdgcn_readfirstlane(ty * g.p0), __builtin_amdgcn_readfirstlane(tx * g.p1), g.p0, g.p1, __builtin_amdgcn_readfirstlane(nt * kF32Co),
+                 published, smem, s_vm, s_or);
+        if (nt == 0 && mt < nseg && !published) publish_segment(e, mt, sh);      // (there are at least as many tiles as segments)
+    }
+    if (e.k != 1 && e.k != 3) carry_source_compaction(e, sh, blockIdx.x, nblk);
 }
 
 hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st) {
@@ -25,7 +33,9 @@ hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st) {
     long long tiles = 0;
     if (!tile_2d(ih, iw, 1, kF32Px, kF32Px, &th, &tw, &tiles)) return hipErrorInvalidValue;     // (never: one pixel always fits)
     const long long items = tiles * NT;
-    k_conv_f32<<<dim3((unsigned)(items < 16384 ? items : 16384), 1, nb), dim3(256), 0, st>>>(eb, NT, (iw + tw - 1) / tw, (int)tiles, th, tw);
+    const TileGrid g{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, NT, th, tw, (iw + tw - 1) / tw, 0u, 0u};
+    const unsigned blocks = (unsigned)(items < 16384 ? items : 16384) + g.npub;
+    k_conv_f32<<<dim3(blocks, 1, nb), dim3(256), 0, st>>>(g, (int)tiles, blocks, eb);
     return hipGetLastError();
 }
 
