@@ -350,4 +350,45 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
     }
 }
 
+// Readout within the last edge into an OUTPUT site: a tile writes f(P) of the entries it updates as it updates them, blocks of
+// their own copy the pixels of the view that it leaves alone.  A launch of its own would wait for the tiles: 64 x 64
+// convolution 15.0 -> 11.6 us, bottleneck 45.9 -> 43.8, five-layer network 60.8 -> 58.3.
+template <typename T, int N>
+__device__ __forceinline__ void write_out(T* out, int relu, size_t at, const T* v) {
+    T o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = relu ? (T)fmaxf((float)v[i], 0.f) : v[i];
+    __builtin_memcpy(out + at, o, N * sizeof(T));
+}
+// s_live: 256 bytes of LDS
+template <typename T>
+__device__ __forceinline__ void read_rest(const EdgeDev& e, unsigned blk, unsigned char* s_live) {
+    constexpr int VEC = 16 / (int)sizeof(T);
+    const int pieces = e.Cout / VEC, ppb = copy_pixels(pieces), first = (int)blk * ppb, tid = threadIdx.x;
+    const int n = e.dH * e.dW - first < ppb ? e.dH * e.dW - first : ppb;
+    const float rw = rcp_of(e.dW), rp = rcp_of(pieces);
+    if (tid < n) {
+        const int oy = div24(first + tid, e.dW, rw);
+        s_live[tid] = tap_mask(e, oy, first + tid - oy * e.dW) != 0;       // (the view is where the convolution's output coordinates start)
+    }
+    __syncthreads();
+    const T* const P = (const T*)e.P;
+    T* const out = (T*)e.dY;
+#pragma unroll 8
+    for (int i = tid; i < n * pieces; i += 256) {
+        const int p = div24(i, pieces, rp), c0 = (i - p * pieces) * VEC, pix = first + p;
+        const int oy = div24(pix, e.dW, rw), ox = pix - oy * e.dW;
+        T v[VEC];
+        __builtin_memcpy(v, P + pdst_offset(e, oy + e.by0, ox + e.bx0) + c0, 16);
+        if (!s_live[p]) write_out<T, VEC>(out, e.s_relu, (size_t)pix * e.Cout + c0, v);
+    }
+}
+
+// What the blocks behind an edge's tiles do: [0, npub) publish, the rest read out.
+template <typename T>
+__device__ __forceinline__ void side_block(const EdgeDev& e, const TileGrid& g, unsigned blk, unsigned char* s_live) {
+    if (blk < g.npub) publish_edge(e, blk, g.npub);
+    else read_rest<T>(e, blk - g.npub, s_live);
+}
+
 }  // namespace mdcnn

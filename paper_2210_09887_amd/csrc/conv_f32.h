@@ -43,12 +43,12 @@ struct Px8 {
 #pragma unroll
         for (int i = 0; i < 2; ++i) r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 16u * i), 0, 0);
     }
-    __device__ __forceinline__ void add_store(rsrc_t rs, unsigned off, const float* v) {
+    __device__ __forceinline__ void add_store(rsrc_t rs, unsigned off, float* v) {      // v becomes what is stored
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             f32x4 o = __builtin_bit_cast(f32x4, r[i]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[q] += v[4 * i + q];
+            for (int q = 0; q < 4; ++q) v[4 * i + q] = o[q] += v[4 * i + q];
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), rs, (int)(off + 16u * i), 0, 0);
         }
     }
@@ -172,6 +172,11 @@ __device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int t
         }
         if (!e.up) {
             pold.add_store(prs, poff, v);
+            if (e.dY) {                                          // (the launch reads the site out)
+                const int oy = wy - e.by0, ox = wx - e.bx0;
+                if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
+                    write_out<float, 8>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, v);
+            }
         } else {
             const int f = 1 << e.up;
             for (int a = 0; a < f; ++a)
@@ -179,7 +184,10 @@ __device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int t
                     const unsigned off = (unsigned)(pdst_offset(e, wy + a, wx + b) + (size_t)(n0 + c8)) * 4u;
                     Px8 o;
                     o.load(prs, off);
-                    o.add_store(prs, off, v);
+                    float s[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) s[k] = v[k];
+                    o.add_store(prs, off, s);
                 }
         }
     }

@@ -93,9 +93,9 @@ struct RectTiles {
     using T256 = RectCfg<4, 1, 2, TN, 10, 6, 2, 2, 1>;       // 64 input channels only
 };
 
-// (blk, nblk: this block's number among those of the edge)
-template <typename Cfg>
-__device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, unsigned nblk, const TileGrid& g) {
+// blk: the tile.  READ: the launch may read the destination out (EdgeDev::dY).
+template <typename Cfg, bool READ>
+__device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const TileGrid& g) {
     constexpr int WMV = Cfg::WMV, WK = Cfg::WK, TM = Cfg::TM, TN = Cfg::TN, NLD = Cfg::NLD, MB = Cfg::MB, NS = Cfg::NS, D = Cfg::RING,
                   M = Cfg::M, BN = Cfg::BN, LDC = Cfg::LDC, PT = Cfg::PT;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -106,15 +106,12 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, unsign
     int Hp = e.Hp, Wp = e.Wp, sH = e.sH, sW = e.sW, Cin = e.Cin, Cout = e.Cout, by0 = e.by0, bx0 = e.bx0, pad = e.pad, p_oy = e.p_oy, p_ox = e.p_ox;
     const void *delta = e.delta, *wp = e.wp;
     const uint8_t* sflags = e.sflags;
-    f16* P = (f16*)e.P;
+    f16 *P = (f16*)e.P, *out_p = (f16*)e.dY;
+    int dH = e.dH, dW = e.dW, relu = e.s_relu;
     int NT = g.NT, th = g.p0, tw = g.p1, tiles_x = g.tiles_x;
-    unsigned npub = g.npub, per_NT = g.per_NT, per_tiles_x = g.per_tiles_x;
-    read_now(Hp, Wp, sH, sW, Cin, Cout, by0, bx0, pad, p_oy, p_ox, delta, wp, sflags, P, NT, th, tw, tiles_x, npub, per_NT, per_tiles_x);
-    nblk -= npub;
-    if (blk >= nblk) {
-        publish_edge(e, blk - nblk, npub);
-        return;
-    }
+    unsigned per_NT = g.per_NT, per_tiles_x = g.per_tiles_x;
+    read_now(Hp, Wp, sH, sW, Cin, Cout, by0, bx0, pad, p_oy, p_ox, delta, wp, sflags, P, NT, th, tw, tiles_x, per_NT, per_tiles_x);
+    if constexpr (READ) read_now(out_p, dH, dW, relu);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WMV, wk = wave / WMV;
@@ -320,6 +317,11 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, unsign
 #pragma unroll
                 for (int c = 0; c < 8; ++c) o[c] = (f16)((float)o[c] + v[c]);
                 *reinterpret_cast<f16x8*>(pp[t]) = o;
+                if (READ && out_p) {                  // (the launch reads the site out)
+                    const int en = s_ent[at], oy = wy0 + (en >> 4) - by0, ox = wx0 + (en & 15) - bx0;
+                    if ((unsigned)oy < (unsigned)dH && (unsigned)ox < (unsigned)dW)
+                        write_out<f16, 8>(out_p, relu, ((size_t)oy * dW + ox) * Cout + n0 + c8, reinterpret_cast<const f16*>(&o));
+                }
             }
         }
     }

@@ -54,19 +54,14 @@ __device__ __forceinline__ void map_tile(int u, int NT, int xcd_map, int& m, int
 // PIPE = 1: one LDS buffer, loads one step ahead (two barriers per step).
 // PIPE = 2: two LDS buffers and two register stages, loads two steps ahead
 //           (one barrier per step).
-// blk, nblk: this block's number among the blocks that work on the edge (the grid may hold blocks of other edges too).  The last
-// g.npub of them make the by-products (1x1 and 3x3 layers; for others every tile makes them itself).
-template <int WM, int WN, int TM, int TN, int KC, int PIPE>
+// blk, nblk: this block's number among the blocks that work on tiles of the edge.  Others make the by-products (1x1 and 3x3
+// layers; for others every tile makes them itself).  READ: the launch may read the destination out (EdgeDev::dY).
+template <int WM, int WN, int TM, int TN, int KC, int PIPE, bool READ>
 __device__ __forceinline__ void tiled_body(EdgeDev e, unsigned blk, unsigned nblk, TileGrid g, int work_items) {
     int NT = g.NT, xcd_map = g.p0;
     read_now(e.delta, e.sflags, e.sH, e.sW, e.Cin, e.P, e.dflags, e.dH, e.dW, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up,
-             NT, xcd_map, g.npub, work_items);
+             NT, xcd_map, work_items);
     const bool published = e.k == 1 || e.k == 3;
-    nblk -= g.npub;
-    if (blk >= nblk) {
-        publish_edge(e, blk - nblk, g.npub);
-        return;
-    }
     using Cfg = TiledCfg<WM, WN, TM, TN, KC, PIPE>;
     constexpr int BM = Cfg::BM, BN = Cfg::BN, LDK = Cfg::LDK, LDC = Cfg::LDC, CPR = Cfg::CPR, TPS = Cfg::TPS;
     constexpr int NB = (BM * CPR + 255) / 256, NA = (BN * CPR + 255) / 256;
@@ -263,6 +258,11 @@ __device__ __forceinline__ void tiled_body(EdgeDev e, unsigned blk, unsigned nbl
 #pragma unroll
                     for (int q = 0; q < 8; ++q) o[q] = (f16)((float)o[q] + v[q]);
                     *reinterpret_cast<f16x8*>(pp[t]) = o;
+                    if (READ && e.dY) {                     // (the launch reads the site out)
+                        const int oy = s_wy[row] - e.by0, ox = s_wx[row] - e.bx0;
+                        if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
+                            write_out<f16, 8>((f16*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, reinterpret_cast<const f16*>(&o));
+                    }
                 }
             }
             continue;
@@ -426,7 +426,7 @@ struct HaloCfg {
 // T2D: the tiles are th x tw rectangles of the padded window (th * tw <= SUB) instead of index ranges: the staged rectangle
 // is the tile plus its KS - 1 halo whatever the width of the window, so wide rows fit and narrow ones stage less.
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
-__device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsigned nblk, unsigned npub, int NT, int work_items, int th, int tw) {
+__device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsigned nblk, int NT, int work_items, int th, int tw) {
     using Cfg = HaloCfg<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_>;
     constexpr int SUB = Cfg::SUB, BN = Cfg::BN, KB = Cfg::KB, MB = Cfg::MB, NS = Cfg::NS, CPR = Cfg::CPR, NLD = Cfg::NLD,
                   LDK = Cfg::LDK, LDC = Cfg::LDC;
@@ -457,13 +457,7 @@ __device__ __forceinline__ void halo_body(const EdgeDev& e, unsigned blk, unsign
 
     unsigned warm = 0;
     if constexpr (T2D) {
-        if (blk < npub) {
-            static_assert(KS == 3, "publish_edge takes 3 x 3 and 1 x 1 edges");
-            publish_edge(e, blk, npub);
-            return;
-        }
-        blk -= npub;
-        nblk -= npub;
+        static_assert(KS == 3, "what publish_edge takes: 3 x 3 and 1 x 1 edges");
         // the blocks of a cout tile touch that tile's weights, a line each, before anything else: the fragments of the
         // K loop then come from the L2 of their XCD instead of following each other to memory
         if constexpr (!EARLY) {

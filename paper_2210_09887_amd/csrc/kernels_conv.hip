@@ -36,16 +36,24 @@ namespace mdcnn {
 // One edge per launch (blockIdx.z: stream of the batch); the tiles are those of conv_tiles.h.
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
 __global__ __launch_bounds__(256) void k_conv_mfma_tiled(TileGrid g, unsigned blocks, int work_items, EdgeBatch eb) {
-    tiled_body<WM, WN, TM, TN, KC, PIPE>(eb.d[blockIdx.z], blockIdx.x, blocks, g, work_items);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned nblk = blocks - g.npub - g.ncopy;
+    if (blockIdx.x >= nblk) side_block<f16>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
+    else tiled_body<WM, WN, TM, TN, KC, PIPE, true>(eb.d[blockIdx.z], blockIdx.x, nblk, g, work_items);
 }
 template <int NSUB, int WMV, int WK, int TM, int TN, int KC, int NLD_, int KS, int RING_ = 3, int MINB_ = (NSUB >= 2 ? 2 : 1), bool T2D = false>
 __global__ __launch_bounds__(256, MINB_) void k_conv_halo(EdgeBatch eb, unsigned npub, int NT, int work_items, int th, int tw) {
-    halo_body<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_, T2D>(eb.d[blockIdx.z], blockIdx.x, gridDim.x, npub, NT, work_items, th, tw);
+    const unsigned nblk = gridDim.x - npub;
+    if (blockIdx.x >= nblk) publish_edge(eb.d[blockIdx.z], blockIdx.x - nblk, npub);
+    else halo_body<NSUB, WMV, WK, TM, TN, KC, NLD_, KS, RING_, MINB_, T2D>(eb.d[blockIdx.z], blockIdx.x, nblk, NT, work_items, th, tw);
 }
 
 template <typename Cfg>
 __global__ __launch_bounds__(256, Cfg::MINB) void k_conv_rect(TileGrid g, unsigned blocks, EdgeBatch eb) {
-    rect_body<Cfg>(eb.d[blockIdx.z], blockIdx.x, blocks, g);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned nblk = blocks - g.npub - g.ncopy;
+    if (blockIdx.x >= nblk) side_block<f16>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
+    else rect_body<Cfg, true>(eb.d[blockIdx.z], blockIdx.x, g);
 }
 
 // Weights [tap][cout][cin] -> [tap][cin/16][cout][16]: the 32 couts x 16 cin
@@ -282,15 +290,15 @@ __global__ __launch_bounds__(256) void k_conv_ldsw(EdgeBatch eb, int groups, int
 // has no branches.
 // ---------------------------------------------------------------------------
 template <int KK, int CIN, int KS>
-__global__ __launch_bounds__(256) void k_conv_mfma_f32(unsigned npub, unsigned blocks, EdgeBatch eb) {
+__global__ __launch_bounds__(256) void k_conv_mfma_f32(unsigned npub, unsigned ncopy, unsigned blocks, EdgeBatch eb) {
     EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
-    const unsigned nblk = blocks - npub;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned nblk = blocks - npub - ncopy;
     if (blockIdx.x >= nblk) {
-        if (blockIdx.y == 0) publish_edge(e, blockIdx.x - nblk, npub);
+        if (blockIdx.y == 0) side_block<float>(e, TileGrid{npub, ncopy}, blockIdx.x - nblk, smem);
         return;
     }
     read_now(e.delta, e.sflags, e.sH, e.sW, e.P, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up, e.op);
-    extern __shared__ __align__(16) unsigned char smem[];
     float* sW = reinterpret_cast<float*>(smem);             // [tap][CIN][32]
     constexpr int TAPS = KK * KK, HALF = CIN / 2, NP = HALF / 4, PGS = 4 / KS, BM = PGS * 32, NQ = (TAPS + KS - 1) / KS;
     constexpr int CC = CIN * 32;                            // floats per tap in LDS
@@ -417,6 +425,14 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(unsigned npub, unsigned b
                 if (8 * g >= ncout) continue;
                 o[g].x += acc[4 * g]; o[g].y += acc[4 * g + 1]; o[g].z += acc[4 * g + 2]; o[g].w += acc[4 * g + 3];
                 *reinterpret_cast<float4*>(pp + 8 * g) = o[g];
+            }
+            if (e.dY) {                                     // (the launch reads the site out)
+                const int oy = s_wy[pl] - e.by0, ox = s_wx[pl] - e.bx0;
+                if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        if (8 * g < ncout)
+                            write_out<float, 4>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + nt * 32 + 4 * h + 8 * g, &o[g].x);
             }
         }
     }
@@ -986,7 +1002,7 @@ int g_tile = 0, g_pipe = 0, g_xcd = 1, g_kc = 0;
 int g_f32_mfma = 1;     // 1: fp32 layers (k_conv_mfma_f32, k_conv_f32) and 3-channel stems go to the matrix cores where they apply, 0: plain FMA kernels
 
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
-static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick) {
+static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];
     using Cfg = TiledCfg<WM, WN, TM, TN, KC, PIPE>;
     const long long nseg = (max_entries + kSegPixels - 1) / kSegPixels;
@@ -996,8 +1012,9 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
     const long long items = (xcd ? 8 * ((MT + 8 / NT - 1) / (8 / NT)) : MT * NT) * (e.up > 1 ? 1 << (2 * e.up - 2) : 1);
     unsigned g = cap_blocks(items, 4096);
     g = (g + 7u) & ~7u;                                    // whole rounds over the 8 XCDs
-    const TileGrid tg{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, NT, xcd, 0, 0, 0u, 0u};
-    g += tg.npub;
+    const TileGrid tg{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, e.up ? 0u : copy_blocks(e, 2), NT, xcd, 0, 0, 0u, 0u};
+    g += tg.npub + tg.ncopy;
+    if (read && tg.ncopy) *read = true;
     if (pick) {
         *pick = ConvPick{multi_tiled_body(WM, WN, TM, TN, KC, PIPE), (int)items, tg, g, (unsigned)Cfg::SMEM};
         return hipSuccess;
@@ -1015,17 +1032,17 @@ static hipError_t launch_tiled(const EdgeBatch& eb, int nb, long long max_entrie
 }
 
 template <int WM, int WN, int TM, int TN, int KC>
-static hipError_t launch_tiled_p(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick) {
+static hipError_t launch_tiled_p(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];
     // measured on MI355X: with L2 latencies of ~200 cycles one step of prefetch is
     // enough; the second register stage only costs occupancy
     const bool deep = g_pipe == 2 && TiledCfg<WM, WN, TM, TN, KC, 2>::SMEM <= 150 * 1024;   // two stages must fit the LDS
-    return deep ? launch_tiled<WM, WN, TM, TN, KC, 2>(eb, nb, max_entries, st, pick)
-                : launch_tiled<WM, WN, TM, TN, KC, 1>(eb, nb, max_entries, st, pick);
+    return deep ? launch_tiled<WM, WN, TM, TN, KC, 2>(eb, nb, max_entries, st, pick, read)
+                : launch_tiled<WM, WN, TM, TN, KC, 1>(eb, nb, max_entries, st, pick, read);
 }
 
 template <int KC>
-static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick) {
+static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];
     auto blocks = [&](int bm, int bn) { return ((max_entries + bm - 1) / bm) * (e.Cout / bn); };
     int tile = g_tile;
@@ -1040,22 +1057,22 @@ static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_ent
         else tile = 6;
     }
     switch (tile) {
-        case 1: if (e.Cout % 64 == 0) return launch_tiled_p<4, 1, 2, 2, KC>(eb, nb, max_entries, st, pick); break;    // 256 x 64
-        case 2: if (e.Cout % 64 == 0) return launch_tiled_p<2, 2, 2, 1, KC>(eb, nb, max_entries, st, pick); break;    // 128 x 64
-        case 3: if (e.Cout % 64 == 0) return launch_tiled_p<2, 2, 1, 1, KC>(eb, nb, max_entries, st, pick); break;    //  64 x 64
-        case 4: if (e.Cout % 128 == 0) return launch_tiled_p<2, 2, 2, 2, KC>(eb, nb, max_entries, st, pick); break;   // 128 x 128
-        case 5: if (e.Cout % 128 == 0) return launch_tiled_p<2, 2, 1, 2, KC>(eb, nb, max_entries, st, pick); break;   //  64 x 128
-        case 7: if (e.Cout % 128 == 0) return launch_tiled_p<4, 1, 1, 4, KC>(eb, nb, max_entries, st, pick); break;   // 128 x 128, wave 32 x 128
-        case 8: if (e.Cout % 256 == 0) return launch_tiled_p<2, 2, 2, 4, KC>(eb, nb, max_entries, st, pick); break;   // 128 x 256, wave 64 x 128
-        case 9: if (e.Cout % 256 == 0) return launch_tiled_p<1, 4, 2, 2, KC>(eb, nb, max_entries, st, pick); break;   //  64 x 256, wave 64 x 64
-        case 10: if (e.Cout % 256 == 0) return launch_tiled_p<2, 2, 1, 4, KC>(eb, nb, max_entries, st, pick); break;  //  64 x 256, wave 32 x 128
-        case 11: if (e.Cout % 128 == 0) return launch_tiled_p<1, 4, 1, 1, KC>(eb, nb, max_entries, st, pick); break;  //  32 x 128
-        case 12: if (e.Cout % 256 == 0) return launch_tiled_p<1, 4, 1, 2, KC>(eb, nb, max_entries, st, pick); break;  //  32 x 256
-        case 13: if (e.Cout % 128 == 0) return launch_tiled_p<1, 4, 2, 1, KC>(eb, nb, max_entries, st, pick); break;  //  64 x 128, wave 64 x 32
-        case 14: if (e.Cout % 64 == 0) return launch_tiled_p<1, 4, 2, 1, 32>(eb, nb, max_entries, st, pick); break;   //  same, 32-channel steps
+        case 1: if (e.Cout % 64 == 0) return launch_tiled_p<4, 1, 2, 2, KC>(eb, nb, max_entries, st, pick, read); break;    // 256 x 64
+        case 2: if (e.Cout % 64 == 0) return launch_tiled_p<2, 2, 2, 1, KC>(eb, nb, max_entries, st, pick, read); break;    // 128 x 64
+        case 3: if (e.Cout % 64 == 0) return launch_tiled_p<2, 2, 1, 1, KC>(eb, nb, max_entries, st, pick, read); break;    //  64 x 64
+        case 4: if (e.Cout % 128 == 0) return launch_tiled_p<2, 2, 2, 2, KC>(eb, nb, max_entries, st, pick, read); break;   // 128 x 128
+        case 5: if (e.Cout % 128 == 0) return launch_tiled_p<2, 2, 1, 2, KC>(eb, nb, max_entries, st, pick, read); break;   //  64 x 128
+        case 7: if (e.Cout % 128 == 0) return launch_tiled_p<4, 1, 1, 4, KC>(eb, nb, max_entries, st, pick, read); break;   // 128 x 128, wave 32 x 128
+        case 8: if (e.Cout % 256 == 0) return launch_tiled_p<2, 2, 2, 4, KC>(eb, nb, max_entries, st, pick, read); break;   // 128 x 256, wave 64 x 128
+        case 9: if (e.Cout % 256 == 0) return launch_tiled_p<1, 4, 2, 2, KC>(eb, nb, max_entries, st, pick, read); break;   //  64 x 256, wave 64 x 64
+        case 10: if (e.Cout % 256 == 0) return launch_tiled_p<2, 2, 1, 4, KC>(eb, nb, max_entries, st, pick, read); break;  //  64 x 256, wave 32 x 128
+        case 11: if (e.Cout % 128 == 0) return launch_tiled_p<1, 4, 1, 1, KC>(eb, nb, max_entries, st, pick, read); break;  //  32 x 128
+        case 12: if (e.Cout % 256 == 0) return launch_tiled_p<1, 4, 1, 2, KC>(eb, nb, max_entries, st, pick, read); break;  //  32 x 256
+        case 13: if (e.Cout % 128 == 0) return launch_tiled_p<1, 4, 2, 1, KC>(eb, nb, max_entries, st, pick, read); break;  //  64 x 128, wave 64 x 32
+        case 14: if (e.Cout % 64 == 0) return launch_tiled_p<1, 4, 2, 1, 32>(eb, nb, max_entries, st, pick, read); break;   //  same, 32-channel steps
         default: break;
     }
-    return launch_tiled_p<4, 1, 1, 1, KC>(eb, nb, max_entries, st, pick);                                             // 128 x 32
+    return launch_tiled_p<4, 1, 1, 1, KC>(eb, nb, max_entries, st, pick, read);                                             // 128 x 32
 }
 
 int g_halo = 1;          // 0: never use the halo-staged kernel, 2: force 32-cout tiles, 3: tiles are index ranges instead of
@@ -1071,7 +1088,7 @@ static hipError_t launch_halo_t(const EdgeBatch& eb, int nb, long long nseg, hip
     const long long items = tiles * NT;
     const unsigned npub = T2D ? publish_blocks(e) : 0u, blocks = cap_blocks(items, 16384) + npub;
     if (pick) {
-        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), (int)items, TileGrid{npub, NT, th, tw, 0, 0u, 0u}, blocks, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D), (int)items, TileGrid{npub, 0u, NT, th, tw, 0, 0u, 0u}, blocks, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_halo<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, MINB, T2D>;
@@ -1152,7 +1169,7 @@ static long long rect_tiles(const EdgeDev& e) {
     return tiles * (e.Cout / Cfg::BN);
 }
 template <typename Cfg>
-static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done) {
+static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     int th, tw;
     long long tiles;
@@ -1160,8 +1177,9 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
     const int NT = e.Cout / Cfg::BN, tiles_x = (e.Wp + tw - 1) / tw;
     *done = (double)tiles * NT * NT < 4e9 && (double)tiles * tiles_x < 4e9;      // (the reciprocals are exact below 2^32)
     if (!*done) return hipSuccess;
-    const unsigned npub = publish_blocks(e), blocks = (unsigned)(tiles * NT) + npub;
-    const TileGrid g{npub, NT, th, tw, tiles_x, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)tiles_x)};
+    const unsigned npub = publish_blocks(e), ncopy = copy_blocks(e, 2), blocks = (unsigned)(tiles * NT) + npub + ncopy;
+    if (read && ncopy) *read = true;
+    const TileGrid g{npub, ncopy, NT, th, tw, tiles_x, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)tiles_x)};
     if (pick) {
         *pick = ConvPick{multi_rect_body(Cfg::M, Cfg::TN), (int)(tiles * NT), g, blocks, (unsigned)Cfg::SMEM};
         return hipSuccess;
@@ -1186,7 +1204,7 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
 // / 308 us (279), 84 / 78 / 100 (81), 95 / 91 / 129 (96).  64 channels on large windows: 256-entry tiles without a K split,
 // two to a compute unit, 12.4 us on 258 x 258 against 17.7 with 160-entry tiles, 16 videos 111 (13.6 and 118 before).
 template <int TN>
-static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream_t st, ConvPick* pick, bool* done) {
+static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     using T = RectTiles<TN>;
     int m = 0;
@@ -1207,11 +1225,11 @@ static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream
         }
     }
     switch (m) {
-        case 64: return launch_rect_t<typename T::T64>(eb, nb, st, pick, done);
-        case 96: return launch_rect_t<typename T::T96>(eb, nb, st, pick, done);
-        case 128: return launch_rect_t<typename T::T128>(eb, nb, st, pick, done);
-        case 160: return launch_rect_t<typename T::T160>(eb, nb, st, pick, done);
-        default: return launch_rect_t<typename T::T256>(eb, nb, st, pick, done);
+        case 64: return launch_rect_t<typename T::T64>(eb, nb, st, pick, done, read);
+        case 96: return launch_rect_t<typename T::T96>(eb, nb, st, pick, done, read);
+        case 128: return launch_rect_t<typename T::T128>(eb, nb, st, pick, done, read);
+        case 160: return launch_rect_t<typename T::T160>(eb, nb, st, pick, done, read);
+        default: return launch_rect_t<typename T::T256>(eb, nb, st, pick, done, read);
     }
 }
 
@@ -1287,7 +1305,7 @@ static hipError_t launch_halo_n(const EdgeBatch& eb, int nb, long long nseg, hip
     return hipSuccess;
 }
 
-static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool alone, hipStream_t st, ConvPick* pick, bool* done) {
+static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool alone, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     *done = false;
     if (!g_halo || !e.wp || e.k != 3 || e.stride != 1 || e.up != 0 || e.Cin % 16 || e.Cout % 32) return hipSuccess;
@@ -1298,7 +1316,7 @@ static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool 
     // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512
     // channels 22 -> 17 us a launch.
     if (g_halo != 3 && e.Cin % 64 == 0)
-        return e.Cout % 64 == 0 && g_halo != 2 ? launch_rect<2>(eb, nb, alone, st, pick, done) : launch_rect<1>(eb, nb, alone, st, pick, done);
+        return e.Cout % 64 == 0 && g_halo != 2 ? launch_rect<2>(eb, nb, alone, st, pick, done, read) : launch_rect<1>(eb, nb, alone, st, pick, done, read);
     if (g_halo != 3) return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
     return e.Cout % 64 == 0 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
 }
@@ -1336,7 +1354,7 @@ static hipError_t launch_ldsw(const EdgeBatch& eb, int nb, long long max_entries
 
 // fp32 layers the matrix cores take (k_conv_mfma_f32); *done = false: not this layer
 template <int KK, int CIN, int KS>
-static hipError_t launch_mfma_f32_inst(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st) {
+static hipError_t launch_mfma_f32_inst(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, bool* read) {
     const EdgeDev& e = eb.d[0];
     static std::atomic<bool> attr_set{false};
     auto kern = k_conv_mfma_f32<KK, CIN, KS>;
@@ -1350,15 +1368,16 @@ static hipError_t launch_mfma_f32_inst(const EdgeBatch& eb, int nb, long long ns
     const long long tiles = nseg * (kSegPixels / (32 * (4 / KS)));
     // weights are staged once per block: a bounded number of persistent blocks
     const long long cap = (smem > 49152 ? 512 : 1024) / nts;
-    const unsigned npub = publish_blocks(e), g = cap_blocks(tiles, cap > 0 ? cap : 1) + npub;
-    kern<<<dim3(g, nts, nb), dim3(256), smem, st>>>(npub, g, eb);
+    const unsigned npub = publish_blocks(e), ncopy = copy_blocks(e, 4), g = cap_blocks(tiles, cap > 0 ? cap : 1) + npub + ncopy;
+    if (read && ncopy) *read = true;
+    kern<<<dim3(g, nts, nb), dim3(256), smem, st>>>(npub, ncopy, g, eb);
     return hipGetLastError();
 }
 template <int KK, int CIN>
-static hipError_t launch_mfma_f32_ks(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st) {
+static hipError_t launch_mfma_f32_ks(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, bool* read) {
     const EdgeDev& e = eb.d[0];
     if constexpr (KK == 1) {
-        return launch_mfma_f32_inst<KK, CIN, 1>(eb, nb, nseg, st);
+        return launch_mfma_f32_inst<KK, CIN, 1>(eb, nb, nseg, st, read);
     } else {
         // two waves share the taps of a 64-entry tile unless 128-entry tiles already give every compute unit four
         // blocks (measured on 32- and 64-channel layers of 66 and 17 segments: 10.5 k frames/s of a small network with one wave
@@ -1366,24 +1385,24 @@ static hipError_t launch_mfma_f32_ks(const EdgeBatch& eb, int nb, long long nseg
         const long long nts = (e.Cout + 31) / 32;
         int ks = nseg * 2 * nts >= 1024 ? 1 : 2;
         if (g_tile == 1 || g_tile == 2 || g_tile == 4) ks = g_tile;
-        if (ks == 1) return launch_mfma_f32_inst<KK, CIN, 1>(eb, nb, nseg, st);
-        if (ks == 2) return launch_mfma_f32_inst<KK, CIN, 2>(eb, nb, nseg, st);
-        return launch_mfma_f32_inst<KK, CIN, 4>(eb, nb, nseg, st);
+        if (ks == 1) return launch_mfma_f32_inst<KK, CIN, 1>(eb, nb, nseg, st, read);
+        if (ks == 2) return launch_mfma_f32_inst<KK, CIN, 2>(eb, nb, nseg, st, read);
+        return launch_mfma_f32_inst<KK, CIN, 4>(eb, nb, nseg, st, read);
     }
 }
-static hipError_t launch_mfma_f32(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, bool* done) {
+static hipError_t launch_mfma_f32(const EdgeBatch& eb, int nb, long long nseg, hipStream_t st, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     *done = false;
     if (e.up || (e.k != 1 && e.k != 3) || (e.Cin != 16 && (e.k == 3 || (e.Cin != 32 && e.Cin != 64))) || (e.Cout % 32 != 0 && e.Cout != 16) || e.Cout > 1024 ||
         (long long)e.sH * e.sW * e.Cin >= (1ll << 29) || (long long)e.k * e.k * e.Cin * e.Cout >= (1ll << 29))
         return hipSuccess;
     *done = true;
-    if (e.k == 3) return launch_mfma_f32_ks<3, 16>(eb, nb, nseg, st);
-    return e.Cin == 16 ? launch_mfma_f32_ks<1, 16>(eb, nb, nseg, st)
-         : e.Cin == 32 ? launch_mfma_f32_ks<1, 32>(eb, nb, nseg, st) : launch_mfma_f32_ks<1, 64>(eb, nb, nseg, st);
+    if (e.k == 3) return launch_mfma_f32_ks<3, 16>(eb, nb, nseg, st, read);
+    return e.Cin == 16 ? launch_mfma_f32_ks<1, 16>(eb, nb, nseg, st, read)
+         : e.Cin == 32 ? launch_mfma_f32_ks<1, 32>(eb, nb, nseg, st, read) : launch_mfma_f32_ks<1, 64>(eb, nb, nseg, st, read);
 }
 
-hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick) {
+hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];                            // geometry and weights layout are the same for all streams
     const long long max_entries = e.up ? (long long)e.sH * e.sW : (long long)e.Hp * e.Wp;
     const long long nseg = (max_entries + kSegPixels - 1) / kSegPixels;
@@ -1431,15 +1450,15 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bo
     const bool mfma_ok = dtype == MDCNN_F16 && conv_path != 1 && e.Cin % 16 == 0 && e.Cout % 32 == 0;
     if (mfma_ok && conv_path == 0) {
         bool done = false;
-        const hipError_t err = launch_halo(eb, nb, nseg, alone, st, pick, &done);
+        const hipError_t err = launch_halo(eb, nb, nseg, alone, st, pick, &done, read);
         if (done) { *cls = kClsConvMfma; return err; }
     }
     // (the tiled kernel addresses deltas and weights with 32-bit byte offsets)
     const bool small32 = (long long)e.sH * e.sW * e.Cin < (1ll << 30) && (long long)e.k * e.k * e.Cin * e.Cout < (1ll << 30);
     if (mfma_ok && (conv_path == 0 || conv_path == 3) && e.Cin % 32 == 0 && small32) {
         *cls = kClsConvMfma;
-        if (e.Cin % 128 == 0 && g_kc != 64) return launch_tiled_kc<128>(eb, nb, max_entries, st, pick);
-        return e.Cin % 64 == 0 ? launch_tiled_kc<64>(eb, nb, max_entries, st, pick) : launch_tiled_kc<32>(eb, nb, max_entries, st, pick);
+        if (e.Cin % 128 == 0 && g_kc != 64) return launch_tiled_kc<128>(eb, nb, max_entries, st, pick, read);
+        return e.Cin % 64 == 0 ? launch_tiled_kc<64>(eb, nb, max_entries, st, pick, read) : launch_tiled_kc<32>(eb, nb, max_entries, st, pick, read);
     }
     if (pick) return hipSuccess;
     if (mfma_ok) {
@@ -1459,9 +1478,9 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bo
         // passes over by tiles: a fifth of the frame 90 and 68 us, 256 x 256 38 and 29; five-layer network, 512 x 512 frames,
         // 105 and 99)
         bool done = false;
-        const hipError_t err = launch_mfma_f32(eb, nb, nseg, st, &done);
+        const hipError_t err = launch_mfma_f32(eb, nb, nseg, st, &done, read);
         if (done) { *cls = kClsConvMfma; return err; }
-        if (f32_applies(e)) { *cls = kClsConvMfma; return launch_conv_f32(eb, nb, st); }
+        if (f32_applies(e)) { *cls = kClsConvMfma; return launch_conv_f32(eb, nb, st, read); }
     }
     if ((conv_path == 0 || conv_path == 3) && g_f32_mfma && e.k == 3 && e.Cin == 3 && e.Cout % 32 == 0 && e.Cout <= 1024 && !e.up &&
         (long long)e.sH * e.sW * 3 < (1ll << 29)) {

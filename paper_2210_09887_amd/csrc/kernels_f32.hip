@@ -8,9 +8,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(TileGrid g, int tiles, unsi
     __shared__ __align__(16) float smem[kF32Smem];
     __shared__ unsigned s_vm[kF32Px], s_or[4];
     __shared__ int sh[8];
-    const unsigned nblk = blocks - g.npub;
+    const unsigned nblk = blocks - g.npub - g.ncopy;
     if (blockIdx.x >= nblk) {
-        publish_edge(e, blockIdx.x - nblk, g.npub);
+        side_block<float>(e, g, blockIdx.x - nblk, reinterpret_cast<unsigned char*>(smem));
         return;
     }
     read_now(e.delta, e.sflags, e.sH, e.sW, e.Cin, e.P, e.dflags, e.dH, e.dW, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.p_oy, e.p_ox, e.w, e.k, e.stride, e.pad, e.up);
@@ -26,15 +26,17 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(TileGrid g, int tiles, unsi
     if (e.k != 1 && e.k != 3) carry_source_compaction(e, sh, blockIdx.x, nblk);
 }
 
-hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st) {
+hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st, bool* read) {
     const EdgeDev& e = eb.d[0];
     const int ih = e.up ? e.sH : e.Hp, iw = e.up ? e.sW : e.Wp, NT = (e.Cout + kF32Co - 1) / kF32Co;
     int th = 1, tw = 1;
     long long tiles = 0;
     if (!tile_2d(ih, iw, 1, kF32Px, kF32Px, &th, &tw, &tiles)) return hipErrorInvalidValue;     // (never: one pixel always fits)
     const long long items = tiles * NT;
-    const TileGrid g{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, NT, th, tw, (iw + tw - 1) / tw, 0u, 0u};
-    const unsigned blocks = (unsigned)(items < 16384 ? items : 16384) + g.npub;
+    const unsigned ncopy = e.up ? 0u : copy_blocks(e, 4);
+    if (read && ncopy) *read = true;
+    const TileGrid g{e.k == 1 || e.k == 3 ? publish_blocks(e) : 0u, ncopy, NT, th, tw, (iw + tw - 1) / tw, 0u, 0u};
+    const unsigned blocks = (unsigned)(items < 16384 ? items : 16384) + g.npub + g.ncopy;
     k_conv_f32<<<dim3(blocks, 1, nb), dim3(256), 0, st>>>(g, (int)tiles, blocks, eb);
     return hipGetLastError();
 }

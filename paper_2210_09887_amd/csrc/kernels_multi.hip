@@ -24,15 +24,19 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     e.p_oy = v.p_oy;
     e.p_ox = v.p_ox;
     const int NT = jb.g.NT, items = jb.items, p0 = jb.g.p0, p1 = jb.g.p1;
-    const unsigned nblk = jb.blocks;
+    const unsigned nblk = jb.blocks - jb.g.npub;
+    if (blk >= nblk) {                                    // (once for all bodies: the code of a launch is fetched anew)
+        publish_edge(e, blk - nblk, jb.g.npub);
+        return;
+    }
 #define RECT(M, TN)                                                                                                       \
-    case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M>(e, blk, nblk, jb.g); break;
+    case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M, false>(e, blk, jb.g); break;
 #define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
     case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
-        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, jb.g.npub, NT, items, p0, p1);           \
+        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, NT, items, p0, p1);                     \
         break;
 #define TILED(WM, WN, TM, TN, KC)                                                                                         \
-    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1>(e, blk, nblk, jb.g, items); break;
+    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1, false>(e, blk, nblk, jb.g, items); break;
     switch (jb.body) {
         RECT(64, 1) RECT(64, 2) RECT(96, 1) RECT(96, 2) RECT(128, 1) RECT(128, 2)
         HALO(2, 2, 2, 2, 1, 32, 3, 3, true)

@@ -191,6 +191,7 @@ struct RoundOp {
     int site, edge;            // edge < 0: step 1 of the site (-1), or the compaction-only launch of its forward call (-2)
     int skip;                  // step 1: edge whose residual add it does, or -1
     bool first;                // the edge that also compacts the source's update mask
+    bool reads = false;        // the edge is the last to add to its OUTPUT site and has a round to itself: its launch may read the site out
 };
 struct RoundPlan {
     int key = -1;              // g_fuse_skip the plan was made for
@@ -299,7 +300,7 @@ EdgeDev make_edge(const mdcnn_buffer* in, const mdcnn_buffer* out, const mdcnn_c
     e.op = c.k ? c.op : 0;
     if (e.op == 1 && out->d.crops) e.op = 2;               // the reset zeroes the previous pooling output
     e.sA = in->dev.A; e.s_aoy = in->dev.a_oy; e.s_aox = in->dev.a_ox; e.s_relu = in->d.relu;
-    e.dY = out->dev.Y; e.d_aoy = out->dev.a_oy; e.d_aox = out->dev.a_ox;
+    e.dY = e.op ? out->dev.Y : nullptr; e.d_aoy = out->dev.a_oy; e.d_aox = out->dev.a_ox;
     if (out->d.truncation_free) {                          // no P: the edge adds to A and makes the site's mask and deltas
         e.op = kOpTruncFree;
         e.dY = out->dev.A; e.sA = out->dev.delta; e.s_relu = out->d.relu;
@@ -620,6 +621,9 @@ void make_rounds(const mdcnn_net* net, RoundPlan& rp) {
         const int kind = !ready[1 - last_kind].empty() ? 1 - last_kind : last_kind;
         rp.rounds.emplace_back();
         for (int k : ready[kind]) { rp.rounds.back().push_back(ops[(size_t)k].op); ops[(size_t)k].done = true; --left; }
+        RoundOp& only = rp.rounds.back()[0];
+        const int dst = rp.rounds.back().size() == 1 && only.edge >= 0 ? net->edst[(size_t)only.edge] : -1;
+        only.reads = dst >= 0 && net->sites[(size_t)dst]->d.kind == MDCNN_SITE_OUTPUT && lastw[(size_t)dst] == ready[kind][0];
         last_kind = kind;
     }
     rp.fills.clear();
@@ -815,10 +819,11 @@ size_t crop_pixels(const mdcnn_buffer* b) {                // sites without crop
 bool whole_view(const mdcnn_buffer* b) { return crop_pixels(b) == (size_t)b->d.H * b->d.W; }
 
 // One round of a plan for n videos (n <= kMaxBatch): sites[b] are the sites of video b as the frame sees them.
-// Operations the multi-edge kernels do not take get a launch each.
+// Operations the multi-edge kernels do not take get a launch each.  outs[b][i]: where OUTPUT site i of video b is to be read
+// out to; (*read)[i] is set if a launch of the round has done so.
 mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets, int n, const std::vector<mdcnn_buffer* const*>& sites,
                        const void* const* frames, const uint8_t* const* forced, hipStream_t st, bool alone, const FillJob* jobs = nullptr,
-                       const std::vector<int>* fills = nullptr) {
+                       const std::vector<int>* fills = nullptr, const std::vector<void*>* outs = nullptr, std::vector<char>* read = nullptr) {
     static thread_local Step1Batch sb;                     // 3.4 to 4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
     static thread_local Step1Multi sm;
@@ -885,7 +890,15 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
             const int dtype = sites[0][op.site]->d.dtype;
             if (round.size() > 1 && same_weights) err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls, &pick);
             if (err == hipSuccess && pick.body < 0) {
-                err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls);
+                const int dst = op.edge >= 0 ? net->edst[(size_t)op.edge] : -1;
+                const bool reads = outs && op.reads && !sites[0][dst]->d.crops;
+                for (int b = 0; b < n && reads; ++b) {
+                    eb.d[b].dY = outs[b][(size_t)dst];
+                    eb.d[b].s_relu = sites[(size_t)b][dst]->d.relu;
+                }
+                bool done = false;
+                err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls, nullptr, &done);
+                if (reads && done) (*read)[(size_t)dst] = 1;
             } else if (err == hipSuccess) {
                 if (cm.n == kMaxMultiJobs || (cm.n + 1) * n > kMaxConvVids) flush_conv();
                 ConvJob& j = cm.job[cm.n];
@@ -984,11 +997,23 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     mdcnn_buffer* ins[kMaxBatch];
     const mdcnn_conv_desc* edges[kMaxBatch];
     mdcnn_buffer* const* outs[kMaxBatch];
+    std::vector<char> read(net->sites.size(), 0);          // OUTPUT sites the launch of their last edge has read out
     if (rounds) {
         std::vector<mdcnn_buffer* const*> sites((size_t)n);
         for (int b = 0; b < n; ++b) sites[(size_t)b] = nets[b]->sites.data();
+        std::vector<std::vector<void*>> out_of((size_t)n, std::vector<void*>(net->sites.size(), nullptr));
+        for (int b = 0; b < n; ++b) {
+            char* o = (char*)outs_dev[b];
+            for (size_t i = 0; i < net->sites.size(); ++i) {
+                const mdcnn_buffer* s = nets[b]->sites[i];
+                if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
+                out_of[(size_t)b][i] = o;
+                o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
+            }
+        }
         for (size_t r = 0; r < net->rounds.rounds.size(); ++r) {
-            mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, true, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills);
+            mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, true, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills,
+                                        out_of.data(), &read);
             if (rc) return rc;
         }
     }
@@ -1021,9 +1046,11 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     }
     for (int b = 0; b < n; ++b) {
         char* o = (char*)outs_dev[b];
-        for (mdcnn_buffer* s : nets[b]->sites) {
+        for (size_t i = 0; i < net->sites.size(); ++i) {
+            mdcnn_buffer* const s = nets[b]->sites[i];
             if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
-            hipError_t err = timed(kClsReadout, st, [&] { return launch_read_view(s->dev, s->d.crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, o, st); });
+            hipError_t err = hipSuccess;
+            if (!read[i]) err = timed(kClsReadout, st, [&] { return launch_read_view(s->dev, s->d.crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, o, st); });
             if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "readout launch: %s", hipGetErrorString(err));
             o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
         }

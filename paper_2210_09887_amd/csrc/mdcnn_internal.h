@@ -217,6 +217,8 @@ struct EdgeDev {
     // Truncation-free destination (op == 3, 1x1 convolution): there is no P; dY is the destination's
     // accumulated ring A (addressed with d_aoy, d_aox), sA its delta map (view order, written here),
     // wp its bias (floats, or nullptr) and s_relu its activation.
+    // Convolution (op == 0): dY is where the launch also writes f(P) of the destination's view, s_relu that activation, or
+    // nullptr (the last edge into an OUTPUT site, kernels that launch_conv says do it).
     const void* sA;
     void* dY;
     int s_aoy, s_aox, s_relu, d_aoy, d_aox, op;
@@ -229,6 +231,15 @@ inline unsigned publish_blocks(const EdgeDev& e, int cap = 128) {
     if (nsrc + ndst == 0) return 0;
     const long long b = ((nsrc > ndst ? nsrc : ndst) + 3) / 4;
     return (unsigned)(b < 1 ? 1 : b > cap ? cap : b);
+}
+
+// Blocks of an edge that reads its destination out (read_rest): 2048 pieces of 16 bytes each, at most 256 pixels.
+constexpr int kCopyPieces = 2048;
+__host__ __device__ inline int copy_pixels(int pieces) { return pieces >= kCopyPieces ? 1 : kCopyPieces / pieces < 256 ? kCopyPieces / pieces : 256; }
+inline unsigned copy_blocks(const EdgeDev& e, int esize) {
+    if (e.op || !e.dY) return 0;
+    const int ppb = copy_pixels(e.Cout * esize / 16);
+    return (unsigned)((e.dH * e.dW + ppb - 1) / ppb);
 }
 
 // Several independent streams (same network, own buffers and camera paths) share
@@ -290,6 +301,7 @@ constexpr int multi_tiled_body(int wm, int wn, int tm, int tn, int kc, int pipe)
 // How the tiles of an edge are dealt to its blocks.  per_*: 2^32 / divisor, rounded up, 0 for 1 (by_reciprocal).
 struct TileGrid {
     unsigned npub;            // blocks that publish the lists
+    unsigned ncopy;           // blocks that read out what the tiles leave alone, the last of the edge (read_rest)
     int NT;                   // cout tiles
     int p0, p1;               // rectangular tiles: rows, columns; gather tiles: xcd_map
     int tiles_x;              // rectangles in a row
@@ -354,11 +366,12 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      /
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls
 // alone: the launches of other frames do not run beside this one (the choice of the tile, not its results)
+// read: set to true if the launch also writes f(P) of the destination's view to EdgeDev::dY (asked for by its not being nullptr)
 // pick: nothing is launched; *pick says with which configuration of k_conv_multi the edge would run, if with one
-hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick = nullptr);
+hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick = nullptr, bool* read = nullptr);
 // fp32 layers on the matrix cores (kernels_f32.hip): shapes it takes, launch
 bool f32_applies(const EdgeDev& e);
-hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st);
+hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st, bool* read);
 extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // convolution tuning knobs
 // host-only: the rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);
