@@ -665,7 +665,7 @@ hipError_t launch_input_mask(const MaskJob& j, hipStream_t st) {
 // View-ordered access (readout of OUTPUT sites is on the per-frame path).
 // ---------------------------------------------------------------------------
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void k_read_tensor(SiteDev s, int what, T* __restrict__ dst) {
+__device__ __forceinline__ void read_tensor(const SiteDev& s, int what, T* __restrict__ dst) {
     const int chunks = s.C / VEC;
     const bool win = what == MDCNN_VIEW_P;
     const bool crop = what == MDCNN_VIEW_CROP_OUT;         // f(P) over the crop, in crop order
@@ -704,6 +704,16 @@ __global__ __launch_bounds__(256) void k_read_tensor(SiteDev s, int what, T* __r
             d[0] = (T)v;
         }
     }
+}
+
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_read_tensor(SiteDev s, int what, T* __restrict__ dst) {
+    read_tensor<T, VEC>(s, what, dst);
+}
+// One site of every video of a batch (blockIdx.z).
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_read_tensors(ReadBatch b, int what) {
+    read_tensor<T, VEC>(b.s[blockIdx.z], what, (T*)b.dst[blockIdx.z]);
 }
 
 template <typename T, int VEC>
@@ -808,13 +818,31 @@ static unsigned grid_for(long long total) {
     return (unsigned)b;
 }
 
+static long long view_pixels(const SiteDev& s, int what) {
+    return what == MDCNN_VIEW_P ? (long long)s.Hp * s.Wp
+         : what == MDCNN_VIEW_CROP_OUT ? (long long)(s.cy1() - s.cy0()) * (s.cx1() - s.cx0()) : (long long)s.H * s.W;
+}
+template <typename T>
+static void read_tensors_t(const ReadBatch& b, int n, int what, long long pix, hipStream_t st) {
+    constexpr int V = V16<T>::N;
+    const int C = b.s[0].C;
+    if (C % V == 0) k_read_tensors<T, V><<<dim3(grid_for(pix * (C / V)), 1, (unsigned)n), dim3(256), 0, st>>>(b, what);
+    else k_read_tensors<T, 1><<<dim3(grid_for(pix * C), 1, (unsigned)n), dim3(256), 0, st>>>(b, what);
+}
+hipError_t launch_read_outputs(const ReadBatch& b, int n, int what, hipStream_t st) {
+    if (n == 1) return launch_read_view(b.s[0], what, b.dst[0], st);
+    long long pix = 0;                                     // (crops may differ)
+    for (int i = 0; i < n; ++i) pix = view_pixels(b.s[i], what) > pix ? view_pixels(b.s[i], what) : pix;
+    if (b.s[0].dtype == MDCNN_F16) read_tensors_t<f16>(b, n, what, pix, st);
+    else read_tensors_t<float>(b, n, what, pix, st);
+    return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t read_tensor_t(const SiteDev& s, int what, void* dst, hipStream_t st) {
     constexpr int V = V16<T>::N;
     const bool vec = (s.C % V) == 0;
-    const long long pix = what == MDCNN_VIEW_P ? (long long)s.Hp * s.Wp
-                        : what == MDCNN_VIEW_CROP_OUT ? (long long)(s.cy1() - s.cy0()) * (s.cx1() - s.cx0())
-                                                      : (long long)s.H * s.W;
+    const long long pix = view_pixels(s, what);
     if (vec)
         k_read_tensor<T, V><<<dim3(grid_for(pix * (s.C / V))), dim3(256), 0, st>>>(s, what, (T*)dst);
     else

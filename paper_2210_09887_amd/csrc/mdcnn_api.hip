@@ -998,19 +998,19 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     const mdcnn_conv_desc* edges[kMaxBatch];
     mdcnn_buffer* const* outs[kMaxBatch];
     std::vector<char> read(net->sites.size(), 0);          // OUTPUT sites the launch of their last edge has read out
+    std::vector<std::vector<void*>> out_of((size_t)n, std::vector<void*>(net->sites.size(), nullptr));
+    for (int b = 0; b < n; ++b) {
+        char* o = (char*)outs_dev[b];
+        for (size_t i = 0; i < net->sites.size(); ++i) {
+            const mdcnn_buffer* s = nets[b]->sites[i];
+            if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
+            out_of[(size_t)b][i] = o;
+            o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
+        }
+    }
     if (rounds) {
         std::vector<mdcnn_buffer* const*> sites((size_t)n);
         for (int b = 0; b < n; ++b) sites[(size_t)b] = nets[b]->sites.data();
-        std::vector<std::vector<void*>> out_of((size_t)n, std::vector<void*>(net->sites.size(), nullptr));
-        for (int b = 0; b < n; ++b) {
-            char* o = (char*)outs_dev[b];
-            for (size_t i = 0; i < net->sites.size(); ++i) {
-                const mdcnn_buffer* s = nets[b]->sites[i];
-                if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
-                out_of[(size_t)b][i] = o;
-                o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
-            }
-        }
         for (size_t r = 0; r < net->rounds.rounds.size(); ++r) {
             mdcnn_status rc = run_round(net->rounds.rounds[r], nets, n, sites, frames, forced, st, true, ride && r == 0 ? jobs.data() : nullptr, &net->rounds.fills,
                                         out_of.data(), &read);
@@ -1044,16 +1044,16 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
         if (err == hipSuccess) err = sched.err;
         if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "stream synchronisation: %s", hipGetErrorString(err));
     }
-    for (int b = 0; b < n; ++b) {
-        char* o = (char*)outs_dev[b];
-        for (size_t i = 0; i < net->sites.size(); ++i) {
-            mdcnn_buffer* const s = nets[b]->sites[i];
-            if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
-            hipError_t err = hipSuccess;
-            if (!read[i]) err = timed(kClsReadout, st, [&] { return launch_read_view(s->dev, s->d.crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, o, st); });
-            if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "readout launch: %s", hipGetErrorString(err));
-            o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
+    static thread_local ReadBatch rb;
+    for (size_t i = 0; i < net->sites.size(); ++i) {
+        const mdcnn_buffer* s0 = net->sites[i];
+        if (s0->d.kind != MDCNN_SITE_OUTPUT || read[i]) continue;
+        for (int b = 0; b < n; ++b) {
+            rb.s[b] = nets[b]->sites[i]->dev;
+            rb.dst[b] = out_of[(size_t)b][i];
         }
+        hipError_t err = timed(kClsReadout, st, [&] { return launch_read_outputs(rb, n, s0->d.crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, st); });
+        if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "readout launch: %s", hipGetErrorString(err));
     }
     unfinished.armed = false;
     return MDCNN_OK;
@@ -1438,15 +1438,19 @@ mdcnn_status frame_seq(mdcnn_net* const* nets, int nb, int n_frames, const void*
             }
         }
         hipStream_t st = s[pp.stream_of(f, n_calls)];
-        for (int v = 0; v < nb; ++v) {
-            char* o = (char*)outs_dev[(size_t)f * nb + v];
-            for (int i = 0; i < n_sites; ++i) {
-                mdcnn_buffer& b = w.sites[(size_t)v * n_sites + i];
-                if (b.d.kind != MDCNN_SITE_OUTPUT) continue;
-                err = timed(kClsReadout, st, [&] { return launch_read_view(b.dev, crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, o, st); });
-                if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: readout launch: %s", f, hipGetErrorString(err));
-                o += crop_pixels(&b) * b.d.C * esize(b.d.dtype);
+        static thread_local ReadBatch rb;
+        char* o[kMaxBatch];
+        for (int v = 0; v < nb; ++v) o[v] = (char*)outs_dev[(size_t)f * nb + v];
+        for (int i = 0; i < n_sites; ++i) {
+            if (w.sites[(size_t)i].d.kind != MDCNN_SITE_OUTPUT) continue;
+            for (int v = 0; v < nb; ++v) {
+                const mdcnn_buffer& b = w.sites[(size_t)v * n_sites + i];
+                rb.s[v] = b.dev;
+                rb.dst[v] = o[v];
+                o[v] += crop_pixels(&b) * b.d.C * esize(b.d.dtype);
             }
+            err = timed(kClsReadout, st, [&] { return launch_read_outputs(rb, nb, crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, st); });
+            if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: readout launch: %s", f, hipGetErrorString(err));
         }
         if (issued(n_calls) != hipSuccess) return fail(MDCNN_ERR_HIP, "frame %d: event: %s", f, hipGetErrorString(err));
         return MDCNN_OK;
