@@ -1315,8 +1315,10 @@ static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool 
     // ranges, whose tiles stage whole rows; with the by-products made by other blocks and the round trips of a small tile
     // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512
     // channels 22 -> 17 us a launch.
+    // A launch of few tiles takes 32 couts to a tile instead of 64: half the products and weights to a tile, twice the tiles (the
+    // low resolutions of the HRNet-like network, 20 to 40 tiles: frame 496 -> 480 us).  No sum changes with it.
     if (g_halo != 3 && e.Cin % 64 == 0)
-        return e.Cout % 64 == 0 && g_halo != 2 ? launch_rect<2>(eb, nb, alone, st, pick, done, read) : launch_rect<1>(eb, nb, alone, st, pick, done, read);
+        return e.Cout % 64 == 0 && g_halo != 2 && (g_halo_sub || rect_tiles<RectTiles<2>::T64>(e) * nb > 64) ? launch_rect<2>(eb, nb, alone, st, pick, done, read) : launch_rect<1>(eb, nb, alone, st, pick, done, read);
     if (g_halo != 3) return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
     return e.Cout % 64 == 0 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
 }
