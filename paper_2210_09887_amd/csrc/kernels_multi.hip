@@ -13,9 +13,14 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     unsigned blk;
     const int j = m.blocks.find(blockIdx.x, &blk);
     const ConvJob& jb = m.job[j];
-    if (blk >= jb.blocks) return;                         // (the numbers between two edges, up to a multiple of 8)
-    const ConvVid& v = m.vid[j * m.videos + (int)blockIdx.z];
+    ConvVid v = m.vid[j * m.videos + (int)blockIdx.z];
     EdgeDev e = jb.e;
+    TileGrid g = jb.g;
+    unsigned blocks = jb.blocks;
+    int body = jb.body, items = jb.items;
+    read_now(v.sd, v.dd, v.p_oy, v.p_ox, blocks, body, items, g.npub, g.NT, g.p0, g.p1, g.tiles_x, g.per_NT, g.per_tiles_x, e.delta, e.sflags, e.sH, e.sW,
+             e.Cin, e.P, e.Cout, e.Hp, e.Wp, e.by0, e.bx0, e.w, e.wp, e.k, e.stride, e.pad, e.up);
+    if (blk >= blocks) return;                            // (the numbers between two edges, up to a multiple of 8)
     auto at = [](auto*& p, long long d) {
         if (p) p = (std::remove_reference_t<decltype(p)>)((uintptr_t)p + (uintptr_t)d);
     };
@@ -23,21 +28,20 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     at(e.P, v.dd); at(e.dflags, v.dd); at(e.clist, v.dd); at(e.ccnt, v.dd); at(e.cacc, v.dd); at(e.dcounters, v.dd);
     e.p_oy = v.p_oy;
     e.p_ox = v.p_ox;
-    const int NT = jb.g.NT, items = jb.items, p0 = jb.g.p0, p1 = jb.g.p1;
-    const unsigned nblk = jb.blocks - jb.g.npub;
+    const unsigned nblk = blocks - g.npub;
     if (blk >= nblk) {                                    // (once for all bodies: the code of a launch is fetched anew)
-        publish_edge(e, blk - nblk, jb.g.npub);
+        publish_edge(e, blk - nblk, g.npub);
         return;
     }
 #define RECT(M, TN)                                                                                                       \
-    case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M, false>(e, blk, jb.g); break;
+    case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M, false>(e, blk, g); break;
 #define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
     case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
-        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, NT, items, p0, p1);                     \
+        halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, g.NT, items, g.p0, g.p1);               \
         break;
 #define TILED(WM, WN, TM, TN, KC)                                                                                         \
-    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1, false>(e, blk, nblk, jb.g, items); break;
-    switch (jb.body) {
+    case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1, false>(e, blk, nblk, g, items); break;
+    switch (body) {
         RECT(64, 1) RECT(64, 2) RECT(96, 1) RECT(96, 2) RECT(128, 1) RECT(128, 2)
         HALO(2, 2, 2, 2, 1, 32, 3, 3, true)
         HALO(4, 2, 2, 1, 1, 32, 2, 9, true)

@@ -499,8 +499,10 @@ hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
 __global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
     unsigned blk;
     const int j = m.blocks.find(blockIdx.x, &blk);
-    const Step1Job& jb = m.job[j];
-    const Step1Vid& v = m.vid[j * m.videos + (int)blockIdx.z];
+    Step1Job jb = m.job[j];
+    Step1Vid v = m.vid[j * m.videos + (int)blockIdx.z];
+    read_now(jb.A, jb.P, jb.delta, jb.flags, jb.skip_P, jb.skip_flags, jb.H, jb.W, jb.C, jb.Hp, jb.Wp, jb.by0, jb.bx0, jb.relu, jb.skip_Hp, jb.skip_Wp,
+             jb.skip_by0, jb.skip_bx0, v.sd, v.kd, v.a_oy, v.a_ox, v.p_oy, v.p_ox, v.k_oy, v.k_ox, v.s_off, v.theta);
     auto at = [](auto* p, long long d) { return p ? (decltype(p))((uintptr_t)p + (uintptr_t)d) : nullptr; };
     SiteDev s{};
     s.kind = MDCNN_SITE_PREACT;
