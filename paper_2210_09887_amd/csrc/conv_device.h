@@ -250,9 +250,9 @@ __device__ __forceinline__ void carry_source_compaction(const EdgeDev& e, int* s
     __syncthreads();
 }
 
-// By-products of a 3 x 3 or 1 x 1 edge that its tiles leave to blocks of their own (publish_blocks of them): the source's list L (on
-// the edge that carries it), the destination's compute list with its counts, the touched marks and the multiply-accumulate
-// count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
+// By-products of a 3 x 3 or 1 x 1 edge, or of a residual skip, that its tiles leave to blocks of their own (publish_blocks of
+// them): the source's list L (on the edge that carries it), the destination's compute list with its counts, the touched marks
+// and the multiply-accumulate count.  A wave takes a segment of either list at a time, no barriers; a tile that made them itself had their loads ahead of
 // its own and its loads behind their stores (memory operations of a wave complete in order): 2.0 us to the start of its K
 // loop, now 1.3.  All loads of the two segments go out together, a row of the footprint is one unaligned word, and a mark is
 // a byte store - a pixel has one owner, so nobody else writes its flag meanwhile - where an atomic OR went past the L2 of its
@@ -344,7 +344,7 @@ __device__ __forceinline__ void publish_edge(const EdgeDev& e, unsigned blk, uns
             if (lane == 0) {
                 ccnt[s] = tot;
                 cacc[s] = csum + (unsigned long long)tot;
-                add_macs(e, taps, 0);
+                if (ks > 0) add_macs(e, taps, 0);              // (a residual skip multiplies nothing)
             }
         }
     }
