@@ -690,7 +690,7 @@ __global__ __launch_bounds__(256) void k_conv_plain(EdgeBatch eb) {
 
 // Residual skip: P_dst[q] += delta[q] for every updated pixel q of the source.  A thread takes VEC channels of a pixel, nothing
 // is ranked: the lists, marks and counts are left to the last npub blocks.  (Compacting a list segment first, a block to a
-// segment and group of channels, took 7.2 to 8.0 us on the sites of a ResNet-18-style network of 312 x 440 frames, this 2.9 to 3.9.)
+// segment and group of channels, took 7.2 to 8.0 us on the sites of a ResNet-18-style network of 296 x 424 frames, this 2.9 to 3.9.)
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void k_identity(unsigned npub, unsigned blocks, EdgeBatch eb) {
     EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
