@@ -4,21 +4,24 @@
 //   P_dst[q] <- P_dst[q] + y[q]        (border pixels included: they are stashed)
 // Output-stationary: one owner per output pixel, fixed summation order, so the
 // result does not depend on scheduling.  Weights are w[tap][cout][cin].
-// There is no separate list kernel: every block finds the entries of its own tile from the source's update mask.  A tile
-// of the gather kernels is a piece of a list segment (kSegPixels indices, one per thread, ballot + popcount ranks); the
-// block of a segment's first piece also writes the segment to the destination's compute list, the copy the ABI exposes,
-// and every block of the first edge of a forward call compacts its share of the source's update mask into L before its
-// tiles.  The halo-staged kernel (rectangles of the padded window) and the 3-channel stem leave both to a few blocks of
-// their own (publish_edge), k_conv_f32 writes segment n with its n-th rectangle and does L after its tiles.
+// There is no separate list kernel: every block finds the entries of its own tile from the source's update mask.  The lists
+// the ABI exposes, the touched marks and the counts of a 3x3 or 1x1 edge on the matrix cores, of a 3-channel stem and of a
+// residual skip are left to a few blocks at the end of the launch (publish_edge), and where the destination is an OUTPUT site
+// that a frame call reads out, blocks behind those copy what the tiles leave alone (read_rest).  The other kernels, and edges
+// of other sizes, do it themselves: the block of a segment's first piece writes the segment (kSegPixels indices, one per
+// thread, ballot + popcount ranks) to the compute list, and every block compacts its share of the source's mask into L.
 //
-//   k_conv_halo       : 3x3 stride-1 fp16 layers: source rectangle of a tile staged once per
-//                       channel chunk in LDS, packed weights straight into MFMA fragments
+//   k_conv_rect       : 3x3 stride-1 fp16 layers of 64 n input channels: rectangles, staged by loads that
+//                       write LDS themselves, packed weights straight into MFMA fragments (conv_rect.h)
+//   k_conv_halo       : the other 3x3 stride-1 fp16 layers of 32 n input channels: rectangles, staged
+//                       through registers once per 32 channels
 //   k_conv_mfma_tiled : LDS-tiled gather-GEMM on the CDNA4 matrix cores (fp16 in, fp32 acc)
 //   k_conv_mfma_f16   : MFMA without LDS staging (fallback for Cin % 32 != 0)
 //   k_conv_mfma_f32   : small fp32 layers, weights in LDS (fp32 matrix instruction)
 //   k_conv_f32        : weights and delta rows staged in LDS (conv_f32.h): all other fp32 layers with
 //                       Cin % 8 == 0 and Cout 16 or a multiple of 32, but for the smallest (f32_applies)
-//   k_conv_small      : 3-channel 3x3 stems, plain FMA
+//   k_conv_stem_mfma  : 3-channel 3x3 stems on the fp32 matrix instruction
+//   k_conv_small      : 3-channel 3x3 stems, plain FMA (upsampling edges and where the matrix cores are switched off)
 //   k_conv_ldsw       : plain FMA with the weights resident in LDS (fp32 layers of few products, other shapes)
 //   k_conv_plain      : plain FMA, any dtype / channel count
 //   k_identity        : residual skip, P_dst[q] += delta[q] (when it is not fused into step 1)
@@ -1205,7 +1208,9 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
 // Which tile.  Alone on the GPU a launch takes as long as the compute unit with the most tiles, one or two of them, and a tile
 // as long as its K loop (per entry, Cin + what the epilogue takes); in a full GPU - several tiles per compute unit, or the
 // frames beside this one, four in flight - it is the sum of the tiles and 2 us of each (12500 in these units) that nothing
-// covers.  Tiles of 160 entries have a compute unit for themselves and an epilogue that takes 1.3 us more.  Measured alone, 64 /
+// covers.  Tiles of 160 entries have a compute unit for themselves and an epilogue that takes 1.3 us more; nothing covers
+// theirs, so they are for launches that are not full (a ResNet-18-style batch frame by frame, 512 x 512, with / without this: 4
+// videos 3951 / 3730 frames/s, 8 videos 4480 / 4080, 16 videos 4750 / 4310).  Measured alone, 64 /
 // 96 / 160 entries: 512 -> 512 channels on a 66 x 66 window 30.9 / 25.2 / 23.2 us (29.9 with the kernel before), 256 -> 256
 // 12.5 / 10.6 / 15.2 (13.3), 128 -> 128 on 130 x 130 14.2 / 11.2 / 12.3 (12.8); 16 videos, 96 / 128 / 160 entries: 293 / 264
 // / 308 us (279), 84 / 78 / 100 (81), 95 / 91 / 129 (96).  64 channels on large windows: 256-entry tiles without a K split,
@@ -1226,6 +1231,7 @@ static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream
             const int px = 64 + 32 * i;
             const double per_cu = (double)(of[i] * nb * (alone ? 1 : 4)) / 256;
             const bool full = per_cu > 2;
+            if (full && px == 160) continue;
             double cost = (full ? per_cu : per_cu <= 1 ? 1 : 2) * ((double)px * (e.Cin + 78) + (full ? 12500 : px == 160 ? 8000 : 0));
             if (pick && of[i] * nb > 352) cost *= 1.4;     // beside the blocks of other edges: some would wait for a place
             if (m == 0 || cost <= best) { best = cost; m = px; }
