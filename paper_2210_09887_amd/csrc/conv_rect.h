@@ -45,7 +45,7 @@ __device__ __forceinline__ i32x4_t raw_rsrc(const void* p, unsigned bytes) {
 // 16 bytes per lane to LDS bytes [lds, lds + 1024), lane after lane.  Written as assembly so that the compiler does not take
 // the LDS reads that follow for readers of these bytes: who reads them waits with dma_wait and a barrier.
 __device__ __forceinline__ void dma16(i32x4_t rs, unsigned lds, unsigned lane_bytes, unsigned wave_bytes) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(lane_bytes), "s"(rs), "s"(wave_bytes) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(lane_bytes), "s"(rs), "s"(wave_bytes) : "memory", "m0");
 }
 template <int LEFT>
 __device__ __forceinline__ void dma_wait() {               // until all but the last LEFT loads of the wave are done
