@@ -128,14 +128,24 @@ typedef struct {
 mdcnn_status mdcnn_pack_weights(const mdcnn_conv_desc* edge, int dtype, void* dst_dev, size_t dst_bytes,
                                 void* stream);
 
-/* Host-only helper.  The tile the halo-staged convolution kernel would cut an Hp x Wp padded window
- * into: the rectangle th x tw of at most max_pixels (1 .. 256) pixels whose footprint
+/* Host-only helper.  The rectangle th x tw of at most max_pixels (1 .. 256) pixels of an Hp x Wp padded window whose footprint
  * (th + k - 1) x (tw + k - 1) has at most max_staged pixels and that covers the window with the
- * fewest tiles (ties: the smaller footprint); *tiles = ceil(Hp / th) * ceil(Wp / tw).
+ * fewest tiles (ties: the smaller footprint); *tiles = ceil(Hp / th) * ceil(Wp / tw).  The halo-staged kernel (3x3
+ * stride-1 fp16 layers with Cin a multiple of 32 and not of 64) and the fp32 kernels cut windows by it; layers of 64 n
+ * input channels: mdcnn_rect_tiles.
  * Errors: MDCNN_ERR_SHAPE if no rectangle fits, MDCNN_ERR_SIZE for arguments out of range.
  * [Padded Convolutions: a tile's outputs read the tile and a border of (k - 1) / 2 pixels around it] */
 mdcnn_status mdcnn_conv_tiles(int Hp, int Wp, int k, int max_pixels, int max_staged, int* th, int* tw,
                               long long* tiles);
+
+/* Host-only helper.  The tile of a 3x3 stride-1 fp16 layer with Cin a multiple of 64 and packed weights on an Hp x Wp padded
+ * window, for one launch of `videos` videos, with frames in flight beside it (in_flight != 0) or not, and with other
+ * layers in the same launch (shared != 0) or not: *entries, the pixels a tile has at most (64, 96, 128, 160 or 256), *couts, its
+ * output channels (32 or 64), its rectangle th x tw, and *tiles, those of one video over all output channels.  Follows
+ * MDCNN_OPT_CONV_HALO and MDCNN_OPT_CONV_HALO_SUB.  Errors: MDCNN_ERR_SHAPE for other channel counts, MDCNN_ERR_SIZE for
+ * arguments out of range.  [Padded Convolutions] */
+mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int in_flight, int shared, int* entries, int* couts,
+                              int* th, int* tw, long long* tiles);
 
 /* Host-only helper.  Width of the dilated border along one axis for a
  * convolution (k, stride, pad) from `in_extent` to `out_extent` pixels: how many

@@ -1148,9 +1148,10 @@ bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, 
     return true;
 }
 
-// Rectangle of at most m pixels, 14 columns and rows - 2 rows for the tiles of conv_rect.h, with the fewest tiles over an
-// Hp x Wp window (ties: the smaller halo).  Asked for by every launch: the answers are kept per host thread, as tile_2d's.
-static void rect_tile(int Hp, int Wp, int m, int rows, int* th_out, int* tw_out, long long* tiles_out) {
+// Rectangle of at most m pixels, 14 columns and rect_rows(m) - 2 rows for the tiles of conv_rect.h, with the fewest tiles over
+// an Hp x Wp window (ties: the smaller halo).  Asked for by every launch: the answers are kept per host thread, as tile_2d's.
+void rect_tile(int Hp, int Wp, int m, int* th_out, int* tw_out, long long* tiles_out) {
+    const int rows = rect_rows(m);
     struct Entry { int Hp = -1, Wp, m, th, tw; long long tiles; };
     static thread_local Entry table[256];
     const unsigned h = (unsigned)Hp * 2654435761u ^ (unsigned)Wp * 2246822519u ^ (unsigned)m * 3266489917u;
@@ -1172,18 +1173,12 @@ static void rect_tile(int Hp, int Wp, int m, int rows, int* th_out, int* tw_out,
     *tiles_out = t.tiles;
 }
 template <typename Cfg>
-static long long rect_tiles(const EdgeDev& e) {
-    int th, tw;
-    long long tiles;
-    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, &th, &tw, &tiles);
-    return tiles * (e.Cout / Cfg::BN);
-}
-template <typename Cfg>
 static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     int th, tw;
     long long tiles;
-    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, &th, &tw, &tiles);
+    static_assert(Cfg::ROWS == rect_rows(Cfg::M), "the rows rect_tile counts on");
+    rect_tile(e.Hp, e.Wp, Cfg::M, &th, &tw, &tiles);
     const int NT = e.Cout / Cfg::BN, tiles_x = (e.Wp + tw - 1) / tw;
     *done = (double)tiles * NT * NT < 4e9 && (double)tiles * tiles_x < 4e9;      // (the reciprocals are exact below 2^32)
     if (!*done) return hipSuccess;
@@ -1205,9 +1200,13 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
     return hipGetLastError();
 }
 
-// Which tile.  Alone on the GPU a launch takes as long as the compute unit with the most tiles, one or two of them, and a tile
-// as long as its K loop (per entry, Cin + what the epilogue takes); in a full GPU - several tiles per compute unit, or the
-// frames beside this one, four in flight - it is the sum of the tiles and 2 us of each (12500 in these units) that nothing
+// Which tile: entries (*m) and couts / 32 (*tn).
+// Couts: a launch of few tiles takes 32 to a tile instead of 64: half the products and weights to a tile, twice the tiles (the
+// low resolutions of the HRNet-like network, 20 to 40 tiles: frame 496 -> 480 us; 0 to 128 in place of 64 for frames in flight: no
+// difference).  No sum changes with it.
+// Entries.  Alone on the GPU a launch takes as long as the compute unit with the most tiles, one or two of them, and a tile
+// as long as its K loop (per entry, Cin + what the epilogue takes); with several tiles per compute unit it is the sum of the
+// tiles and 2 us of each (12500 in these units) that nothing
 // covers.  Tiles of 160 entries have a compute unit for themselves and an epilogue that takes 1.3 us more; nothing covers
 // theirs, so they are for launches that are not full (a ResNet-18-style batch frame by frame, 512 x 512, with / without this: 4
 // videos 3951 / 3730 frames/s, 8 videos 4480 / 4080, 16 videos 4750 / 4310).  Measured alone, 64 /
@@ -1215,28 +1214,47 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
 // 12.5 / 10.6 / 15.2 (13.3), 128 -> 128 on 130 x 130 14.2 / 11.2 / 12.3 (12.8); 16 videos, 96 / 128 / 160 entries: 293 / 264
 // / 308 us (279), 84 / 78 / 100 (81), 95 / 91 / 129 (96).  64 channels on large windows: 256-entry tiles without a K split,
 // two to a compute unit, 12.4 us on 258 x 258 against 17.7 with 160-entry tiles, 16 videos 111 (13.6 and 118 before).
-template <int TN>
-static hipError_t launch_rect(const EdgeBatch& eb, int nb, bool alone, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
-    const EdgeDev& e = eb.d[0];
-    using T = RectTiles<TN>;
-    int m = 0;
+// Frames in flight: about three launches share the 512 places, so a launch has some 170.  With fewer tiles it takes as long as
+// one tile, with more as their sum divided by its places; equal cost, the smaller tile.  (Clips of 30 frames, this rule / four times
+// the tiles and a step at two per compute unit / 64 / 96 / 128 entries everywhere: 256 x 256 3848 / 3975 / 3850 / 3966 / 4349
+// us, 288 x 288 4120 / 4453 / 4159 / 4121 / 4459, 320 x 320 4363 / 4630 / 4469 / 4398 / 4618, 512 x 512 7047 / 7034 / 7648 / 7151
+// / 7043, 640 x 640 9870 / 9843 / - / 10055 / -.)
+void rect_choice(int Hp, int Wp, int Cin, int Cout, int nb, bool alone, bool shared, int* tn, int* m_out) {
+    auto tiles_of = [&](int m, int couts) {
+        int th, tw;
+        long long tiles;
+        rect_tile(Hp, Wp, m, &th, &tw, &tiles);
+        return tiles * (Cout / couts);
+    };
+    *tn = Cout % 64 == 0 && g_halo != 2 && (g_halo_sub || tiles_of(64, 64) * nb > 64) ? 2 : 1;
     if (g_halo_sub) {
-        m = g_halo_sub == 4 ? 64 : g_halo_sub == 2 ? 128 : e.Cin == 64 ? 256 : 160;
-    } else if (e.Cin == 64 && rect_tiles<typename T::T96>(e) > 512) {
-        m = 256;
-    } else {
-        const long long of[4] = {rect_tiles<typename T::T64>(e), rect_tiles<typename T::T96>(e), rect_tiles<typename T::T128>(e), rect_tiles<typename T::T160>(e)};
-        double best = 0;
-        for (int i = 0; i < (alone && !pick ? 4 : 3); ++i) {
-            const int px = 64 + 32 * i;
-            const double per_cu = (double)(of[i] * nb * (alone ? 1 : 4)) / 256;
-            const bool full = per_cu > 2;
-            if (full && px == 160) continue;
-            double cost = (full ? per_cu : per_cu <= 1 ? 1 : 2) * ((double)px * (e.Cin + 78) + (full ? 12500 : px == 160 ? 8000 : 0));
-            if (pick && of[i] * nb > 352) cost *= 1.4;     // beside the blocks of other edges: some would wait for a place
-            if (m == 0 || cost <= best) { best = cost; m = px; }
-        }
+        *m_out = g_halo_sub == 4 ? 64 : g_halo_sub == 2 ? 128 : Cin == 64 ? 256 : 160;
+        return;
     }
+    if (Cin == 64 && tiles_of(96, 32 * *tn) > 512) {
+        *m_out = 256;
+        return;
+    }
+    double best = 0;
+    *m_out = 0;
+    for (int px = 64; px <= (alone && !shared ? 160 : 128); px += 32) {
+        const double tiles = (double)(tiles_of(px, 32 * *tn) * nb), loop = (double)px * (Cin + 78);
+        double cost;
+        if (alone) {
+            const double per_cu = tiles / 256;
+            if (per_cu > 2 && px == 160) continue;
+            cost = (per_cu > 2 ? per_cu : per_cu <= 1 ? 1 : 2) * (loop + (per_cu > 2 ? 12500 : px == 160 ? 8000 : 0));
+        } else {
+            const double turns = tiles * 3 / 512;
+            cost = (turns > 1 ? turns : 1) * (loop + 10000);
+        }
+        if (shared && tiles > 352) cost *= 1.4;            // beside the blocks of other edges: some would wait for a place
+        if (*m_out == 0 || (alone ? cost <= best : cost < best)) { best = cost; *m_out = px; }
+    }
+}
+template <int TN>
+static hipError_t launch_rect(const EdgeBatch& eb, int nb, int m, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
+    using T = RectTiles<TN>;
     switch (m) {
         case 64: return launch_rect_t<typename T::T64>(eb, nb, st, pick, done, read);
         case 96: return launch_rect_t<typename T::T96>(eb, nb, st, pick, done, read);
@@ -1328,10 +1346,11 @@ static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool 
     // ranges, whose tiles stage whole rows; with the by-products made by other blocks and the round trips of a small tile
     // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512
     // channels 22 -> 17 us a launch.
-    // A launch of few tiles takes 32 couts to a tile instead of 64: half the products and weights to a tile, twice the tiles (the
-    // low resolutions of the HRNet-like network, 20 to 40 tiles: frame 496 -> 480 us).  No sum changes with it.
-    if (g_halo != 3 && e.Cin % 64 == 0)
-        return e.Cout % 64 == 0 && g_halo != 2 && (g_halo_sub || rect_tiles<RectTiles<2>::T64>(e) * nb > 64) ? launch_rect<2>(eb, nb, alone, st, pick, done, read) : launch_rect<1>(eb, nb, alone, st, pick, done, read);
+    if (g_halo != 3 && e.Cin % 64 == 0) {
+        int tn, m;
+        rect_choice(e.Hp, e.Wp, e.Cin, e.Cout, nb, alone, pick != nullptr, &tn, &m);
+        return tn == 2 ? launch_rect<2>(eb, nb, m, st, pick, done, read) : launch_rect<1>(eb, nb, m, st, pick, done, read);
+    }
     if (g_halo != 3) return e.Cout % 64 == 0 && g_halo != 2 ? launch_halo_2d<2>(eb, nb, st, pick, done) : launch_halo_2d<1>(eb, nb, st, pick, done);
     return e.Cout % 64 == 0 ? launch_halo_n<2>(eb, nb, nseg, st, pick, done) : launch_halo_n<1>(eb, nb, nseg, st, pick, done);
 }

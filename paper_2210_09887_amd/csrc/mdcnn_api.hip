@@ -1609,6 +1609,19 @@ mdcnn_status mdcnn_conv_tiles(int Hp, int Wp, int k, int max_pixels, int max_sta
     return MDCNN_OK;
 }
 
+mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int in_flight, int shared, int* entries, int* couts, int* th, int* tw, long long* tiles) {
+    if (!entries || !couts || !th || !tw || !tiles) return fail(MDCNN_ERR_NULL, "rect_tiles: NULL argument");
+    if (Hp < 1 || Wp < 1 || (long long)Hp * Wp > (1ll << 30) || Cin < 64 || Cin > 4096 || Cout < 32 || Cout > 4096 || videos < 1 || videos > 128)
+        return fail(MDCNN_ERR_SIZE, "rect_tiles: argument out of range");
+    if (Cin % 64 || Cout % 32) return fail(MDCNN_ERR_SHAPE, "rect_tiles: layers of 64 n input and 32 n output channels");
+    int tn;
+    rect_choice(Hp, Wp, Cin, Cout, videos, !in_flight, shared != 0, &tn, entries);
+    *couts = 32 * tn;
+    rect_tile(Hp, Wp, *entries, th, tw, tiles);
+    *tiles *= Cout / *couts;
+    return MDCNN_OK;
+}
+
 mdcnn_status mdcnn_conv_border(int k, int stride, int pad, int in_extent, int out_extent, int* before, int* after) {
     if (!before || !after) return fail(MDCNN_ERR_NULL, "before/after is NULL");
     return border_1d(k, stride, pad, in_extent, out_extent, before, after);

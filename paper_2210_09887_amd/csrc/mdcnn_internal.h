@@ -375,6 +375,11 @@ hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st, bool* re
 extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // convolution tuning knobs
 // host-only: the rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);
+// host-only: rows of 16 source pixels a tile of m entries stages (conv_rect.h), its rectangle, and which tile a launch takes
+constexpr int rect_rows(int m) { return m <= 96 ? 10 : m == 128 ? 12 : m == 160 ? 14 : 20; }
+void rect_tile(int Hp, int Wp, int m, int* th_out, int* tw_out, long long* tiles_out);
+// alone: see launch_conv; shared: beside other edges in one launch
+void rect_choice(int Hp, int Wp, int Cin, int Cout, int videos, bool alone, bool shared, int* tn, int* m);
 hipError_t launch_pack_weights(const void* src, void* dst, int taps, int Cout, int Cin, hipStream_t st);
 // Post-processed update mask of an INPUT site over the rectangle (y0, x0, Hc, Wc) of its view.
 struct MaskJob {

@@ -298,9 +298,9 @@ def test_which_networks_run_in_rounds():
 
 
 def test_rectangular_tiles_cover_the_window_within_their_limits():
-    """mdcnn_conv_tiles (host only): the tile the halo-staged kernel would take.  It holds no more pixels than allowed,
-    its footprint no more than the staging buffer does, it is not larger than the window, no other rectangle within the
-    limits needs fewer tiles (brute force), and the shapes the benchmark networks meet come out as documented."""
+    """mdcnn_conv_tiles (host only): the rectangles of the halo-staged and the fp32 kernels.  One holds no more pixels than allowed,
+    its footprint no more than the staging buffer does, it is not larger than the window, and no other rectangle within the
+    limits needs fewer tiles (brute force)."""
     import itertools
     import numpy as np
     rng = np.random.default_rng(3)
@@ -314,9 +314,59 @@ def test_rectangular_tiles_cover_the_window_within_their_limits():
         best = min(-(-Hp // a) * -(-Wp // b) for a, b in itertools.product(range(1, min(Hp, sub) + 1), range(1, min(Wp, sub) + 1))
                    if a * b <= sub and (a + 2) * (b + 2) <= cap)
         assert tiles == best, (Hp, Wp, sub, cap, th, tw, tiles, best)
-    assert B.mdcnn_conv_tiles(66, 66, 3, 128, 192) == (11, 11, 36)          # stages 3 and 4 of the ResNet-18-style network
-    assert B.mdcnn_conv_tiles(258, 258, 3, 256, 352)[2] == 280               # its stage 1
+    assert B.mdcnn_conv_tiles(66, 66, 3, 128, 192) == (11, 11, 36)
+    assert B.mdcnn_conv_tiles(258, 258, 3, 256, 352)[2] == 280
     with pytest.raises(B.MdcnnError):
         B.mdcnn_conv_tiles(66, 66, 3, 128, 8)                                # nothing fits a staging buffer of 8 pixels
     with pytest.raises(B.MdcnnError):
         B.mdcnn_conv_tiles(66, 66, 3, 300, 192)                              # more pixels than a list segment
+
+
+RECT_ROWS = {64: 10, 96: 10, 128: 12, 160: 14, 256: 20}                     # rows of 16 pixels a tile stages
+
+
+def fewest_rect_tiles(Hp, Wp, entries):
+    """Fewest rectangles of at most `entries` pixels, 14 columns and the staged rows less two that cover the window."""
+    rows = RECT_ROWS[entries] - 2
+    return min(-(-Hp // min(rows, entries // tw, Hp)) * -(-Wp // tw) for tw in range(1, min(14, Wp) + 1))
+
+
+def test_rect_tiles_cover_the_window_within_their_limits():
+    """mdcnn_rect_tiles (host only): the tiles of the layers of 64 n input channels."""
+    import numpy as np
+    rng = np.random.default_rng(5)
+    windows = [(258, 258), (130, 130), (66, 66), (34, 34), (1, 1), (1, 300), (300, 1), (5, 5), (15, 14)]
+    windows += [(int(rng.integers(1, 300)), int(rng.integers(1, 300))) for _ in range(60)]
+    for Hp, Wp in windows:
+        for cin, cout in [(64, 64), (64, 96), (128, 128), (256, 512), (512, 32)]:
+            for videos, in_flight, shared in [(1, 0, 0), (1, 1, 0), (1, 0, 1), (8, 0, 0), (16, 1, 0)]:
+                m, couts, th, tw, tiles = B.mdcnn_rect_tiles(Hp, Wp, cin, cout, videos, in_flight, shared)
+                assert 1 <= th <= min(Hp, RECT_ROWS[m] - 2) and 1 <= tw <= min(Wp, 14) and th * tw <= m
+                assert cout % couts == 0 and couts in (32, 64)
+                assert tiles == -(-Hp // th) * -(-Wp // tw) * (cout // couts) == fewest_rect_tiles(Hp, Wp, m) * (cout // couts)
+                assert m != 256 or cin == 64                                 # (larger tiles do not split the channels)
+    for bad in [(0, 5, 64, 64), (5, 5, 96, 64), (5, 5, 64, 48), (5, 5, 0, 64), (5, 5, 64, 8192)]:
+        with pytest.raises(B.MdcnnError):
+            B.mdcnn_rect_tiles(*bad)
+
+
+def test_rect_tiles_of_one_layer_split_its_channels_alike():
+    """The split of the channels fixes the order of the sums: whatever the batch, whatever runs beside, it is the same."""
+    for Hp, Wp in [(114, 114), (130, 130), (162, 162), (200, 190), (210, 215), (258, 258), (40, 700)]:
+        for cout in (32, 64, 96, 128):
+            split = {B.mdcnn_rect_tiles(Hp, Wp, 64, cout, v, f, s)[0] != 256 for v in (1, 2, 7, 16) for f in (0, 1) for s in (0, 1)}
+            assert len(split) == 1, (Hp, Wp, cout)
+
+
+@pytest.mark.parametrize("view", [96, 128, 160, 192, 224, 256, 288, 320, 352])
+def test_small_layers_in_flight_keep_their_blocks(view):
+    """A launch among frames in flight has about a third of the 512 places of the GPU.  As long as its tiles of 64 entries fit
+    those, larger ones only make it longer: no layer of a small view is put onto fewer blocks than it has places for."""
+    for cin, stride in [(64, 2), (128, 4), (256, 8), (512, 16)]:
+        window = view // stride + 2
+        m, couts, _, _, tiles = B.mdcnn_rect_tiles(window, window, cin, cin, 1, True)
+        small = fewest_rect_tiles(window, window, 64) * (cin // couts)
+        if small <= 512 // 3:
+            assert m == 64, (window, cin, m, tiles, small)
+        else:
+            assert tiles >= 512 // 6, (window, cin, m, tiles, small)
