@@ -35,6 +35,12 @@ struct TiledCfg {
     static constexpr int MAIN_BYTES = SLAB_BYTES > C_BYTES ? SLAB_BYTES : C_BYTES;
     static constexpr int SMEM = MAIN_BYTES + (4 * BM + 8) * 4;      // + the entries' rows and a few counts
     static constexpr int TPS = kSegPixels / BM;    // tiles per list segment
+    // Blocks a compute unit is to hold: what fits its LDS, as far as the accumulators leave registers.  The kernel is bounded by
+    // the round trips of its gathers, which the other blocks cover.  Left to itself the compiler takes a few registers more than
+    // a wave's share: 16 videos, 128 -> 256 channels, stride 2 on 128 x 128 (64 x 64 tiles of 128 channels, 130 registers, three
+    // blocks) 99.3 us, with four 89.9; 64 -> 128 on 256 x 256 111 and 100 us, its 1x1 50 and 43.
+    static constexpr int FIT = 160 * 1024 / SMEM, ROOM = TM * TN == 1 ? 4 : TM * TN == 2 ? 3 : TM * TN == 4 ? 2 : 1;
+    static constexpr int WAVES = PIPE > 1 || FIT < 1 ? 1 : FIT < ROOM ? FIT : ROOM;
 };
 
 // Work item u of a 1-D grid -> (pixel tile m, cout tile n).  Work groups are
@@ -57,7 +63,7 @@ __device__ __forceinline__ void map_tile(int u, int NT, int xcd_map, int& m, int
 // blk, nblk: this block's number among the blocks that work on tiles of the edge.  Others make the by-products (1x1 and 3x3
 // layers; for others every tile makes them itself).  READ: the launch may read the destination out (EdgeDev::dY).
 template <int WM, int WN, int TM, int TN, int KC, int PIPE, bool READ>
-__device__ __forceinline__ void tiled_body(EdgeDev e, unsigned blk, unsigned nblk, TileGrid g, int work_items) {
+__device__ __forceinline__ void tiled_body(const EdgeDev& e, unsigned blk, unsigned nblk, TileGrid g, int work_items) {
     int NT = g.NT, xcd_map = g.p0;
     // (the descriptor's fields are fetched where they are used: all held from the start, bottleneck 44.0 against 43.6 us, HRNet-like
     // frame 478 against 473)

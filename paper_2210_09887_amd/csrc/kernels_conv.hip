@@ -44,7 +44,7 @@ static unsigned cap_blocks(long long b, long long cap) {
 
 // One edge per launch (blockIdx.z: stream of the batch); the tiles are those of conv_tiles.h.
 template <int WM, int WN, int TM, int TN, int KC, int PIPE>
-__global__ __launch_bounds__(256) void k_conv_mfma_tiled(TileGrid g, unsigned blocks, int work_items, EdgeBatch eb) {
+__global__ __launch_bounds__(256, (TiledCfg<WM, WN, TM, TN, KC, PIPE>::WAVES)) void k_conv_mfma_tiled(TileGrid g, unsigned blocks, int work_items, EdgeBatch eb) {
     extern __shared__ __align__(16) unsigned char smem[];
     const unsigned nblk = blocks - g.npub - g.ncopy;
     if (blockIdx.x >= nblk) side_block<f16>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
@@ -465,9 +465,12 @@ __global__ __launch_bounds__(256) void k_conv_mfma_f32(unsigned npub, unsigned n
 // frames 29.5 either way.  What bounds it: the round trips of a tile, flags,
 // deltas and pending rows.  (64 couts to a block with P updated through LDS in
 // whole rows has half the blocks and is slower: 15.9 us, 33 on the boxes.)
+// Five waves to a SIMD cover those round trips better than the four the
+// compiler's own choice of registers (102) leaves: 512 x 512 frames of 16 videos
+// 170 -> 161 us, of one 17.0 -> 16.6.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void k_conv_stem_mfma(unsigned npub, unsigned blocks, EdgeBatch eb) {
+__global__ __launch_bounds__(256, 5) void k_conv_stem_mfma(unsigned npub, unsigned blocks, EdgeBatch eb) {
     EdgeDev e = eb.d[blockIdx.z];                         // blockIdx.z: stream of the batch
     const unsigned nblk = blocks - npub;
     if (blockIdx.x >= nblk) {
