@@ -147,6 +147,12 @@ mdcnn_status mdcnn_conv_tiles(int Hp, int Wp, int k, int max_pixels, int max_sta
 mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int in_flight, int shared, int* entries, int* couts,
                               int* th, int* tw, long long* tiles);
 
+/* Host-only helper.  The tile of the gather kernel (fp16 layers on the matrix cores that are not 3x3 stride-1) for a list of at
+ * most `entries` entries (the pixels of the padded window, or of the source of an upsampling edge), in a launch of its own or
+ * (shared != 0) with other layers: *pixels x *couts.  Errors: MDCNN_ERR_SHAPE if Cout is no multiple of 32,
+ * MDCNN_ERR_SIZE for arguments out of range.  [Padded Convolutions] */
+mdcnn_status mdcnn_gather_tile(long long entries, int k, int Cout, int shared, int* pixels, int* couts);
+
 /* Host-only helper.  Width of the dilated border along one axis for a
  * convolution (k, stride, pad) from `in_extent` to `out_extent` pixels: how many
  * outputs before 0 / after out_extent-1 still read an in-view input.

@@ -28,7 +28,7 @@ STATE_UNSEEN, STATE_DIRTY = 1, 2
 STATUS_NAMES = {0: "OK", 1: "ERR_NULL", 2: "ERR_SHAPE", 3: "ERR_DTYPE", 4: "ERR_ALIGN",
                 5: "ERR_SIZE", 6: "ERR_STATE", 7: "ERR_HIP"}
 
-EXPORTS = ["mdcnn_conv_border", "mdcnn_conv_tiles", "mdcnn_rect_tiles", "mdcnn_buffer_bytes", "mdcnn_create_buffer", "mdcnn_destroy_buffer",
+EXPORTS = ["mdcnn_conv_border", "mdcnn_conv_tiles", "mdcnn_rect_tiles", "mdcnn_gather_tile", "mdcnn_buffer_bytes", "mdcnn_create_buffer", "mdcnn_destroy_buffer",
            "mdcnn_shift_camera", "mdcnn_set_crop", "mdcnn_layer_forward", "mdcnn_layer_forward_noalloc", "mdcnn_net_create", "mdcnn_net_destroy",
            "mdcnn_frame", "mdcnn_frame_crop", "mdcnn_frame_batch", "mdcnn_frame_batch_crop", "mdcnn_frame_plan", "mdcnn_frames", "mdcnn_frames_batch", "mdcnn_frames_crop", "mdcnn_frames_masked", "mdcnn_frames_plan", "mdcnn_frames_rounds", "mdcnn_input_mask", "mdcnn_read_view", "mdcnn_write_view", "mdcnn_set_option", "mdcnn_profile_read", "mdcnn_profile_read_launches", "mdcnn_bench_copy", "mdcnn_bench_mfma",
            "mdcnn_pack_weights", "mdcnn_last_error", "mdcnn_version"]
@@ -71,6 +71,7 @@ def lib():
         L.mdcnn_conv_border.argtypes = [C.c_int] * 5 + [ip, ip]
         L.mdcnn_conv_tiles.argtypes = [C.c_int] * 5 + [ip, ip, C.POINTER(C.c_longlong)]
         L.mdcnn_rect_tiles.argtypes = [C.c_int] * 7 + [ip] * 4 + [C.POINTER(C.c_longlong)]
+        L.mdcnn_gather_tile.argtypes = [C.c_longlong] + [C.c_int] * 3 + [ip, ip]
         L.mdcnn_buffer_bytes.argtypes = [C.POINTER(mdcnn_buffer_desc), C.POINTER(sz)]
         L.mdcnn_create_buffer.argtypes = [C.POINTER(mdcnn_buffer_desc), vp, sz, C.POINTER(vp)]
         L.mdcnn_destroy_buffer.argtypes = [vp]
@@ -210,6 +211,13 @@ def mdcnn_rect_tiles(Hp: int, Wp: int, Cin: int, Cout: int, videos: int = 1, in_
     v, n = [C.c_int() for _ in range(4)], C.c_longlong()
     _check(lib().mdcnn_rect_tiles(int(Hp), int(Wp), int(Cin), int(Cout), int(videos), int(in_flight), int(shared), *map(C.byref, v), C.byref(n)))
     return (*(x.value for x in v), n.value)
+
+
+def mdcnn_gather_tile(entries: int, k: int, Cout: int, shared: bool = False):
+    """(pixels, couts) of the tiles a layer of the gather kernel takes."""
+    v = C.c_int(), C.c_int()
+    _check(lib().mdcnn_gather_tile(int(entries), int(k), int(Cout), int(shared), *map(C.byref, v)))
+    return v[0].value, v[1].value
 
 
 def mdcnn_layer_forward_noalloc(buf: int, frame_ptr, forced_ptr, edges, outs, stream: int = 0):

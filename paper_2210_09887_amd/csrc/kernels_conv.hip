@@ -1054,21 +1054,22 @@ static hipError_t launch_tiled_p(const EdgeBatch& eb, int nb, long long max_entr
                 : launch_tiled<WM, WN, TM, TN, KC, 1>(eb, nb, max_entries, st, pick, read);
 }
 
+// The largest tile that still yields about one block per compute unit.  A 1x1 edge that shares its launch leaves the
+// places to the other one (two blocks to a compute unit, and a block more than that starts when the first are done:
+// 3x3 and 1x1, 64 -> 128 channels on 130 x 130 pixels, 536 blocks 18.0 us, 403 blocks 16.0) - but takes 256 x 64, which the
+// shared kernel does not carry, only where it fills the GPU by itself.
+int gather_choice(long long entries, int k, int Cout, bool shared) {
+    auto blocks = [&](int bm, int bn) { return (entries + bm - 1) / bm * (Cout / bn); };
+    const long long want = shared && k == 1 ? 112 : 224;
+    if (Cout % 128 == 0 && blocks(128, 128) >= want) return 4;
+    if (Cout % 128 == 0 && blocks(64, 128) >= want) return 5;
+    if (Cout % 64 == 0) return blocks(256, 64) >= 224 ? 1 : blocks(128, 64) >= want ? 2 : 3;
+    return 6;
+}
 template <int KC>
 static hipError_t launch_tiled_kc(const EdgeBatch& eb, int nb, long long max_entries, hipStream_t st, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];
-    auto blocks = [&](int bm, int bn) { return ((max_entries + bm - 1) / bm) * (e.Cout / bn); };
-    int tile = g_tile;
-    if (tile == 0) {
-        // the largest tile that still yields about one block per compute unit; a 1x1 edge that shares its launch leaves the
-        // places to the other one (two blocks to a compute unit, and a block more than that starts when the first are done:
-        // 3x3 and 1x1, 64 -> 128 channels on 130 x 130 pixels, 536 blocks 18.0 us, 403 blocks 16.0)
-        const long long want = pick && e.k == 1 ? 112 : 224;
-        if (e.Cout % 128 == 0 && blocks(128, 128) >= want) tile = 4;
-        else if (e.Cout % 128 == 0 && blocks(64, 128) >= want) tile = 5;
-        else if (e.Cout % 64 == 0) tile = blocks(256, 64) >= want ? 1 : blocks(128, 64) >= want ? 2 : 3;
-        else tile = 6;
-    }
+    const int tile = g_tile ? g_tile : gather_choice(max_entries, e.k, e.Cout, pick != nullptr);
     switch (tile) {
         case 1: if (e.Cout % 64 == 0) return launch_tiled_p<4, 1, 2, 2, KC>(eb, nb, max_entries, st, pick, read); break;    // 256 x 64
         case 2: if (e.Cout % 64 == 0) return launch_tiled_p<2, 2, 2, 1, KC>(eb, nb, max_entries, st, pick, read); break;    // 128 x 64

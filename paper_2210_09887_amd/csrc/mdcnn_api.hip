@@ -1622,6 +1622,16 @@ mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int
     return MDCNN_OK;
 }
 
+mdcnn_status mdcnn_gather_tile(long long entries, int k, int Cout, int shared, int* pixels, int* couts) {
+    if (!pixels || !couts) return fail(MDCNN_ERR_NULL, "gather_tile: NULL argument");
+    if (entries < 1 || entries > (1ll << 30) || k < 1 || k > 5 || Cout < 32 || Cout > 4096) return fail(MDCNN_ERR_SIZE, "gather_tile: argument out of range");
+    if (Cout % 32) return fail(MDCNN_ERR_SHAPE, "gather_tile: layers of 32 n output channels");
+    const int of[6][2] = {{256, 64}, {128, 64}, {64, 64}, {128, 128}, {64, 128}, {128, 32}}, *t = of[gather_choice(entries, k, Cout, shared != 0) - 1];
+    *pixels = t[0];
+    *couts = t[1];
+    return MDCNN_OK;
+}
+
 mdcnn_status mdcnn_conv_border(int k, int stride, int pad, int in_extent, int out_extent, int* before, int* after) {
     if (!before || !after) return fail(MDCNN_ERR_NULL, "before/after is NULL");
     return border_1d(k, stride, pad, in_extent, out_extent, before, after);

@@ -380,6 +380,8 @@ constexpr int rect_rows(int m) { return m <= 96 ? 10 : m == 128 ? 12 : m == 160 
 void rect_tile(int Hp, int Wp, int m, int* th_out, int* tw_out, long long* tiles_out);
 // alone: see launch_conv; shared: beside other edges in one launch
 void rect_choice(int Hp, int Wp, int Cin, int Cout, int videos, bool alone, bool shared, int* tn, int* m);
+// host-only: which tile of the gather kernel a launch takes (MDCNN_OPT_CONV_TILE's number)
+int gather_choice(long long entries, int k, int Cout, bool shared);
 hipError_t launch_pack_weights(const void* src, void* dst, int taps, int Cout, int Cin, hipStream_t st);
 // Post-processed update mask of an INPUT site over the rectangle (y0, x0, Hc, Wc) of its view.
 struct MaskJob {

@@ -358,6 +358,24 @@ def test_rect_tiles_of_one_layer_split_its_channels_alike():
             assert len(split) == 1, (Hp, Wp, cout)
 
 
+@pytest.mark.parametrize("k", [1, 3, 5])
+def test_gather_tiles_of_a_shared_launch_are_among_its_own(k):
+    """mdcnn_gather_tile (host only): an edge asked for by a shared launch takes a tile that launch does not carry (256 x 64) only
+    where it would alone as well - 224 blocks of it, about one per compute unit - and never a smaller one than alone."""
+    for entries in [1, 64, 6144, 128 * 112, 192 * 192, 256 * 112, 256 * 223, 256 * 224, 258 * 258, 10 ** 6]:
+        for cout in (32, 64, 96, 128, 192, 256, 320, 512):
+            alone, shared = B.mdcnn_gather_tile(entries, k, cout), B.mdcnn_gather_tile(entries, k, cout, True)
+            for pixels, couts in (alone, shared):
+                assert cout % couts == 0 and 256 % pixels == 0
+            assert shared[0] * shared[1] >= alone[0] * alone[1] and (k == 1 or shared == alone), (entries, cout)
+            if (256, 64) in (alone, shared):
+                assert alone == shared and -(-entries // 256) * (cout // 64) >= 224, (entries, cout)
+    assert B.mdcnn_gather_tile(192 * 192, 1, 64, True) == (128, 64)
+    for bad in [(0, 1, 64), (5, 0, 64), (5, 1, 48), (5, 1, 8192)]:
+        with pytest.raises(B.MdcnnError):
+            B.mdcnn_gather_tile(*bad)
+
+
 @pytest.mark.parametrize("view", [96, 128, 160, 192, 224, 256, 288, 320, 352])
 def test_small_layers_in_flight_keep_their_blocks(view):
     """A launch among frames in flight has about a third of the 512 places of the GPU.  As long as its tiles of 64 entries fit
