@@ -819,11 +819,11 @@ size_t crop_pixels(const mdcnn_buffer* b) {                // sites without crop
 bool whole_view(const mdcnn_buffer* b) { return crop_pixels(b) == (size_t)b->d.H * b->d.W; }
 
 // One round of a plan for n videos (n <= kMaxBatch): sites[b] are the sites of video b as the frame sees them.
-// Operations the multi-edge kernels do not take get a launch each.  outs[b][i]: where OUTPUT site i of video b is to be read
+// Operations the multi-edge kernels do not take get a launch each.  outs[b * sites + i]: where OUTPUT site i of video b is to be read
 // out to; (*read)[i] is set if a launch of the round has done so.
 mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets, int n, const std::vector<mdcnn_buffer* const*>& sites,
                        const void* const* frames, const uint8_t* const* forced, hipStream_t st, bool alone, const FillJob* jobs = nullptr,
-                       const std::vector<int>* fills = nullptr, const std::vector<void*>* outs = nullptr, std::vector<char>* read = nullptr) {
+                       const std::vector<int>* fills = nullptr, void* const* outs = nullptr, std::vector<char>* read = nullptr) {
     static thread_local Step1Batch sb;                     // 3.4 to 4 KiB each: kept off the stack
     static thread_local EdgeBatch eb;
     static thread_local Step1Multi sm;
@@ -893,7 +893,7 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 const int dst = op.edge >= 0 ? net->edst[(size_t)op.edge] : -1;
                 const bool reads = outs && op.reads && !sites[0][dst]->d.crops;
                 for (int b = 0; b < n && reads; ++b) {
-                    eb.d[b].dY = outs[b][(size_t)dst];
+                    eb.d[b].dY = outs[(size_t)b * net->sites.size() + (size_t)dst];
                     eb.d[b].s_relu = sites[(size_t)b][dst]->d.relu;
                 }
                 bool done = false;
@@ -997,14 +997,17 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
     mdcnn_buffer* ins[kMaxBatch];
     const mdcnn_conv_desc* edges[kMaxBatch];
     mdcnn_buffer* const* outs[kMaxBatch];
-    std::vector<char> read(net->sites.size(), 0);          // OUTPUT sites the launch of their last edge has read out
-    std::vector<std::vector<void*>> out_of((size_t)n, std::vector<void*>(net->sites.size(), nullptr));
+    const size_t n_sites = net->sites.size();
+    static thread_local std::vector<char> read;            // OUTPUT sites the launch of their last edge has read out
+    static thread_local std::vector<void*> out_of;         // where they go, video by video
+    read.assign(n_sites, 0);
+    out_of.assign(n * n_sites, nullptr);
     for (int b = 0; b < n; ++b) {
         char* o = (char*)outs_dev[b];
-        for (size_t i = 0; i < net->sites.size(); ++i) {
+        for (size_t i = 0; i < n_sites; ++i) {
             const mdcnn_buffer* s = nets[b]->sites[i];
             if (s->d.kind != MDCNN_SITE_OUTPUT) continue;
-            out_of[(size_t)b][i] = o;
+            out_of[b * n_sites + i] = o;
             o += crop_pixels(s) * s->d.C * esize(s->d.dtype);
         }
     }
@@ -1050,7 +1053,7 @@ mdcnn_status frame_batch(mdcnn_net* const* nets, int n, const void* const* frame
         if (s0->d.kind != MDCNN_SITE_OUTPUT || read[i]) continue;
         for (int b = 0; b < n; ++b) {
             rb.s[b] = nets[b]->sites[i]->dev;
-            rb.dst[b] = out_of[(size_t)b][i];
+            rb.dst[b] = out_of[b * n_sites + i];
         }
         hipError_t err = timed(kClsReadout, st, [&] { return launch_read_outputs(rb, n, s0->d.crops ? MDCNN_VIEW_CROP_OUT : MDCNN_VIEW_OUT, st); });
         if (err != hipSuccess) return fail(MDCNN_ERR_HIP, "readout launch: %s", hipGetErrorString(err));

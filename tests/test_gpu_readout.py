@@ -50,3 +50,29 @@ def test_frame_output_is_the_view(dtype, chans, k, stride, H, W):
 def test_networks(config, H, W, batch):
     from inputs import build_net
     check(build_net(config, H=H, W=W), batch)
+
+
+def test_networks_in_turn_on_one_thread():
+    """Networks of two to many sites, alone and in a batch, frame by frame in turn: what a call has read out is its own affair."""
+    from gpu_harness import dev
+    from inputs import build_net
+    from inputs.nets import tiny_net
+    from paper_2210_09887_amd import binding as B
+    from paper_2210_09887_amd.runtime import GpuBatch, GpuNet
+    nets = [build_net(4, H=64, W=64), tiny_net("f16", 31, 45, (64, 64), k=3, stride=1, theta=0.05, seed=1, total_stride=1),
+            build_net(5, H=16, W=16), tiny_net("f32", 9, 9, (3, 5), k=3, stride=1, theta=0.05, seed=2, total_stride=1)]
+    gs = [GpuNet(nets[0]), GpuNet(nets[1]), GpuBatch(nets[2], 3), GpuNet(nets[3])]
+    rng = np.random.default_rng(8)
+    try:
+        for t in range(3):
+            for net, g in zip(nets, gs):
+                batch = len(getattr(g, "streams", []))
+                fs = [dev(rng.normal(0, 1, (net.H, net.W, net.sites[0].C)).astype(net.np_dtype)) for _ in range(max(batch, 1))]
+                outs = g.frame(fs, [0] * batch, [0] * batch)[0] if batch else [g.frame(fs[0], 0, 0)[0]]
+                for b, s in enumerate(g.streams if batch else [g]):
+                    for o, i in zip(s.split_outputs(outs[b]), s.terminals):
+                        want = s.read(i, B.MDCNN_VIEW_OUT)
+                        assert np.array_equal(o.cpu().numpy().reshape(want.shape), want), f"frame {t} {net.name} video {b} site {i}"
+    finally:
+        for g in gs:
+            g.close()
