@@ -376,6 +376,35 @@ def test_gather_tiles_of_a_shared_launch_are_among_its_own(k):
             B.mdcnn_gather_tile(*bad)
 
 
+def test_batches_in_flight_take_tiles_by_what_they_hold():
+    """In a full GPU a launch costs its row tiles of 32 pixels and, per tile, weights and epilogue: no other size has fewer
+    tiles and no more row tiles than the one taken."""
+    def cost(Hp, Wp, m):                                                    # the rectangle as rect_tile picks it: fewest tiles, then the smaller footprint
+        best = None
+        for tw in range(1, min(14, Wp) + 1):
+            th = min(m // tw, RECT_ROWS[m] - 2, Hp)
+            down, across = -(-Hp // th), -(-Wp // tw)
+            th = -(-Hp // down)
+            key = (down * across, (th + 2) * (tw + 2))
+            if best is None or key < best[0]:
+                best = key, -(-th * tw // 32) * down * across
+        return best[0][0], best[1]
+
+    for view in range(96, 640, 16):
+        for cin, stride in [(64, 4), (128, 8), (256, 16), (512, 32), (512, 16)]:
+            w = view // stride + 2
+            for videos in (8, 16):
+                m, couts, _, _, tiles = B.mdcnn_rect_tiles(w, w, cin, cin, videos, True)
+                of = {s: cost(w, w, s) for s in (64, 96, 128)}
+                if m == 256 or any(t * (cin // couts) * videos * 3 <= 512 for t, _ in of.values()):
+                    continue
+                assert tiles == of[m][0] * (cin // couts)
+                for s, (t, rows) in of.items():
+                    assert not (t < of[m][0] and rows <= of[m][1]), (w, cin, videos, m, s)
+    # weights: 512 channels on 34 x 34, 96 tiles of 128 instead of 160 of 64
+    assert B.mdcnn_rect_tiles(34, 34, 512, 512, 8, True)[0] == 128
+
+
 @pytest.mark.parametrize("view", [96, 128, 160, 192, 224, 256, 288, 320, 352])
 def test_small_layers_in_flight_keep_their_blocks(view):
     """A launch among frames in flight has about a third of the 512 places of the GPU.  As long as its tiles of 64 entries fit
