@@ -1333,7 +1333,8 @@ static hipError_t launch_halo_n(const EdgeBatch& eb, int nb, long long nseg, hip
             if (c64 && worst <= HaloCfg<1, 2, 2, 4, TN, 64, 16, 3>::CAP) return launch_halo_t<1, 2, 2, 4, TN, 64, 16>(eb, nb, nseg, st, pick);
             if (c32 && worst <= HaloCfg<1, 2, 2, 4, TN, 32, 12, 3>::CAP) return launch_halo_t<1, 2, 2, 4, TN, 32, 12>(eb, nb, nseg, st, pick);
         } else if (nsub == 2) {
-            if (c64 && worst <= HaloCfg<2, 1, 4, 4, TN, 64, 11, 3>::CAP) return launch_halo_t<2, 1, 4, 4, TN, 64, 11>(eb, nb, nseg, st, pick);
+            // (split four ways as the rectangles are; 32 couts whatever TN: with 64 the accumulators of four row tiles leave no registers)
+            if (c64 && worst <= HaloCfg<2, 1, 4, 4, 1, 64, 11, 3>::CAP) return launch_halo_t<2, 1, 4, 4, 1, 64, 11>(eb, nb, nseg, st, pick);
             if (c32 && worst <= HaloCfg<2, 2, 2, 2, TN, 32, 9, 3>::CAP) return launch_halo_t<2, 2, 2, 2, TN, 32, 9>(eb, nb, nseg, st, pick);
         } else {
             if (c64 && worst <= HaloCfg<4, 1, 4, 2, TN, 64, 9, 3>::CAP) return launch_halo_t<4, 1, 4, 2, TN, 64, 9, 9>(eb, nb, nseg, st, pick);

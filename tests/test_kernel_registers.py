@@ -73,3 +73,11 @@ def test_stems_run_five_waves_to_a_simd(meta):
     assert len(stems) == 2
     for k in stems:
         assert waves_per_simd(k) >= 5 and k[".vgpr_spill_count"] == 0, (k[".name"], k[".vgpr_count"])
+
+
+def test_convolutions_the_rules_choose_from_keep_their_registers(meta):
+    """Nothing in scratch memory but in tiles that only options reach: 256-entry index ranges of 64 couts, gather tiles of eight
+    accumulators or two stages."""
+    for name, k in meta.items():
+        option = re.search(r"k_conv_haloILi1ELi2ELi2ELi4ELi2E|k_conv_mfma_tiledILi\d+ELi\d+ELi\d+ELi\d+ELi\d+ELi2E|k_conv_mfma_tiledILi2ELi2ELi2ELi4E", name)
+        assert option or k[".vgpr_spill_count"] == 0, (name, k[".vgpr_spill_count"])
