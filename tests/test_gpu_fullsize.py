@@ -61,8 +61,9 @@ def test_config3_full_512_teacher_forced():
 
 
 def test_config3_full_512_teacher_forced_whole_segment_tiles():
-    """The same with whole-segment convolution tiles everywhere (MDCNN_OPT_CONV_HALO_SUB = 1, what bench.py sets for its
-    batch legs): the 128- to 512-channel layers then run without a K split, two frames."""
+    """The same with the largest convolution tiles everywhere (MDCNN_OPT_CONV_HALO_SUB = 1), two frames: 160 entries for the 128-
+    to 512-channel layers, which frames this small take for few of them, 256 for 64 channels.  (The tile of 256 entries, the one
+    that does not split the channels, is what the 64-channel layers take at this size anyway: the test above has it too.)"""
     import gpu_harness as H
     from paper_2210_09887_amd import binding as B
     net = build_net(3)

@@ -327,7 +327,7 @@ def test_conv_kernel_shapes(cin, cout, H, W, k, stride):
 @pytest.mark.parametrize("cin,cout,H,W,sub", [
     (64, 64, 40, 56, 1),           # whole-segment rectangles, no K split, 64-channel chunk; ragged last tiles in both directions
     (32, 32, 24, 88, 1),           # the same with a 32-channel chunk and 32-cout tiles
-    (128, 64, 40, 40, 2),          # half-segment rectangles, K split two ways, two chunks
+    (128, 64, 40, 40, 2),          # half-segment rectangles, K split four ways, two chunks
     (96, 64, 33, 47, 2),           # 32-channel chunks (three of them), odd window
     (256, 128, 16, 24, 4),         # quarter-segment rectangles, K split four ways, four chunks, two cout tiles
     (32, 32, 9, 70, 4),            # quarter segments with 32-channel chunks; a window lower than a tile is high
@@ -372,8 +372,8 @@ def test_halo_kernel_on_rectangular_tiles(cin, cout, H, W, sub):
         B.mdcnn_set_option(B.MDCNN_OPT_CONV_HALO, 1)
         B.mdcnn_set_option(B.MDCNN_OPT_CONV_HALO_SUB, 0)
     log(f"[rectangular tiles] {cin}->{cout} {H}x{W} split {sub}: worst {worst:.3e}")
-    if sub in (2, 4):  # (whole-segment tiles: the rectangles do not split K, the index ranges do - other sums; left to
-                       # themselves the two may also choose different splits)
+    if sub in (2, 4):  # (whole segments: index ranges split K two ways, rectangles four ways above 64 channels and not at
+                       # all at 64 or 32 n - other sums; left to themselves the two may also choose different splits)
         for t, (a, b) in enumerate(zip(rect, ranges)):
             assert np.array_equal(a, b), f"frame {t}: rectangular and index-range tiles differ"
 

@@ -1,6 +1,7 @@
 """3 x 3 stride-1 fp16 layers of 64 n input channels (conv_rect.h): every tile against the oracle, and the same bits whatever the
 tile where the channels are split four ways - windows lower or narrower than a tile, ragged last tiles, numbers of cout tiles
-that are no power of two, one to five chunks, frames in flight (which take other tiles than a frame alone)."""
+that are no power of two, one to five chunks, frames in flight where they take other tiles than a frame alone.  The rule itself
+takes tiles of 64 entries on small windows; the last two cases are the smallest for which it takes 96, of 32 and of 64 couts."""
 import numpy as np
 import pytest
 
@@ -20,13 +21,15 @@ def frames_of(cin, H, W, n=3):
     return out
 
 
-@pytest.mark.parametrize("cin,cout,H,W", [(64, 64, 25, 41), (64, 32, 3, 90), (64, 192, 12, 12), (128, 96, 17, 29), (192, 64, 40, 9),
-                                          (256, 192, 14, 15), (320, 64, 1, 30)])
-def test_tiles_agree(cin, cout, H, W):
+@pytest.mark.parametrize("cin,cout,H,W,entries,couts", [
+    (64, 64, 25, 41, 64, 32), (64, 32, 3, 90, 64, 32), (64, 192, 12, 12, 64, 32), (128, 96, 17, 29, 64, 32), (192, 64, 40, 9, 64, 32),
+    (256, 192, 14, 15, 64, 32), (320, 64, 1, 30, 64, 32), (64, 96, 64, 73, 96, 32), (64, 192, 64, 73, 96, 64)])
+def test_tiles_agree(cin, cout, H, W, entries, couts):
     import gpu_harness as H_
     from inputs.nets import tiny_net
     from paper_2210_09887_amd import binding as B
     from paper_2210_09887_amd.runtime import GpuNet
+    assert B.mdcnn_rect_tiles(H + 2, W + 2, cin, cout)[:2] == (entries, couts)
     net = tiny_net("f16", H, W, (cin, cout), k=3, stride=1, theta=0.05, seed=cin + cout + H, total_stride=1)
     frames, shifts = frames_of(cin, H, W), [(0, 0), (0, 0), (0, -1)]
     outs = {}
@@ -45,12 +48,16 @@ def test_tiles_agree(cin, cout, H, W):
                 assert np.array_equal(a, b), f"split {sub}, frame {t}"
 
 
-@pytest.mark.parametrize("cin,cout,H,W", [(64, 64, 60, 60), (128, 128, 66, 70), (512, 64, 40, 34)])
-def test_frames_in_flight_take_other_tiles(cin, cout, H, W):
+@pytest.mark.parametrize("cin,cout,H,W,alone,flying", [(64, 96, 55, 64, (64, 32), (96, 32)), (64, 256, 73, 52, (96, 64), (128, 64)),
+                                                        (64, 96, 55, 97, (96, 32), (128, 32)), (512, 256, 73, 52, (96, 64), (64, 64)),
+                                                        (192, 256, 76, 97, (160, 64), (128, 64))])
+def test_frames_in_flight_take_other_tiles(cin, cout, H, W, alone, flying):
     import gpu_harness as H_
     from inputs.nets import tiny_net
+    from paper_2210_09887_amd import binding as B
     from paper_2210_09887_amd.runtime import GpuNet
-    net = tiny_net("f16", H, W, (cin, cout, cout), k=3, stride=1, theta=0.05, seed=cin + cout + H, total_stride=1)
+    assert (B.mdcnn_rect_tiles(H + 2, W + 2, cin, cout)[:2], B.mdcnn_rect_tiles(H + 2, W + 2, cin, cout, in_flight=True)[:2]) == (alone, flying)
+    net = tiny_net("f16", H, W, (cin, cout, 32), k=3, stride=1, theta=0.05, seed=cin + cout + H, total_stride=1)
     frames = [H_.dev(f) for f in frames_of(cin, H, W, 6)]
     dy, dx = [0, 0, 1, 0, 0, -1], [0, 0, -1, 0, 1, 0]
     a, b = GpuNet(net), GpuNet(net)
