@@ -15,11 +15,13 @@ namespace mdcnn {
 // register in between (buffer loads with the lds flag: a wave places 1 KiB at a
 // time, 8 pixels).  A pixel out of view or not updated is loaded from beyond the
 // end of the delta map, which places zeros, and that is all the masking the taps
-// need.  Rows of 128 bytes would put a column of pixels on the same banks, and
-// these loads cannot pad a row, so piece p of pixel x sits at p ^ (x % 8): the
-// lane that fetches a piece asks for the one that belongs there.  With rows of
-// 16 pixels the place of a tap's piece is one of three registers (dx) plus a
-// constant (dy).
+// need.  Rows of 128 bytes would put the same piece of every other pixel on the
+// same banks, and these loads cannot pad a row, so piece p of pixel x sits at
+// p ^ (x % 8): the lane that fetches a piece asks for the one that belongs
+// there.  Eight neighbouring pixels are apart, sixteen are not (pixels x and x + 8
+// share their banks), nor are the rows of a tile: 4.9 to 6.7 conflict cycles per
+// LDS instruction are left.  With rows of 16 pixels the place of a tap's piece is
+// one of three registers (dx) plus a constant (dy).
 //
 // The four waves are WMV (groups of row tiles) x WK (16-channel blocks of a
 // chunk); a wave multiplies its row tiles x TN 32 x 32 accumulators over its
@@ -35,7 +37,7 @@ namespace mdcnn {
 // a 20 us tile, 93 % of what a loop of nothing else reaches), instruction latency and round trips around the loop where they
 // are few: descriptor and flags 0.9 us, rows 0.6, ranks 0.35, sums and pending update 1.0 for 96 entries.  Before, with rows
 // staged through registers a chunk at a time and the K loop at 49 % of the pipe: ResNet-18-style 512 x 512 frame 425 -> 387
-// us, 30 frames 7.11 -> 6.91 ms, 16 videos 13.4 -> 13.0 ms, HRNet-like 384 x 288 frame 565 -> 526 us (launch_rect: by layer).
+// us, 30 frames 7.11 -> 6.91 ms, 16 videos 13.4 -> 13.0 ms, HRNet-like 384 x 288 frame 565 -> 520 us (rect_choice: by layer).
 // ---------------------------------------------------------------------------
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4_t raw_rsrc(const void* p, unsigned bytes) {
