@@ -73,7 +73,7 @@ def test_config3_full_512_teacher_forced_whole_segment_tiles():
         worst = H.teacher_forced(net, seq.frames, seq.shifts, log=log)
     finally:
         B.mdcnn_set_option(B.MDCNN_OPT_CONV_HALO_SUB, 0)
-    log(f"config 3 teacher-forced, full size, whole-segment tiles: worst fp error {worst:.2e}")
+    log(f"config 3 teacher-forced, full size, largest tiles: worst fp error {worst:.2e}")
 
 
 def test_config3_full_512_followed():
@@ -361,8 +361,8 @@ def test_full_size_frames_in_flight(cfg, n):
 
 
 def test_config3_full_512_batch_with_frames_in_flight():
-    """Two videos of the headline workload through mdcnn_frames_batch (frames of both in flight, whole-segment convolution
-    tiles as bench.py uses them for its batch legs) equal the same videos frame by frame through mdcnn_frame_batch, bit for
+    """Two videos of the headline workload through mdcnn_frames_batch (frames of both in flight, the largest convolution
+    tiles: 160 entries, 256 for 64 channels) equal the same videos frame by frame through mdcnn_frame_batch, bit for
     bit in every output, reset decision and state view; the frame-by-frame outputs of video 0 are held against the oracle
     with the default tiles by the tests above."""
     import gpu_harness as H

@@ -325,17 +325,17 @@ def test_conv_kernel_shapes(cin, cout, H, W, k, stride):
 
 
 @pytest.mark.parametrize("cin,cout,H,W,sub", [
-    (64, 64, 40, 56, 1),           # whole-segment rectangles, no K split, 64-channel chunk; ragged last tiles in both directions
-    (32, 32, 24, 88, 1),           # the same with a 32-channel chunk and 32-cout tiles
-    (128, 64, 40, 40, 2),          # half-segment rectangles, K split four ways, two chunks
-    (96, 64, 33, 47, 2),           # 32-channel chunks (three of them), odd window
-    (256, 128, 16, 24, 4),         # quarter-segment rectangles, K split four ways, four chunks, two cout tiles
+    (64, 64, 40, 56, 1),           # rectangles of 256 entries, no K split, one 64-channel chunk; ragged last tiles in both directions
+    (32, 32, 24, 88, 1),           # whole-segment rectangles of a 32-channel chunk, 32-cout tiles
+    (128, 64, 40, 40, 2),          # rectangles of 128 entries, K split four ways, two chunks
+    (96, 64, 33, 47, 2),           # half-segment rectangles, 32-channel chunks (three of them), odd window
+    (256, 128, 16, 24, 4),         # rectangles of 64 entries, K split four ways, four chunks
     (32, 32, 9, 70, 4),            # quarter segments with 32-channel chunks; a window lower than a tile is high
     (64, 64, 72, 96, 0),           # the library's own choice on a window of more than 4096 pixels
 ])
 def test_halo_kernel_on_rectangular_tiles(cin, cout, H, W, sub):
-    """The halo-staged kernel with rectangular tiles in each of its configurations, forced for windows the library would
-    give index-range tiles: a dense frame, a sparse frame and a frame after a camera shift, teacher-forced against the
+    """The 3x3 kernels on rectangular tiles (k_conv_rect, and k_conv_halo for channels that are no multiple of 64) in each
+    configuration, forced where the library would take another: a dense frame, a sparse frame and a frame after a camera shift, teacher-forced against the
     oracle (masks, lists and compute lists bit for bit), and the same frames with index-range tiles: the same bits in
     every output (both walk the chunks and taps of an entry in the same order)."""
     import gpu_harness as H_
