@@ -102,8 +102,8 @@ typedef struct mdcnn_net mdcnn_net;
  * the sites it joins, 16-byte aligned.  k == 0: identity edge (w_dev ignored,
  * stride 1, pad 0, up 0, Cin == Cout).  up > 0 requires k == 1, stride 1, pad 0.
  * w_packed_dev: NULL, or the copy of w_dev that mdcnn_pack_weights wrote (fp16,
- * Cin % 16 == 0); with it 3x3 stride-1 edges run on the faster matrix-core
- * kernel.  Both copies must stay valid and equal while the edge is in use. */
+ * Cin % 16 == 0); with it 3x3 edges of stride 1 and, where Cin % 32 == 0, 2 run on
+ * the faster matrix-core kernel.  Both copies must stay valid and equal while the edge is in use. */
 typedef struct {
     int k, stride, pad;
     int Cin, Cout;
@@ -147,7 +147,7 @@ mdcnn_status mdcnn_conv_tiles(int Hp, int Wp, int k, int max_pixels, int max_sta
 mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int in_flight, int shared, int* entries, int* couts,
                               int* th, int* tw, long long* tiles);
 
-/* Host-only helper.  The tile of the gather kernel (fp16 layers on the matrix cores that are not 3x3 stride-1) for a list of at
+/* Host-only helper.  The tile of the gather kernel (fp16 layers on the matrix cores that are not 3x3 with packed weights) for a list of at
  * most `entries` entries (the pixels of the padded window, or of the source of an upsampling edge), in a launch of its own or
  * (shared != 0) with other layers: *pixels x *couts.  Errors: MDCNN_ERR_SHAPE if Cout is no multiple of 32,
  * MDCNN_ERR_SIZE for arguments out of range.  [Padded Convolutions] */

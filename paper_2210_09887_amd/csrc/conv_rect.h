@@ -1,4 +1,4 @@
-// Convolution tile of the 3 x 3 stride-1 fp16 layers of 64 n input channels.
+// Convolution tile of the 3 x 3 fp16 layers of 64 n input channels, and of those of 32 n with stride 2.
 #pragma once
 
 #include <type_traits>
@@ -8,10 +8,11 @@
 namespace mdcnn {
 
 // ---------------------------------------------------------------------------
-// A tile is a th x tw rectangle of the padded window (tw <= 14, th * tw <= M) x
-// BN couts, weights in the packed order [tap][cin/16][cout][16] (k_pack_weights).
-// The source pixels it reads, (th + 2) x (tw + 2) of them in rows of 16, are
-// staged per 64-channel chunk, 128 bytes a pixel: global memory -> LDS without a
+// A tile is a th x tw rectangle of the padded window (tw <= 14, stride 2: 7;
+// th * tw <= M) x BN couts, weights in the packed order [tap][cin/16][cout][16]
+// (k_pack_weights).  The source pixels it reads, (th + 2) x (tw + 2) of them
+// (stride 2: (2 th + 1) x (2 tw + 1)) in rows of 16, are staged per 64-channel
+// chunk, 128 bytes a pixel (32 channels, 64 bytes where 64 do not divide): global memory -> LDS without a
 // register in between (buffer loads with the lds flag: a wave places 1 KiB at a
 // time, 8 pixels).  A pixel out of view or not updated is loaded from beyond the
 // end of the delta map, which places zeros, and that is all the masking the taps
@@ -65,20 +66,26 @@ __device__ __forceinline__ void spread() {
     }
 }
 
-template <int WMV_, int WK_, int TM_, int TN_, int NLD_, int RING_, int PT_, int MINB_, int NBUF_ = 2>
+// S: stride of the convolution; KB: 16-channel blocks of a chunk (4, or 2 where the channels are no multiple of 64).
+template <int WMV_, int WK_, int TM_, int TN_, int NLD_, int RING_, int PT_, int MINB_, int NBUF_ = 2, int S_ = 1, int KB_ = 4>
 struct RectCfg {
-    static constexpr int WMV = WMV_, WK = WK_, TM = TM_, TN = TN_, NLD = NLD_, RING = RING_, PT = PT_, MINB = MINB_, NBUF = NBUF_;
+    static constexpr int WMV = WMV_, WK = WK_, TM = TM_, TN = TN_, NLD = NLD_, RING = RING_, PT = PT_, MINB = MINB_, NBUF = NBUF_, S = S_, KB = KB_;
     static constexpr int M = 32 * WMV * TM, BN = 32 * TN;
-    static constexpr int MB = 4 / WK;                // 16-channel blocks of a chunk per wave
+    static constexpr int MB = KB / WK;               // 16-channel blocks of a chunk per wave
     static constexpr int NS = 9 * MB;                // steps per chunk and wave
-    static constexpr int ROWS = 2 * NLD;             // staged rows of 16 pixels
-    static constexpr int BUF = ROWS * 2048;          // bytes of a staged chunk
+    static constexpr int PXB = 32 * KB;              // bytes of a staged pixel
+    static constexpr int ROWB = 16 * PXB;            //       of a staged row of 16 pixels
+    static constexpr int LPP = PXB / 16;             // pieces of a pixel, a lane each
+    static constexpr int WPR = ROWB / 1024;          // waves that stage a row together
+    static constexpr int RPJ = 4 / WPR;              // rows the four waves stage at a time
+    static constexpr int ROWS = RPJ * NLD;
+    static constexpr int BUF = ROWS * ROWB;          // bytes of a staged chunk
     static constexpr int LDC = BN + 4;               // partial-sum row, floats
     static constexpr int CROWS = 32 * WMV * PT;      // entries per pass of the epilogue
     static constexpr int SUM_BYTES = WK * CROWS * LDC * 4;
     static constexpr int MAIN_BYTES = NBUF * BUF > SUM_BYTES ? NBUF * BUF : SUM_BYTES;
     static constexpr int SMEM = MAIN_BYTES + M * 4 + 64 * 2;
-    static_assert(WMV * WK == 4 && (2 * NS) % RING == 0 && 2 * NS > RING, "four waves; static ring slots over a pair of chunks");
+    static_assert(WMV * WK == 4 && KB % WK == 0 && (2 * NS) % RING == 0 && 2 * NS > RING, "four waves; static ring slots over a pair of chunks");
     static_assert((RING - 1) * TN + NLD < 63, "the counter of outstanding loads has six bits");
 };
 
@@ -93,13 +100,22 @@ struct RectTiles {
     using T128 = RectCfg<1, 4, 4, TN, 6, TN == 1 ? 6 : 3, 2, 2>;
     using T160 = RectCfg<1, 4, 5, TN, 7, 9, 3, 1>;
     using T256 = RectCfg<4, 1, 2, TN, 10, 6, 2, 2, 1>;       // 64 input channels only
+    // stride 2, 64 entries: 64 input channels, 64 n, 32 n
+    using S2One = RectCfg<1, 4, 2, TN, 10, TN == 4 ? 3 : 9, 1, 2, 1, 2>;
+    using S2 = RectCfg<1, 4, 2, TN, 8, TN == 4 ? 3 : 9, 1, 2, 2, 2>;
+    using S2Half = RectCfg<2, 2, 1, TN, 5, 9, 1, 2, 2, 2, 2>;
 };
+
+template <typename Cfg>
+constexpr int rect_body_number() {
+    return Cfg::S == 1 ? multi_rect_body(Cfg::M, Cfg::TN) : multi_rect_body(Cfg::KB == 2 ? kRectS2Half : Cfg::NBUF == 1 ? kRectS2One : kRectS2, Cfg::TN);
+}
 
 // blk: the tile.  READ: the launch may read the destination out (EdgeDev::dY).
 template <typename Cfg, bool READ>
 __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const TileGrid& g) {
     constexpr int WMV = Cfg::WMV, WK = Cfg::WK, TM = Cfg::TM, TN = Cfg::TN, NLD = Cfg::NLD, MB = Cfg::MB, NS = Cfg::NS, D = Cfg::RING,
-                  M = Cfg::M, BN = Cfg::BN, LDC = Cfg::LDC, PT = Cfg::PT;
+                  M = Cfg::M, BN = Cfg::BN, LDC = Cfg::LDC, PT = Cfg::PT, S = Cfg::S, PXB = Cfg::PXB, ROWB = Cfg::ROWB, LPP = Cfg::LPP, WPR = Cfg::WPR, RPJ = Cfg::RPJ;
     extern __shared__ __align__(16) unsigned char smem[];
     float* const sC = reinterpret_cast<float*>(smem);
     int* const s_ent = reinterpret_cast<int*>(smem + Cfg::MAIN_BYTES);      // entry -> ly << 4 | lx
@@ -118,7 +134,7 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WMV, wk = wave / WMV;
     const int r32 = lane & 31, kh = lane >> 5;
-    const int nchunks = Cfg::NBUF > 1 ? Cin / 64 : 1;
+    const int nchunks = Cfg::NBUF > 1 ? Cin / (16 * Cfg::KB) : 1;
     const unsigned row = (unsigned)Cin * 2u;         // bytes of a source pixel
     constexpr unsigned kOutside = 0x80000000u;       // past the end of every tensor
     // (the host checks that both tensors are smaller than 2 GiB)
@@ -136,22 +152,25 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const 
     f16x8 fa[D][TN];                                  // weight fragments in flight
     auto load_a = [&](int slot, int c, int i) {       // step i of chunk c; i may run into the next chunk
         const int cc = i < NS ? c : (c + 1 < nchunks ? c + 1 : c), ii = i < NS ? i : i - NS;
-        const unsigned src = wwave + (unsigned)(ii / MB) * tap_stride + (unsigned)(cc * 4 + WK * (ii % MB)) * blk_stride;
+        const unsigned src = wwave + (unsigned)(ii / MB) * tap_stride + (unsigned)(cc * Cfg::KB + WK * (ii % MB)) * blk_stride;
 #pragma unroll
         for (int j = 0; j < TN; ++j) fa[slot][j] = buf_load16(wrs, wlane, src + (unsigned)j * 32u * 32u);
     };
     const int ty = by_reciprocal(mt, per_tiles_x), tx = mt - ty * tiles_x;
     const int wy0 = ty * th, wx0 = tx * tw;
     const int nty = wy0 + th < Hp ? th : Hp - wy0, ntx = wx0 + tw < Wp ? tw : Wp - wx0;
-    // staged pixels of this thread: rows 2 j + wave / 2, column sx, 16-byte piece lane % 8 of the pixel in LDS
-    const int sx = (wave & 1) * 8 + (lane >> 3), ix = wx0 - bx0 - pad + sx, iy = wy0 - by0 - pad + (wave >> 1);
-    const unsigned out = sx < ntx + 2 && ix >= 0 && ix < sW ? 0u : kOutside;
-    const unsigned pix = (unsigned)(iy * sW + ix), piece = (unsigned)((lane & 7) ^ (sx & 7)) * 16u;
+    // where piece p of pixel x of a row lies: at p ^ swz(x)
+    auto swz = [](int x) { return LPP == 8 ? (S == 1 ? x & 7 : x >> 1) : x >> 2; };
+    // staged pixels of this thread: rows RPJ j + row0, column sx, 16-byte piece lane % LPP of the pixel in LDS
+    const int row0 = wave / WPR, sx = (wave % WPR) * (16 / WPR) + lane / LPP, ix = (wx0 - bx0) * S - pad + sx, iy = (wy0 - by0) * S - pad + row0;
+    const int nsy = (nty - 1) * S + 3, nsx = (ntx - 1) * S + 3;              // staged rows, columns
+    const unsigned out = sx < nsx && ix >= 0 && ix < sW ? 0u : kOutside;
+    const unsigned pix = (unsigned)(iy * sW + ix), piece = (unsigned)((lane % LPP) ^ swz(sx)) * 16u;
     unsigned fl[NLD], hsrc[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {                   // (a flag outside the source reads as 0)
-        const bool in = 2 * j + (wave >> 1) < nty + 2 && iy + 2 * j >= 0 && iy + 2 * j < sH;
-        fl[j] = __builtin_amdgcn_raw_buffer_load_b8(frs, (int)(in ? (pix + (unsigned)(2 * j * sW)) | out : kOutside), 0, 0);
+        const bool in = RPJ * j + row0 < nsy && iy + RPJ * j >= 0 && iy + RPJ * j < sH;
+        fl[j] = __builtin_amdgcn_raw_buffer_load_b8(frs, (int)(in ? (pix + (unsigned)(RPJ * j * sW)) | out : kOutside), 0, 0);
     }
     // loads come back in order: the weights of the first steps, the slowest here, behind the flags
     __builtin_amdgcn_sched_barrier(0);
@@ -159,31 +178,49 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const 
     for (int i = 0; i < D - 1; ++i) load_a(i, 0, i);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < NLD; ++j) hsrc[j] = ((pix + (unsigned)(2 * j * sW)) * row + piece) | (~fl[j] >> 2) << 31;      // kFlagM == 4
+    for (int j = 0; j < NLD; ++j) hsrc[j] = ((pix + (unsigned)(RPJ * j * sW)) * row + piece) | (~fl[j] >> 2) << 31;      // kFlagM == 4
     auto stage = [&](int c) {                          // chunk c -> its buffer
 #pragma unroll
         for (int j = 0; j < NLD; ++j)
-            dma16(drs, lds0 + (unsigned)((c & 1) * Cfg::BUF + (wave + 4 * j) * 1024), hsrc[j], (unsigned)c * 128u);
+            dma16(drs, lds0 + (unsigned)((c & 1) * Cfg::BUF + (wave + 4 * j) * 1024), hsrc[j], (unsigned)(c * PXB));
     };
     stage(0);
     if (nchunks > 1) stage(1);
-    unsigned char bits[NLD];
+    unsigned short bits[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
-        const unsigned long long b = __ballot(fl[j] & kFlagM) & 0x0101010101010101ull;             // eight lanes to a pixel
-        bits[j] = (unsigned char)((b * 0x0102040810204080ull) >> 56);
+        if constexpr (LPP == 8) {
+            const unsigned long long b = __ballot(fl[j] & kFlagM) & 0x0101010101010101ull;         // eight lanes to a pixel
+            bits[j] = (unsigned char)((b * 0x0102040810204080ull) >> 56);
+        } else {
+            unsigned long long b = __ballot(fl[j] & kFlagM) & 0x1111111111111111ull;               // four
+            b = (b | b >> 3) & 0x0303030303030303ull;
+            b = (b | b >> 6) & 0x000f000f000f000full;
+            b = (b | b >> 12) & 0x000000ff000000ffull;
+            bits[j] = (unsigned short)(b | b >> 24);
+        }
     }
     if (lane == 0) {
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) s_mask[(2 * j + (wave >> 1)) * 2 + (wave & 1)] = bits[j];
+        for (int j = 0; j < NLD; ++j) {
+            if constexpr (LPP == 8) s_mask[(2 * j + row0) * 2 + (wave & 1)] = (unsigned char)bits[j];
+            else reinterpret_cast<unsigned short*>(s_mask)[4 * j + row0] = bits[j];
+        }
     }
     __syncthreads();
     // the live pixels of the tile, ranked row by row: lane l of every wave has row l
     int any = 0, upto = 0;
     if (lane < nty) {
-        const unsigned short* r = reinterpret_cast<const unsigned short*>(s_mask) + lane;
-        const int m = r[0] | r[1] | r[2];
-        any = (m | m >> 1 | m >> 2) & ((1 << ntx) - 1);
+        const unsigned short* r = reinterpret_cast<const unsigned short*>(s_mask) + lane * S;
+        int m = r[0] | r[1] | r[2];
+        m = m | m >> 1 | m >> 2;
+        if constexpr (S == 2) {                       // every other column
+            m &= 0x5555;
+            m = (m | m >> 1) & 0x3333;
+            m = (m | m >> 2) & 0x0f0f;
+            m = m | m >> 4;
+        }
+        any = m & ((1 << ntx) - 1);
     }
     upto = __popc(any);
     upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8: sums within 16 lanes
@@ -222,8 +259,8 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const 
         const int r = (t * WMV + wm) * 32 + r32, ent = s_ent[r < tot ? r : 0];
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx) {
-            const int x = (ent & 15) + dx;
-            off[t][dx] = ((ent >> 4) * 16 + x) * 128 + (((2 * wk + kh) ^ (x & 7)) << 4);
+            const int x = (ent & 15) * S + dx;
+            off[t][dx] = ((ent >> 4) * S * 16 + x) * PXB + (((2 * wk + kh) ^ swz(x)) << 4);
         }
     }
 
@@ -237,7 +274,7 @@ __device__ __forceinline__ void rect_body(const EdgeDev& e, unsigned blk, const 
                 const int tap = i / MB, flip = (WK * (i % MB)) * 2 * 16;         // block wk + WK q: another bit of the piece number
 #pragma unroll
                 for (int t = 0; t < L; ++t)
-                    fb[slot][t] = *reinterpret_cast<const f16x8*>(smem + P * Cfg::BUF + (tap / 3) * 2048 + (off[t][tap % 3] ^ flip));
+                    fb[slot][t] = *reinterpret_cast<const f16x8*>(smem + P * Cfg::BUF + (tap / 3) * ROWB + (off[t][tap % 3] ^ flip));
             };
             if (c > 0 && c + 1 < nchunks) stage(c + 1);
             load_b(0, 0);

@@ -11,11 +11,13 @@
 // of other sizes, do it themselves: the block of a segment's first piece writes the segment (kSegPixels indices, one per
 // thread, ballot + popcount ranks) to the compute list, and every block compacts its share of the source's mask into L.
 //
-//   k_conv_rect       : 3x3 stride-1 fp16 layers of 64 n input channels: rectangles, staged by loads that
-//                       write LDS themselves, packed weights straight into MFMA fragments (conv_rect.h)
+//   k_conv_rect       : 3x3 fp16 layers with packed weights, stride 1 and 64 n input channels or stride 2 and
+//                       32 n: rectangles, staged by loads that write LDS themselves, packed weights straight into
+//                       MFMA fragments (conv_rect.h)
 //   k_conv_halo       : the other 3x3 stride-1 fp16 layers of 32 n input channels: rectangles, staged
 //                       through registers once per 32 channels
-//   k_conv_mfma_tiled : LDS-tiled gather-GEMM on the CDNA4 matrix cores (fp16 in, fp32 acc)
+//   k_conv_mfma_tiled : LDS-tiled gather-GEMM on the CDNA4 matrix cores (fp16 in, fp32 acc): 1x1 and upsampling
+//                       edges, strides above 2, layers without packed weights
 //   k_conv_mfma_f16   : MFMA without LDS staging (fallback for Cin % 32 != 0)
 //   k_conv_mfma_f32   : small fp32 layers, weights in LDS (fp32 matrix instruction)
 //   k_conv_f32        : weights and delta rows staged in LDS (conv_f32.h): all other fp32 layers with
@@ -1152,23 +1154,23 @@ bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, 
     return true;
 }
 
-// Rectangle of at most m pixels, 14 columns and rect_rows(m) - 2 rows for the tiles of conv_rect.h, with the fewest tiles over
-// an Hp x Wp window (ties: the smaller halo).  Asked for by every launch: the answers are kept per host thread, as tile_2d's.
-void rect_tile(int Hp, int Wp, int m, int* th_out, int* tw_out, long long* tiles_out) {
-    const int rows = rect_rows(m);
-    struct Entry { int Hp = -1, Wp, m, th, tw; long long tiles; };
+// Rectangle of at most m pixels for the tiles of conv_rect.h, whose footprint fits `rows` rows of 16, with the fewest tiles over
+// an Hp x Wp window (ties: the smaller footprint).  Asked for by every launch: the answers are kept per host thread, as tile_2d's.
+void rect_tile(int Hp, int Wp, int m, int rows, int stride, int* th_out, int* tw_out, long long* tiles_out) {
+    struct Entry { int Hp = -1, Wp, m, rows, stride, th, tw; long long tiles; };
     static thread_local Entry table[256];
-    const unsigned h = (unsigned)Hp * 2654435761u ^ (unsigned)Wp * 2246822519u ^ (unsigned)m * 3266489917u;
+    const unsigned h = (unsigned)Hp * 2654435761u ^ (unsigned)Wp * 2246822519u ^ (unsigned)(m * 64 + rows * 2 + stride) * 3266489917u;
     Entry& t = table[(h >> 16) % 256];
-    if (t.Hp != Hp || t.Wp != Wp || t.m != m) {
-        t = Entry{Hp, Wp, m, 0, 0, -1};
+    if (t.Hp != Hp || t.Wp != Wp || t.m != m || t.rows != rows || t.stride != stride) {
+        t = Entry{Hp, Wp, m, rows, stride, 0, 0, -1};
         long long halo = 0;
-        for (int tw = 1; tw <= 14 && tw <= Wp; ++tw) {
-            int th = m / tw < rows - 2 ? m / tw : rows - 2;
+        const int highest = (rows - 3) / stride + 1, widest = 13 / stride + 1;
+        for (int tw = 1; tw <= widest && tw <= Wp; ++tw) {
+            int th = m / tw < highest ? m / tw : highest;
             if (th > Hp) th = Hp;
             const int down = (Hp + th - 1) / th, across = (Wp + tw - 1) / tw;
             th = (Hp + down - 1) / down;                   // the lowest tile with as many rows of tiles
-            const long long n = (long long)down * across, hl = (long long)(th + 2) * (tw + 2);
+            const long long n = (long long)down * across, hl = (long long)((th - 1) * stride + 3) * ((tw - 1) * stride + 3);
             if (t.tiles < 0 || n < t.tiles || (n == t.tiles && hl < halo)) { t.tiles = n; halo = hl; t.th = th; t.tw = tw; }
         }
     }
@@ -1181,8 +1183,8 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
     const EdgeDev& e = eb.d[0];
     int th, tw;
     long long tiles;
-    static_assert(Cfg::ROWS == rect_rows(Cfg::M), "the rows rect_tile counts on");
-    rect_tile(e.Hp, e.Wp, Cfg::M, &th, &tw, &tiles);
+    static_assert(Cfg::S != 1 || Cfg::ROWS == rect_rows(Cfg::M), "the rows mdcnn_rect_tiles counts on");
+    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, Cfg::S, &th, &tw, &tiles);
     const int NT = e.Cout / Cfg::BN, tiles_x = (e.Wp + tw - 1) / tw;
     *done = (double)tiles * NT * NT < 4e9 && (double)tiles * tiles_x < 4e9;      // (the reciprocals are exact below 2^32)
     if (!*done) return hipSuccess;
@@ -1190,7 +1192,7 @@ static hipError_t launch_rect_t(const EdgeBatch& eb, int nb, hipStream_t st, Con
     if (read && ncopy) *read = true;
     const TileGrid g{npub, ncopy, NT, th, tw, tiles_x, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)tiles_x)};
     if (pick) {
-        *pick = ConvPick{multi_rect_body(Cfg::M, Cfg::TN), (int)(tiles * NT), g, blocks, (unsigned)Cfg::SMEM};
+        *pick = ConvPick{rect_body_number<Cfg>(), (int)(tiles * NT), g, blocks, (unsigned)Cfg::SMEM};
         return hipSuccess;
     }
     auto kern = k_conv_rect<Cfg>;
@@ -1229,7 +1231,7 @@ void rect_choice(int Hp, int Wp, int Cin, int Cout, int nb, bool alone, bool sha
     auto tiles_of = [&](int m, int couts, int* pixels = nullptr) {
         int th, tw;
         long long tiles;
-        rect_tile(Hp, Wp, m, &th, &tw, &tiles);
+        rect_tile(Hp, Wp, m, rect_rows(m), 1, &th, &tw, &tiles);
         if (pixels) *pixels = (th * tw + 31) / 32 * 32;
         return tiles * (Cout / couts);
     };
@@ -1270,6 +1272,30 @@ static hipError_t launch_rect(const EdgeBatch& eb, int nb, int m, hipStream_t st
         case 160: return launch_rect_t<typename T::T160>(eb, nb, st, pick, done, read);
         default: return launch_rect_t<typename T::T256>(eb, nb, st, pick, done, read);
     }
+}
+
+// Stride 2: tiles of 64 entries (at most 7 columns: the footprint of 15 columns is a row of 16 staged pixels), couts / 32 by the
+// number of tiles: 32 couts where a launch has few (rect_choice), 128 where 64 would take more than a compute unit's share of
+// blocks twice - a tile is round trips whatever it multiplies, and its footprint is staged once for 128 couts.  64 -> 128
+// channels on 129 x 129 pixels beside the projection of the block: 64 couts 18.0 us, 128 couts 13.1, the gather tiles before
+// 15.1; 128 -> 256 on 65 x 65: 15.7, 12.7, 14.6; 16 videos of them 99 / 87 / 85 and 101 / 76 / 79.  64 -> 64 on 97 x 73
+// 8.1 us (gather tiles 12.1), 32 -> 32 on 49 x 37 5.5 (11.4): HRNet-like 384 x 288 frame 471 -> 439 us.
+int rect_choice_s2(int Hp, int Wp, int Cin, int Cout, int nb) {
+    int th, tw;
+    long long tiles;
+    rect_tile(Hp, Wp, 64, 16, 2, &th, &tw, &tiles);
+    tiles = tiles * nb * (Cout / 64);
+    if (Cout % 64 || g_halo == 2 || tiles <= 64) return 1;
+    return Cout % 128 || Cin % 64 || tiles <= 256 ? 2 : 4;
+}
+template <int TN>
+static hipError_t launch_rect_s2(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
+    using T = RectTiles<TN>;
+    const int Cin = eb.d[0].Cin;
+    if (Cin == 64) return launch_rect_t<typename T::S2One>(eb, nb, st, pick, done, read);
+    if (Cin % 64 == 0) return launch_rect_t<typename T::S2>(eb, nb, st, pick, done, read);
+    if constexpr (TN <= 2) return launch_rect_t<typename T::S2Half>(eb, nb, st, pick, done, read);
+    else return hipErrorInvalidValue;
 }
 
 // Rectangular tiles of the layers whose input channels are a multiple of 32 and not of 64.  The tile size follows the number
@@ -1348,9 +1374,15 @@ static hipError_t launch_halo_n(const EdgeBatch& eb, int nb, long long nseg, hip
 static hipError_t launch_halo(const EdgeBatch& eb, int nb, long long nseg, bool alone, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
     const EdgeDev& e = eb.d[0];
     *done = false;
-    if (!g_halo || !e.wp || e.k != 3 || e.stride != 1 || e.up != 0 || e.Cin % 16 || e.Cout % 32) return hipSuccess;
+    if (!g_halo || !e.wp || e.k != 3 || e.stride > 2 || e.up != 0 || e.Cin % 16 || e.Cout % 32) return hipSuccess;
     if ((long long)e.sH * e.sW * e.Cin >= (1ll << 30) || (long long)e.k * e.k * e.Cin * e.Cout >= (1ll << 30))
         return hipSuccess;                                                     // 32-bit byte offsets into deltas and weights
+    if (e.stride == 2) {
+        if (g_halo == 3 || e.Cin % 32) return hipSuccess;
+        const int tn = rect_choice_s2(e.Hp, e.Wp, e.Cin, e.Cout, nb);
+        return tn == 1 ? launch_rect_s2<1>(eb, nb, st, pick, done, read) : tn == 2 ? launch_rect_s2<2>(eb, nb, st, pick, done, read)
+                                                                                  : launch_rect_s2<4>(eb, nb, st, pick, done, read);
+    }
     // Rectangular tiles (one of up to 64 pixels fits every window).  Windows of a few list segments used to stay on index
     // ranges, whose tiles stage whole rows; with the by-products made by other blocks and the round trips of a small tile
     // overlapped the rectangles are faster there too: HRNet-like network 659 -> 611 us a frame, 37 x 53 windows of 256 and 512

@@ -35,6 +35,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     }
 #define RECT(M, TN)                                                                                                       \
     case multi_rect_body(M, TN): rect_body<RectTiles<TN>::T##M, false>(e, blk, g); break;
+#define RECT_S2(T, TN)                                                                                                    \
+    case multi_rect_body(kRect##T, TN): rect_body<RectTiles<TN>::T, false>(e, blk, g); break;
 #define HALO(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D)                                                                   \
     case multi_halo_body(NSUB, WMV, WK, TM, TN, KC, NLD, RING, T2D):                                                      \
         halo_body<NSUB, WMV, WK, TM, TN, KC, NLD, 3, RING, 2, T2D>(e, blk, nblk, g.NT, items, g.p0, g.p1);               \
@@ -43,6 +45,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
     case multi_tiled_body(WM, WN, TM, TN, KC, 1): tiled_body<WM, WN, TM, TN, KC, 1, false>(e, blk, nblk, g, items); break;
     switch (body) {
         RECT(64, 1) RECT(64, 2) RECT(96, 1) RECT(96, 2) RECT(128, 1) RECT(128, 2)
+        RECT_S2(S2One, 1) RECT_S2(S2One, 2) RECT_S2(S2One, 4) RECT_S2(S2, 1) RECT_S2(S2, 2) RECT_S2(S2, 4) RECT_S2(S2Half, 1) RECT_S2(S2Half, 2)
         HALO(2, 2, 2, 2, 1, 32, 3, 3, true)
         HALO(4, 2, 2, 1, 1, 32, 2, 9, true)
         TILED(2, 2, 1, 1, 32) TILED(2, 2, 1, 1, 64) TILED(2, 2, 1, 1, 128)
@@ -53,6 +56,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
         default: break;
     }
 #undef RECT
+#undef RECT_S2
 #undef HALO
 #undef TILED
 }

@@ -1620,7 +1620,7 @@ mdcnn_status mdcnn_rect_tiles(int Hp, int Wp, int Cin, int Cout, int videos, int
     int tn;
     rect_choice(Hp, Wp, Cin, Cout, videos, !in_flight, shared != 0, &tn, entries);
     *couts = 32 * tn;
-    rect_tile(Hp, Wp, *entries, th, tw, tiles);
+    rect_tile(Hp, Wp, *entries, rect_rows(*entries), 1, th, tw, tiles);
     *tiles *= Cout / *couts;
     return MDCNN_OK;
 }

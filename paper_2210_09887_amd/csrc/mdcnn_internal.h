@@ -281,8 +281,11 @@ hipError_t launch_step1(const Step1Batch& b, int n, hipStream_t st);
 hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
 // half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
-constexpr int kMultiRectBodies = 6, kMultiHaloBodies = 2, kMultiTiledBodies = 15;
-constexpr int multi_rect_body(int m, int tn) { return m == 64 || m == 96 || m == 128 ? (m / 32 - 2) * 2 + tn - 1 : -1; }
+constexpr int kMultiRectBodies = 15, kMultiHaloBodies = 2, kMultiTiledBodies = 15;
+constexpr int kRectS2One = 1, kRectS2 = 2, kRectS2Half = 3;      // the stride-2 tiles, in place of their entries
+constexpr int multi_rect_body(int m, int tn) {
+    return m == 64 || m == 96 || m == 128 ? (m / 32 - 2) * 2 + tn - 1 : m >= kRectS2One && m <= kRectS2Half ? 6 + (m - 1) * 3 + tn / 2 : -1;
+}
 constexpr int multi_halo_body(int nsub, int wmv, int wk, int tm, int tn, int kc, int nld, int ring, bool t2d) {
     const int c[kMultiHaloBodies][9] = {{2, 2, 2, 2, 1, 32, 3, 3, 1}, {4, 2, 2, 1, 1, 32, 2, 9, 1}};
     for (int i = 0; i < kMultiHaloBodies; ++i)
@@ -377,7 +380,7 @@ extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // con
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);
 // host-only: rows of 16 source pixels a tile of m entries stages (conv_rect.h), its rectangle, and which tile a launch takes
 constexpr int rect_rows(int m) { return m <= 96 ? 10 : m == 128 ? 12 : m == 160 ? 14 : 20; }
-void rect_tile(int Hp, int Wp, int m, int* th_out, int* tw_out, long long* tiles_out);
+void rect_tile(int Hp, int Wp, int m, int rows, int stride, int* th_out, int* tw_out, long long* tiles_out);
 // alone: see launch_conv; shared: beside other edges in one launch
 void rect_choice(int Hp, int Wp, int Cin, int Cout, int videos, bool alone, bool shared, int* tn, int* m);
 // host-only: which tile of the gather kernel a launch takes (MDCNN_OPT_CONV_TILE's number)

@@ -56,7 +56,7 @@ class GpuNet:
                     assert w.dtype == self.tdtype
                     self.weights.append(w)
                     cd.w_dev = w.data_ptr()
-                    if dt == B.MDCNN_F16 and e.k == 3 and e.stride == 1 and not e.up and cd.Cin % 16 == 0 and cd.Cout % 32 == 0:
+                    if dt == B.MDCNN_F16 and e.k == 3 and e.stride <= 2 and not e.up and cd.Cin % 16 == 0 and cd.Cout % 32 == 0:
                         wp = torch.empty_like(w)             # second copy in matrix-core operand order
                         B.mdcnn_pack_weights(cd, dt, wp.data_ptr(), wp.numel() * 2)
                         self.weights.append(wp)

@@ -1,7 +1,8 @@
 """3 x 3 stride-1 fp16 layers of 64 n input channels (conv_rect.h): every tile against the oracle, and the same bits whatever the
 tile where the channels are split four ways - windows lower or narrower than a tile, ragged last tiles, numbers of cout tiles
 that are no power of two, one to five chunks, frames in flight where they take other tiles than a frame alone.  The rule itself
-takes tiles of 64 entries on small windows; the last two cases are the smallest for which it takes 96, of 32 and of 64 couts."""
+takes tiles of 64 entries on small windows; the last two cases are the smallest for which it takes 96, of 32 and of 64 couts.
+Stride 2 likewise (32 n input channels; 32, 64 or 128 couts to a tile by the number of tiles)."""
 import numpy as np
 import pytest
 
@@ -67,3 +68,24 @@ def test_frames_in_flight_take_other_tiles(cin, cout, H, W, alone, flying):
         assert np.array_equal(p.cpu().numpy(), q.cpu().numpy()), f"frame {t}"
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("cin,cout,H,W,videos", [
+    (64, 96, 2, 46, 1), (64, 64, 54, 38, 1), (64, 64, 100, 126, 1), (64, 128, 130, 252, 1), (64, 256, 100, 120, 2),     # 32, 32, 64, 128 couts; 64 alone, 128 in a batch
+    (128, 32, 34, 2, 1), (192, 192, 58, 90, 1), (128, 128, 132, 260, 1), (32, 32, 18, 30, 1), (32, 64, 130, 92, 1), (96, 192, 44, 62, 2)])
+def test_stride_2(cin, cout, H, W, videos):
+    import gpu_harness as H_
+    from inputs.nets import tiny_net
+    from paper_2210_09887_amd.runtime import GpuBatch, GpuNet
+    net = tiny_net("f16", H, W, (cin, cout), k=3, stride=2, theta=0.05, seed=cin + cout + H, total_stride=2)
+    frames, shifts = frames_of(cin, H, W), [(0, 0), (0, 0), (0, -1)]
+    H_.teacher_forced(net, frames, shifts)
+    if videos > 1:                                 # a video of a batch gives the bits it gives alone
+        one, many = GpuNet(net), GpuBatch(net, videos)
+        for f, (dy, dx) in zip(frames, shifts):
+            want = one.frame(H_.dev(f), dy, dx)[0].cpu().numpy()
+            outs, _ = many.frame([H_.dev(f)] * videos, [dy] * videos, [dx] * videos)
+            for o in outs:
+                assert np.array_equal(o.cpu().numpy().reshape(-1), want.reshape(-1))
+        one.close()
+        many.close()
