@@ -13,6 +13,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ int wrapc(int v, int n) { return v >= n ? v - n : v; }
 
+// Division by a number known on the host.
+inline unsigned reciprocal_of(unsigned d) { return d > 1 ? 0xffffffffu / d + 1 : 0u; }
+__device__ __forceinline__ int by_reciprocal(int a, unsigned r) { return r ? (int)__umulhi((unsigned)a, r) : a; }     // a * divisor < 2^32
+
 // Buffer loads: the address is a resource (base, size) in scalar registers + a per-lane byte offset + a
 // scalar byte offset, so a wave spends one vector register on all the addresses of a tensor instead of a
 // 64-bit pointer per load (reads past `bytes` return zero instead of faulting).

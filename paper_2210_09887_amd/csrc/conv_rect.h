@@ -89,9 +89,6 @@ struct RectCfg {
     static_assert((RING - 1) * TN + NLD < 63, "the counter of outstanding loads has six bits");
 };
 
-inline unsigned reciprocal_of(unsigned d) { return d > 1 ? 0xffffffffu / d + 1 : 0u; }
-__device__ __forceinline__ int by_reciprocal(int a, unsigned r) { return r ? (int)__umulhi((unsigned)a, r) : a; }     // a * divisor < 2^32
-
 // The tiles in use, by their entries.  All but the last split the channels four ways and give the same bits.
 template <int TN>
 struct RectTiles {

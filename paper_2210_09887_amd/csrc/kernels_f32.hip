@@ -1,5 +1,7 @@
 // Launch of the fp32 convolution tile (conv_f32.h).
-#include "conv_f32.h"
+#include <atomic>
+
+#include "conv_f32s.h"
 
 namespace mdcnn {
 
@@ -26,8 +28,69 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(TileGrid g, int tiles, unsi
     if (e.k != 1 && e.k != 3) carry_source_compaction(e, sh, blockIdx.x, nblk);
 }
 
+template <typename Cfg>
+__global__ __launch_bounds__(256, Cfg::MINB) void k_conv_f32s(TileGrid g, unsigned blocks, EdgeBatch eb) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned nblk = blocks - g.npub - g.ncopy;
+    if (blockIdx.x >= nblk) side_block<float>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
+    else split_tile<Cfg>(eb.d[blockIdx.z], blockIdx.x, g);
+}
+
+template <typename Cfg>
+static hipError_t launch_split(const EdgeBatch& eb, int nb, hipStream_t st, bool* done, bool* read) {
+    const EdgeDev& e = eb.d[0];
+    int th, tw;
+    long long tiles;
+    rect_tile(e.Hp, e.Wp, Cfg::M, Cfg::ROWS, 1, &th, &tw, &tiles);
+    const int NT = e.Cout / 32, tiles_x = (e.Wp + tw - 1) / tw;
+    *done = (double)tiles * NT * NT < 4e9 && (double)tiles * tiles_x < 4e9;      // (the reciprocals are exact below 2^32)
+    if (!*done) return hipSuccess;
+    const unsigned npub = publish_blocks(e), ncopy = copy_blocks(e, 4), blocks = (unsigned)(tiles * NT) + npub + ncopy;
+    if (read && ncopy) *read = true;
+    const TileGrid g{npub, ncopy, NT, th, tw, tiles_x, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)tiles_x)};
+    auto kern = k_conv_f32s<Cfg>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::SMEM);
+        if (err != hipSuccess) { (void)hipGetLastError(); return err; }    // do not leave it for the next call to report
+        attr_set.store(true, std::memory_order_release);
+    }
+    kern<<<dim3(blocks, 1, nb), dim3(256), Cfg::SMEM, st>>>(g, blocks, eb);
+    return hipGetLastError();
+}
+
+// Row tiles of a tile: what the compute unit with the most tiles takes, a tile's start and end and its steps one behind the other (a
+// compute unit issues the steps of two tiles in the time of both).  Measured as in conv_f32s.h, us a frame with 1 / 2 / 3: 64 -> 32 on
+// 16 x 16 10.0 / 11.3 / 12.4, 192 -> 96 on 37 x 53 18.3 / 21.0 / 25.2, 512 -> 512 on 8 x 8 27.8 / 35.6 / 37.6; 64 -> 64 on 64 x 64
+// 13.4 / 13.1 / 15.2, on 128 x 128 28.7 / 25.4 / 29.7, on 256 x 256 82.5 / 65.9 / 82.3, 256 -> 256 on 32 x 32 26.5 / 24.7 / 29.5;
+// 128 -> 128 on 64 x 64 23.6 / 23.4 / 22.8, 512 -> 512 on 32 x 32 82.2 / 62.2 / 58.0.
+int split_choice(int Hp, int Wp, int Cin, int Cout, int nb) {
+    constexpr double start[3] = {2.6, 3.5, 5.0}, step[3] = {0.22, 0.34, 0.62};
+    int best = 0;
+    double least = 0;
+    for (int tm = 1; tm <= 3; ++tm) {
+        int th, tw;
+        long long tiles;
+        rect_tile(Hp, Wp, 32 * tm, split_rows(tm), 1, &th, &tw, &tiles);
+        const double per_cu = (double)tiles * (Cout / 32) * nb / 256;
+        const double cost = (per_cu > 4 ? per_cu : (double)(int)(per_cu + 0.9999)) * (start[tm - 1] + 9.0 * (Cin / 64) * step[tm - 1]);
+        if (!best || cost < least) { best = tm; least = cost; }
+    }
+    return best;
+}
+
 hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st, bool* read) {
     const EdgeDev& e = eb.d[0];
+    if (e.k == 3 && e.stride == 1 && e.Cin % 64 == 0 && e.Cout % 32 == 0) {
+        bool done = false;
+        hipError_t err;
+        switch (split_choice(e.Hp, e.Wp, e.Cin, e.Cout, nb)) {
+            case 1: err = launch_split<SplitCfg<1>>(eb, nb, st, &done, read); break;
+            case 2: err = launch_split<SplitCfg<2>>(eb, nb, st, &done, read); break;
+            default: err = launch_split<SplitCfg<3>>(eb, nb, st, &done, read); break;
+        }
+        if (done) return err;
+    }
     const int ih = e.up ? e.sH : e.Hp, iw = e.up ? e.sW : e.Wp, NT = (e.Cout + kF32Co - 1) / kF32Co;
     int th = 1, tw = 1;
     long long tiles = 0;

@@ -375,6 +375,8 @@ hipError_t launch_conv(const EdgeBatch& eb, int n, int dtype, int conv_path, boo
 // fp32 layers on the matrix cores (kernels_f32.hip): shapes it takes, launch
 bool f32_applies(const EdgeDev& e);
 hipError_t launch_conv_f32(const EdgeBatch& eb, int nb, hipStream_t st, bool* read);
+// host-only: row tiles of a tile of conv_f32s.h
+int split_choice(int Hp, int Wp, int Cin, int Cout, int nb);
 extern int g_tile, g_pipe, g_xcd, g_kc, g_halo, g_halo_sub, g_f32_mfma;   // convolution tuning knobs
 // host-only: the rectangle th x tw of at most `sub` pixels whose halo fits `cap` staged pixels, with the fewest tiles over an Hp x Wp window
 bool tile_2d(int Hp, int Wp, int k, int sub, int cap, int* th_out, int* tw_out, long long* tiles_out);

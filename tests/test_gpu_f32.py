@@ -98,3 +98,66 @@ def test_small_upsampling_edges_on_large_views(rows, kernel):
     frames = frames_of(net, 2)
     assert kernel_of_last_site(net, frames[0]) == kernel
     G.teacher_forced(net, frames, [(0, 0), (0, 1), (0, 0)])
+
+
+@pytest.mark.parametrize("cin,cout,H,W", [
+    (64, 32, 16, 16),              # few tiles: one row tile each (2 x 14 pixels of an 18 x 18 window), one chunk of channels
+    (192, 96, 37, 53),             # the same with three chunks and three cout tiles, ragged in both directions
+    (512, 32, 1, 1),               # one pixel, eight chunks
+    (64, 64, 64, 64),              # two row tiles, one chunk
+    (128, 64, 61, 75),             # two chunks, ragged
+    (64, 64, 96, 96),              # three row tiles, one chunk: nothing staged ahead
+    (128, 64, 95, 97),             # three row tiles, two chunks
+    (192, 64, 94, 99),             # three chunks: the last in the first buffer
+])
+def test_fp32_layers_of_64_n_channels(cin, cout, H, W):
+    """The tiles whose products are made of bf16 parts: every number of row tiles, dense frames (the first) and sparse ones."""
+    import gpu_harness as G
+    net = tiny_net("f32", H, W, (cin, cout), theta=0.05, seed=cin + cout)
+    G.teacher_forced(net, frames_of(net, cin * 10 + cout), [(0, 0), (0, 0), (1, -1)])
+
+
+def dense_frame(net, X):
+    """Output of the first frame of a one-layer network, and the same in 64 bits."""
+    import gpu_harness as G
+    import torch
+    from paper_2210_09887_amd.runtime import GpuNet
+    g = GpuNet(net)
+    try:
+        out = g.split_outputs(g.frame(G.dev(X))[0])[0].double().cpu()
+    finally:
+        g.close()
+    e, (cin, cout) = net.edges[0], (net.sites[0].C, net.sites[1].C)
+    w = torch.from_numpy(e.w.reshape(3, 3, cout, cin).transpose(2, 3, 0, 1).copy()).double()
+    ref = torch.nn.functional.conv2d(torch.from_numpy(X).double().permute(2, 0, 1)[None], w, torch.from_numpy(e.b).double(), padding=1)
+    return out.reshape(net.H, net.W, cout), ref[0].permute(1, 2, 0)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 1e30])
+@pytest.mark.parametrize("cin,n", [(64, 64), (512, 16)])
+def test_precision_of_split_products(cin, n, scale):
+    """Against 64 bits: a sum of 9 cin products is rounded 9 cin / 64 times in each of four waves, to 2^-25 of a partial sum (of
+    the sum's size or less) on average: at most 2^-25 sqrt(9 cin / 16 + 8), 2^-22.8 and 2^-21 here, where fp32 products, each of
+    them rounded, come to 2^-22.1 and 2^-20.7.  At the ends of the exponents too."""
+    net = tiny_net("f32", n, n, (cin, 32), theta=0.0, seed=cin)
+    net.edges[0].b[:] = 0
+    X = (np.maximum(np.random.default_rng(cin).normal(0, 1, (n, n, cin)), 0) * scale).astype(np.float32)
+    out, ref = dense_frame(net, X)
+    assert float((out - ref).norm() / ref.norm()) < 2.0 ** -25 * (9 * cin / 16 + 8) ** 0.5
+
+
+@pytest.mark.parametrize("n", [16, 64, 96])
+def test_values_that_are_not_finite(n):
+    """An infinity or NaN in the frame, and a finite value past what bf16 holds: what it reaches is what fp32 sums make of it, all else is
+    untouched."""
+    net = tiny_net("f32", n, n, (64, 64), theta=0.0, seed=n)
+    X = np.random.default_rng(n).normal(0, 1, (n, n, 64)).astype(np.float32)
+    X[3, 4, 5], X[9, 9, 60], X[n - 1, 2, 33], X[n - 2, n - 3, 7] = np.inf, np.nan, -np.inf, 3.4e38
+    out, ref = dense_frame(net, X)
+    big = ref.abs() > 1e30         # (sums with the large value: near the largest fp32, or past it)
+    assert bool((out.isnan() == ref.isnan()).all())
+    assert bool((out.isinf() & ~big == ref.isinf() & ~big).all()) and bool((out[ref.isinf()] == ref[ref.isinf()]).all())
+    fin = ref.isfinite() & ~big
+    assert int((~fin).sum()) <= 4 * 9 * 64 and float((out - ref)[fin].abs().max()) < 1e-4
+    near = big & (ref.abs() < 3.4e38)
+    assert float(((out - ref)[near] / ref[near]).abs().max()) < 1e-6
