@@ -373,7 +373,9 @@ __device__ __forceinline__ void read_rest(const EdgeDev& e, unsigned blk, unsign
     const float rw = rcp_of(e.dW), rp = rcp_of(pieces);
     if (tid < n) {
         const int oy = div24(first + tid, e.dW, rw);
-        s_live[tid] = tap_mask(e, oy, first + tid - oy * e.dW) != 0;       // (the view is where the convolution's output coordinates start)
+        const int ox = first + tid - oy * e.dW;
+        s_live[tid] = e.up ? (e.sflags[(oy >> e.up) * e.sW + (ox >> e.up)] & kFlagM) != 0
+                           : tap_mask(e, oy, ox) != 0;                   // (the view is where the convolution's output coordinates start)
     }
     __syncthreads();
     const T* const P = (const T*)e.P;

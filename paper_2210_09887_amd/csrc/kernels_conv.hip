@@ -35,6 +35,7 @@
 
 #include "conv_rect.h"
 #include "conv_tiles.h"
+#include "conv_up.h"
 
 namespace mdcnn {
 
@@ -65,6 +66,13 @@ __global__ __launch_bounds__(256, Cfg::MINB) void k_conv_rect(TileGrid g, unsign
     const unsigned nblk = blocks - g.npub - g.ncopy;
     if (blockIdx.x >= nblk) side_block<f16>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
     else rect_body<Cfg, true>(eb.d[blockIdx.z], blockIdx.x, g);
+}
+
+__global__ __launch_bounds__(256) void k_conv_up(TileGrid g, unsigned blocks, EdgeBatch eb) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const unsigned nblk = blocks - g.npub - g.ncopy;
+    if (blockIdx.x >= nblk) side_block<f16>(eb.d[blockIdx.z], g, blockIdx.x - nblk, smem);
+    else up_body<true>(eb.d[blockIdx.z], blockIdx.x, g);
 }
 
 // Weights [tap][cout][cin] -> [tap][cin/16][cout][16]: the 32 couts x 16 cin
@@ -1477,6 +1485,25 @@ static hipError_t launch_mfma_f32(const EdgeBatch& eb, int nb, long long nseg, h
          : e.Cin == 32 ? launch_mfma_f32_ks<1, 32>(eb, nb, nseg, st, read) : launch_mfma_f32_ks<1, 64>(eb, nb, nseg, st, read);
 }
 
+// Upsampling 1x1 edges of 64 n channels; *done: false if the edge is not one of them.
+static hipError_t launch_up(const EdgeBatch& eb, int nb, hipStream_t st, ConvPick* pick, bool* done, bool* read) {
+    const EdgeDev& e = eb.d[0];
+    const long long HW = (long long)e.sH * e.sW, MT = (HW + kUpPx - 1) / kUpPx, NT = e.Cout / kUpCo, tiles = MT * up_parts(e.up);
+    *done = e.k == 1 && e.up && e.Cin % 64 == 0 && HW * e.Cin < (1ll << 30) && (long long)e.Cin * e.Cout < (1ll << 30) && (long long)e.dH * e.dW < (1ll << 31) &&
+            (double)tiles * NT * NT < 4e9 && (double)tiles * MT < 4e9;        // (the reciprocals are exact below 2^32)
+    if (!*done) return hipSuccess;
+    const unsigned npub = publish_blocks(e), ncopy = copy_blocks(e, 2), blocks = (unsigned)(tiles * NT) + npub + ncopy;
+    if (read && ncopy) *read = true;
+    const int early = nb * HW * (e.Cin + ((long long)e.Cout << (2 * e.up))) <= 8 << 20;
+    const TileGrid g{npub, ncopy, (int)NT, 0, 0, (int)MT, reciprocal_of((unsigned)NT), reciprocal_of((unsigned)MT), early};
+    if (pick) {
+        *pick = ConvPick{kMultiUpBody, 0, g, blocks, (unsigned)kUpSmem};
+        return hipSuccess;
+    }
+    k_conv_up<<<dim3(blocks, 1, nb), dim3(256), kUpSmem, st>>>(g, blocks, eb);
+    return hipGetLastError();
+}
+
 hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bool alone, hipStream_t st, int* cls, ConvPick* pick, bool* read) {
     const EdgeDev& e = eb.d[0];                            // geometry and weights layout are the same for all streams
     const long long max_entries = e.up ? (long long)e.sH * e.sW : (long long)e.Hp * e.Wp;
@@ -1524,7 +1551,8 @@ hipError_t launch_conv(const EdgeBatch& eb, int nb, int dtype, int conv_path, bo
     const bool mfma_ok = dtype == MDCNN_F16 && conv_path != 1 && e.Cin % 16 == 0 && e.Cout % 32 == 0;
     if (mfma_ok && conv_path == 0) {
         bool done = false;
-        const hipError_t err = launch_halo(eb, nb, nseg, alone, st, pick, &done, read);
+        hipError_t err = launch_halo(eb, nb, nseg, alone, st, pick, &done, read);
+        if (!done) err = launch_up(eb, nb, st, pick, &done, read);
         if (done) { *cls = kClsConvMfma; return err; }
     }
     // (the tiled kernel addresses deltas and weights with 32-bit byte offsets)

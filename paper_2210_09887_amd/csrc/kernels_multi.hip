@@ -6,6 +6,7 @@
 
 #include "conv_rect.h"
 #include "conv_tiles.h"
+#include "conv_up.h"
 
 namespace mdcnn {
 
@@ -53,6 +54,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
         TILED(2, 2, 2, 1, 32) TILED(2, 2, 2, 1, 64) TILED(2, 2, 2, 1, 128)
         TILED(2, 2, 1, 2, 32) TILED(2, 2, 1, 2, 64) TILED(2, 2, 1, 2, 128)
         TILED(2, 2, 2, 2, 32) TILED(2, 2, 2, 2, 64) TILED(2, 2, 2, 2, 128)
+        case kMultiUpBody: up_body<false>(e, blk, g); break;
         default: break;
     }
 #undef RECT

@@ -888,7 +888,12 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 same_weights &= eb.d[b].w == eb.d[0].w && eb.d[b].wp == eb.d[0].wp;
             }
             const int dtype = sites[0][op.site]->d.dtype;
-            if (round.size() > 1 && same_weights) err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls, &pick);
+            if (round.size() > 1 && op.edge < 0 && dtype == MDCNN_F16) {      // lists only: blocks of the launch the round's edges share
+                pick.body = kMultiListBody;
+                pick.g.npub = pick.blocks = publish_blocks(eb.d[0]);
+            } else if (round.size() > 1 && same_weights) {
+                err = launch_conv(eb, n, dtype, g_conv_path, alone, st, &cls, &pick);
+            }
             if (err == hipSuccess && pick.body < 0) {
                 const int dst = op.edge >= 0 ? net->edst[(size_t)op.edge] : -1;
                 const bool reads = outs && op.reads && !sites[0][dst]->d.crops;
@@ -905,7 +910,7 @@ mdcnn_status run_round(const std::vector<RoundOp>& round, mdcnn_net* const* nets
                 j.e = eb.d[0];
                 j.body = pick.body; j.items = pick.items; j.g = pick.g; j.blocks = pick.blocks;
                 for (int b = 0; b < n; ++b)
-                    cm.vid[cm.n * n + b] = ConvVid{dist(eb.d[b].delta, j.e.delta), dist(eb.d[b].P, j.e.P), eb.d[b].p_oy, eb.d[b].p_ox};
+                    cm.vid[cm.n * n + b] = ConvVid{dist(eb.d[b].sflags, j.e.sflags), dist(eb.d[b].P, j.e.P), eb.d[b].p_oy, eb.d[b].p_ox};
                 smem = pick.smem > smem ? pick.smem : smem;
                 ++cm.n;
             }

@@ -282,6 +282,7 @@ hipError_t launch_step1_fill(Step1Fill& a, hipStream_t st);
 // Tile configurations k_conv_multi carries: -1, or the number of the body.  They are the small ones - tiles of at most
 // half a list segment - plus the 64- and 128-pixel gather tiles: an edge that takes larger tiles fills the GPU by itself.
 constexpr int kMultiRectBodies = 15, kMultiHaloBodies = 2, kMultiTiledBodies = 15;
+constexpr int kMultiUpBody = kMultiRectBodies + kMultiHaloBodies + kMultiTiledBodies, kMultiListBody = kMultiUpBody + 1;      // (the last: lists only, no tiles)
 constexpr int kRectS2One = 1, kRectS2 = 2, kRectS2Half = 3;      // the stride-2 tiles, in place of their entries
 constexpr int multi_rect_body(int m, int tn) {
     return m == 64 || m == 96 || m == 128 ? (m / 32 - 2) * 2 + tn - 1 : m >= kRectS2One && m <= kRectS2Half ? 6 + (m - 1) * 3 + tn / 2 : -1;
@@ -309,6 +310,7 @@ struct TileGrid {
     int p0, p1;               // rectangular tiles: rows, columns; gather tiles: xcd_map
     int tiles_x;              // rectangles in a row
     unsigned per_NT, per_tiles_x;
+    int early;                // upsampling tiles: everything is requested at once
 };
 // How launch_conv would run an edge; body < 0: not with one of those configurations.
 struct ConvPick {
