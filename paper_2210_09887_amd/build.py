@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmdcnn.so")
 SOURCES = ["mdcnn_api.hip", "kernels_state.hip", "kernels_conv.hip", "kernels_f32.hip", "kernels_multi.hip", "kernels_bench.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=6",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -10,11 +10,11 @@
 
 namespace mdcnn {
 
-__global__ __launch_bounds__(256, 2) void k_conv_multi(ConvMulti m) {
+__global__ __launch_bounds__(256, 2) void k_conv_multi(unsigned b1, unsigned b2, unsigned b3, unsigned b4, unsigned b5, unsigned videos, ConvMulti m) {
     unsigned blk;
-    const int j = m.blocks.find(blockIdx.x, &blk);
+    const int j = find_job(b1, b2, b3, b4, b5, blockIdx.x, &blk);
     const ConvJob& jb = m.job[j];
-    ConvVid v = m.vid[j * m.videos + (int)blockIdx.z];
+    ConvVid v = m.vid[j * (int)videos + (int)blockIdx.z];
     EdgeDev e = jb.e;
     TileGrid g = jb.g;
     unsigned blocks = jb.blocks;
@@ -74,7 +74,8 @@ hipError_t launch_conv_multi(ConvMulti& m, int videos, unsigned smem, hipStream_
         attr_set.store(true, std::memory_order_release);
     }
     if (smem > 80u * 1024u) return hipErrorInvalidValue;
-    k_conv_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), smem, st>>>(m);
+    k_conv_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), smem, st>>>(m.blocks.begin[1], m.blocks.begin[2], m.blocks.begin[3], m.blocks.begin[4], m.blocks.begin[5],
+                                                                                                (unsigned)videos, m);
     return hipGetLastError();
 }
 

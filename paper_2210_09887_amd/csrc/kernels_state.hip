@@ -496,11 +496,11 @@ hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
 }
 
 // Step 1 of several sites that do not depend on each other (see k_conv_multi): one 16-byte chunk per lane, fp16.
-__global__ __launch_bounds__(256) void k_step1_multi(Step1Multi m) {
+__global__ __launch_bounds__(256) void k_step1_multi(unsigned b1, unsigned b2, unsigned b3, unsigned b4, unsigned b5, unsigned videos, Step1Multi m) {
     unsigned blk;
-    const int j = m.blocks.find(blockIdx.x, &blk);
+    const int j = find_job(b1, b2, b3, b4, b5, blockIdx.x, &blk);
     Step1Job jb = m.job[j];
-    Step1Vid v = m.vid[j * m.videos + (int)blockIdx.z];
+    Step1Vid v = m.vid[j * (int)videos + (int)blockIdx.z];
     read_now(jb.A, jb.P, jb.delta, jb.flags, jb.skip_P, jb.skip_flags, jb.H, jb.W, jb.C, jb.Hp, jb.Wp, jb.by0, jb.bx0, jb.relu, jb.skip_Hp, jb.skip_Wp,
              jb.skip_by0, jb.skip_bx0, v.sd, v.kd, v.a_oy, v.a_ox, v.p_oy, v.p_ox, v.k_oy, v.k_ox, v.s_off, v.theta);
     auto at = [](auto* p, long long d) { return p ? (decltype(p))((uintptr_t)p + (uintptr_t)d) : nullptr; };
@@ -540,7 +540,8 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
         const int ppb = 256 / G;
         m.blocks.add(j, (unsigned)((jb.H * jb.W + ppb - 1) / ppb));
     }
-    k_step1_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m);
+    k_step1_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m.blocks.begin[1], m.blocks.begin[2], m.blocks.begin[3], m.blocks.begin[4],
+                                                                                             m.blocks.begin[5], (unsigned)videos, m);
     return hipGetLastError();
 }
 

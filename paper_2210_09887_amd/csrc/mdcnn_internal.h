@@ -171,6 +171,24 @@ struct JobBlocks {
         return j;
     }
 };
+// The same for a launch whose begins come as numbers of their own, the first arguments of the kernel (b0 is 0): those the command
+// processor leaves in scalar registers (build flag amdgpu-kernarg-preload-count), and the job's descriptor is the first thing a block asks memory for.
+__device__ __forceinline__ int find_job(unsigned b1, unsigned b2, unsigned b3, unsigned b4, unsigned b5, unsigned blk, unsigned* rel) {
+    int j = 0;
+    unsigned b0 = 0;
+    auto next = [&](int k, unsigned b) {
+        const bool on = blk >= b;
+        j = on ? k : j;
+        b0 = on ? b : b0;
+    };
+    next(1, b1);
+    next(2, b2);
+    next(3, b3);
+    next(4, b4);
+    next(5, b5);
+    *rel = blk - b0;
+    return j;
+}
 constexpr int kMaxFillJobs = 20;
 struct FillBatch {
     JobBlocks<kMaxFillJobs> blocks;

@@ -22,9 +22,14 @@ def test_upsampling_edges(cin, cout, h, w, up):
     net = NetSpec("up", "f16", h * f, w * f, f)
     b = _Builder(net, np.random.default_rng(cin + up), 0.1)
     x = b.site("in", 8, 1, "input", False, 0.05)
+    m = b.site("mid", 16, 2, theta=0.02) if f > 4 else None      # (strides go up to four)
     s = b.site("low", cin, f, theta=0.02)
     y = b.site("out", cout, 1, "output", False, 0.0)
-    b.conv(x, s, 3, f)
+    if m:
+        b.conv(x, m, 3, 2)
+        b.conv(m, s, 3, 4)
+    else:
+        b.conv(x, s, 3, f)
     b.conv(s, y, 1, 1, pad=0, up=up)
     rng = np.random.default_rng(h + w)
     v = rng.normal(0, 1, (net.H, net.W, 8)).astype(np.float32)
