@@ -16,6 +16,7 @@ __device__ __forceinline__ int wrap(int v, int n) { return v >= n ? v - n : v; }
 template <typename T> struct V16;
 template <> struct V16<float> {
     static constexpr int N = 4;
+    using raw = float4;
     __device__ static void load(const float* p, float* v) {
         float4 t = *reinterpret_cast<const float4*>(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
@@ -26,6 +27,7 @@ template <> struct V16<float> {
 };
 template <> struct V16<f16> {
     static constexpr int N = 8;
+    using raw = f16x8;
     __device__ static void load(const f16* p, float* v) {
         f16x8 t = *reinterpret_cast<const f16x8*>(p);
 #pragma unroll
@@ -248,12 +250,18 @@ __device__ __forceinline__ bool unveiled(const FillJob& j, int vy, int vx) {
     return vy < j.ay0 || vy >= j.ay1 || vx < j.ax0 || vx >= j.ax1;
 }
 
-template <typename T, int G, int CH>
+// EARLY (accumulator sites without a mask): what a pixel may need is asked for with its flags, not after them.
+// The pointers are named global again after read_now(): their loads were flat ones, each waited for by itself.  With values kept as loaded
+// until all are asked for, HRNet-like 512 x 512 16 videos a frame 2720 -> 2586 us, one 445 -> 423; nothing updated at all 1100 -> 1120, 318 -> 320.
+template <typename T, int G, int CH, bool EARLY = false>
 __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __restrict__ X,
                                             const uint8_t* __restrict__ forced, unsigned blk, const FillJob* own = nullptr) {
     constexpr int VEC = V16<T>::N;
     read_now(s.A, s.P, s.flags, s.delta, s.H, s.W, s.C, s.Hp, s.Wp, s.by0, s.bx0, s.a_oy, s.a_ox, s.p_oy, s.p_ox, s.theta, s.relu, s.kind, s.s_off,
              skip.P, skip.dflags, skip.Hp, skip.Wp, skip.by0, skip.bx0, skip.p_oy, skip.p_ox, X, forced);
+    s.A = in_global(s.A); s.P = in_global(s.P); s.flags = in_global(s.flags); s.delta = in_global(s.delta);
+    skip.P = in_global(skip.P); skip.dflags = in_global(skip.dflags);
+    X = in_global(X); forced = in_global(forced);
     constexpr int PPB = 256 / G;
     const int tid = threadIdx.x;
     const int lp = tid % G;
@@ -262,44 +270,57 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
     bool m = false, cand = false;
     if (pix < HW) {
         int fl = s.flags[pix];
-        const bool is_input = s.kind == MDCNN_SITE_INPUT;
+        __builtin_amdgcn_sched_barrier(0);                 // (on its way before the addresses of the rest are worked out)
+        const int vy = div24(pix, s.W, rcp_of(s.W)), vx = pix - vy * s.W;
+        const bool is_input = !EARLY && s.kind == MDCNN_SITE_INPUT;
+        T* Ap = (T*)s.A + a_offset(s, vy, vx);
+        T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
+        T* Sp = skip.P ? (T*)skip.P + skip_offset(skip, vy, vx, s.C) : nullptr;
+        using raw = typename V16<T>::raw;
+        raw ra[CH], rt[CH], rk[CH];
+        int sfl = 0;
+        auto at = [&](const T* p, int j) { return *reinterpret_cast<const raw*>(p + (lp + j * G) * VEC); };
+        // what a fused residual skip adds to, before the stores: a load after them is back only once they are done
+        auto ask_skip = [&] {
+            if (Sp) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j) rk[j] = at(Sp, j);
+                if (lp == 0 && skip.dflags) sfl = skip.dflags[pix];
+            }
+        };
+        if constexpr (EARLY) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) { ra[j] = at(Ap, j); rt[j] = at(Pp, j); }
+            ask_skip();
+        }
         int xpix = pix;                                    // index into the frame and the forced mask
         bool inside = true;
         if (s.s_off) inside = crop_state(s, pix, lp == 0, fl, xpix);
-        const bool chosen = forced && inside && forced[xpix] != 0;
-        cand = inside && (is_input || forced != nullptr || (fl & (kFlagN | kFlagU)));
-        const int vy = div24(pix, s.W, rcp_of(s.W)), vx = pix - vy * s.W;
+        const bool chosen = !EARLY && forced && inside && forced[xpix] != 0;
+        cand = inside && (is_input || (!EARLY && forced != nullptr) || (fl & (kFlagN | kFlagU)));
         if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
-        if (forced ? inside && (chosen || (fl & kFlagN)) : cand) {      // (a pixel that its mask leaves out is not read)
-            T* Ap = (T*)s.A + a_offset(s, vy, vx);
-            T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
-            const T* Xp = is_input ? X + (size_t)xpix * s.C : nullptr;
-            float na[CH][VEC], out[CH][VEC], sk[CH][VEC];
-            // what a fused residual skip adds to, before the stores: a load after them is back only once they are done
-            T* Sp = skip.P ? (T*)skip.P + skip_offset(skip, vy, vx, s.C) : nullptr;
-            int sfl = 0;
-            if (Sp) {
+        if (!EARLY && forced ? inside && (chosen || (fl & kFlagN)) : cand) {      // (a pixel that its mask leaves out is not read)
+            if constexpr (!EARLY) {
+                const T* tp = is_input ? X + (size_t)xpix * s.C : Pp;
+                ask_skip();
 #pragma unroll
-                for (int j = 0; j < CH; ++j) V16<T>::load(Sp + (lp + j * G) * VEC, sk[j]);
-                if (lp == 0 && skip.dflags) sfl = skip.dflags[pix];
+                for (int j = 0; j < CH; ++j) {
+                    if (!(fl & kFlagN)) ra[j] = at(Ap, j);
+                    rt[j] = at(tp, j);
+                }
             }
+            float na[CH][VEC], out[CH][VEC];
             float mx = 0.f;
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-                const int c0 = (lp + j * G) * VEC;
+                if (fl & kFlagN) ra[j] = raw{};      // nothing accumulated yet (and perhaps not even set to zero)
                 float a[VEC], t[VEC];
-                if (fl & kFlagN) {                         // nothing accumulated yet (and perhaps not even set to zero)
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) a[i] = 0.f;
-                } else {
-                    V16<T>::load(Ap + c0, a);
-                }
+                V16<T>::load(reinterpret_cast<const T*>(&ra[j]), a);
+                V16<T>::load(reinterpret_cast<const T*>(&rt[j]), t);
                 if (is_input) {
-                    V16<T>::load(Xp + c0, t);
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) { na[j][i] = t[i]; out[j][i] = t[i] - a[i]; }
                 } else {
-                    V16<T>::load(Pp + c0, t);
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
                         float n = a[i] + t[i];
@@ -311,7 +332,7 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
                 for (int i = 0; i < VEC; ++i) mx = fmaxf(mx, fabsf(out[j][i]));
             }
             mx = group_max<G>(mx);
-            m = forced || (fl & kFlagN) || mx > s.theta;
+            m = (!EARLY && forced) || (fl & kFlagN) || mx > s.theta;
             if (m) {
                 T* Dp = (T*)s.delta + (size_t)pix * s.C;
                 float z[VEC];
@@ -327,9 +348,11 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
                 if (Sp) {                                  // fused residual skip: P_dst += delta (as stored)
 #pragma unroll
                     for (int j = 0; j < CH; ++j) {
+                        float t[VEC];
+                        V16<T>::load(reinterpret_cast<const T*>(&rk[j]), t);
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) sk[j][i] += (float)(T)out[j][i];
-                        V16<T>::store(Sp + (lp + j * G) * VEC, sk[j]);
+                        for (int i = 0; i < VEC; ++i) t[i] += (float)(T)out[j][i];
+                        V16<T>::store(Sp + (lp + j * G) * VEC, t);
                     }
                     if (lp == 0 && skip.dflags) skip.dflags[pix] = (uint8_t)(sfl | kFlagU);
                 }
@@ -468,6 +491,12 @@ static void step1_scalar(const Step1Batch& bt, dim3 grid, hipStream_t st, f16) {
 static void step1_scalar(const Step1Fill& a, dim3 grid, hipStream_t st, float) { k_step1_scalar_fill<float><<<grid, dim3(256), 0, st>>>(a); }
 static void step1_scalar(const Step1Fill& a, dim3 grid, hipStream_t st, f16) { k_step1_scalar_fill<f16><<<grid, dim3(256), 0, st>>>(a); }
 
+// Shared launches ask early up to as many blocks, about one video: below, the round trip is what they last; above, the values of pixels
+// that turn out not to be candidates cost more.  HRNet-like networks, late / early, us a frame: 96 x 96 one video 354 / 342, 512 x 512 431 / 424;
+// 8 videos of 384 x 288 frames that stand still 512 late, 571 with all asked early.  Launches of one site gained nothing (ResNet-18-style
+// frame 373.5 late, 375 early).
+constexpr unsigned kEarlyBlocks = 512u;
+
 // Blocks the step-1 kernel of a site takes per grid layer.
 static unsigned step1_blocks_of(const SiteDev& s) {
     int G = 0, CH = 0;
@@ -502,6 +531,20 @@ hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
     return bt.s[0].dtype == MDCNN_F16 ? step1_t<f16>(bt, bt.s[0], n, 0u, st) : step1_t<float>(bt, bt.s[0], n, 0u, st);
 }
 
+template <bool EARLY>
+__device__ __forceinline__ void step1_site(const SiteDev& s, const SkipDev& k, unsigned blk) {
+    const f16* const X = nullptr;
+    switch (s.C / V16<f16>::N) {                           // lanes per pixel
+        case 1: step1_block<f16, 1, 1, EARLY>(s, k, X, nullptr, blk); break;
+        case 2: step1_block<f16, 2, 1, EARLY>(s, k, X, nullptr, blk); break;
+        case 4: step1_block<f16, 4, 1, EARLY>(s, k, X, nullptr, blk); break;
+        case 8: step1_block<f16, 8, 1, EARLY>(s, k, X, nullptr, blk); break;
+        case 16: step1_block<f16, 16, 1, EARLY>(s, k, X, nullptr, blk); break;
+        case 32: step1_block<f16, 32, 1, EARLY>(s, k, X, nullptr, blk); break;
+        default: step1_block<f16, 64, 1, EARLY>(s, k, X, nullptr, blk); break;
+    }
+}
+
 // Step 1 of several sites that do not depend on each other (see k_conv_multi): one 16-byte chunk per lane, fp16.
 __global__ __launch_bounds__(256) void k_step1_multi(unsigned b1, unsigned b2, unsigned b3, unsigned b4, unsigned b5, unsigned videos, Step1Multi m) {
     unsigned blk;
@@ -520,16 +563,8 @@ __global__ __launch_bounds__(256) void k_step1_multi(unsigned b1, unsigned b2, u
     SkipDev k{};
     k.P = at(jb.skip_P, v.kd); k.dflags = at(jb.skip_flags, v.kd);
     k.Hp = jb.skip_Hp; k.Wp = jb.skip_Wp; k.by0 = jb.skip_by0; k.bx0 = jb.skip_bx0; k.p_oy = v.k_oy; k.p_ox = v.k_ox;
-    const f16* const X = nullptr;
-    switch (s.C / V16<f16>::N) {                           // lanes per pixel
-        case 1: step1_block<f16, 1, 1>(s, k, X, nullptr, blk); break;
-        case 2: step1_block<f16, 2, 1>(s, k, X, nullptr, blk); break;
-        case 4: step1_block<f16, 4, 1>(s, k, X, nullptr, blk); break;
-        case 8: step1_block<f16, 8, 1>(s, k, X, nullptr, blk); break;
-        case 16: step1_block<f16, 16, 1>(s, k, X, nullptr, blk); break;
-        case 32: step1_block<f16, 32, 1>(s, k, X, nullptr, blk); break;
-        default: step1_block<f16, 64, 1>(s, k, X, nullptr, blk); break;
-    }
+    if (m.early) step1_site<true>(s, k, blk);
+    else step1_site<false>(s, k, blk);
 }
 
 bool step1_multi_applies(const SiteDev& s) {
@@ -547,6 +582,7 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
         const int ppb = 256 / G;
         m.blocks.add(j, (unsigned)((jb.H * jb.W + ppb - 1) / ppb));
     }
+    m.early = m.blocks.total * (unsigned)videos <= kEarlyBlocks;
     k_step1_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m.blocks.begin[1], m.blocks.begin[2], m.blocks.begin[3], m.blocks.begin[4],
                                                                                              m.blocks.begin[5], (unsigned)videos, m);
     return hipGetLastError();

@@ -44,6 +44,15 @@ __device__ __forceinline__ void read_now(A& a, R&... r) {
     }
 }
 
+// A pointer that read_now() has hidden is to global memory all the same: without this its loads are flat ones, which return
+// out of order with those of LDS, so that each is waited for by itself.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+    auto g = (__attribute__((address_space(1))) T*)p;
+    asm("" : "+s"(g));                             // (or the two casts are taken for none)
+    return (T*)g;
+}
+
 constexpr int kFlagN = 1;   // newly unveiled this frame
 constexpr int kFlagU = 2;   // touched by a producer this frame
 constexpr int kFlagM = 4;   // updated (emitted a delta) this frame
@@ -378,13 +387,13 @@ struct Step1Vid {
 };
 struct Step1Multi {
     JobBlocks<kMaxMultiJobs> blocks;
-    int n, videos;
+    int n, videos, early;
     Step1Job job[kMaxMultiJobs];
     Step1Vid vid[kMaxStep1Vids];
 };
 static_assert(sizeof(Step1Multi) <= 4000, "kernel arguments stay below 4 KiB");
 bool step1_multi_applies(const SiteDev& s);
-hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      // fills in blocks and videos
+hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      // fills in blocks, videos and early
 
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls

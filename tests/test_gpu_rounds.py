@@ -19,6 +19,13 @@ def test_rounds_do_not_change_a_bit(H, W, batch):
     same(run(net, seq, 1, batch=batch), run(net, seq, 0, batch=batch))
 
 
+# step 1 of a round asks for its values with the flags up to 512 blocks (one video of 512 x 512: about 480, two of 352 x 480: 620) and after them above
+@pytest.mark.parametrize("H,W,batch", [(352, 480, 2), (352, 480, 3)])
+def test_rounds_of_many_blocks(H, W, batch):
+    net, seq = build_net(4, H=H, W=W, blocks=1), build_sequence(4, n_frames=3, H=H, W=W)
+    same(run(net, seq, 1, batch=batch), run(net, seq, 0, batch=batch))
+
+
 @pytest.mark.parametrize("seed", range(4))
 def test_rounds_of_random_networks(seed):
     net = random_dag_net(seed, "f16", n_inner=9)
