@@ -43,12 +43,15 @@ struct Px8 {
 #pragma unroll
         for (int i = 0; i < 2; ++i) r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 16u * i), 0, 0);
     }
-    __device__ __forceinline__ void add_store(rsrc_t rs, unsigned off, float* v) {      // v becomes what is stored
+    __device__ __forceinline__ void add_store(rsrc_t rs, unsigned off, float* v, unsigned take = 0xffu) {      // take: bit k, v[k] is added; v becomes what is stored
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             f32x4 o = __builtin_bit_cast(f32x4, r[i]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[4 * i + q] = o[q] += v[4 * i + q];
+            for (int q = 0; q < 4; ++q) {
+                if (take >> (4 * i + q) & 1u) o[q] += v[4 * i + q];
+                v[4 * i + q] = o[q];
+            }
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), rs, (int)(off + 16u * i), 0, 0);
         }
     }
@@ -58,8 +61,14 @@ constexpr unsigned kBeyond = 0x80000000u;            // a byte offset past every
 
 // Tile with top left index-space pixel (y0, x0) - the padded window, or the source view of an upsampling edge - and first
 // cout n0.  Block-uniform; called by all 256 threads; smem: kF32Smem floats, s_vm: kF32Px words, s_or: 4 words.  The caller
-// has a barrier before the call.
-__device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int th, int tw, int n0, bool published, float* smem, unsigned* s_vm, unsigned* s_or) {
+// has a barrier before the call.  take(wy, wx, c): which of the couts n0 + c .. n0 + c + 7 of a window pixel are wanted, a bit each
+// (edges without upsampling); the others are left as they are.
+struct AllCouts {
+    __device__ __forceinline__ unsigned operator()(int, int, int) const { return 0xffu; }
+};
+template <typename Take = AllCouts>
+__device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int th, int tw, int n0, bool published, float* smem, unsigned* s_vm, unsigned* s_or,
+                                         Take take = Take()) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5;
@@ -171,8 +180,9 @@ __device__ __forceinline__ void f32_tile(const EdgeDev& e, int y0, int x0, int t
             for (int k = 0; k < 8; ++k) v[k] = w ? v[k] + u[k] : u[k];
         }
         if (!e.up) {
-            pold.add_store(prs, poff, v);
-            if (e.dY) {                                          // (the launch reads the site out)
+            const unsigned want = take(wy, wx, c8);
+            if (want) pold.add_store(prs, poff, v, want);
+            if (want && e.dY) {                                        // (the launch reads the site out)
                 const int oy = wy - e.by0, ox = wx - e.bx0;
                 if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
                     write_out<float, 8>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, v);

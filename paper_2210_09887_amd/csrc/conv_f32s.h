@@ -25,7 +25,9 @@ constexpr int split_rows(int tm) { return tm == 1 ? 4 : tm == 2 ? 7 : 9; }      
 // splits them, and passes them between its lanes through LDS of its own, which takes no barrier, the LDS operations of a wave
 // being in order.  The four partial sums are added through LDS in wave order, so the tile does not change a result.
 //
-// A part of an infinity or NaN is none: a tile with a sum that is not finite is done again, with products in fp32 (f32_tile).
+// A part of an infinity or NaN is none: sums that are not finite are made again, with products in fp32 (f32_tile), and they alone, from
+// runs of 16 window columns that every tile has in common - a value is that of its own operands, whatever shares the tile, and a
+// video of a batch, where tiles are of another size, gives the bits it gives alone.
 //
 // What bounds it: the issue of instructions, about 75 of a step beside its 6 TM products, 44 of them the split of the weights,
 // at 4.6 cycles each - 0.34 us a step with two row tiles, whether one block is on a compute unit or two share it.  Chains of
@@ -45,7 +47,7 @@ struct SplitCfg {
     static constexpr int WP = 48, WPLANE = 32 * WP;  // a wave's weights: bytes from cout to cout, from part to part
     static constexpr int SUMS = 4 * M * kF32Sum * 4;
     static constexpr int ROW_BYTES = 3 * NBUF * PLANE > SUMS ? 3 * NBUF * PLANE : SUMS;
-    static constexpr int SMEM = ROW_BYTES + 4 * 3 * WPLANE + M * 4 + ROWS * 4;
+    static constexpr int SMEM = ROW_BYTES + 4 * 3 * WPLANE + M * 4 + M * 4 + ROWS * 4;
     static_assert(ROW_BYTES >= kF32Smem * 4 + kF32Px * 4 + 16, "the tile of conv_f32.h in the same place");
     static_assert(SMEM * MINB <= 160 * 1024);
 };
@@ -73,6 +75,8 @@ __device__ __forceinline__ void split_bf16(u32x4_t raw, u32x2_t* p) {
     }
 }
 
+__device__ __forceinline__ bool finite(float x) { return __builtin_fabsf(x) <= 3.4028234e38f; }
+
 // Which of 32 entries a lane has: the 16 lanes whose 16-byte LDS reads go together (0-3, 12-15, 20-27; the others) have consecutive ones.
 __device__ __forceinline__ int entry_of_lane(int l) {
     const bool second = (l >= 4 && l < 12) || (l >= 16 && l < 20) || l >= 28;
@@ -85,7 +89,8 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* const s_w = smem + Cfg::ROW_BYTES;
     int* const s_ent = reinterpret_cast<int*>(s_w + 4 * 3 * WPLANE);        // entry -> ly << 4 | lx
-    unsigned char* const s_mask = reinterpret_cast<unsigned char*>(s_ent + M);  // updated pixels of a staged row, four bits a wave
+    unsigned char* const s_left = reinterpret_cast<unsigned char*>(s_ent + M);  // sums to be made again: [pixel of the tile][cout / 8], a bit each
+    unsigned char* const s_mask = s_left + 4 * M;                              // updated pixels of a staged row, four bits a wave
     int Hp = e.Hp, Wp = e.Wp, sH = e.sH, sW = e.sW, Cin = e.Cin, Cout = e.Cout, by0 = e.by0, bx0 = e.bx0, pad = e.pad;
     int NT = g.NT, th = g.p0, tw = g.p1, tiles_x = g.tiles_x;
     unsigned per_NT = g.per_NT, per_tiles_x = g.per_tiles_x;
@@ -315,29 +320,47 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
             for (int k = 0; k < 8; ++k) v[t][k] = w ? v[t][k] + u[k] : u[k];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) bad |= !(__builtin_fabsf(v[t][k]) <= 3.4028234e38f);
+        for (int k = 0; k < 8; ++k) bad |= !finite(v[t][k]);
     }
-    if (__syncthreads_or(bad)) {
-        // an operand that is not finite has parts that are none of its own: the tile again, row by row, with products in fp32
-        float* const sm = reinterpret_cast<float*>(smem);
-        unsigned* const s_vm = reinterpret_cast<unsigned*>(sm + kF32Smem);
-        for (int r = 0; r < nty; ++r) {
-            __syncthreads();
-            f32_tile(e, wy0 + r, wx0, 1, ntx, n0, true, sm, s_vm, s_vm + kF32Px);
+    auto finish = [&](auto some) {                    // some: there are sums that are not finite
+#pragma unroll
+        for (int t = 0; t < NPASS; ++t) {
+            const int at = t * 64 + (tid >> 2);
+            if (at >= tot) continue;
+            const int en = s_ent[at], ly = en >> 4, lx = en & 15;
+            unsigned done = 0xffu;
+            if constexpr (decltype(some)::value) {
+                done = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) done |= finite(v[t][k]) ? 1u << k : 0u;
+                s_left[(ly * tw + lx) * 4 + (tid & 3)] = (unsigned char)~done;
+            }
+            pold[t].add_store(prs, poff[t], v[t], done);
+            if (e.dY) {                               // (the launch reads the site out)
+                const int oy = wy0 + ly - by0, ox = wx0 + lx - bx0;
+                if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
+                    write_out<float, 8>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, v[t]);
+            }
         }
+    };
+    if (!__syncthreads_or(bad)) {
+        finish(std::false_type{});
         return;
     }
-#pragma unroll
-    for (int t = 0; t < NPASS; ++t) {
-        const int at = t * 64 + (tid >> 2);
-        if (at >= tot) continue;
-        pold[t].add_store(prs, poff[t], v[t]);
-        if (e.dY) {                                   // (the launch reads the site out)
-            const int en = s_ent[at], oy = wy0 + (en >> 4) - by0, ox = wx0 + (en & 15) - bx0;
-            if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
-                write_out<float, 8>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, v[t]);
+    if (tid < M) reinterpret_cast<int*>(s_left)[tid] = 0;
+    __syncthreads();
+    finish(std::true_type{});
+    __syncthreads();
+    float* const sm = reinterpret_cast<float*>(smem);
+    unsigned* const s_vm = reinterpret_cast<unsigned*>(sm + kF32Smem);
+    for (int r = 0; r < nty; ++r)
+        for (int x = wx0 & ~15; x < wx0 + ntx; x += 16) {
+            const int lx = x - wx0 + tid;
+            if (!__syncthreads_or(tid < 16 && (unsigned)lx < (unsigned)ntx && reinterpret_cast<int*>(s_left)[r * tw + lx])) continue;
+            f32_tile(e, wy0 + r, x, 1, 16, n0, true, sm, s_vm, s_vm + kF32Px, [&](int, int wx, int c) -> unsigned {
+                return (unsigned)(wx - wx0) < (unsigned)ntx ? s_left[(r * tw + wx - wx0) * 4 + (c >> 3)] : 0u;
+            });
         }
-    }
 }
 
 }  // namespace mdcnn

@@ -161,3 +161,40 @@ def test_values_that_are_not_finite(n):
     assert int((~fin).sum()) <= 4 * 9 * 64 and float((out - ref)[fin].abs().max()) < 1e-4
     near = big & (ref.abs() < 3.4e38)
     assert float(((out - ref)[near] / ref[near]).abs().max()) < 1e-6
+
+
+def row_tiles(n, cin, cout, videos):
+    """Row tiles of a tile that the library takes for 3x3 fp32 layers of 64 n channels on n x n views (an internal rule)."""
+    from paper_2210_09887_amd import binding as B
+    return getattr(B.lib(), "_ZN5mdcnn12split_choiceEiiiii")(n + 2, n + 2, cin, cout, videos)
+
+
+@pytest.mark.parametrize("bad", ["finite", "frame", "weight"])
+@pytest.mark.parametrize("cin,n,videos,alone,together", [(64, 64, 2, 2, 3), (64, 96, 2, 3, 2), (64, 32, 4, 1, 2), (64, 32, 8, 1, 3), (128, 64, 2, 2, 3)])
+def test_bits_in_a_batch(cin, n, videos, alone, together, bad):
+    """A video of a batch gives the bits it gives alone where the batch takes other tiles: dense and sparse frames, and frames with a few
+    sums that are not finite, from infinities, NaN and overflow in the frame or from a weight."""
+    import gpu_harness as G
+    from paper_2210_09887_amd.runtime import GpuBatch, GpuNet
+    net = tiny_net("f32", n, n, (cin, 64), theta=0.05, seed=n + videos)
+    assert (row_tiles(n, cin, 64, 1), row_tiles(n, cin, 64, videos)) == (alone, together)
+    frames = frames_of(net, n + videos)
+    if bad == "weight":
+        w = net.edges[0].w.reshape(9, 64, cin)
+        w[2, 5, 7], w[4, 40, 63] = np.inf, np.nan
+    if bad == "frame":
+        for t, (y, x) in enumerate([(3, 4), (n // 2, n - 1), (n - 1, n // 3)]):
+            frames[t][y, x, :5] += np.float32([np.inf, 0, 0, 0, 0])
+            frames[t][n - 1 - y, n - 1 - x, 9] = [np.nan, 3.4e38, -np.inf][t]
+    many = GpuBatch(net, videos)
+    one = GpuNet(net)
+    try:
+        for f, (dy, dx) in zip(frames, [(0, 0), (0, 0), (1, -1)]):
+            want = one.frame(G.dev(f), dy, dx)[0].cpu().numpy().reshape(-1)
+            outs, _ = many.frame([G.dev(f)] * videos, [dy] * videos, [dx] * videos)
+            for o in outs:
+                o = o.cpu().numpy().reshape(-1)
+                assert np.array_equal(o, want, equal_nan=True), f"{int((~((o == want) | (np.isnan(o) & np.isnan(want)))).sum())} values differ"
+    finally:
+        one.close()
+        many.close()
