@@ -12,11 +12,15 @@ constexpr int split_rows(int tm) { return tm == 1 ? 4 : tm == 2 ? 7 : 9; }      
 
 // ---------------------------------------------------------------------------
 // A tile is a th x tw rectangle of the padded window (tw <= 14, th * tw <= 32 TM) x 32 couts; its live pixels are ranked as
-// those of conv_rect.h and TM row tiles of 32 of them multiplied.  An fp32 value is the exact sum of three bf16 (each the rest
-// rounded to the nearest), and a product the six products of parts that are above 2^-27 of it, each exact in the fp32
-// accumulators of v_mfma_f32_32x32x16_bf16: 192 cycles for 16 channels where v_mfma_f32_32x32x2_f32 takes 512.  Those of the
-// leading parts have accumulators of their own, a rounding per 16 channels instead of one per channel: against 64 bits, 64 to
-// 512 channels of normal and rectified values, 0.8e-7 to 2.0e-7 of the result, with fp32 products 1.6e-7 to 6.0e-7.
+// those of conv_rect.h and TM row tiles of 32 of them multiplied.  An fp32 value is the exact sum of three bf16, each the rest
+// rounded to the nearest (Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations", 2019), and a product six of the nine products of their parts, each exact in the fp32 accumulators of
+// v_mfma_f32_32x32x16_bf16: 192 cycles for 16 channels where v_mfma_f32_32x32x2_f32 takes 512.  Those of the leading parts have
+// accumulators of their own, a rounding per 16 channels instead of one per channel: against 64 bits, 64 to 512 channels of normal
+// and rectified values, 0.8e-7 to 2.0e-7 of the result, with fp32 products 1.6e-7 to 6.0e-7.  The three products left out are 2^-24 of
+// the whole one at most, half a unit of its last place: a sum of ONE product is off by 2.59e-8 (root mean square; worst seen 0.9 units), with
+// fp32 products 2.53e-8 (0.5); of two 3.54e-8 against 3.58e-8, of 16 4.9e-8 against 5.8e-8.  Two products more would mend the first at 500
+// us for 470 of a 256 x 256 frame of the ResNet-18-style network.
 //
 // The footprint of the tile is fetched per 64-channel chunk, split once for its nine taps and kept in LDS, part by part, in rows
 // of 16 pixels.  A pixel takes 144 bytes and a row is further on by as many 16-byte steps as its tw entries have taken, so
@@ -25,16 +29,17 @@ constexpr int split_rows(int tm) { return tm == 1 ? 4 : tm == 2 ? 7 : 9; }      
 // splits them, and passes them between its lanes through LDS of its own, which takes no barrier, the LDS operations of a wave
 // being in order.  The four partial sums are added through LDS in wave order, so the tile does not change a result.
 //
-// A part of an infinity or NaN is none: sums that are not finite are made again, with products in fp32 (f32_tile), and they alone, from
+// A part of an infinity or NaN is none: sums that are not finite then either are made with products in fp32 (f32_tile), and they alone, from
 // runs of 16 window columns that every tile has in common - a value is that of its own operands, whatever shares the tile, and a
 // video of a batch, where tiles are of another size, gives the bits it gives alone.
 //
-// What bounds it: the issue of instructions, about 75 of a step beside its 6 TM products, 44 of them the split of the weights,
+// What bounds it: the issue of instructions, about 83 of a step beside its 6 TM products, 52 of them the split of the weights,
 // at 4.6 cycles each - 0.34 us a step with two row tiles, whether one block is on a compute unit or two share it.  Chains of
 // one layer, all pixels updated, us a frame (10 of them not this launch), before (k_conv_f32) and now: 512 -> 512 on 32 x 32 84.9 and
 // 58.0, 256 -> 256 34.1 and 24.7, 128 -> 128 on 64 x 64 28.5 and 22.8, 64 -> 64 on 128 x 128 27.9 and 25.4, on 256 x 256
 // 82.7 and 65.9.  Stride 2, with a footprint four times the tile, was no faster than k_conv_f32 (64 -> 128: 23.4 and 21.3).  Not
-// faster either: weights fetched nine steps ahead, other orders of the instructions of a step.
+// faster either: weights fetched nine steps ahead, other orders of the instructions of a step.  The multiplications by powers of two
+// of the split are within the noise where they are (512 -> 512 47.8 and 48.4, 256 -> 256 23.0 and 22.4, in another run).
 // ---------------------------------------------------------------------------
 template <int TM_>
 struct SplitCfg {
@@ -47,7 +52,8 @@ struct SplitCfg {
     static constexpr int WP = 48, WPLANE = 32 * WP;  // a wave's weights: bytes from cout to cout, from part to part
     static constexpr int SUMS = 4 * M * kF32Sum * 4;
     static constexpr int ROW_BYTES = 3 * NBUF * PLANE > SUMS ? 3 * NBUF * PLANE : SUMS;
-    static constexpr int SMEM = ROW_BYTES + 4 * 3 * WPLANE + M * 4 + M * 4 + ROWS * 4;
+    static constexpr int LEFT = ROW_BYTES + 4 * 3 * WPLANE + M * 4;
+    static constexpr int SMEM = LEFT + M * 4 + ROWS * 4;
     static_assert(ROW_BYTES >= kF32Smem * 4 + kF32Px * 4 + 16, "the tile of conv_f32.h in the same place");
     static_assert(SMEM * MINB <= 160 * 1024);
 };
@@ -57,12 +63,13 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
-// x = p[0] + p[1] + p[2], exactly (each the rest rounded to the nearest bf16)
-__device__ __forceinline__ void split_bf16(u32x4_t raw, u32x2_t* p) {
+// x scale = p[0] + p[1] + p[2] (each the rest rounded to the nearest bf16), exactly if x scale is below 2^128 and x's last place, scaled,
+// 2^-126 or above: the matrix instruction takes a subnormal operand for zero
+__device__ __forceinline__ void split_bf16(u32x4_t raw, float scale, u32x2_t* p) {
     const f32x4 x = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        float a = x[2 * i], b = x[2 * i + 1];
+        float a = x[2 * i] * scale, b = x[2 * i + 1] * scale;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const unsigned h = pack_bf16(a, b);
@@ -83,13 +90,21 @@ __device__ __forceinline__ int entry_of_lane(int l) {
     return second ? (l < 12 ? l + 12 : l < 20 ? l + 8 : l) : (l < 4 ? l : l < 16 ? l - 8 : l - 12);
 }
 
+// Weights and delta rows are multiplied by powers of two first, so that the parts of the smallest values are normal numbers: 2^-149
+// becomes 2^-125 (as they were, frames of 1e-36 came out 2^-15 off and weights of 1e-36 2^-11, subnormal ones as zeros; fp32 products are
+// 2^-22.5 off there as everywhere, these now 2^-23.7).  What that makes too large, rows from 2^104 or sums from 2^80 on, comes out not
+// finite and is made again with rows divided by 2^40: what those lose is far below the roundings of such a sum.
+constexpr float kSplitWeights = 0x1p24f, kSplitRows = 0x1p24f, kSplitRowsLarge = 0x1p-40f;
+
+// The sums of a tile; false: that was all of them.  again: those that are not finite once more (left: this thread's, eight bits to an entry),
+// and which are not even then goes to s_left.
 template <typename Cfg>
-__device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const TileGrid& g) {
+__device__ __forceinline__ bool split_pass(const EdgeDev& e, unsigned blk, const TileGrid& g, bool again, unsigned& left) {
     constexpr int TM = Cfg::TM, M = Cfg::M, ROWS = Cfg::ROWS, PXP = Cfg::PXP, PLANE = Cfg::PLANE, WP = Cfg::WP, WPLANE = Cfg::WPLANE, NBUF = Cfg::NBUF, R = 3;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* const s_w = smem + Cfg::ROW_BYTES;
     int* const s_ent = reinterpret_cast<int*>(s_w + 4 * 3 * WPLANE);        // entry -> ly << 4 | lx
-    unsigned char* const s_left = reinterpret_cast<unsigned char*>(s_ent + M);  // sums to be made again: [pixel of the tile][cout / 8], a bit each
+    unsigned char* const s_left = smem + Cfg::LEFT;                            // sums still to be made: [pixel of the tile][cout / 8], a bit each
     unsigned char* const s_mask = s_left + 4 * M;                              // updated pixels of a staged row, four bits a wave
     int Hp = e.Hp, Wp = e.Wp, sH = e.sH, sW = e.sW, Cin = e.Cin, Cout = e.Cout, by0 = e.by0, bx0 = e.bx0, pad = e.pad;
     int NT = g.NT, th = g.p0, tw = g.p1, tiles_x = g.tiles_x;
@@ -99,6 +114,7 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, h = lane >> 5, e32 = entry_of_lane(r32);
     const int nchunks = Cin / 64;
+    const float up = again ? kSplitRowsLarge : kSplitRows, down = again ? 1 / (kSplitWeights * kSplitRowsLarge) : 1 / (kSplitWeights * kSplitRows);
     const int pitch = 16 * (PXP + (9 * tw & 15));
     const unsigned row = (unsigned)Cin * 4u;         // bytes of a source pixel
     const rsrc_t drs = make_rsrc(e.delta, (unsigned)sH * (unsigned)sW * row);
@@ -168,7 +184,7 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
     upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
     upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
     const int tot = __builtin_amdgcn_readlane(upto, 15);
-    if (tot == 0) return;                             // block-uniform
+    if (tot == 0) return false;                       // block-uniform
     if (tid < M) {
         const int ly = fast_div(tid, tw, rcp_of(tw)), lx = tid - ly * tw;
         const int a = __shfl(any, ly), before = __shfl(upto, ly) - __popc(a);
@@ -176,7 +192,7 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
     }
     auto store_row = [&](int j, int buf) {
         u32x2_t p[3];
-        split_bf16(raw[j], p);
+        split_bf16(raw[j], up, p);
 #pragma unroll
         for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2_t*>(smem + (buf * 3 + q) * PLANE + j * pitch + sx * PXP + piece * 8) = p[q];
     };
@@ -189,7 +205,8 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             u32x2_t p[3];
-            split_bf16(rw[slot][i], p);
+            asm volatile("" : "+v"(rw[slot][i]));      // (or the multiplication goes up to where the weights are asked for, and waits: 490 us for 470)
+            split_bf16(rw[slot][i], kSplitWeights, p);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2_t*>(my_w + q * WPLANE + (i * 16 + (lane >> 2)) * WP + (lane & 3) * 8) = p[q];
         }
@@ -253,6 +270,13 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
                     for (int t = 0; t < L; ++t) {
                         f32x16& to = u ? low[t] : acc[t];
                         to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[slot][qw[u]], fr[slot][qr[u]][t], to, 0, 0, 0);
+                    }
+                }
+                if constexpr (TM == 3) {               // four others between two products: pays for the multiplications here, 465 -> 458 us a 256 x 256 frame (fewer row tiles: slower)
+#pragma unroll
+                    for (int u = 0; u < 6 * L; ++u) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
                     }
                 }
                 if constexpr (NBUF == 2) {
@@ -322,43 +346,67 @@ __device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const
 #pragma unroll
         for (int k = 0; k < 8; ++k) bad |= !finite(v[t][k]);
     }
-    auto finish = [&](auto some) {                    // some: there are sums that are not finite
+    auto finish = [&](auto some) {                    // some: not all of them, or not all are finite
 #pragma unroll
         for (int t = 0; t < NPASS; ++t) {
             const int at = t * 64 + (tid >> 2);
             if (at >= tot) continue;
-            const int en = s_ent[at], ly = en >> 4, lx = en & 15;
             unsigned done = 0xffu;
             if constexpr (decltype(some)::value) {
                 done = 0;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) done |= finite(v[t][k]) ? 1u << k : 0u;
-                s_left[(ly * tw + lx) * 4 + (tid & 3)] = (unsigned char)~done;
+                done &= left >> (8 * t);
             }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[t][k] *= down;
             pold[t].add_store(prs, poff[t], v[t], done);
+            const int en = s_ent[at], ly = en >> 4, lx = en & 15;
             if (e.dY) {                               // (the launch reads the site out)
                 const int oy = wy0 + ly - by0, ox = wx0 + lx - bx0;
                 if ((unsigned)oy < (unsigned)e.dH && (unsigned)ox < (unsigned)e.dW)
                     write_out<float, 8>((float*)e.dY, e.s_relu, ((size_t)oy * e.dW + ox) * e.Cout + n0 + c8, v[t]);
             }
+            if constexpr (decltype(some)::value) {
+                left &= ~(done << (8 * t));
+                if (again) s_left[(ly * tw + lx) * 4 + (tid & 3)] = (unsigned char)(left >> (8 * t));
+            }
         }
     };
-    if (!__syncthreads_or(bad)) {
+    if (!again && !__syncthreads_or(bad)) {
         finish(std::false_type{});
-        return;
+        return false;
     }
-    if (tid < M) reinterpret_cast<int*>(s_left)[tid] = 0;
-    __syncthreads();
+    if (!again) {
+#pragma unroll
+        for (int t = 0; t < NPASS; ++t) left |= t * 64 + (tid >> 2) < tot ? 0xffu << (8 * t) : 0u;
+    } else {
+        if (tid < M) reinterpret_cast<int*>(s_left)[tid] = 0;
+        __syncthreads();
+    }
     finish(std::true_type{});
-    __syncthreads();
+    return __syncthreads_or(left != 0);
+}
+
+template <typename Cfg>
+__device__ __forceinline__ void split_tile(const EdgeDev& e, unsigned blk, const TileGrid& g) {
+    unsigned left = 0;
+#pragma unroll 1
+    for (int again = 0; again < 2; ++again)
+        if (!split_pass<Cfg>(e, blk, g, again != 0, left)) return;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int* const s_left = reinterpret_cast<const int*>(smem + Cfg::LEFT);
     float* const sm = reinterpret_cast<float*>(smem);
     unsigned* const s_vm = reinterpret_cast<unsigned*>(sm + kF32Smem);
+    const int th = g.p0, tw = g.p1, mt = by_reciprocal((int)blk, g.per_NT), n0 = ((int)blk - mt * g.NT) * 32;
+    const int ty = by_reciprocal(mt, g.per_tiles_x), wy0 = ty * th, wx0 = (mt - ty * g.tiles_x) * tw;
+    const int nty = wy0 + th < e.Hp ? th : e.Hp - wy0, ntx = wx0 + tw < e.Wp ? tw : e.Wp - wx0;
     for (int r = 0; r < nty; ++r)
         for (int x = wx0 & ~15; x < wx0 + ntx; x += 16) {
-            const int lx = x - wx0 + tid;
-            if (!__syncthreads_or(tid < 16 && (unsigned)lx < (unsigned)ntx && reinterpret_cast<int*>(s_left)[r * tw + lx])) continue;
+            const int lx = x - wx0 + (int)threadIdx.x;
+            if (!__syncthreads_or(threadIdx.x < 16 && (unsigned)lx < (unsigned)ntx && s_left[r * tw + lx])) continue;
             f32_tile(e, wy0 + r, x, 1, 16, n0, true, sm, s_vm, s_vm + kF32Px, [&](int, int wx, int c) -> unsigned {
-                return (unsigned)(wx - wx0) < (unsigned)ntx ? s_left[(r * tw + wx - wx0) * 4 + (c >> 3)] : 0u;
+                return (unsigned)(wx - wx0) < (unsigned)ntx ? (unsigned)s_left[r * tw + wx - wx0] >> c & 0xffu : 0u;
             });
         }
 }

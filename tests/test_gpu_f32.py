@@ -198,3 +198,36 @@ def test_bits_in_a_batch(cin, n, videos, alone, together, bad):
     finally:
         one.close()
         many.close()
+
+
+@pytest.mark.parametrize("in_frame,in_weights", [(1e-34, 1.0), (1e-36, 1.0), (1.0, 1e-36), (1e-20, 1e-16), (1e35, 1e-36), (3e-38, 1e4), (1e-42, 1e10), (1e10, 1e-39), (1e37, 1.0)])
+@pytest.mark.parametrize("cin,n", [(64, 64), (512, 16)])
+def test_precision_at_the_ends_of_the_range(cin, n, in_frame, in_weights):
+    """The bound of test_precision_of_split_products wherever the sums are normal numbers: the second and third part of a value below 2^-110
+    would not be, and the matrix instruction takes what is not for zero.  At the upper end sums of 2^80 and more, which take a second pass."""
+    net = tiny_net("f32", n, n, (cin, 32), theta=0.0, seed=cin)
+    net.edges[0].b[:] = 0
+    net.edges[0].w *= np.float32(in_weights)
+    X = (np.maximum(np.random.default_rng(cin).normal(0, 1, (n, n, cin)), 0) * in_frame).astype(np.float32)
+    out, ref = dense_frame(net, X)
+    err = float((out - ref).norm() / ref.norm())
+    assert err < 2.0 ** -25 * (9 * cin / 16 + 8) ** 0.5
+
+
+@pytest.mark.parametrize("tap", [0, 4])
+def test_one_product(tap):
+    """One live product to a sum.  Left out of it are the products of parts 1, 2 and 2, 1, at most 2^-25 of a unit pair's product each, and 2, 2,
+    2^-34: half a unit of the last place and 2^-11 of one.  Rounding the sum takes another half, and each of the three sums of the smaller parts, at
+    most 2^-7 of the whole, at most a unit of its own last place: 2^-5 in all."""
+    net = tiny_net("f32", 32, 32, (64, 32), theta=0.0, seed=7)
+    net.edges[0].b[:] = 0
+    rng = np.random.default_rng(tap)
+    w = rng.uniform(1, 2, 32).astype(np.float32)
+    net.edges[0].w[:] = 0
+    net.edges[0].w.reshape(9, 32, 64)[tap, :, 17] = w
+    X = np.zeros((32, 32, 64), np.float32)
+    X[:, :, 17] = rng.uniform(1, 2, (32, 32)).astype(np.float32)
+    out, ref = dense_frame(net, X)
+    ulp = 2.0 ** (ref.abs().clamp_min(1e-30).log2().floor() - 23)
+    worst = float(((out - ref).abs() / ulp)[ref != 0].max())
+    assert worst <= 1 + 2.0 ** -5 + 2.0 ** -11
