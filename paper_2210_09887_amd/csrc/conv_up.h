@@ -14,13 +14,15 @@ namespace mdcnn {
 // updated is multiplied and its result dropped.  Flags, rows, weights and pending values are all requested at once (early) where
 // they are little; where they are more than the round trip takes, rows and pending values once the flags are there, of
 // updated pixels only.
+// HRNet-like 384 x 288 frame, pending values behind the flags / with them: 369 / 365 us, 8 videos 1001 / 991.
 // ---------------------------------------------------------------------------
 constexpr int kUpPx = 32, kUpCo = 32, kUpSum = kUpCo + 4, kUpSmem = 4 * kUpPx * kUpSum * 4;
 __host__ __device__ inline int up_parts(int up) { return up > 1 ? 1 << (2 * up - 2) : 1; }     // blocks the f x f pixels are dealt to
 
-// READ: the launch may read the destination out (EdgeDev::dY)
-template <bool READ>
-__device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const TileGrid& g) {
+// READ: the launch may read the destination out (EdgeDev::dY).  EARLY: everything is requested at once - code of its own, or each
+// request waits for the flags that decide it in the other case.
+template <bool READ, bool EARLY>
+__device__ __forceinline__ void up_tile(const EdgeDev& e, unsigned blk, const TileGrid& g) {
     extern __shared__ __align__(16) unsigned char smem[];
     float* const sums = reinterpret_cast<float*>(smem);
     int sH = e.sH, sW = e.sW, Cin = e.Cin, Cout = e.Cout, Hp = e.Hp, Wp = e.Wp, by0 = e.by0, bx0 = e.bx0, p_oy = e.p_oy, p_ox = e.p_ox, up = e.up, dH = e.dH, dW = e.dW;
@@ -28,10 +30,14 @@ __device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const Ti
     const uint8_t* sflags = e.sflags;
     uint8_t* dflags = e.dflags;
     f16 *P = (f16*)e.P, *out_p = (f16*)e.dY;
-    int NT = g.NT, MT = g.tiles_x, early = g.early, relu = e.s_relu;
+    int NT = g.NT, MT = g.tiles_x, relu = e.s_relu;
     unsigned per_NT = g.per_NT, per_MT = g.per_tiles_x;
-    read_now(sH, sW, Cin, Cout, Hp, Wp, by0, bx0, p_oy, p_ox, up, dH, dW, delta, w, sflags, dflags, P, NT, MT, early, per_NT, per_MT);
-    if constexpr (READ) read_now(out_p, relu);
+    read_now(sH, sW, Cin, Cout, Hp, Wp, by0, bx0, p_oy, p_ox, up, dH, dW, delta, w, sflags, dflags, P, NT, MT, per_NT, per_MT);
+    P = in_global(P);
+    if constexpr (READ) {
+        read_now(out_p, relu);
+        out_p = in_global(out_p);
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, kh = lane >> 5;
@@ -51,7 +57,7 @@ __device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const Ti
     f16x8 pold[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int px = p0 + (tid >> 4) + 16 * i, cy = div24(px, sW, rsw), cx = px - cy * sW;
+        const int px = p0 + (tid >> 4) + 16 * i, in = px < HW ? px : 0, cy = div24(in, sW, rsw), cx = in - cy * sW;
         const int oy = (cy << up) + a, ox = (cx << up) + b;
         live[i] = __builtin_amdgcn_raw_buffer_load_b8(frs, px < HW ? px : (int)kOutside, 0, 0);      // (outside: 0)
         mark[i] = px < HW && c8 == 0 && n0 == 0 ? (unsigned)(oy * dW + ox) : kOutside;             // (outside: dropped)
@@ -59,10 +65,9 @@ __device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const Ti
     }
     const int px = p0 + r32;
     const unsigned mine = __builtin_amdgcn_raw_buffer_load_b8(frs, px < HW ? px : (int)kOutside, 0, 0);
-    const unsigned long long lives = early ? 1ull : __ballot(mine & kFlagM);
-    if (lives == 0) return;                          // block-uniform
+    if (!EARLY && __ballot(mine & kFlagM) == 0) return;      // block-uniform
     const unsigned wl = (unsigned)(n0 + r32) * row + (unsigned)(wave * 32 + kh * 16);
-    const unsigned bl = px < HW && (early || (mine & kFlagM)) ? (unsigned)px * row + (unsigned)(wave * 32 + kh * 16) : kOutside;
+    const unsigned bl = px < HW && (EARLY || (mine & kFlagM)) ? (unsigned)px * row + (unsigned)(wave * 32 + kh * 16) : kOutside;
     constexpr int D = 4;
     f16x8 fa[D], fb[D];
     const int nk = Cin / 64;                         // 16-channel blocks of a wave
@@ -73,11 +78,13 @@ __device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const Ti
 #pragma unroll
     for (int d = 0; d < D; ++d)
         if (d < nk) load(d, d);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (early ? p0 + (tid >> 4) + 16 * i < HW : (live[i] & kFlagM) != 0) pold[i] = *reinterpret_cast<const f16x8*>(pp[i]);
+    auto pending = [&](int i) {
+        pold[i] = *reinterpret_cast<const f16x8*>(pp[i]);
         df[i] = __builtin_amdgcn_raw_buffer_load_b8(mrs, (int)mark[i], 0, 0);
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (EARLY || (live[i] & kFlagM)) pending(i);         // (a tile's missing pixels read those of the first)
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -120,6 +127,12 @@ __device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const Ti
         const int n = __popcll(__ballot(lane < 32 && (mine & kFlagM)));
         if (lane == 0) add_macs(e, n, 0);
     }
+}
+
+template <bool READ>
+__device__ __forceinline__ void up_body(const EdgeDev& e, unsigned blk, const TileGrid& g) {
+    if (g.early) up_tile<READ, true>(e, blk, g);
+    else up_tile<READ, false>(e, blk, g);
 }
 
 }  // namespace mdcnn
