@@ -43,16 +43,16 @@ template <> struct V16<f16> {
 
 __device__ __forceinline__ size_t a_offset(const SiteDev& s, int vy, int vx) {
     int ay = wrap(s.a_oy + vy, s.H), ax = wrap(s.a_ox + vx, s.W);
-    return ((size_t)ay * s.W + ax) * s.C;
+    return (size_t)((unsigned)ay * (unsigned)s.W + (unsigned)ax) * (unsigned)s.C;       // (pixels of a window: below 2^32)
 }
 // wy, wx: padded-window coordinates
 __device__ __forceinline__ size_t p_offset(const SiteDev& s, int wy, int wx) {
     int py = wrap(s.p_oy + wy, s.Hp), px = wrap(s.p_ox + wx, s.Wp);
-    return ((size_t)py * s.Wp + px) * s.C;
+    return (size_t)((unsigned)py * (unsigned)s.Wp + (unsigned)px) * (unsigned)s.C;
 }
 __device__ __forceinline__ size_t skip_offset(const SkipDev& k, int vy, int vx, int C) {
     int py = wrap(k.p_oy + vy + k.by0, k.Hp), px = wrap(k.p_ox + vx + k.bx0, k.Wp);
-    return ((size_t)py * k.Wp + px) * C;
+    return (size_t)((unsigned)py * (unsigned)k.Wp + (unsigned)px) * (unsigned)C;
 }
 
 // ---------------------------------------------------------------------------
@@ -218,8 +218,8 @@ __device__ __forceinline__ float group_max(float v) {
 // G lanes share one pixel, each lane owns CH 16-byte chunks of its channels.
 // The block writes its update / candidate counts for the compaction pass.
 // With a mask given, a pixel that it leaves out is not read: bottleneck block, 128 x 128, a fifth of the pixels updated, 43.9 -> 41.2 us
-// a frame (its sites read A and P of all pixels before).  What a skip adds to is asked for with A
-// and P, not behind the stores: no launch was measurably slower or faster for it.
+// a frame (its sites read A and P of all pixels before).  What a skip adds to is asked for with A and P, of every candidate, not
+// behind the stores: of emitted pixels only, once they are known, 16 videos of HRNet-like 512 x 512 frames took 1790 us for 1768.
 // ---------------------------------------------------------------------------
 // Sites with crops.  A pixel inside the crop takes its flags from the state ring: newly
 // unveiled if no frame has covered it since it was allocated, touched if a producer touched
@@ -250,12 +250,15 @@ __device__ __forceinline__ bool unveiled(const FillJob& j, int vy, int vx) {
     return vy < j.ay0 || vy >= j.ay1 || vx < j.ax0 || vx >= j.ax1;
 }
 
-// EARLY (accumulator sites without a mask): what a pixel may need is asked for with its flags, not after them.
+// What is done while a pixel's flags are on their way (the rules: kAheadBlocks, kEarlyBlocks): nothing; its addresses are worked out and its
+// mask value is asked for; all it may need is asked for (accumulator sites without a mask).
 // The pointers are named global again after read_now(): their loads were flat ones, each waited for by itself.  With values kept as loaded
-// until all are asked for, HRNet-like 512 x 512 16 videos a frame 2720 -> 2586 us, one 445 -> 423; nothing updated at all 1100 -> 1120, 318 -> 320.
-template <typename T, int G, int CH, bool EARLY = false>
+// until all are asked for, HRNet-like 512 x 512 16 videos a frame 2720 -> 2586 us, one 445 -> 423.
+enum Step1When { kLate, kAhead, kEarly };
+template <typename T, int G, int CH, int WHEN>
 __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __restrict__ X,
                                             const uint8_t* __restrict__ forced, unsigned blk, const FillJob* own = nullptr) {
+    constexpr bool EARLY = WHEN == kEarly;
     constexpr int VEC = V16<T>::N;
     read_now(s.A, s.P, s.flags, s.delta, s.H, s.W, s.C, s.Hp, s.Wp, s.by0, s.bx0, s.a_oy, s.a_ox, s.p_oy, s.p_ox, s.theta, s.relu, s.kind, s.s_off,
              skip.P, skip.dflags, skip.Hp, skip.Wp, skip.by0, skip.bx0, skip.p_oy, skip.p_ox, X, forced);
@@ -271,23 +274,29 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
     if (pix < HW) {
         int fl = s.flags[pix];
         __builtin_amdgcn_sched_barrier(0);                 // (on its way before the addresses of the rest are worked out)
-        const int vy = div24(pix, s.W, rcp_of(s.W)), vx = pix - vy * s.W;
         const bool is_input = !EARLY && s.kind == MDCNN_SITE_INPUT;
-        T* Ap = (T*)s.A + a_offset(s, vy, vx);
-        T* Pp = is_input ? nullptr : (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
-        T* Sp = skip.P ? (T*)skip.P + skip_offset(skip, vy, vx, s.C) : nullptr;
+        int vy = 0, vx = 0;
+        T *Ap = nullptr, *Pp = nullptr, *Sp = nullptr;
+        auto locate = [&] {
+            vy = div24(pix, s.W, rcp_of(s.W));
+            vx = pix - vy * s.W;
+            Ap = (T*)s.A + a_offset(s, vy, vx);
+            if (!is_input) Pp = (T*)s.P + p_offset(s, vy + s.by0, vx + s.bx0);
+            if (skip.P) Sp = (T*)skip.P + skip_offset(skip, vy, vx, s.C);
+        };
         using raw = typename V16<T>::raw;
         raw ra[CH], rt[CH], rk[CH];
-        int sfl = 0;
+        uint8_t sfl;
         auto at = [&](const T* p, int j) { return *reinterpret_cast<const raw*>(p + (lp + j * G) * VEC); };
         // what a fused residual skip adds to, before the stores: a load after them is back only once they are done
         auto ask_skip = [&] {
             if (Sp) {
 #pragma unroll
                 for (int j = 0; j < CH; ++j) rk[j] = at(Sp, j);
-                if (lp == 0 && skip.dflags) sfl = skip.dflags[pix];
+                if (skip.dflags) sfl = skip.dflags[pix];
             }
         };
+        if constexpr (WHEN != kLate) locate();
         if constexpr (EARLY) {
 #pragma unroll
             for (int j = 0; j < CH; ++j) { ra[j] = at(Ap, j); rt[j] = at(Pp, j); }
@@ -296,18 +305,28 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
         int xpix = pix;                                    // index into the frame and the forced mask
         bool inside = true;
         if (s.s_off) inside = crop_state(s, pix, lp == 0, fl, xpix);
-        const bool chosen = !EARLY && forced && inside && forced[xpix] != 0;
         cand = inside && (is_input || (!EARLY && forced != nullptr) || (fl & (kFlagN | kFlagU)));
-        if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
-        if (!EARLY && forced ? inside && (chosen || (fl & kFlagN)) : cand) {      // (a pixel that its mask leaves out is not read)
+        bool work = cand;                                  // (a pixel that its mask leaves out is not read)
+        if constexpr (WHEN == kLate) {
+            if (cand) {
+                locate();
+                if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
+                if (forced) work = (fl & kFlagN) || forced[xpix] != 0;
+            }
+        } else {
+            const bool chosen = !EARLY && forced && inside && forced[xpix] != 0;
+            if (own) fl = unveiled(*own, vy, vx) ? kFlagN : 0;
+            if (!EARLY && forced) work = inside && (chosen || (fl & kFlagN));
+        }
+        if (work) {
             if constexpr (!EARLY) {
                 const T* tp = is_input ? X + (size_t)xpix * s.C : Pp;
-                ask_skip();
 #pragma unroll
                 for (int j = 0; j < CH; ++j) {
                     if (!(fl & kFlagN)) ra[j] = at(Ap, j);
                     rt[j] = at(tp, j);
                 }
+                ask_skip();
             }
             float na[CH][VEC], out[CH][VEC];
             float mx = 0.f;
@@ -320,12 +339,17 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
                 if (is_input) {
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) { na[j][i] = t[i]; out[j][i] = t[i] - a[i]; }
+                } else if (s.relu) {                       // (a question of its own: asked per value, it was two branches for each)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        na[j][i] = a[i] + t[i];
+                        out[j][i] = fmaxf(na[j][i], 0.f) - fmaxf(a[i], 0.f);
+                    }
                 } else {
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
-                        float n = a[i] + t[i];
-                        na[j][i] = n;
-                        out[j][i] = s.relu ? fmaxf(n, 0.f) - fmaxf(a[i], 0.f) : n - a[i];
+                        na[j][i] = a[i] + t[i];
+                        out[j][i] = na[j][i] - a[i];
                     }
                 }
 #pragma unroll
@@ -362,9 +386,9 @@ __device__ __forceinline__ void step1_block(SiteDev s, SkipDev skip, const T* __
     }
 }
 
-template <typename T, int G, int CH>
+template <typename T, int G, int CH, int WHEN>
 __global__ __launch_bounds__(256) void k_step1(Step1Batch bt) {
-    step1_block<T, G, CH>(bt.s[blockIdx.z], bt.skip[blockIdx.z], (const T*)bt.X[blockIdx.z], bt.forced[blockIdx.z], blockIdx.x);
+    step1_block<T, G, CH, WHEN>(bt.s[blockIdx.z], bt.skip[blockIdx.z], (const T*)bt.X[blockIdx.z], bt.forced[blockIdx.z], blockIdx.x);
 }
 
 // One site, and in the same launch the initialisation jobs of other sites: the first
@@ -372,7 +396,7 @@ __global__ __launch_bounds__(256) void k_step1(Step1Batch bt) {
 template <typename T, int G, int CH>
 __global__ __launch_bounds__(256) void k_step1_fill(Step1Fill a) {
     if (blockIdx.x >= a.blocks.total) {
-        step1_block<T, G, CH>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.blocks.total, a.has_own ? &a.own : nullptr);
+        step1_block<T, G, CH, kAhead>(a.s, a.skip, (const T*)a.X, a.forced, blockIdx.x - a.blocks.total, a.has_own ? &a.own : nullptr);
         return;
     }
     unsigned lb;
@@ -468,22 +492,26 @@ static bool step1_shape(int C, int vec, int& G, int& CH) {
     return false;
 }
 
-template <typename T, int G>
-static void step1_g(const Step1Batch& bt, int CH, dim3 grid, hipStream_t st) {
-    switch (CH) {
-        case 1: k_step1<T, G, 1><<<grid, dim3(256), 0, st>>>(bt); break;
-        case 2: k_step1<T, G, 2><<<grid, dim3(256), 0, st>>>(bt); break;
-        case 3: k_step1<T, G, 3><<<grid, dim3(256), 0, st>>>(bt); break;
-        default: k_step1<T, G, 4><<<grid, dim3(256), 0, st>>>(bt); break;
-    }
+// Launches of up to as many blocks, twice what the compute units hold, work out addresses ahead: below, the round trip is what they last
+// (late / ahead, us a frame: ResNet-18-style 512 x 512 376.0 / 372.9, HRNet-like 384 x 288 380.8 / 375.3, 8 videos 991 / 984); above, the
+// instructions of pixels without work cost more (a 256 x 256 x 64 site of 16 videos that stand still 16.0 / 19.5 us, the whole frame 702 / 725;
+// with a tenth of the rows moving 1392 / 1414).
+constexpr unsigned kAheadBlocks = 4096u;
+
+template <typename T, int G, int CH>
+static void step1_when(const Step1Batch& bt, dim3 grid, hipStream_t st) {
+    if (grid.x * grid.z <= kAheadBlocks) k_step1<T, G, CH, kAhead><<<grid, dim3(256), 0, st>>>(bt);
+    else k_step1<T, G, CH, kLate><<<grid, dim3(256), 0, st>>>(bt);
 }
-template <typename T, int G>
-static void step1_g(const Step1Fill& a, int CH, dim3 grid, hipStream_t st) {
+template <typename T, int G, int CH>
+static void step1_when(const Step1Fill& a, dim3 grid, hipStream_t st) { k_step1_fill<T, G, CH><<<grid, dim3(256), 0, st>>>(a); }
+template <typename T, int G, typename Args>
+static void step1_g(const Args& a, int CH, dim3 grid, hipStream_t st) {
     switch (CH) {
-        case 1: k_step1_fill<T, G, 1><<<grid, dim3(256), 0, st>>>(a); break;
-        case 2: k_step1_fill<T, G, 2><<<grid, dim3(256), 0, st>>>(a); break;
-        case 3: k_step1_fill<T, G, 3><<<grid, dim3(256), 0, st>>>(a); break;
-        default: k_step1_fill<T, G, 4><<<grid, dim3(256), 0, st>>>(a); break;
+        case 1: step1_when<T, G, 1>(a, grid, st); break;
+        case 2: step1_when<T, G, 2>(a, grid, st); break;
+        case 3: step1_when<T, G, 3>(a, grid, st); break;
+        default: step1_when<T, G, 4>(a, grid, st); break;
     }
 }
 static void step1_scalar(const Step1Batch& bt, dim3 grid, hipStream_t st, float) { k_step1_scalar<float><<<grid, dim3(256), 0, st>>>(bt); }
@@ -531,21 +559,8 @@ hipError_t launch_step1(const Step1Batch& bt, int n, hipStream_t st) {
     return bt.s[0].dtype == MDCNN_F16 ? step1_t<f16>(bt, bt.s[0], n, 0u, st) : step1_t<float>(bt, bt.s[0], n, 0u, st);
 }
 
-template <bool EARLY>
-__device__ __forceinline__ void step1_site(const SiteDev& s, const SkipDev& k, unsigned blk) {
-    const f16* const X = nullptr;
-    switch (s.C / V16<f16>::N) {                           // lanes per pixel
-        case 1: step1_block<f16, 1, 1, EARLY>(s, k, X, nullptr, blk); break;
-        case 2: step1_block<f16, 2, 1, EARLY>(s, k, X, nullptr, blk); break;
-        case 4: step1_block<f16, 4, 1, EARLY>(s, k, X, nullptr, blk); break;
-        case 8: step1_block<f16, 8, 1, EARLY>(s, k, X, nullptr, blk); break;
-        case 16: step1_block<f16, 16, 1, EARLY>(s, k, X, nullptr, blk); break;
-        case 32: step1_block<f16, 32, 1, EARLY>(s, k, X, nullptr, blk); break;
-        default: step1_block<f16, 64, 1, EARLY>(s, k, X, nullptr, blk); break;
-    }
-}
-
 // Step 1 of several sites that do not depend on each other (see k_conv_multi): one 16-byte chunk per lane, fp16.
+template <int WHEN>
 __global__ __launch_bounds__(256) void k_step1_multi(unsigned b1, unsigned b2, unsigned b3, unsigned b4, unsigned b5, unsigned videos, Step1Multi m) {
     unsigned blk;
     const int j = find_job(b1, b2, b3, b4, b5, blockIdx.x, &blk);
@@ -563,8 +578,16 @@ __global__ __launch_bounds__(256) void k_step1_multi(unsigned b1, unsigned b2, u
     SkipDev k{};
     k.P = at(jb.skip_P, v.kd); k.dflags = at(jb.skip_flags, v.kd);
     k.Hp = jb.skip_Hp; k.Wp = jb.skip_Wp; k.by0 = jb.skip_by0; k.bx0 = jb.skip_bx0; k.p_oy = v.k_oy; k.p_ox = v.k_ox;
-    if (m.early) step1_site<true>(s, k, blk);
-    else step1_site<false>(s, k, blk);
+    const f16* const X = nullptr;
+    switch (s.C / V16<f16>::N) {                           // lanes per pixel
+        case 1: step1_block<f16, 1, 1, WHEN>(s, k, X, nullptr, blk); break;
+        case 2: step1_block<f16, 2, 1, WHEN>(s, k, X, nullptr, blk); break;
+        case 4: step1_block<f16, 4, 1, WHEN>(s, k, X, nullptr, blk); break;
+        case 8: step1_block<f16, 8, 1, WHEN>(s, k, X, nullptr, blk); break;
+        case 16: step1_block<f16, 16, 1, WHEN>(s, k, X, nullptr, blk); break;
+        case 32: step1_block<f16, 32, 1, WHEN>(s, k, X, nullptr, blk); break;
+        default: step1_block<f16, 64, 1, WHEN>(s, k, X, nullptr, blk); break;
+    }
 }
 
 bool step1_multi_applies(const SiteDev& s) {
@@ -582,9 +605,10 @@ hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st) {
         const int ppb = 256 / G;
         m.blocks.add(j, (unsigned)((jb.H * jb.W + ppb - 1) / ppb));
     }
-    m.early = m.blocks.total * (unsigned)videos <= kEarlyBlocks;
-    k_step1_multi<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m.blocks.begin[1], m.blocks.begin[2], m.blocks.begin[3], m.blocks.begin[4],
-                                                                                             m.blocks.begin[5], (unsigned)videos, m);
+    const unsigned blocks = m.blocks.total * (unsigned)videos;
+    auto kern = blocks <= kEarlyBlocks ? k_step1_multi<kEarly> : blocks <= kAheadBlocks ? k_step1_multi<kAhead> : k_step1_multi<kLate>;
+    kern<<<dim3(m.blocks.total, 1, (unsigned)videos), dim3(256), 0, st>>>(m.blocks.begin[1], m.blocks.begin[2], m.blocks.begin[3], m.blocks.begin[4], m.blocks.begin[5],
+                                                                          (unsigned)videos, m);
     return hipGetLastError();
 }
 

@@ -387,13 +387,13 @@ struct Step1Vid {
 };
 struct Step1Multi {
     JobBlocks<kMaxMultiJobs> blocks;
-    int n, videos, early;
+    int n, videos;
     Step1Job job[kMaxMultiJobs];
     Step1Vid vid[kMaxStep1Vids];
 };
 static_assert(sizeof(Step1Multi) <= 4000, "kernel arguments stay below 4 KiB");
 bool step1_multi_applies(const SiteDev& s);
-hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      // fills in blocks, videos and early
+hipError_t launch_step1_multi(Step1Multi& m, int videos, hipStream_t st);      // fills in blocks and videos
 
 // e.k < 0: no operator, only the compaction of the source's update mask.
 // returns the kernel class that was launched in *cls
