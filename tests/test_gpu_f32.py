@@ -22,15 +22,20 @@ def frames_of(net, seed, n=3):
 
 
 @pytest.mark.parametrize("cin,cout,H,W,k,stride", [
-    (128, 32, 8, 8, 3, 1),         # one tile and a bit: the 10 x 10 window in tiles of up to 32 pixels
+    (96, 32, 8, 8, 3, 1),          # one tile and a bit: the 10 x 10 window in tiles of up to 32 pixels
     (8, 32, 5, 37, 3, 1),          # a quarter of a chunk: one wave multiplies
     (24, 96, 33, 18, 3, 1),        # three quarters of a chunk, three cout tiles
     (72, 16, 30, 22, 1, 1),        # half a cout tile
     (128, 128, 48, 40, 3, 2),      # stride 2
     (40, 64, 90, 100, 5, 1),       # 25 taps; a chunk and a quarter
-    (512, 64, 11, 9, 3, 1),        # a long K loop
+    (480, 64, 11, 9, 3, 1),        # a long K loop
+    (512, 64, 11, 9, 3, 2),
     (32, 32, 41, 29, 3, 1),        # one chunk: an odd number of steps
-    (64, 96, 3, 75, 3, 1),         # two chunks; a window narrower than a tile is high
+    (64, 72, 3, 75, 3, 1),         # two chunks, a quarter of a cout tile; a window narrower than a tile is high
+    (96, 96, 3, 75, 3, 1),         # three chunks: an odd number, three cout tiles
+    (128, 32, 8, 8, 3, 1),         # from here on the tiles of conv_f32s.h: 3x3, stride 1, 64 n channels, 32 m couts
+    (512, 64, 11, 9, 3, 1),
+    (64, 96, 3, 75, 3, 1),
 ])
 def test_fp32_layers(cin, cout, H, W, k, stride):
     import gpu_harness as G
@@ -100,19 +105,26 @@ def test_small_upsampling_edges_on_large_views(rows, kernel):
     G.teacher_forced(net, frames, [(0, 0), (0, 1), (0, 0)])
 
 
-@pytest.mark.parametrize("cin,cout,H,W", [
-    (64, 32, 16, 16),              # few tiles: one row tile each (2 x 14 pixels of an 18 x 18 window), one chunk of channels
-    (192, 96, 37, 53),             # the same with three chunks and three cout tiles, ragged in both directions
-    (512, 32, 1, 1),               # one pixel, eight chunks
-    (64, 64, 64, 64),              # two row tiles, one chunk
-    (128, 64, 61, 75),             # two chunks, ragged
-    (64, 64, 96, 96),              # three row tiles, one chunk: nothing staged ahead
-    (128, 64, 95, 97),             # three row tiles, two chunks
-    (192, 64, 94, 99),             # three chunks: the last in the first buffer
+def row_tiles(H, W, cin, cout, videos=1):
+    """Row tiles of a tile that the library takes for 3x3 fp32 layers of 64 n channels on H x W views (an internal rule)."""
+    from paper_2210_09887_amd import binding as B
+    return getattr(B.lib(), "_ZN5mdcnn12split_choiceEiiiii")(H + 2, W + 2, cin, cout, videos)
+
+
+@pytest.mark.parametrize("cin,cout,H,W,tiles", [
+    (64, 32, 16, 16, 1),           # few tiles: one row tile each (2 x 14 pixels of an 18 x 18 window), one chunk of channels
+    (192, 96, 37, 53, 1),          # the same with three chunks and three cout tiles, ragged in both directions
+    (512, 32, 1, 1, 1),            # one pixel, eight chunks
+    (64, 64, 64, 64, 2),           # two row tiles, one chunk
+    (128, 64, 61, 75, 2),          # two chunks, ragged
+    (64, 64, 96, 96, 3),           # three row tiles, one chunk: nothing staged ahead
+    (128, 64, 95, 97, 3),          # three row tiles, two chunks
+    (192, 64, 94, 99, 3),          # three chunks: the last in the first buffer
 ])
-def test_fp32_layers_of_64_n_channels(cin, cout, H, W):
+def test_fp32_layers_of_64_n_channels(cin, cout, H, W, tiles):
     """The tiles whose products are made of bf16 parts: every number of row tiles, dense frames (the first) and sparse ones."""
     import gpu_harness as G
+    assert row_tiles(H, W, cin, cout) == tiles
     net = tiny_net("f32", H, W, (cin, cout), theta=0.05, seed=cin + cout)
     G.teacher_forced(net, frames_of(net, cin * 10 + cout), [(0, 0), (0, 0), (1, -1)])
 
@@ -138,7 +150,7 @@ def dense_frame(net, X):
 def test_precision_of_split_products(cin, n, scale):
     """Against 64 bits: a sum of 9 cin products is rounded 9 cin / 64 times in each of four waves, to 2^-25 of a partial sum (of
     the sum's size or less) on average: at most 2^-25 sqrt(9 cin / 16 + 8), 2^-22.8 and 2^-21 here, where fp32 products, each of
-    them rounded, come to 2^-22.1 and 2^-20.7.  At the ends of the exponents too."""
+    them rounded, come to 2^-22.1 and 2^-20.7.  (The ends of the range: test_precision_at_the_ends_of_the_range.)"""
     net = tiny_net("f32", n, n, (cin, 32), theta=0.0, seed=cin)
     net.edges[0].b[:] = 0
     X = (np.maximum(np.random.default_rng(cin).normal(0, 1, (n, n, cin)), 0) * scale).astype(np.float32)
@@ -163,12 +175,6 @@ def test_values_that_are_not_finite(n):
     assert float(((out - ref)[near] / ref[near]).abs().max()) < 1e-6
 
 
-def row_tiles(n, cin, cout, videos):
-    """Row tiles of a tile that the library takes for 3x3 fp32 layers of 64 n channels on n x n views (an internal rule)."""
-    from paper_2210_09887_amd import binding as B
-    return getattr(B.lib(), "_ZN5mdcnn12split_choiceEiiiii")(n + 2, n + 2, cin, cout, videos)
-
-
 @pytest.mark.parametrize("bad", ["finite", "frame", "weight"])
 @pytest.mark.parametrize("cin,n,videos,alone,together", [(64, 64, 2, 2, 3), (64, 96, 2, 3, 2), (64, 32, 4, 1, 2), (64, 32, 8, 1, 3), (128, 64, 2, 2, 3)])
 def test_bits_in_a_batch(cin, n, videos, alone, together, bad):
@@ -177,7 +183,7 @@ def test_bits_in_a_batch(cin, n, videos, alone, together, bad):
     import gpu_harness as G
     from paper_2210_09887_amd.runtime import GpuBatch, GpuNet
     net = tiny_net("f32", n, n, (cin, 64), theta=0.05, seed=n + videos)
-    assert (row_tiles(n, cin, 64, 1), row_tiles(n, cin, 64, videos)) == (alone, together)
+    assert (row_tiles(n, n, cin, 64), row_tiles(n, n, cin, 64, videos)) == (alone, together)
     frames = frames_of(net, n + videos)
     if bad == "weight":
         w = net.edges[0].w.reshape(9, 64, cin)

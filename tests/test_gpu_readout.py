@@ -46,6 +46,18 @@ def test_frame_output_is_the_view(dtype, chans, k, stride, H, W):
     check(tiny_net(dtype, H * stride, W * stride, chans, k=k, stride=stride, theta=0.05, seed=H, total_stride=stride))
 
 
+@pytest.mark.parametrize("dtype,C,h,w,up", [("f16", 64, 5, 7, 1), ("f16", 128, 6, 9, 2), ("f16", 64, 212, 210, 1), ("f16", 32, 9, 11, 1), ("f32", 64, 9, 11, 1)])
+def test_upsampling_edges(dtype, C, h, w, up):
+    from inputs.nets import NetSpec, _Builder
+    f = 1 << up
+    net = NetSpec("up", dtype, h * f, w * f, f)
+    b = _Builder(net, np.random.default_rng(C + up), 0.1)
+    x, s, y = b.site("in", 8, 1, "input", False, 0.05), b.site("low", C, f, theta=0.02), b.site("out", 32, 1, "output", False, 0.0)
+    b.conv(x, s, 3, f)
+    b.conv(s, y, 1, 1, pad=0, up=up)
+    check(net)
+
+
 @pytest.mark.parametrize("config,H,W,batch", [(5, 21, 30, 0), (5, 16, 16, 3), (3, 64, 96, 2), (4, 64, 64, 0)])
 def test_networks(config, H, W, batch):
     from inputs import build_net

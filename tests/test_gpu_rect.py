@@ -70,14 +70,20 @@ def test_frames_in_flight_take_other_tiles(cin, cout, H, W, alone, flying):
     b.close()
 
 
-@pytest.mark.parametrize("cin,cout,H,W,videos", [
-    (64, 96, 2, 46, 1), (64, 64, 54, 38, 1), (64, 64, 100, 126, 1), (64, 128, 130, 252, 1), (64, 256, 100, 120, 2),     # 32, 32, 64, 128 couts; 64 alone, 128 in a batch
-    (128, 32, 34, 2, 1), (192, 192, 58, 90, 1), (128, 128, 132, 260, 1), (32, 32, 18, 30, 1), (32, 64, 130, 92, 1), (96, 192, 44, 62, 2)])
-def test_stride_2(cin, cout, H, W, videos):
+@pytest.mark.parametrize("cin,cout,H,W,videos,couts", [                              # couts of a tile, alone and in the batch
+    (64, 96, 2, 46, 1, (32, 32)), (64, 64, 54, 38, 1, (32, 32)), (64, 64, 100, 126, 1, (64, 64)), (64, 128, 130, 252, 1, (128, 128)), (64, 256, 100, 120, 2, (128, 128)),
+    (64, 128, 100, 120, 2, (64, 128)),
+    (128, 32, 34, 2, 1, (32, 32)), (192, 192, 58, 90, 1, (64, 64)), (128, 128, 132, 260, 1, (128, 128)),
+    (32, 32, 18, 30, 1, (32, 32)), (32, 64, 130, 92, 1, (64, 64)), (96, 192, 44, 62, 2, (32, 64))])
+def test_stride_2(cin, cout, H, W, videos, couts):
     import gpu_harness as H_
     from inputs.nets import tiny_net
+    from paper_2210_09887_amd import binding as B
     from paper_2210_09887_amd.runtime import GpuBatch, GpuNet
     net = tiny_net("f16", H, W, (cin, cout), k=3, stride=2, theta=0.05, seed=cin + cout + H, total_stride=2)
+    by, bx = B.mdcnn_conv_border(3, 2, 1, H, H // 2), B.mdcnn_conv_border(3, 2, 1, W, W // 2)
+    rule = getattr(B.lib(), "_ZN5mdcnn14rect_choice_s2Eiiiii")               # (an internal one, on the padded window)
+    assert tuple(32 * rule(H // 2 + by[0] + by[1], W // 2 + bx[0] + bx[1], cin, cout, n) for n in (1, videos)) == couts
     frames, shifts = frames_of(cin, H, W), [(0, 0), (0, 0), (0, -1)]
     H_.teacher_forced(net, frames, shifts)
     if videos > 1:                                 # a video of a batch gives the bits it gives alone

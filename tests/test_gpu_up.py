@@ -1,5 +1,5 @@
 """Upsampling 1x1 fp16 edges of 64 n channels against the oracle: every factor, ragged views, more 16-channel blocks than travel at once,
-maps small enough to be requested at once and larger ones; a second edge into the same site."""
+maps small enough to be requested at once and larger ones; edges into an OUTPUT site, and several into a site that keeps marks."""
 import numpy as np
 import pytest
 
@@ -39,3 +39,31 @@ def test_upsampling_edges(cin, cout, h, w, up):
         v[net.H // 3:net.H // 3 + 3, net.W // 4:net.W // 4 + 9] += 0.5
         frames.append(v.astype(np.float16))
     G.teacher_forced(net, frames, [(0, 0), (0, 0), (1, -1) if min(h, w) > 1 else (0, 0)])
+
+
+@pytest.mark.parametrize("h,w", [(5, 7), (52, 40)])        # source pixels of the smaller map; requested at once, and later
+def test_two_edges_into_a_site_with_marks(h, w):
+    """A site fed by two upsampling edges of different factors and a 3x3 edge: pending values add up, and what an edge has marked as touched is
+    there for the next and for the site's own step."""
+    import gpu_harness as G
+    net = NetSpec("up2", "f16", 4 * h, 4 * w, 4)
+    b = _Builder(net, np.random.default_rng(h), 0.1)
+    x = b.site("in", 8, 1, "input", False, 0.05)
+    half = b.site("half", 64, 2, theta=0.3)
+    low = b.site("low", 192, 4, theta=0.3)
+    s = b.site("sum", 64, 1, theta=0.05)
+    y = b.site("out", 32, 1, "output", False, 0.0)
+    b.conv(x, half, 3, 2)
+    b.conv(x, s, 3, 1)
+    b.conv(half, low, 3, 2)
+    b.conv(half, s, 1, 1, pad=0, up=1)
+    b.conv(low, s, 1, 1, pad=0, up=2)
+    b.conv(s, y, 1, 1, pad=0)
+    rng = np.random.default_rng(w)
+    v = rng.normal(0, 1, (net.H, net.W, 8)).astype(np.float32)
+    frames = [v.astype(np.float16)]
+    for _ in range(2):
+        v = v.copy()
+        v[net.H // 3:net.H // 3 + 3, net.W // 4:net.W // 4 + 9] += 0.5
+        frames.append(v.astype(np.float16))
+    G.teacher_forced(net, frames, [(0, 0), (0, 0), (1, -1)])
