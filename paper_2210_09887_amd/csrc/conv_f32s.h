@@ -29,7 +29,7 @@ constexpr int split_rows(int tm) { return tm == 1 ? 4 : tm == 2 ? 7 : 9; }      
 // splits them, and passes them between its lanes through LDS of its own, which takes no barrier, the LDS operations of a wave
 // being in order.  The four partial sums are added through LDS in wave order, so the tile does not change a result.
 //
-// A part of an infinity or NaN is none: sums that are not finite then either are made with products in fp32 (f32_tile), and they alone, from
+// A part of an infinity or NaN is none: sums that are not finite in either of two passes are made with products in fp32 (f32_tile), and they alone, from
 // runs of 16 window columns that every tile has in common - a value is that of its own operands, whatever shares the tile, and a
 // video of a batch, where tiles are of another size, gives the bits it gives alone.
 //
@@ -93,11 +93,12 @@ __device__ __forceinline__ int entry_of_lane(int l) {
 // Weights and delta rows are multiplied by powers of two first, so that the parts of the smallest values are normal numbers: 2^-149
 // becomes 2^-125 (as they were, frames of 1e-36 came out 2^-15 off and weights of 1e-36 2^-11, subnormal ones as zeros; fp32 products are
 // 2^-22.5 off there as everywhere, these now 2^-23.7).  What that makes too large, rows from 2^104 or sums from 2^80 on, comes out not
-// finite and is made again with rows divided by 2^40: what those lose is far below the roundings of such a sum.
-constexpr float kSplitWeights = 0x1p24f, kSplitRows = 0x1p24f, kSplitRowsLarge = 0x1p-40f;
+// finite and is made again with rows divided by 2^40.  Rows below 2^-62 lose up to 2^-86 by that, products with the largest weight that
+// this pass holds 2^18: far below the roundings of a sum of 2^64.  Smaller ones, where weights of zero meet the large rows, are left to fp32.
+constexpr float kSplitWeights = 0x1p24f, kSplitRows = 0x1p24f, kSplitRowsLarge = 0x1p-40f, kSplitLeast = 0x1p64f * kSplitWeights * kSplitRowsLarge;
 
 // The sums of a tile; false: that was all of them.  again: those that are not finite once more (left: this thread's, eight bits to an entry),
-// and which are not even then goes to s_left.
+// and which are not even then, or too small for this pass, goes to s_left.
 template <typename Cfg>
 __device__ __forceinline__ bool split_pass(const EdgeDev& e, unsigned blk, const TileGrid& g, bool again, unsigned& left) {
     constexpr int TM = Cfg::TM, M = Cfg::M, ROWS = Cfg::ROWS, PXP = Cfg::PXP, PLANE = Cfg::PLANE, WP = Cfg::WP, WPLANE = Cfg::WPLANE, NBUF = Cfg::NBUF, R = 3;
@@ -346,7 +347,7 @@ __device__ __forceinline__ bool split_pass(const EdgeDev& e, unsigned blk, const
 #pragma unroll
         for (int k = 0; k < 8; ++k) bad |= !finite(v[t][k]);
     }
-    auto finish = [&](auto some) {                    // some: not all of them, or not all are finite
+    auto finish = [&](auto some) {                    // some: not all of them, or not all are as they should be
 #pragma unroll
         for (int t = 0; t < NPASS; ++t) {
             const int at = t * 64 + (tid >> 2);
@@ -355,7 +356,7 @@ __device__ __forceinline__ bool split_pass(const EdgeDev& e, unsigned blk, const
             if constexpr (decltype(some)::value) {
                 done = 0;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) done |= finite(v[t][k]) ? 1u << k : 0u;
+                for (int k = 0; k < 8; ++k) done |= finite(v[t][k]) && (!again || __builtin_fabsf(v[t][k]) >= kSplitLeast) ? 1u << k : 0u;
                 done &= left >> (8 * t);
             }
 #pragma unroll

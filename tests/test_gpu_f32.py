@@ -220,6 +220,20 @@ def test_precision_at_the_ends_of_the_range(cin, n, in_frame, in_weights):
     assert err < 2.0 ** -25 * (9 * cin / 16 + 8) ** 0.5
 
 
+@pytest.mark.parametrize("large", [1e32, 1e38])
+@pytest.mark.parametrize("n", [16, 64, 96])
+def test_small_sums_beside_large_values(n, large):
+    """Values from 2^104 on with weights of zero: the second pass, which divides the rows by 2^40, loses all the others, and its sums are left to
+    fp32 products.  The bound is theirs: a rounding per product, 9 cin / 4 in each of four waves, of 2^-25 of the sum on average."""
+    net = tiny_net("f32", n, n, (64, 32), theta=0.0, seed=n)
+    net.edges[0].b[:] = 0
+    net.edges[0].w.reshape(9, 32, 64)[:, :, 7] = 0
+    X = (np.maximum(np.random.default_rng(n).normal(0, 1, (n, n, 64)), 0) * 1e-28).astype(np.float32)
+    X[2::5, 1::7, 7] = large
+    out, ref = dense_frame(net, X)
+    assert float((out - ref).norm() / ref.norm()) < 2.0 ** -25 * (9 * 64 / 4 + 8) ** 0.5
+
+
 @pytest.mark.parametrize("tap", [0, 4])
 def test_one_product(tap):
     """One live product to a sum.  Left out of it are the products of parts 1, 2 and 2, 1, at most 2^-25 of a unit pair's product each, and 2, 2,
