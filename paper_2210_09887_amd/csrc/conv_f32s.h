@@ -34,7 +34,9 @@ constexpr int split_rows(int tm) { return tm == 1 ? 4 : tm == 2 ? 7 : 9; }      
 // video of a batch, where tiles are of another size, gives the bits it gives alone.
 //
 // What bounds it: the issue of instructions, about 83 of a step beside its 6 TM products, 52 of them the split of the weights,
-// at 4.6 cycles each - 0.34 us a step with two row tiles, whether one block is on a compute unit or two share it.  Chains of
+// at 4.6 cycles each - 0.34 us a step with two row tiles, whether one block is on a compute unit or two share it.  Counted on 512 -> 512, three
+// row tiles, one wave to a SIMD: vector instructions are issued 38 % of a wave's time, the matrix pipe is busy 41 %, the two hardly at once; 24 %
+// are waits.  Chains of
 // one layer, all pixels updated, us a frame (10 of them not this launch), before (k_conv_f32) and now: 512 -> 512 on 32 x 32 84.9 and
 // 58.0, 256 -> 256 34.1 and 24.7, 128 -> 128 on 64 x 64 28.5 and 22.8, 64 -> 64 on 128 x 128 27.9 and 25.4, on 256 x 256
 // 82.7 and 65.9.  Stride 2, with a footprint four times the tile, was no faster than k_conv_f32 (64 -> 128: 23.4 and 21.3).  Not

@@ -1288,6 +1288,10 @@ static hipError_t launch_rect(const EdgeBatch& eb, int nb, int m, hipStream_t st
 // channels on 129 x 129 pixels beside the projection of the block: 64 couts 18.0 us, 128 couts 13.1, the gather tiles before
 // 15.1; 128 -> 256 on 65 x 65: 15.7, 12.7, 14.6; 16 videos of them 99 / 87 / 85 and 101 / 76 / 79.  64 -> 64 on 97 x 73
 // 8.1 us (gather tiles 12.1), 32 -> 32 on 49 x 37 5.5 (11.4): HRNet-like 384 x 288 frame 471 -> 439 us.
+// The one batch that the gather tiles are ahead in does not go to them: they add up in another order, and a video of a batch gives
+// the bits it gives alone.  Nor does a scene that stands still, of which nobody knows beforehand: the launch of 16 HRNet-like 512 x 512
+// videos, 64 -> 64, takes 30 us for 15 when there is nothing to do.  Weights and rows asked for once a tile is known to have entries took
+// 6 us off such a frame of 1101 and added 6 to the frame of 8 videos of 972, in the launches that carry these tiles beside others.
 int rect_choice_s2(int Hp, int Wp, int Cin, int Cout, int nb) {
     int th, tw;
     long long tiles;
